@@ -11,12 +11,20 @@ namespace mosaic {
 
 constexpr int kUnmaskThreads = 1024;
 
-// First row j in [0, n) with idx[j] >= pos (idx ascending).
+// First row j in [0, n) with idx[j] >= pos (idx ascending), found by the whole block: every round the threads probe
+// kUnmaskThreads evenly spaced rows of what is left and count those below pos, so a list of up to 10^6 rows takes two
+// dependent memory latencies, where a binary search by every thread took twenty (~0.6 us each).
 __device__ __forceinline__ int lower_bound_rows(const int32_t* __restrict__ idx, int n, int pos) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (idx[mid] < pos) lo = mid + 1; else hi = mid;
+  int lo = 0, len = n;   // the answer lies in [lo, lo + len]
+  while (len > 0) {
+    const int step = (len + kUnmaskThreads - 1) / kUnmaskThreads;
+    const int64_t probe = (int64_t)threadIdx.x * step + step - 1;      // the last row of this thread's stretch
+    const bool below = probe < len && idx[lo + probe] < pos;
+    const int full = __syncthreads_count(below);                       // stretches that lie below pos as a whole
+    const int skip = full * step;
+    const int rest = len - skip < step - 1 ? len - skip : step - 1;    // the next one's last row is known not to
+    lo += skip;
+    len = rest;
   }
   return lo;
 }
@@ -40,16 +48,41 @@ __device__ __forceinline__ int block_exclusive_scan_flag(int flag, int* wave_tot
   return before + excl;
 }
 
-// One block per sequence: exact top-n by confidence (ties: lower position) through a 4-pass radix
-// select on the float bit patterns (confidences are non-negative, so the patterns order like the values).
+// Bins 0..255 of `hist`, read by the first wave (four bins per lane): the largest bin whose "at least" count reaches
+// `need`, and what of `need` is left inside it.  One wave-wide suffix sum; one thread walking the bins took ~10 us.
+__device__ __forceinline__ void find_threshold_bin(const int* hist, int need, int* bin, int* left) {
+  const int lane = threadIdx.x;   // of the first wave
+  int c[4], sum = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) { c[k] = hist[4 * lane + k]; sum += c[k]; }
+  int at_least = sum;             // inclusive suffix sum over the lanes
+#pragma unroll
+  for (int x = 1; x < 64; x <<= 1) {
+    const int other = __shfl_down(at_least, x, 64);
+    at_least += lane + x < 64 ? other : 0;
+  }
+  const int above = at_least - sum;
+  if (above < need && need <= at_least) {   // exactly one lane
+    int a = above, k = 3;
+    while (k > 0 && a + c[k] < need) a += c[k--];
+    *bin = 4 * lane + k;
+    *left = need - a;
+  }
+}
+
+// One block per sequence: exact top-n by confidence (ties: lower position).  Confidences are non-negative, so their
+// bit patterns order like the values.  Up to kRankRows rows (a block of a block-wise decoder): one thread per row
+// counts the rows that come before it.  More: a radix select of the threshold key, four passes of eight bits.
+// Bound by latency (a chain of barriers and dependent reads by one block): 24 rows 46 -> 6 us, 1004 rows 33 -> 10 us.
+constexpr int kRankRows = 256;   // the count is 64 LDS reads of four keys there, ~1 us; a radix pass ~2 us
 __global__ __launch_bounds__(kUnmaskThreads) void unmask_topn_kernel(
     const float* __restrict__ conf, const int32_t* __restrict__ token, const int32_t* __restrict__ idx,
     const int32_t* __restrict__ count, int32_t max_rows, const int32_t* __restrict__ seq_starts,
     const int32_t* __restrict__ n_per_seq, int32_t* __restrict__ tokens, uint8_t* __restrict__ mask, int32_t T) {
-  __shared__ int hist[256];
+  __shared__ __attribute__((aligned(16))) int hist[256];   // bin counts, or the keys of up to kRankRows rows
   __shared__ int wave_tot[kUnmaskThreads / 64];
-  __shared__ uint32_t sh_prefix;
-  __shared__ int sh_need;
+  __shared__ int sh_bin, sh_need;
+  static_assert(kRankRows <= 256, "the keys share the bins' memory");
   const int b = blockIdx.x, tid = threadIdx.x;
   int total = *count;
   if (total > max_rows) total = max_rows;
@@ -60,6 +93,31 @@ __global__ __launch_bounds__(kUnmaskThreads) void unmask_topn_kernel(
   if (n > m) n = m;
   if (n <= 0) return;
   const uint32_t* keys = reinterpret_cast<const uint32_t*>(conf);
+  auto unmask_row = [&](int j) {
+    const int t = idx[j];
+    if (t >= 0 && t < T) {   // an entry outside [0, T) of a caller-built list is skipped, never written through
+      tokens[t] = token[j];
+      mask[t] = 0;
+    }
+  };
+
+  if (m <= kRankRows) {
+    const uint32_t key = tid < m ? keys[lo + tid] : 0u;
+    if (tid < 256) hist[tid] = (int)key;
+    __syncthreads();
+    if (tid < m) {
+      int before = 0;                       // rows taken ahead of this one
+      for (int j = 0; j < m; j += 4) {      // rows past m hold key 0 behind every real row: they count for nobody
+        const uint4 k = *reinterpret_cast<const uint4*>(hist + j);
+        before += (k.x > key || (k.x == key && j + 0 < tid)) ? 1 : 0;
+        before += (k.y > key || (k.y == key && j + 1 < tid)) ? 1 : 0;
+        before += (k.z > key || (k.z == key && j + 2 < tid)) ? 1 : 0;
+        before += (k.w > key || (k.w == key && j + 3 < tid)) ? 1 : 0;
+      }
+      if (before < n) unmask_row(lo + tid);
+    }
+    return;
+  }
 
   uint32_t prefix = 0;   // bytes of the threshold key decided so far
   int need = n;          // rows still to find among keys matching the prefix
@@ -71,22 +129,24 @@ __global__ __launch_bounds__(kUnmaskThreads) void unmask_topn_kernel(
       __syncthreads();
       for (int j = lo + tid; j < hi; j += kUnmaskThreads) {
         const uint32_t k = keys[j];
-        if ((k & high_mask) == prefix) atomicAdd(&hist[(k >> shift) & 0xffu], 1);
-      }
-      __syncthreads();
-      if (tid == 0) {
-        int above = 0, byte = 255;
-        for (; byte > 0; --byte) {          // largest byte value whose "at least" count reaches need
-          if (above + hist[byte] >= need) break;
-          above += hist[byte];
+        const int bin = (int)((k >> shift) & 0xffu);
+        if (pass == 3) {   // a handful of exponents: one addition per distinct bin of the wave, not one per row
+          uint64_t open = __ballot(1);
+          while (open != 0) {
+            const int lead = __ffsll((unsigned long long)open) - 1;
+            const uint64_t same = __ballot(bin == __builtin_amdgcn_readlane(bin, lead)) & open;
+            if (((int)threadIdx.x & 63) == lead) atomicAdd(&hist[bin], (int)__popcll(same));
+            open &= ~same;
+          }
+        } else if ((k & high_mask) == prefix) {
+          atomicAdd(&hist[bin], 1);
         }
-        sh_prefix = prefix | ((uint32_t)byte << shift);
-        sh_need = need - above;
       }
       __syncthreads();
-      prefix = sh_prefix;
-      need = sh_need;
+      if (tid < 64) find_threshold_bin(hist, need, &sh_bin, &sh_need);
       __syncthreads();
+      prefix |= (uint32_t)sh_bin << shift;
+      need = sh_need;
     }
   }
   // Rows above the threshold key are taken; of the rows equal to it, the first `need` in position order.
@@ -100,14 +160,7 @@ __global__ __launch_bounds__(kUnmaskThreads) void unmask_topn_kernel(
     int eq_total;
     const int rank = base + block_exclusive_scan_flag(eq, wave_tot, &eq_total);
     base += eq_total;
-    const bool take = valid && (all || k > prefix || (eq && rank < need));
-    if (take) {
-      const int t = idx[j];
-      if (t >= 0 && t < T) {   // an entry outside [0, T) of a caller-built list is skipped, never written through
-        tokens[t] = token[j];
-        mask[t] = 0;
-      }
-    }
+    if (valid && (all || k > prefix || (eq && rank < need))) unmask_row(j);
   }
 }
 
