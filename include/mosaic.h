@@ -57,7 +57,8 @@ const char *mosaic_status_string(int status);
 #define MOSAIC_K_TILE 64
 #define MOSAIC_MAX_VOCAB_SPLITS 256
 /* Bytes at the end of every workspace for the round counters of the persistent grid (see mosaic_plan_workspace);
- * the last word is the flag of the device-side check described at MOSAIC_PLAN_GENERAL_KERNEL. */
+ * the last word is the flag of the device-side check described at MOSAIC_PLAN_GENERAL_KERNEL, the word before it the
+ * number of vocabulary splits that a launch settled on. */
 #define MOSAIC_SYNC_BYTES 1024
 
 /* Result of the chunk-size selector.  All fields are filled by mosaic_plan_workspace;
@@ -99,9 +100,9 @@ typedef struct {
  *   T          total positions, >= 0, < 2^31
  *   max_rows   host-side upper bound on M (the search in the paper is driven by the
  *              number of masks and the number of tokens; pass T if M is unknown), 0..T.  Results do
- *              not depend on it, speed does: the number of vocabulary splits is chosen so that
- *              max_rows rows fill the chip, so a bound far above the actual M leaves compute units idle
- *              (planning is a host-side function of a few microseconds: plan again as the masks shrink)
+ *              not depend on it.  The device divides the work by the rows it finds, within the partial
+ *              results this bound makes room for; a bound far above M costs little, a close one
+ *              also saves that search (~1 us) and, for few rows, gives room for more splits
  *   d, V       hidden and vocabulary size; d must be a multiple of MOSAIC_K_TILE
  *   budget_bytes  <= 0 means unbounded
  *   num_cus    compute units to schedule for; <= 0 means 256 (one MI355X)

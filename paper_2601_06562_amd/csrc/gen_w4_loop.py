@@ -13,8 +13,8 @@ import os
 import re
 import sys
 
-# fragment double buffer (2 x 16 tuples of 4 VGPRs) and two address temporaries: early-clobber outputs, so the
-# register allocator places them (a fixed clobbered range made it spill everything that lives across the loop)
+# fragment double buffer (2 x 16 tuples of 4 VGPRs) and two address temporaries.  Operand names here; the statements
+# that are built in name the fragments by number (frag_names_literal), so that the reduction can reuse them
 FA = [[f"%[fa{b}{i}]" for i in range(8)] for b in range(2)]
 FB = [[f"%[fb{b}{j}]" for j in range(8)] for b in range(2)]
 VT0, VT1 = "%[vt0]", "%[vt1]"
@@ -262,8 +262,11 @@ def step_end(top):
 
 LOG2E = 0x3FB8AA3B        # fp32 1.4426950408889634
 NEG_LOG2E = 0xBFB8AA3B
-X = [f"%[x{i}]" for i in range(32)]
-ET, EMN, ENML, ESEL, EY = "%[et]", "%[emn]", "%[enml]", "%[esel]", "%[ey]"
+# Fragments by number: v[112:239].  The reduction's 32 logits and its temporaries alias the first of them, so that the
+# compiler keeps 128 registers for what lives across a tile (with both as operands it spills).
+FRAG_BASE = 112
+X = [f"v{FRAG_BASE + i}" for i in range(32)]
+ET, EMN, ENML, EY, ESEL = (f"v{FRAG_BASE + 32 + k}" for k in range(5))
 MASK = ["s[88:89]", "s[90:91]", "s[92:93]"]
 
 
@@ -322,13 +325,11 @@ def reduce_column(tb):
 
 
 # ---- the sampling statement (Gumbel-max at temperature tau; noise from Philox4x32-10 keyed by seed, counter =
-# (vocabulary id / 4, position, 0, 0), word id % 4).  Its big register blocks are named by number so that the
-# reduction can reuse the fragment registers: v[112:239] fragments (the reduction's 32 logits alias the first 32),
-# v[240:247] two generations of the generator's two 64-bit products, v[248:249] the per-column product, v[250:255]
-# temporaries of the rare exact path.
-FRAG_BASE = 112
+# (vocabulary id / 4, position, 0, 0), word id % 4).  Its registers beyond the
+# greedy reduction's are fragment registers that are dead by then: v[164:171] two generations of the generator's two
+# 64-bit products, v[172:173] the per-column product, v[174:179] temporaries of the rare exact path.
 PHILOX_M0, PHILOX_M1 = "%[pm0]", "%[pm1]"
-KNEG = 0xF149F2CA          # -1.0e30f
+KNEG = 0xF1800000          # -2^100
 TWO23_101 = 0x4B0147AE     # 2^23 * 1.01
 TWO23 = 0x4B000000
 NEG_LN2 = 0xBF317218
@@ -356,16 +357,16 @@ def philox_quad(tb, bi, XS):
     """Words of the four ids vb + 16*bi .. +3 of column tb's position, and the jump to the exact path when one of
     them could still win.  Rounds 0 and 1 use what is known of the counter: (v4, position, 0, 0) makes the second
     product of round 0 vanish, and the first product of round 1 depends on the position alone (per column, in
-    v[248:249], its high half already xored with the round key)."""
-    A, B, C, D = ("v240", "v241"), ("v242", "v243"), ("v244", "v245"), ("v246", "v247")
+    v[172:173], its high half already xored with the round key)."""
+    A, B, C, D = ("v164", "v165"), ("v166", "v167"), ("v168", "v169"), ("v170", "v171")
     pair = lambda r: f"v[{r[0][1:]}:{r[1][1:]}]"
     e(f"v_add_u32 %[v4q], {4 * bi}, %[v4b]")
     e(f"v_mad_u64_u32 {pair(A)}, vcc, {PHILOX_M0}, %[v4q], 0")       # round 0: lo -> a3, hi
     e(f"v_xor_b32 {A[1]}, %[k1_0], {A[1]}")                          # a2 = hi ^ k1
     e(f"v_mad_u64_u32 {pair(B)}, vcc, {PHILOX_M1}, {A[1]}, 0")       # round 1, second product: lo -> b1, hi
     e(f"v_xor_b32 {B[1]}, %[k0_1], {B[1]}")                          # b0 = hi ^ k0   (a1 = 0)
-    e(f"v_xor_b32 {A[1]}, v249, {A[0]}")                             # b2 = (hi(M0 a0) ^ k1) ^ a3
-    c0, c1, c2, c3 = B[1], B[0], A[1], "v248"                        # b3 = lo(M0 a0)
+    e(f"v_xor_b32 {A[1]}, v173, {A[0]}")                             # b2 = (hi(M0 a0) ^ k1) ^ a3
+    c0, c1, c2, c3 = B[1], B[0], A[1], "v172"                        # b3 = lo(M0 a0)
     cur, nxt = (A, B), (C, D)
     for r in range(2, 10):
         PA, PB = nxt
@@ -431,39 +432,39 @@ def score_candidate(word, x, el):
     -ln(1 - e)), and the tile's best (score, element, logit) updated by it: a higher score wins, the lower element
     on equal scores."""
     M3, M2, M1 = MASK
-    return [f"v_lshrrev_b32 v250, 9, {word}",                            # k
-            f"v_sub_u32 v251, {hex(0x7FFFFF)}, v250",                    # 2^23 - 1 - k
-            "v_cvt_f32_u32 v250, v250",
-            "v_cvt_f32_u32 v251, v251",
-            "v_add_f32 v250, 0.5, v250",
-            "v_add_f32 v251, 0.5, v251",
-            f"v_mul_f32 v250, {hex(TWO_M23)}, v250",                     # u
-            f"v_mul_f32 v251, {hex(TWO_M23)}, v251",                     # e = 1 - u
-            "v_log_f32 v252, v250",
-            f"v_mul_f32 v253, {hex(THIRD)}, v251",                       # e (1 + e (1/2 + e/3)) = -ln(1 - e) near u = 1
-            "v_add_f32 v253, 0.5, v253",
-            f"v_mul_f32 v252, {hex(NEG_LN2)}, v252",                     # -ln u
-            "v_mul_f32 v253, v251, v253",
-            "v_add_f32 v253, 1.0, v253",
-            f"v_cmp_gt_f32 vcc, {hex(TWO_M8)}, v251",
-            "v_mul_f32 v253, v251, v253",
+    return [f"v_lshrrev_b32 v174, 9, {word}",                            # k
+            f"v_sub_u32 v175, {hex(0x7FFFFF)}, v174",                    # 2^23 - 1 - k
+            "v_cvt_f32_u32 v174, v174",
+            "v_cvt_f32_u32 v175, v175",
+            "v_add_f32 v174, 0.5, v174",
+            "v_add_f32 v175, 0.5, v175",
+            f"v_mul_f32 v174, {hex(TWO_M23)}, v174",                     # u
+            f"v_mul_f32 v175, {hex(TWO_M23)}, v175",                     # e = 1 - u
+            "v_log_f32 v176, v174",
+            f"v_mul_f32 v177, {hex(THIRD)}, v175",                       # e (1 + e (1/2 + e/3)) = -ln(1 - e) near u = 1
+            "v_add_f32 v177, 0.5, v177",
+            f"v_mul_f32 v176, {hex(NEG_LN2)}, v176",                     # -ln u
+            "v_mul_f32 v177, v175, v177",
+            "v_add_f32 v177, 1.0, v177",
+            f"v_cmp_gt_f32 vcc, {hex(TWO_M8)}, v175",
+            "v_mul_f32 v177, v175, v177",
             "s_nop 0",
-            "v_cndmask_b32 v252, v252, v253, vcc",                       # inner = e < 2^-8 ? series : by the logarithm
-            "v_log_f32 v252, v252",
+            "v_cndmask_b32 v176, v176, v177, vcc",                       # inner = e < 2^-8 ? series : by the logarithm
+            "v_log_f32 v176, v176",
             "s_nop 0",
-            f"v_mul_f32 v252, {hex(NEG_LN2)}, v252",                     # g = -ln(inner)
-            "v_mul_f32 v252, %[tau], v252",
-            f"v_add_f32 v252, {x}, v252",                                # y = x + tau g
-            f"v_cmp_eq_f32_e64 {M2}, v252, %[yt]",
+            f"v_mul_f32 v176, {hex(NEG_LN2)}, v176",                     # g = -ln(inner)
+            "v_mul_f32 v176, %[tau], v176",
+            f"v_add_f32 v176, {x}, v176",                                # y = x + tau g
+            f"v_cmp_eq_f32_e64 {M2}, v176, %[yt]",
             f"v_cmp_gt_u32_e64 {M1}, %[sels], {el}",
-            "v_cmp_gt_f32 vcc, v252, %[yt]",
+            "v_cmp_gt_f32 vcc, v176, %[yt]",
             "s_nop 1",
             f"s_and_b64 {M2}, {M2}, {M1}",
             f"s_or_b64 vcc, vcc, {M2}",
             "s_nop 1",
             f"v_cndmask_b32_e64 %[sels], %[sels], {el}, vcc",
             f"v_cndmask_b32 %[xsel], %[xsel], {x}, vcc",
-            "v_cndmask_b32 %[yt], %[yt], v252, vcc"]
+            "v_cndmask_b32 %[yt], %[yt], v176, vcc"]
 
 
 def reduce_column_sample(tb):
@@ -475,9 +476,9 @@ def reduce_column_sample(tb):
     XS = [f"v{FRAG_BASE + i}" for i in range(32)]
     # the best score so far of the three other lanes that hold the same token (lane ^ 16, ^ 32, ^ 48): any score
     # already reached for the row bounds what can still win it
-    e(f"ds_bpermute_b32 v253, %[sw16], {YM}")
-    e(f"ds_bpermute_b32 v254, %[sw32], {YM}")
-    e(f"ds_bpermute_b32 v255, %[sw48], {YM}")
+    e(f"ds_bpermute_b32 v177, %[sw16], {YM}")
+    e(f"ds_bpermute_b32 v178, %[sw32], {YM}")
+    e(f"ds_bpermute_b32 v179, %[sw48], {YM}")
     for el in range(32):
         e(f"v_accvgpr_read_b32 {XS[el]}, {acc_reg(el // 4, tb, el % 4)}")
     e(f"v_max3_f32 {ET}, {XS[0]}, {XS[1]}, {XS[2]}")
@@ -486,18 +487,18 @@ def reduce_column_sample(tb):
     e(f"v_max_f32 {ET}, {ET}, {XS[31]}")
     # the bound on the words: candidates have (w >> 9) >= 2^23 - Z, Z = min(2^23, 1.01 * 2^23 * exp((t - ym)/tau) + 2)
     e("s_waitcnt lgkmcnt(0)")
-    e(f"v_max3_f32 v253, v253, v254, v255")
-    e(f"v_max_f32 v253, v253, {YM}")
-    e(f"v_sub_f32 {EY}, {ET}, v253")
+    e(f"v_max3_f32 v177, v177, v178, v179")
+    e(f"v_max_f32 v177, v177, {YM}")
+    e(f"v_sub_f32 {EY}, {ET}, v177")
     e(f"v_mul_f32 {EY}, %[itl], {EY}")                               # log2(e) / tau
     e(f"v_exp_f32 {EY}, {EY}")
     e(f"v_xor_b32 %[a0], %[k0_0], {POS}")                            # round 0: a0 = position ^ k0
     e(f"v_mul_f32 {EY}, {hex(TWO23_101)}, {EY}")
-    e(f"v_mad_u64_u32 v[248:249], vcc, {PHILOX_M0}, %[a0], 0")       # round 1, first product: position only
+    e(f"v_mad_u64_u32 v[172:173], vcc, {PHILOX_M0}, %[a0], 0")       # round 1, first product: position only
     e(f"v_add_f32 {EY}, 2.0, {EY}")
     e(f"v_min_f32 {EY}, {hex(TWO23)}, {EY}")
     e(f"v_cvt_u32_f32 %[wlo], {EY}")
-    e(f"v_xor_b32 v249, %[k1_1], v249")
+    e(f"v_xor_b32 v173, %[k1_1], v173")
     e(f"v_sub_u32 %[wlo], {hex(0x800000)}, %[wlo]")
     e(f"v_lshlrev_b32 %[wlo], 9, %[wlo]")
     e(f"v_mov_b32 %[yt], {hex(KNEG)}")
@@ -545,13 +546,8 @@ def reduce_column_sample(tb):
 def build_tile_sample():
     """The statement of the sampling kernel: K-loop on fragments and accumulators named by number, then the
     reduction with the noise; the rare exact paths sit behind the end of the statement."""
-    saved = ([row[:] for row in FA], [row[:] for row in FB])
-    fa, fb = frag_names_literal()
-    for b in range(2):
-        FA[b][:], FB[b][:] = fa[b], fb[b]
-    LITERAL_ACC[0] = True
     slow_blocks.clear()
-    build()
+    build_literal()
     e(f"s_mov_b32 %[k0_0], %[seed_lo]")                              # key of round r = seed + r * (golden-ratio words)
     e(f"s_mov_b32 %[k1_0], %[seed_hi]")
     for r in range(1, 10):
@@ -574,9 +570,6 @@ def build_tile_sample():
         for ln in blk:
             e(ln)
     e(f"{done}:")
-    LITERAL_ACC[0] = False
-    for b in range(2):
-        FA[b][:], FB[b][:] = saved[0][b], saved[1][b]
     named = re.compile(r"%\[(\w+)\]")
     lines[:] = [named.sub(lambda m: SAMPLE_TEMPS.get(m.group(1), m.group(0)), ln) for ln in lines]
 
@@ -584,11 +577,22 @@ def build_tile_sample():
 def build_tile():
     """The statement of the greedy kernel: the K-loop on accumulators it starts itself, then the reduction of the
     tile."""
-    LITERAL_ACC[0] = True
-    build()
+    build_literal()
     for tb in range(8):
         reduce_column(tb)
+
+
+def build_literal():
+    """The K-loop on fragments and accumulators named by number."""
+    saved = ([row[:] for row in FA], [row[:] for row in FB])
+    fa, fb = frag_names_literal()
+    for b in range(2):
+        FA[b][:], FB[b][:] = fa[b], fb[b]
+    LITERAL_ACC[0] = True
+    build()
     LITERAL_ACC[0] = False
+    for b in range(2):
+        FA[b][:], FB[b][:] = saved[0][b], saved[1][b]
 
 
 def build():
@@ -662,24 +666,15 @@ def write_statement(path, sample=False):
         build_tile_sample()
         outs = []
         for tb in range(8):
-            outs += [f'[m{tb}] "+v"(run_m[{tb}])', f'[s{tb}] "+v"(run_s[{tb}])', f'[i{tb}] "+v"(run_i[{tb}])',
+            outs += [f'[m{tb}] "+v"(tile_m[{tb}])', f'[s{tb}] "+v"(tile_s[{tb}])', f'[i{tb}] "+v"(run_i[{tb}])',
                      f'[ym{tb}] "+v"(run_ym[{tb}])', f'[xa{tb}] "+v"(run_xa[{tb}])']
     else:
         build_tile()
         outs = []
         for tb in range(8):
-            outs += [f'[m{tb}] "+v"(run_m[{tb}])', f'[s{tb}] "+v"(run_s[{tb}])', f'[i{tb}] "+v"(run_i[{tb}])']
-        outs += [f'[x{i}] "=&v"(red_x[{i}])' for i in range(32)]
-        outs += ['[et] "=&v"(red_t)', '[emn] "=&v"(red_mn)', '[enml] "=&v"(red_nml)', '[esel] "=&v"(red_sel)',
-                 '[ey] "=&v"(red_y)']
+            outs += [f'[m{tb}] "+v"(tile_m[{tb}])', f'[s{tb}] "+v"(tile_s[{tb}])', f'[i{tb}] "+v"(tile_i[{tb}])']
     for name in ("wsrc_lo", "wsrc_hi", "hsrc_lo", "hsrc_hi", "wrd", "hrd", "wdst", "hdst", "wk", "hk", "g"):
         outs.append(f'[{name}] "+s"(st_{name})')
-    if not sample:
-        for b in range(2):
-            for i in range(8):
-                outs.append(f'[fa{b}{i}] "=&v"(frag_a[{b}][{i}])')
-            for j in range(8):
-                outs.append(f'[fb{b}{j}] "=&v"(frag_b[{b}][{j}])')
     outs.append('[vt0] "=&v"(addr_tmp0)')
     outs.append('[vt1] "=&v"(addr_tmp1)')
     ins = []
@@ -701,7 +696,7 @@ def write_statement(path, sample=False):
         ins += ['[seed_lo] "s"(seed_lo)', '[seed_hi] "s"(seed_hi)']
         clob = [f'"s{i}"' for i in range(66, KEY1_BASE + 10)] + clob
         ins += ['[pm0] "s"(philox_m0)', '[pm1] "s"(philox_m1)', '[itl] "s"(inv_tau_log2e)', '[tau] "s"(tau_s)']
-        clob = [f'"v{i}"' for i in range(FRAG_BASE, 256)] + clob
+    clob = [f'"v{i}"' for i in range(FRAG_BASE, FRAG_BASE + 128)] + clob
     with open(path, "w") as f:
         f.write("// GENERATED by gen_w4_loop.py -- do not edit.  " +
                 ("One vocabulary tile of the sampling 4-wave kernel: K-loop and vocabulary reduction.\n" if sample else

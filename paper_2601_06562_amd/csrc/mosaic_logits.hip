@@ -17,9 +17,10 @@
 //
 // Work decomposition.  A unit is (row tile of 256 masked tokens, vocabulary split); a workgroup (4 waves
 // in the hand-scheduled kernel, 8 in the general one) walks the 256-wide vocabulary tiles of its split,
-// carrying the running triple in registers, and writes one partial triple per row at the end.  A second
-// tiny kernel merges the S partials per row in an order fixed by S (deterministic) and emits token,
-// confidence and log-sum-exp.
+// folding each finished tile into a running triple in registers, and writes one partial triple per row at the
+// end.  A second tiny kernel merges the S partials per row and emits token, confidence and log-sum-exp.  How many
+// splits there are is decided on the device from the rows found (mosaic_schedule.h); the fold makes the results
+// independent of it.
 //
 // Sampling.  The SAMPLE instantiations of both kernels draw the token by the Gumbel-max form of categorical
 // sampling at temperature tau (paper section 2.1 leaves the sampler open): arg-max of x + tau*g with g from a
@@ -37,6 +38,7 @@
 #include <stdlib.h>
 
 #include "mosaic_internal.h"
+#include "mosaic_schedule.h"
 
 namespace mosaic {
 
@@ -48,7 +50,9 @@ typedef const __attribute__((address_space(1))) void* gbl_ptr_t;
 constexpr int kTileRows = MOSAIC_ROW_TILE;     // masked tokens per tile (MFMA N side)
 constexpr int kTileVocab = MOSAIC_VOCAB_TILE;  // vocabulary ids per tile (MFMA M side)
 constexpr int kThreads = 512;                  // 8 waves: 2 (vocabulary halves) x 4 (token quarters)
-constexpr float kNeg = -1.0e30f;                     // "minus infinity" that survives subtraction
+// "Minus infinity" that survives subtraction.  A power of two: its product with log2 e is then exact, so that a lane
+// whose ids all lie past the vocabulary holds a plain finite sum relative to it, which every merge scales to zero.
+constexpr float kNeg = -0x1p100f;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -65,25 +69,25 @@ struct KernelParams {
   int32_t row0;        // first compacted row of this chunk
   int32_t chunk_rows;  // capacity of the chunk (C)
   int32_t max_rows;
-  int32_t splits;      // S
   int32_t panel;       // row tiles scheduled side by side
-  int32_t vocab_tiles; // vocabulary tiles this launch covers (all ceil(V / 256) of them unless the launch is one of a pair)
-  int32_t tile_first;  // first of those tiles
-  int32_t split_first; // partial slot of this launch's split 0
-  int32_t c_pad;       // row capacity of the partial arrays
-  float* part_m;
-  float* part_s;
-  int32_t* part_i;
+  ScheduleInput sched; // what the division of the work is made from (of a pair of launches: the first one's)
+  Schedule bound;      // ... and the division for bound_rows rows
+  int32_t bound_rows;
+  int32_t ragged_tile; // second launch of a pair: it covers this vocabulary tile alone, behind the other splits; else -1
+  int32_t id_bits;     // bits of a vocabulary id in a packed partial
+  float* part_m;       // largest logit per row and split
+  uint64_t* part_si;   // the sum of exponentials and the id (pack_sum_id)
   int32_t* out_token;
   float* out_conf;
   float* out_lse;
   // sampling with temperature (tau > 0): two more partial planes and the generator key
   float tau;
   uint32_t seed_lo, seed_hi;
-  float* part_ym;   // best perturbed score x + tau*g
+  float* part_ym;   // best perturbed score x + tau*g (the id in part_si is then this score's)
   float* part_xa;   // the unperturbed logit at that arg-max
   int32_t* sync;    // round counters of the persistent grid (cleared before the launch), sync_slots of them
   int32_t sync_slots;
+  int32_t* found_splits;   // the splits of the division a launch found, for the merge kernel
   // Hidden tensors of 4 GiB or more.  The 4-wave kernel addresses a wave's 64 rows by 32-bit offsets from the lowest of
   // them, which works unless those rows lie 4 GiB or more apart; a small kernel looks for such a group in the list
   // and raises *wide_flag, and of the two launches that follow (4-wave kernel, general kernel) the one whose
@@ -92,22 +96,50 @@ struct KernelParams {
   int32_t wide_run_if;
 };
 
-// (m, s, i) monoid: max, sum of exp relative to the max, lowest index attaining the max.
-__device__ __forceinline__ void merge_triple(float& m, float& s, int& i, float m2, float s2, int i2) {
-  const float mn = fmaxf(m, m2);
-  const float a = __builtin_amdgcn_exp2f((m - mn) * kLog2e);
-  const float b = __builtin_amdgcn_exp2f((m2 - mn) * kLog2e);
-  const bool keep = (m > m2) || (m == m2 && i < i2);
-  s = s * a + s2 * b;
-  i = keep ? i : i2;
-  m = mn;
+// Fold.  The running state of a row is (m, s, i): the largest logit, the sum of exponentials, and the lowest id that
+// attains m.  s is kept relative to 2^E, E = ceil(m log2 e), in double precision: a change of m only ever scales s by
+// an exact power of two, and what a tile adds depends on the tile alone.  Any order and any grouping of the tiles
+// then gives the same sum to ~2^-50, so the outputs, rounded to fp32, are those of one pass over the vocabulary
+// however it was split (only a sum within 2^-46 of a rounding boundary could tell), and the division of the work is
+// free to follow the number of rows.  A scale factor exp(m - m') rounded in fp32 at each step, as the state once had,
+// makes the last bits follow the split count.
+__device__ __forceinline__ float ref_exponent(float m) { return __builtin_ceilf(m * kLog2e); }
+__device__ __forceinline__ int scale_steps(float d) { return (int)fmaxf(d, -2000.f); }   // 2^-2000 is 0 either way
+
+// One tile's triple (s relative to exp(m), fp32) as a folded sum, relative to 2^ref_exponent(m).
+__device__ __forceinline__ double tile_sum(float m, float s) {
+  return (double)(s * __builtin_amdgcn_exp2f(__builtin_fmaf(m, kLog2e, -ref_exponent(m))));
 }
 
-// log-sum-exp pair alone (max, sum of exp relative to the max).
-__device__ __forceinline__ void merge_ms(float& m, float& s, float m2, float s2) {
-  const float mn = fmaxf(m, m2);
-  s = s * __builtin_amdgcn_exp2f((m - mn) * kLog2e) + s2 * __builtin_amdgcn_exp2f((m2 - mn) * kLog2e);
-  m = mn;
+// Folded sums added; m becomes the larger maximum.
+__device__ __forceinline__ void merge_sum(float& m, double& s, float m2, double s2) {
+  const float e = ref_exponent(m), e2 = ref_exponent(m2), en = fmaxf(e, e2);
+  s = __builtin_ldexp(s, scale_steps(e - en)) + __builtin_ldexp(s2, scale_steps(e2 - en));
+  m = fmaxf(m, m2);
+}
+__device__ __forceinline__ void merge_triple(float& m, double& s, int& i, float m2, double s2, int i2) {
+  const bool keep = (m > m2) || (m == m2 && i < i2);
+  i = keep ? i : i2;
+  merge_sum(m, s, m2, s2);
+}
+
+// A partial result is 12 bytes: m, and one 64-bit word with the id in its low id_bits bits and above them s as a
+// floating-point number of 6 exponent bits (s lies between 1/2 and the number of ids) and the remaining
+// 58 - id_bits mantissa bits (41 for 126464 ids), rounded to nearest.  0 stands for an empty sum.
+constexpr int kSumBias = 1019;   // exponent field of a double that is stored as 0
+__device__ __forceinline__ uint64_t pack_sum_id(double s, int i, int id_bits) {
+  const int drop = id_bits > 6 ? id_bits - 6 : 0;       // mantissa bits of the double that do not fit
+  uint64_t b = (uint64_t)__double_as_longlong(s);
+  if (drop > 0) b += (uint64_t)1 << (drop - 1);
+  b = (b >> drop) - ((uint64_t)kSumBias << (52 - drop));
+  if (s == 0.0) b = 0;
+  return b << id_bits | ((uint64_t)(uint32_t)i & (((uint64_t)1 << id_bits) - 1));
+}
+__device__ __forceinline__ void unpack_sum_id(uint64_t w, int id_bits, double& s, int& i) {
+  const int drop = id_bits > 6 ? id_bits - 6 : 0;
+  i = (int)(w & (((uint64_t)1 << id_bits) - 1));
+  const uint64_t b = w >> id_bits;
+  s = b == 0 ? 0.0 : __longlong_as_double((long long)((b + ((uint64_t)kSumBias << (52 - drop))) << drop));
 }
 
 // Sampled candidate: best perturbed score, the plain logit there, its id (lowest id on equal scores).
@@ -154,6 +186,19 @@ __device__ __forceinline__ int xcd_contiguous_position(int b, int G) {
   int first = 0;
   for (int y = 0; y < x; ++y) first += (G - y + 7) >> 3;
   return first + (b >> 3);
+}
+
+// Rows of this launch's chunk, and the division of the work for them.
+__device__ __forceinline__ int chunk_rows_found(const KernelParams& p) {
+  int total = *p.count;
+  if (total > p.max_rows) total = p.max_rows;
+  const int rows = total - p.row0;
+  return rows > p.chunk_rows ? p.chunk_rows : rows;
+}
+__device__ __forceinline__ Schedule launch_schedule(const KernelParams& p, int rows) {
+  const Schedule sched = rows == p.bound_rows ? p.bound : choose_schedule_wave(p.sched, rows);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *p.found_splits = sched.splits;
+  return sched;
 }
 
 // Round alignment of the persistent grid.  A workgroup that takes more than one unit meets the others before each
@@ -227,7 +272,7 @@ __device__ __forceinline__ float exp_rel(float x, float mn, float nml) {
 }
 
 // Reduce one finished 256x256 logits tile (this wave's 128 vocabulary ids x 64 tokens) into the
-// lane's running triples.  vb = vocabulary id of this lane's element (block 0, register 0).
+// lane's triples of the tile.  vb = vocabulary id of this lane's element (block 0, register 0).
 template <bool TAIL>
 __device__ __forceinline__ void reduce_tile(f32x16 (&acc)[4][2], float (&m)[2], float (&s)[2], int (&ix)[2], int vb,
                                             int V) {
@@ -341,12 +386,12 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
   constexpr int kSubSteps = 4;
   constexpr int kDW = NW - 1, kDH = NH - 1;             // prefetch distance in K-tiles
   constexpr int kRing = (NW + NH) * kOperandBytes;
-  constexpr int kLds = (NW + NH == 5) ? kRing : kRing + 5 * 256 * 4;
+  constexpr int kLds = (NW + NH == 5) ? kRing : kRing + 6 * 256 * 4;
   constexpr int kRedOff = (NW + NH == 5) ? 0 : kRing;   // 5 slots fill the LDS: merge scratch aliases slot 0
   __shared__ __attribute__((aligned(1024))) char smem[kLds];
-  float* red_m = reinterpret_cast<float*>(smem + kRedOff);
-  float* red_s = red_m + 256;
-  int* red_i = reinterpret_cast<int*>(red_s + 256);
+  double* red_s = reinterpret_cast<double*>(smem + kRedOff);
+  float* red_m = reinterpret_cast<float*>(red_s + 256);
+  int* red_i = reinterpret_cast<int*>(red_m + 256);
   float* red_ym = reinterpret_cast<float*>(red_i + 256);   // sampling only
   float* red_xa = red_ym + 256;
 
@@ -356,16 +401,15 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
   const int l32 = lane & 31, lhalf = lane >> 5;
 
   if (p.wide_flag != nullptr && *p.wide_flag != p.wide_run_if) return;   // the other kernel of the two serves this list
-  int total = *p.count;
-  if (total > p.max_rows) total = p.max_rows;
-  int rows = total - p.row0;
-  if (rows > p.chunk_rows) rows = p.chunk_rows;
+  const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
-  const int n_tt = (rows + kTileRows - 1) / kTileRows;
+  const Schedule sched = launch_schedule(p, rows);
+  const int n_tt = sched.row_tiles;
 
   const int G = gridDim.x;
   const int pos = xcd_contiguous_position((int)blockIdx.x, G);
-  const int S = p.splits;
+  const bool ragged_only = p.ragged_tile >= 0;
+  const int S = ragged_only ? 1 : sched.splits;
   const int n_units = n_tt * S;
   const int A = p.panel < n_tt ? p.panel : n_tt;
   const int full_panel_units = A * S;
@@ -389,8 +433,8 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
     const int hp = (n_tt - pnl * A) < A ? (n_tt - pnl * A) : A;
     const int sp = ul / hp;
     const int tt = pnl * A + ul % hp;
-    const int vt0 = p.tile_first + (int)(((int64_t)sp * p.vocab_tiles) / S);
-    const int vt1 = p.tile_first + (int)(((int64_t)(sp + 1) * p.vocab_tiles) / S);
+    const int vt0 = ragged_only ? p.ragged_tile : (int)(((int64_t)sp * p.sched.vocab_tiles) / S);
+    const int vt1 = ragged_only ? p.ragged_tile + 1 : (int)(((int64_t)(sp + 1) * p.sched.vocab_tiles) / S);
     const int ntile = vt1 - vt0;
     const int total_steps = ntile * nk;
 
@@ -452,7 +496,7 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
     constexpr int kDMin = kDW < kDH ? kDW : kDH;
 
     float run_m[2] = {kNeg, kNeg};
-    float run_s[2] = {0.f, 0.f};
+    double run_s[2] = {0.0, 0.0};
     int run_i[2] = {INT_MAX, INT_MAX};
     float run_ym[2] = {kNeg, kNeg};   // sampling: best x + tau*g, the plain logit there
     float run_xa[2] = {0.f, 0.f};
@@ -509,24 +553,32 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 
       const int v_tile0 = (vt0 + n) * kTileVocab;
       const int vb = v_tile0 + wv * 128 + 4 * lhalf;
+      float tile_m[2] = {kNeg, kNeg}, tile_s[2] = {0.f, 0.f};   // this tile's own triple, folded in below
+      int tile_i[2] = {INT_MAX, INT_MAX};
       if constexpr (SAMPLE) {
         if (v_tile0 + kTileVocab > p.V)
-          reduce_tile_sample<true>(acc, run_m, run_s, run_ym, run_xa, run_i, vb, p.V, pos, p.seed_lo, p.seed_hi, p.tau);
+          reduce_tile_sample<true>(acc, tile_m, tile_s, run_ym, run_xa, run_i, vb, p.V, pos, p.seed_lo, p.seed_hi, p.tau);
         else
-          reduce_tile_sample<false>(acc, run_m, run_s, run_ym, run_xa, run_i, vb, p.V, pos, p.seed_lo, p.seed_hi, p.tau);
+          reduce_tile_sample<false>(acc, tile_m, tile_s, run_ym, run_xa, run_i, vb, p.V, pos, p.seed_lo, p.seed_hi, p.tau);
       } else {
-        if (v_tile0 + kTileVocab > p.V) reduce_tile<true>(acc, run_m, run_s, run_i, vb, p.V);
-        else reduce_tile<false>(acc, run_m, run_s, run_i, vb, p.V);
+        if (v_tile0 + kTileVocab > p.V) reduce_tile<true>(acc, tile_m, tile_s, tile_i, vb, p.V);
+        else reduce_tile<false>(acc, tile_m, tile_s, tile_i, vb, p.V);
+      }
+#pragma unroll
+      for (int bj = 0; bj < 2; ++bj) {
+        const double ts = tile_sum(tile_m[bj], tile_s[bj]);
+        if constexpr (SAMPLE) merge_sum(run_m[bj], run_s[bj], tile_m[bj], ts);
+        else merge_triple(run_m[bj], run_s[bj], run_i[bj], tile_m[bj], ts, tile_i[bj]);
       }
     }
 
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj) {
       const float m2 = __shfl_xor(run_m[bj], 32, 64);
-      const float s2 = __shfl_xor(run_s[bj], 32, 64);
+      const double s2 = __shfl_xor(run_s[bj], 32, 64);
       const int i2 = __shfl_xor(run_i[bj], 32, 64);
       if constexpr (SAMPLE) {
-        merge_ms(run_m[bj], run_s[bj], m2, s2);
+        merge_sum(run_m[bj], run_s[bj], m2, s2);
         merge_pick(run_ym[bj], run_xa[bj], run_i[bj], __shfl_xor(run_ym[bj], 32, 64), __shfl_xor(run_xa[bj], 32, 64), i2);
       } else {
         merge_triple(run_m[bj], run_s[bj], run_i[bj], m2, s2, i2);
@@ -551,9 +603,10 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 #pragma unroll
       for (int bj = 0; bj < 2; ++bj) {
         const int e = (wt * 2 + bj) * 32 + l32;
-        const int64_t slot = (int64_t)(p.split_first + sp) * p.c_pad + tt * kTileRows + e;
+        if (tt * kTileRows + e >= rows) continue;
+        const int64_t slot = (int64_t)(ragged_only ? sched.splits : sp) * sched.stride + tt * kTileRows + e;
         if constexpr (SAMPLE) {
-          merge_ms(run_m[bj], run_s[bj], red_m[e], red_s[e]);
+          merge_sum(run_m[bj], run_s[bj], red_m[e], red_s[e]);
           merge_pick(run_ym[bj], run_xa[bj], run_i[bj], red_ym[e], red_xa[e], red_i[e]);
           p.part_ym[slot] = run_ym[bj];
           p.part_xa[slot] = run_xa[bj];
@@ -561,8 +614,7 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
           merge_triple(run_m[bj], run_s[bj], run_i[bj], red_m[e], red_s[e], red_i[e]);
         }
         p.part_m[slot] = run_m[bj];
-        p.part_s[slot] = run_s[bj];
-        p.part_i[slot] = run_i[bj];
+        p.part_si[slot] = pack_sum_id(run_s[bj], run_i[bj], p.id_bits);
       }
     }
     __syncthreads();  // the scratch is read before the next unit's copies may overwrite it
@@ -585,9 +637,9 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   constexpr int kOperandBytes = 256 * kRowBytes;        // 32 KiB
   constexpr int kSwzShift = 1;
   __shared__ __attribute__((aligned(1024))) char smem[(NW + NH) * kOperandBytes];
-  float* red_m = reinterpret_cast<float*>(smem);        // merge scratch aliases W slot 0 at unit end
-  float* red_s = red_m + 256;
-  int* red_i = reinterpret_cast<int*>(red_s + 256);
+  double* red_s = reinterpret_cast<double*>(smem);      // merge scratch aliases W slot 0 at unit end
+  float* red_m = reinterpret_cast<float*>(red_s + 256);
+  int* red_i = reinterpret_cast<int*>(red_m + 256);
   float* red_ym = reinterpret_cast<float*>(red_i + 256);   // sampling only
   float* red_xa = red_ym + 256;
 
@@ -597,16 +649,14 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   const int l16 = lane & 15, q = lane >> 4;   // MFMA 16x16x32: row/column lane%16, k group lane/16
 
   if (p.wide_flag != nullptr && *p.wide_flag != p.wide_run_if) return;   // the other kernel of the two serves this list
-  int total = *p.count;
-  if (total > p.max_rows) total = p.max_rows;
-  int rows = total - p.row0;
-  if (rows > p.chunk_rows) rows = p.chunk_rows;
+  const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
-  const int n_tt = (rows + kTileRows - 1) / kTileRows;
+  const Schedule sched = launch_schedule(p, rows);
+  const int n_tt = sched.row_tiles;
 
   const int G = gridDim.x;
   const int pos = xcd_contiguous_position((int)blockIdx.x, G);
-  const int S = p.splits;
+  const int S = sched.splits;
   const int n_units = n_tt * S;
   const int A = p.panel < n_tt ? p.panel : n_tt;
   const int full_panel_units = A * S;
@@ -650,8 +700,8 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
     const int hp = (n_tt - pnl * A) < A ? (n_tt - pnl * A) : A;
     const int sp = ul / hp;
     const int tt = pnl * A + ul % hp;
-    const int vt0 = (int)(((int64_t)sp * p.vocab_tiles) / S);
-    const int vt1 = (int)(((int64_t)(sp + 1) * p.vocab_tiles) / S);
+    const int vt0 = (int)(((int64_t)sp * p.sched.vocab_tiles) / S);
+    const int vt1 = (int)(((int64_t)(sp + 1) * p.sched.vocab_tiles) / S);
     const int ntile = vt1 - vt0;
     const int total_steps = ntile * nk;
     const uint32_t u_total = (uint32_t)total_steps;
@@ -719,11 +769,12 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
     uint32_t st_wk = (uint32_t)(gw % nk), st_hk = (uint32_t)(gh % nk);
     uint32_t st_g = 0;
 
-    float run_m[8], run_s[8], run_ym[8], run_xa[8];
+    float run_m[8], run_ym[8], run_xa[8];
+    double run_s[8];
     int run_i[8], pos[8];
 #pragma unroll
     for (int tb = 0; tb < 8; ++tb) {
-      run_m[tb] = kNeg; run_s[tb] = 0.f; run_i[tb] = INT_MAX; run_ym[tb] = kNeg; run_xa[tb] = 0.f; pos[tb] = 0;
+      run_m[tb] = kNeg; run_s[tb] = 0.0; run_i[tb] = INT_MAX; run_ym[tb] = kNeg; run_xa[tb] = 0.f; pos[tb] = 0;
       if constexpr (SAMPLE) {   // the position whose row this lane's column tb holds
         int j = tt * kTileRows + wt * 128 + tb * 16 + l16;
         if (j > rows - 1) j = rows - 1;
@@ -750,17 +801,25 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
       const uint32_t st_hwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_hwrap);
         uint32_t addr_tmp0, addr_tmp1;
         const int vb = (vt0 + n) * kTileVocab + wv * 128 + 4 * q;   // vocabulary id of this lane's element 0
+        float tile_m[8], tile_s[8];   // this tile's own triples
+        int tile_i[8];
+#pragma unroll
+        for (int tb = 0; tb < 8; ++tb) { tile_m[tb] = kNeg; tile_s[tb] = 0.f; tile_i[tb] = INT_MAX; }
         if constexpr (SAMPLE) {
-          // sampling: the same, with the Gumbel-max draw in the reduction (fragments, accumulators, the
-          // reduction's temporaries and the round keys all by number)
+          // sampling: the same, with the Gumbel-max draw in the reduction (round keys by number too).  The drawn
+          // candidate is carried from tile to tile: it bounds what can still win
 #include "mosaic_w4_tile_sample.inc"
         } else {
-          // greedy: one statement clears the accumulators (the AGPR file, by number), runs the K-loop and folds
-          // the tile into the running triples, so nothing of it is left to the compiler's scheduling
-          bf16x8 frag_a[2][8], frag_b[2][8];   // written and consumed inside the statement only
-          float red_x[32], red_t, red_mn, red_nml, red_y;
-          int red_sel;
+          // greedy: one statement clears the accumulators (the AGPR file, by number), runs the K-loop and reduces
+          // the tile to a triple per column (fragments and temporaries by number), so nothing of it is left to the
+          // compiler's scheduling
 #include "mosaic_w4_tile.inc"
+        }
+        // the fold, ~25 instructions per column and tile of 64 K-tiles: 0.5% of the tile
+#pragma unroll
+        for (int tb = 0; tb < 8; ++tb) {
+          if constexpr (!SAMPLE) run_i[tb] = tile_m[tb] > run_m[tb] ? tile_i[tb] : run_i[tb];   // ascending tiles
+          merge_sum(run_m[tb], run_s[tb], tile_m[tb], tile_sum(tile_m[tb], tile_s[tb]));
         }
       }
     }
@@ -772,10 +831,10 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
 #pragma unroll
       for (int x = 16; x <= 32; x <<= 1) {
         const float m2 = __shfl_xor(run_m[tb], x, 64);
-        const float s2 = __shfl_xor(run_s[tb], x, 64);
+        const double s2 = __shfl_xor(run_s[tb], x, 64);
         const int i2 = __shfl_xor(run_i[tb], x, 64);
         if constexpr (SAMPLE) {
-          merge_ms(run_m[tb], run_s[tb], m2, s2);
+          merge_sum(run_m[tb], run_s[tb], m2, s2);
           merge_pick(run_ym[tb], run_xa[tb], run_i[tb], __shfl_xor(run_ym[tb], x, 64), __shfl_xor(run_xa[tb], x, 64), i2);
         } else {
           merge_triple(run_m[tb], run_s[tb], run_i[tb], m2, s2, i2);
@@ -801,9 +860,10 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
 #pragma unroll
       for (int tb = 0; tb < 8; ++tb) {
         const int e = wt * 128 + tb * 16 + l16;
-        const int64_t slot = (int64_t)sp * p.c_pad + tt * kTileRows + e;
+        if (tt * kTileRows + e >= rows) continue;
+        const int64_t slot = (int64_t)sp * sched.stride + tt * kTileRows + e;
         if constexpr (SAMPLE) {
-          merge_ms(run_m[tb], run_s[tb], red_m[e], red_s[e]);
+          merge_sum(run_m[tb], run_s[tb], red_m[e], red_s[e]);
           merge_pick(run_ym[tb], run_xa[tb], run_i[tb], red_ym[e], red_xa[e], red_i[e]);
           p.part_ym[slot] = run_ym[tb];
           p.part_xa[slot] = run_xa[tb];
@@ -811,90 +871,103 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
           merge_triple(run_m[tb], run_s[tb], run_i[tb], red_m[e], red_s[e], red_i[e]);
         }
         p.part_m[slot] = run_m[tb];
-        p.part_s[slot] = run_s[tb];
-        p.part_i[slot] = run_i[tb];
+        p.part_si[slot] = pack_sum_id(run_s[tb], run_i[tb], p.id_bits);
       }
     }
     __syncthreads();
   }
 }
 
-// Merge the S partial results of every row and emit the outputs.  A block of 256 threads handles ROWS rows with
-// G = 256 / ROWS thread groups: group g folds the splits g, g + G, g + 2G, ... in ascending order (their loads
-// issued together), then the G group results are folded pairwise, group g with group g + stride for stride = G/2,
-// G/4, ..., 1.  The order is a function of S alone (run-to-run and chunking-independent results) and a row's chain
-// of dependent steps is S / G + log2 G long instead of S.  Few splits: 16 rows x 16 groups; many splits (one row
-// tile spread over ~250 of them, where this kernel is a visible part of the step): 4 rows x 64 groups -- the
+// Merge the S partial results of every row and emit the outputs.  A block of 256 threads handles ROWS rows at a time
+// with G = 256 / ROWS thread groups: group g folds the splits g, g + G, g + 2G, ... (their loads issued together),
+// then the G group results are folded pairwise, group g with group g + stride for stride = G/2, G/4, ..., 1: a row's
+// chain of dependent steps is S / G + log2 G long instead of S.  Few splits: 16 rows x 16 groups; many splits (one row
+// tile spread over ~250 of them, where this kernel is a visible part of the step): 4 rows x 64 groups -- a
 // sequential merge took 114 us there, 16 groups with a sequential second level 16 us.
+struct CombineScratch {
+  double s[256];
+  float m[256], ym[256], xa[256];
+  int i[256];
+};
 template <int ROWS>
-__global__ __launch_bounds__(256) void combine_kernel(const KernelParams p) {
+__device__ __forceinline__ void combine_rows(const KernelParams& p, int splits, int rows, CombineScratch& sh) {
   constexpr int G = 256 / ROWS;
-  constexpr int kPerGroup = (MOSAIC_MAX_VOCAB_SPLITS + G - 1) / G;   // splits one group folds at most
-  __shared__ float sh_m[G][ROWS], sh_s[G][ROWS], sh_ym[G][ROWS], sh_xa[G][ROWS];
-  __shared__ int sh_i[G][ROWS];
-  int total = *p.count;
-  if (total > p.max_rows) total = p.max_rows;
-  int rows = total - p.row0;
-  if (rows > p.chunk_rows) rows = p.chunk_rows;
-  const int lr = threadIdx.x % ROWS, g = threadIdx.x / ROWS;
-  const int r = blockIdx.x * ROWS + lr;
-  const bool valid = r < rows;
+  constexpr int kPerGroup = (MOSAIC_MAX_VOCAB_SPLITS + 1 + G - 1) / G;   // splits one group folds at most
   const bool sample = p.tau > 0.f;   // sampling: the token is the arg-max of the perturbed scores
-  float m = kNeg, s = 0.f, ym = kNeg, xa = 0.f;
-  int i = INT_MAX;
-  if (valid) {
-    float lm[kPerGroup], ls[kPerGroup], lym[kPerGroup], lxa[kPerGroup];
-    int li[kPerGroup];
+  const int lr = threadIdx.x % ROWS, g = threadIdx.x / ROWS;
+  for (int r0 = (int)blockIdx.x * ROWS; r0 < rows; r0 += (int)gridDim.x * ROWS) {
+    const int r = r0 + lr;
+    const bool valid = r < rows;
+    float m = kNeg, ym = kNeg, xa = 0.f;
+    double s = 0.0;
+    int i = INT_MAX;
+    if (valid) {
+      float lm[kPerGroup], lym[kPerGroup], lxa[kPerGroup];
+      uint64_t lsi[kPerGroup];
 #pragma unroll
-    for (int k = 0; k < kPerGroup; ++k) {
-      const int sp = g + k * G;
-      const bool on = sp < p.splits;
-      const int64_t slot = (int64_t)(on ? sp : 0) * p.c_pad + r;
-      lm[k] = on ? p.part_m[slot] : kNeg;        // beyond S: the neutral element
-      ls[k] = on ? p.part_s[slot] : 0.f;
-      li[k] = on ? p.part_i[slot] : INT_MAX;
-      lym[k] = (on && sample) ? p.part_ym[slot] : kNeg;
-      lxa[k] = (on && sample) ? p.part_xa[slot] : 0.f;
-    }
+      for (int k = 0; k < kPerGroup; ++k) {
+        const int sp = g + k * G;
+        const bool on = sp < splits;
+        const int64_t slot = (int64_t)(on ? sp : 0) * partial_stride(rows) + r;
+        lm[k] = on ? p.part_m[slot] : kNeg;        // beyond S: the neutral element
+        lsi[k] = on ? p.part_si[slot] : 0;
+        lym[k] = (on && sample) ? p.part_ym[slot] : kNeg;
+        lxa[k] = (on && sample) ? p.part_xa[slot] : 0.f;
+      }
 #pragma unroll
-    for (int k = 0; k < kPerGroup; ++k) {
-      if (sample) {
-        merge_ms(m, s, lm[k], ls[k]);
-        merge_pick(ym, xa, i, lym[k], lxa[k], li[k]);
-      } else {
-        merge_triple(m, s, i, lm[k], ls[k], li[k]);
+      for (int k = 0; k < kPerGroup; ++k) {
+        if (g + k * G >= splits) break;
+        double s2;
+        int i2;
+        unpack_sum_id(lsi[k], p.id_bits, s2, i2);
+        if (sample) {
+          merge_sum(m, s, lm[k], s2);
+          merge_pick(ym, xa, i, lym[k], lxa[k], i2);
+        } else {
+          merge_triple(m, s, i, lm[k], s2, i2);
+        }
       }
     }
-  }
-  sh_m[g][lr] = m;
-  sh_s[g][lr] = s;
-  sh_i[g][lr] = i;
-  sh_ym[g][lr] = ym;
-  sh_xa[g][lr] = xa;
-  __syncthreads();
 #pragma unroll
-  for (int stride = G / 2; stride >= 1; stride >>= 1) {
-    if (g < stride) {
-      if (sample) {
-        merge_ms(m, s, sh_m[g + stride][lr], sh_s[g + stride][lr]);
-        merge_pick(ym, xa, i, sh_ym[g + stride][lr], sh_xa[g + stride][lr], sh_i[g + stride][lr]);
-      } else {
-        merge_triple(m, s, i, sh_m[g + stride][lr], sh_s[g + stride][lr], sh_i[g + stride][lr]);
+    for (int stride = G / 2; stride >= 1; stride >>= 1) {
+      if (g >= stride && g < 2 * stride) {
+        const int e = (g - stride) * ROWS + lr;
+        sh.m[e] = m;
+        sh.s[e] = s;
+        sh.i[e] = i;
+        sh.ym[e] = ym;
+        sh.xa[e] = xa;
       }
-      sh_m[g][lr] = m;
-      sh_s[g][lr] = s;
-      sh_i[g][lr] = i;
-      sh_ym[g][lr] = ym;
-      sh_xa[g][lr] = xa;
+      __syncthreads();
+      if (g < stride) {
+        const int e = g * ROWS + lr;
+        if (sample) {
+          merge_sum(m, s, sh.m[e], sh.s[e]);
+          merge_pick(ym, xa, i, sh.ym[e], sh.xa[e], sh.i[e]);
+        } else {
+          merge_triple(m, s, i, sh.m[e], sh.s[e], sh.i[e]);
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
+    if (g == 0 && valid) {
+      // back from 2^E to exp(m)
+      const float rel = (float)(s / (double)__builtin_amdgcn_exp2f(__builtin_fmaf(m, kLog2e, -ref_exponent(m))));
+      p.out_token[p.row0 + r] = i;
+      p.out_lse[p.row0 + r] = m + __builtin_amdgcn_logf(rel) * kLn2;
+      p.out_conf[p.row0 + r] = sample ? __builtin_amdgcn_exp2f((xa - m) * kLog2e) / rel : 1.0f / rel;
+    }
   }
-  if (g != 0 || !valid) return;
-  p.out_token[p.row0 + r] = i;
-  p.out_lse[p.row0 + r] = m + __builtin_amdgcn_logf(s) * kLn2;
-  p.out_conf[p.row0 + r] = sample ? __builtin_amdgcn_exp2f((xa - m) * kLog2e) / s : 1.0f / s;
 }
 constexpr int kWideMergeSplits = 64;   // from this many splits on, the 64-group merge
+__global__ __launch_bounds__(256) void combine_kernel(const KernelParams p) {
+  __shared__ CombineScratch sh;
+  const int rows = chunk_rows_found(p);
+  if (rows <= 0) return;
+  const int splits = *p.found_splits + (int)p.sched.extra;   // a pair's second launch adds one
+  if (splits >= kWideMergeSplits) combine_rows<4>(p, splits, rows, sh);
+  else combine_rows<16>(p, splits, rows, sh);
+}
 
 int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream_t stream) {
   KernelParams p;
@@ -909,15 +982,11 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.T = (int32_t)a.T;
   p.chunk_rows = plan.rows_per_chunk;
   p.max_rows = (int32_t)a.max_rows;
-  p.splits = plan.vocab_splits;
   p.panel = plan.tile_panel;
-  p.vocab_tiles = (a.V + kTileVocab - 1) / kTileVocab;
-  p.tile_first = 0;
-  p.split_first = 0;
-  p.c_pad = plan.rows_per_chunk;
-  p.part_m = static_cast<float*>(a.workspace);
-  p.part_s = p.part_m + (int64_t)plan.vocab_splits * plan.rows_per_chunk;
-  p.part_i = reinterpret_cast<int32_t*>(p.part_s + (int64_t)plan.vocab_splits * plan.rows_per_chunk);
+  const int64_t slots = (int64_t)plan.vocab_splits * plan.rows_per_chunk;   // a multiple of 256
+  p.part_si = static_cast<uint64_t*>(a.workspace);
+  p.part_m = reinterpret_cast<float*>(p.part_si + slots);
+  p.id_bits = a.V > 1 ? 32 - __builtin_clz((unsigned)(a.V - 1)) : 1;
   p.out_token = a.out_token;
   p.out_conf = a.out_conf;
   p.out_lse = a.out_lse;
@@ -925,56 +994,50 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.tau = sample ? a.temperature : 0.f;
   p.seed_lo = (uint32_t)a.seed;
   p.seed_hi = (uint32_t)(a.seed >> 32);
-  p.part_ym = reinterpret_cast<float*>(p.part_i + (int64_t)plan.vocab_splits * plan.rows_per_chunk);
-  p.part_xa = p.part_ym + (int64_t)plan.vocab_splits * plan.rows_per_chunk;
+  p.part_ym = p.part_m + slots;
+  p.part_xa = p.part_ym + slots;
   // the round counters sit behind the partial planes (three for a greedy pass, five for a sampling one)
-  constexpr int kSyncSlots = MOSAIC_SYNC_BYTES / 4 - 1;   // the last word is the flag of the span check
-  p.sync = reinterpret_cast<int32_t*>(sample ? p.part_xa + (int64_t)plan.vocab_splits * plan.rows_per_chunk
-                                             : p.part_ym);
+  constexpr int kSyncSlots = MOSAIC_SYNC_BYTES / 4 - 2;   // then the division found, and the flag of the span check
+  p.sync = reinterpret_cast<int32_t*>(sample ? p.part_xa + slots : p.part_ym);
   p.sync_slots = kSyncSlots;
   p.wide_flag = nullptr;
   p.wide_run_if = 0;
 
   const KernelChoice choice = choose_kernel(a.T, a.ld_h, a.d, a.V, plan);
   const bool fast = choice.fast, paired = choice.paired, wide = choice.wide;
-  int32_t* const flag = p.sync + kSyncSlots;
-  // The selector gives a ragged vocabulary one split more than fills the chip (for the pair's second launch);
-  // the general kernel alone works best without it.
-  if (!fast && !paired && a.V % kTileVocab != 0 && p.vocab_tiles >= 2 && p.splits >= 2) p.splits -= 1;
-  KernelParams body = p, tail = p;   // the two launches of a pair
+  p.found_splits = p.sync + kSyncSlots;
+  int32_t* const flag = p.found_splits + 1;
+  const int32_t vocab_tiles = (a.V + kTileVocab - 1) / kTileVocab;
+  p.sched.vocab_tiles = (uint32_t)(paired ? vocab_tiles - 1 : vocab_tiles);
+  p.sched.grid = (uint32_t)plan.grid;
+  p.sched.extra = paired ? 1 : 0;
+  p.sched.slots64 = (uint32_t)(slots / 64 < INT32_MAX ? slots / 64 : INT32_MAX);
+  p.ragged_tile = -1;
+  KernelParams tail = p;   // the second launch of a pair
   if (paired) {
-    body.vocab_tiles = p.vocab_tiles - 1;
-    body.splits = plan.vocab_splits - 1;
-    if (body.splits > body.vocab_tiles) body.splits = body.vocab_tiles;
-    tail.vocab_tiles = 1;
-    tail.tile_first = p.vocab_tiles - 1;
-    tail.splits = 1;
-    tail.split_first = body.splits;
-    p.splits = body.splits + 1;        // what the merge reads
-    body.sync_slots = tail.sync_slots = kSyncSlots / 2;   // each launch of the pair meets on its own counters
+    tail.ragged_tile = vocab_tiles - 1;
+    p.sync_slots = tail.sync_slots = kSyncSlots / 2;   // each launch of the pair meets on its own counters
     tail.sync = p.sync + kSyncSlots / 2;
   }
+  int32_t* const counters = p.sync;
   // A hidden tensor of 4 GiB or more: the 4-wave launch and a general-kernel launch of the same work both go out,
   // and the flag of the span check decides on the device which of the two does it.
-  KernelParams fallback = paired ? body : p;
-  if (wide) {
-    p.wide_flag = body.wide_flag = fallback.wide_flag = flag;
-    fallback.wide_run_if = 1;
-  }
+  if (wide) p.wide_flag = flag;
   int rc = 0;
   for (int c = 0; c < plan.num_chunks; ++c) {
     const int64_t row0 = (int64_t)c * plan.rows_per_chunk;
     if (row0 >= a.max_rows) break;
-    p.row0 = body.row0 = tail.row0 = (int32_t)row0;
     int64_t cap = a.max_rows - row0;
     if (cap > plan.rows_per_chunk) cap = plan.rows_per_chunk;
+    p.row0 = tail.row0 = (int32_t)row0;
+    p.bound_rows = tail.bound_rows = (int32_t)cap;
+    p.bound = tail.bound = choose_schedule(p.sched, (int32_t)cap);
     const int64_t tiles = (cap + kTileRows - 1) / kTileRows;
-    const KernelParams& q = paired ? body : p;
-    int64_t grid = tiles * q.splits;
-    const bool several_rounds = grid > plan.grid || (paired && tiles > plan.grid);
-    if (grid > plan.grid) grid = plan.grid;
+    const bool several_rounds = tiles * p.bound.splits > plan.grid || (paired && tiles > plan.grid);
     if (several_rounds || wide)
-      rc |= launch_kernel(clear_round_counters_kernel, dim3(1), dim3(256), stream, p.sync, kSyncSlots + 1);
+      rc |= launch_kernel(clear_round_counters_kernel, dim3(1), dim3(256), stream, counters, kSyncSlots + 2);
+    p.sync = several_rounds ? counters : nullptr;   // not cleared: nobody meets (fewer rows may still take two rounds)
+    if (!several_rounds) tail.sync = nullptr;
     if (wide)
       rc |= launch_kernel(span_check_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), stream, a.idx, a.count,
                           (int32_t)row0, plan.rows_per_chunk, (int32_t)a.max_rows, (int32_t)a.T, p.ldh_bytes, flag);
@@ -983,20 +1046,18 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
                     : launch_kernel(masked_logits_kernel<3, 2, false>, dim3((unsigned)blocks), dim3(kThreads), stream, kp);
     };
     if (fast || paired) {
-      rc |= sample ? launch_kernel(masked_logits_kernel_w4<true>, dim3((unsigned)grid), dim3(256), stream, q)
-                   : launch_kernel(masked_logits_kernel_w4<false>, dim3((unsigned)grid), dim3(256), stream, q);
+      rc |= sample ? launch_kernel(masked_logits_kernel_w4<true>, dim3((unsigned)plan.grid), dim3(256), stream, p)
+                   : launch_kernel(masked_logits_kernel_w4<false>, dim3((unsigned)plan.grid), dim3(256), stream, p);
       if (wide) {   // the same work on the general kernel, for lists the span check flags
-        fallback.row0 = (int32_t)row0;
-        rc |= launch_general(fallback, grid);
+        KernelParams fallback = p;
+        fallback.wide_run_if = 1;
+        rc |= launch_general(fallback, plan.grid);
       }
     } else {
-      rc |= launch_general(p, grid);
+      rc |= launch_general(p, plan.grid);
     }
     if (paired) rc |= launch_general(tail, tiles < plan.grid ? tiles : plan.grid);
-    if (p.splits >= kWideMergeSplits)
-      rc |= launch_kernel(combine_kernel<4>, dim3((unsigned)((cap + 3) / 4)), dim3(256), stream, p);
-    else
-      rc |= launch_kernel(combine_kernel<16>, dim3((unsigned)((cap + 15) / 16)), dim3(256), stream, p);
+    rc |= launch_kernel(combine_kernel, dim3((unsigned)((cap + 3) / 4 < 4096 ? (cap + 3) / 4 : 4096)), dim3(256), stream, p);
     if (rc != 0) break;
   }
   return rc;
