@@ -1,13 +1,19 @@
 #!/usr/bin/env python3
 """Generates mosaic_w4_tile.inc (greedy) and mosaic_w4_tile_sample.inc (sampling): one vocabulary tile of the 4-wave
-fused kernel as one inline-asm statement, the hand-scheduled K-loop followed by the tile's vocabulary reduction.
+fused kernel as one inline-asm statement, the hand-scheduled K-loop followed by the tile's vocabulary reduction, for
+each width of the row tile (32*NB tokens, NB = 1..8, chosen by `if constexpr`).
 
-The K-loop covers the nk K-tiles of the vocabulary tile.  Per K-tile (step g) a wave issues 128
-v_mfma_f32_16x16x32_bf16 in two groups of 64 (k 0..31 and k 32..63 of the tile); after every second MFMA
-of a group's first half sits one of the 16 ds_read_b128 that fetch the next group's fragments, and after every
-fourth one of the group's 8 direct-to-LDS copies, so that nothing but MFMAs is ever waited on in steady state.  The steady-state body (1 <= g, g + 2 < total)
-contains no branch at all -- a taken branch costs more than one 16-cycle MFMA -- and all slot / pointer
-book-keeping is s_cselect arithmetic; the first step and the last two run a guarded copy of the same schedule.
+The K-loop covers the nk K-tiles of the vocabulary tile.  Per K-tile (step g) a wave issues 16*nb
+v_mfma_f32_16x16x32_bf16 in two groups of 8*nb (k 0..31 and k 32..63 of the tile): its 128 vocabulary ids (8 blocks)
+against its half of the tokens (nb blocks).  Between the MFMAs of a group sit the ds_read_b128 that fetch the next
+group's fragments and the group's direct-to-LDS copies, so that nothing but MFMAs is ever waited on in steady state.
+The steady-state body (1 <= g, g + DEPTH < total) contains no branch at all -- a taken branch costs more than one
+16-cycle MFMA -- and all slot / pointer book-keeping is s_cselect arithmetic; the first step and the last DEPTH run a
+guarded copy of the same schedule.
+
+A ring holds DEPTH + 1 LM-head slots of 32 KiB and DEPTH hidden slots of 4*nb KiB.  DEPTH is two from nb = 3 on (nb = 8
+fills the 160 KiB); one or two token blocks leave room for a third K-tile under way, which the copies need there,
+because such a launch runs at the speed of memory.
 """
 import os
 import re
@@ -24,6 +30,27 @@ NK128 = "s94"
 
 lines = []
 uid = [0]
+SHAPE = {"nb": 8}          # token blocks of 16 per wave
+
+
+def nb():
+    return SHAPE["nb"]
+
+
+def depth():
+    return 3 if nb() <= 2 else 2
+
+
+def w_ring():
+    return (depth() + 1) * 0x8000
+
+
+def h_slot():
+    return nb() * 0x1000
+
+
+def h_ring():
+    return depth() * h_slot()
 
 
 def e(s):
@@ -42,13 +69,13 @@ LITERAL_ACC = [False]
 
 def acc_block(bi, bj):
     if LITERAL_ACC[0]:
-        base = (bi * 8 + bj) * 4
+        base = (bi * nb() + bj) * 4
         return f"a[{base}:{base + 3}]"
     return f"%[a{bi}{bj}]"
 
 
 def acc_reg(bi, bj, r):
-    return f"a{(bi * 8 + bj) * 4 + r}"
+    return f"a{(bi * nb() + bj) * 4 + r}"
 
 
 def mfma(bi, bj, buf, zero_c=False):
@@ -67,7 +94,7 @@ def reads(buf):
     for i in range(8):
         off = f" offset:{2048 * i}" if i else ""
         out.append(f"ds_read_b128 {FA[buf][i]}, {VT0}{off}")
-    for j in range(8):
+    for j in range(nb()):
         off = f" offset:{2048 * j}" if j else ""
         out.append(f"ds_read_b128 {FB[buf][j]}, {VT1}{off}")
     return out
@@ -78,7 +105,7 @@ def dma_w(i):
 
 
 def dma_h(i):
-    return [f"s_add_u32 m0, %[hdst], {98304 + 1024 * i}", "s_nop 0", f"global_load_lds_dwordx4 %[hoff{i}], {HSRC}"]
+    return [f"s_add_u32 m0, %[hdst], {w_ring() + 1024 * i}", "s_nop 0", f"global_load_lds_dwordx4 %[hoff{i}], {HSRC}"]
 
 
 def dma_split(i, hidden):
@@ -86,6 +113,16 @@ def dma_split(i, hidden):
     supplies the wait state an M0 write needs before a direct-to-LDS load"""
     seq = dma_h(i) if hidden else dma_w(i)
     return seq[0], seq[2]
+
+
+def next_slot(dst, slot, ring):
+    """`dst` (a slot's offset plus this wave's share of it) to the ring's next slot"""
+    if ring == 2 * slot and slot & (slot - 1) == 0:
+        return [f"s_xor_b32 %[{dst}], %[{dst}], {hex(slot)}"]
+    return [f"s_add_u32 %[{dst}], %[{dst}], {hex(slot)}",
+            f"s_cmp_ge_u32 %[{dst}], {hex(ring)}",
+            f"s_cselect_b32 vcc_lo, {hex(ring)}, 0",
+            f"s_sub_u32 %[{dst}], %[{dst}], vcc_lo"]
 
 
 def advance_h_ops():
@@ -97,8 +134,7 @@ def advance_h_ops():
             f"s_cselect_b32 vcc_lo, {NK128}, 0",
             "s_cselect_b32 %[hk], 0, %[hk]",
             "s_sub_u32 s98, s98, vcc_lo",
-            "s_subb_u32 s99, s99, 0",
-            "s_xor_b32 %[hdst], %[hdst], 0x8000"]
+            "s_subb_u32 s99, s99, 0"] + next_slot("hdst", h_slot(), h_ring())
 
 
 def advance_w_ops():
@@ -108,18 +144,18 @@ def advance_w_ops():
             "s_cselect_b32 vcc_lo, %[wwrap], 128",
             "s_cselect_b32 %[wk], 0, %[wk]",
             "s_add_u32 s96, s96, vcc_lo",
-            "s_addc_u32 s97, s97, 0",
-            "s_add_u32 %[wdst], %[wdst], 0x8000",
-            "s_cmp_ge_u32 %[wdst], 0x18000",
-            "s_cselect_b32 vcc_lo, 0x18000, 0",
-            "s_sub_u32 %[wdst], %[wdst], vcc_lo"]
+            "s_addc_u32 s97, s97, 0"] + next_slot("wdst", 0x8000, w_ring())
 
 
 def rotate_read_slots_ops():
-    return ["s_add_u32 %[wrd], %[wrd], 0x8000",
-            "s_cmp_ge_u32 %[wrd], 0x18000",
-            "s_cselect_b32 %[wrd], 0, %[wrd]",
-            "s_xor_b32 %[hrd], %[hrd], 0x8000"]
+    ops = ["s_add_u32 %[wrd], %[wrd], 0x8000",
+           f"s_cmp_ge_u32 %[wrd], {hex(w_ring())}",
+           "s_cselect_b32 %[wrd], 0, %[wrd]"]
+    if depth() == 2 and h_slot() & (h_slot() - 1) == 0:
+        return ops + [f"s_xor_b32 %[hrd], %[hrd], {hex(h_slot())}"]
+    return ops + [f"s_add_u32 %[hrd], %[hrd], {hex(h_slot())}",
+                  f"s_cmp_ge_u32 %[hrd], {hex(h_ring())}",
+                  "s_cselect_b32 %[hrd], 0, %[hrd]"]
 
 
 def read_addr_ops(ks):
@@ -157,10 +193,29 @@ def cond_plus(plus):
     e("s_cmp_lt_u32 vcc_lo, %[total]")
 
 
-# Copy i of a tile goes out after MFMA COPY_POS[i] of its group: early in the group, so a copy has the longest
+# The widest tile: copy i goes out after MFMA COPY_POS[i] of its group: early in the group, so a copy has the longest
 # possible time to land before the sync that publishes it, and four MFMAs apart, so the 16 KiB a workgroup
 # requests per position never queue up behind the texture addresser (denser or later placement measured slower).
 COPY_POS = [1, 5, 9, 13, 17, 21, 25, 29]
+
+
+def copy_pos(copies):
+    """positions of a group's copies: COPY_POS in the widest tile, else spread over the group's first half or, where
+    that is too short, over all of it"""
+    if nb() == 8:
+        return COPY_POS
+    n = 8 * nb()
+    step = max(1, n // 2 // copies)
+    return [min(1, n - copies) + i * step for i in range(copies)]
+
+
+def read_pos(rd):
+    """fragment reads by the MFMA they follow: one after each even MFMA, or as many a gap as a short group needs"""
+    n = 8 * nb()
+    at = {}
+    for i, x in enumerate(rd or []):
+        at.setdefault(min(2 * i, n - 2) if len(rd) * 2 <= n + 1 else i * n // len(rd), []).append(x)
+    return at
 
 
 def spread(fill, first, ops, per_gap=2):
@@ -173,38 +228,41 @@ def spread(fill, first, ops, per_gap=2):
 
 
 def scheduled_group(buf, fill, zero_c=False):
-    """64 MFMAs on fragment buffer `buf`; fill[k] = the instructions that follow MFMA k.  A wave is alone on its
+    """8*nb MFMAs on fragment buffer `buf`; fill[k] = the instructions that follow MFMA k.  A wave is alone on its
     SIMD and issues one instruction every few cycles, so whatever sits between two MFMAs beyond ~3 instructions
-    delays the second one: the steady state keeps every gap that short."""
-    order = [(bi, bj) for bi in range(8) for bj in range(8)]
-    for k in range(64):
+    delays the second one: the steady state keeps the gaps as short as the group's length allows."""
+    order = [(bi, bj) for bi in range(8) for bj in range(nb())]
+    for k in range(8 * nb()):
         mfma(*order[k], buf, zero_c)
         for x in fill.get(k, []):
             e(x)
 
 
-def group(buf, rd=None, dma=None, cond=None, after=None, pos=None):
-    """64 MFMAs on fragment buffer `buf` for the guarded (first / last steps) path.  rd = 16 ds_reads, one after
-    each even MFMA 0..30.  dma = 8 copy sequences, copy i after MFMA pos[i]; guarded by `cond` when given (then
-    the guarded span is pos[0]..pos[7]); `after` runs once the copies are out."""
+def group(buf, rd=None, dma=None, cond=None, after=None):
+    """8*nb MFMAs on fragment buffer `buf` for the guarded (first / last steps) path.  rd = the ds_reads, spread over
+    the group.  dma = copy sequences, copy i after MFMA pos[i]; guarded by `cond` when given (then the guarded
+    span is pos[0]..pos[-1]); `after` runs once the copies are out."""
     e("s_waitcnt lgkmcnt(0)")
-    order = [(bi, bj) for bi in range(8) for bj in range(8)]
+    n = 8 * nb()
+    order = [(bi, bj) for bi in range(8) for bj in range(nb())]
+    at = read_pos(rd)
+
+    def step(k):
+        mfma(*order[k], buf)
+        for x in at.get(k, []):
+            e(x)
     if not dma:
-        for k in range(64):
-            mfma(*order[k], buf)
-            if rd and k % 2 == 0 and k < 32:
-                e(rd[k // 2])
+        for k in range(n):
+            step(k)
         return
+    pos = copy_pos(len(dma))
     lo, hi = pos[0], pos[-1]
     for k in range(lo):
-        mfma(*order[k], buf)
-        if rd and k % 2 == 0 and k < 32:
-            e(rd[k // 2])
+        step(k)
+
     def span(with_dma):
         for k in range(lo, hi + 1):
-            mfma(*order[k], buf)
-            if rd and k % 2 == 0 and k < 32:
-                e(rd[k // 2])
+            step(k)
             if with_dma and k in pos:
                 for x in dma[pos.index(k)]:
                     e(x)
@@ -221,35 +279,47 @@ def group(buf, rd=None, dma=None, cond=None, after=None, pos=None):
         e(f"{skip}:")
         span(False)
         e(f"{join}:")
-    for k in range(hi + 1, 64):
-        mfma(*order[k], buf)
-        if rd and k % 2 == 0 and k < 32:
-            e(rd[k // 2])
+    for k in range(hi + 1, n):
+        step(k)
 
 
 def steady_fill(buf):
-    """Gap contents of one steady-state group: the 16 fragment reads of the other buffer after the even MFMAs of
-    the first half, the 8 copies after every fourth MFMA of that half, and the scalar book-keeping spread over the
-    second half two instructions at a time."""
-    fill = {}
+    """Gap contents of one steady-state group: the fragment reads of the other buffer, the copies, and the scalar
+    book-keeping behind them."""
+    copies = nb() if buf == 1 else 8
+    split = [dma_split(i, hidden=(buf == 1)) for i in range(copies)]
     rd = reads(1 - buf)
-    for k in range(0, 32, 2):
-        fill.setdefault(k, []).append(rd[k // 2])
-    for i, k in enumerate(COPY_POS):
-        setup, load = dma_split(i, hidden=(buf == 1))
-        fill.setdefault(k - 1, []).append(setup)
-        fill.setdefault(k, []).append(load)
     if buf == 0:
-        k = spread(fill, 33, advance_w_ops())
-        k = spread(fill, k + 1, rotate_read_slots_ops())     # the read slots of the NEXT tile, ahead of the sync
-        spread(fill, k + 1, read_addr_ops(0))                # addresses of its first-half fragments
+        # the read slots of the NEXT tile, ahead of the sync, and the addresses of its first-half fragments
+        ops = [advance_w_ops(), rotate_read_slots_ops(), read_addr_ops(0)]
     else:
-        k = spread(fill, 33, advance_h_ops())
-        k = spread(fill, k + 1, ["s_add_u32 %[g], %[g], 1", f"s_add_u32 {KT}, {KT}, 1"])
-        spread(fill, k + 1, read_addr_ops(1))                # next step's second-half fragment addresses
-        # scc = (k-tile index < nk) && (g + 2 < total): the next step belongs to this statement and is steady
-        spread(fill, 60, ["s_add_u32 vcc_lo, %[g], 2", "s_cmp_lt_u32 vcc_lo, %[total]",
-                          "s_cselect_b32 vcc_lo, %[nk], 0", f"s_cmp_lt_u32 {KT}, vcc_lo"])
+        # next step's second-half fragment addresses;
+        # scc = (k-tile index < nk) && (g + depth < total): the next step belongs to this statement and is steady
+        ops = [advance_h_ops(), ["s_add_u32 %[g], %[g], 1", f"s_add_u32 {KT}, {KT}, 1"], read_addr_ops(1)]
+    last = ["s_add_u32 vcc_lo, %[g], " + str(depth()), "s_cmp_lt_u32 vcc_lo, %[total]",
+            "s_cselect_b32 vcc_lo, %[nk], 0", f"s_cmp_lt_u32 {KT}, vcc_lo"] if buf == 1 else []
+    fill = {}
+    if nb() == 8:
+        # the 16 reads after the even MFMAs of the first half, the copies after every fourth MFMA of that half, the
+        # book-keeping two instructions at a time over the second half
+        for k in range(0, 32, 2):
+            fill.setdefault(k, []).append(rd[k // 2])
+        for (setup, load), k in zip(split, COPY_POS):
+            fill.setdefault(k - 1, []).append(setup)
+            fill.setdefault(k, []).append(load)
+        k = spread(fill, 33, ops[0])
+        k = spread(fill, k + 1, ops[1])
+        spread(fill, k + 1, ops[2])
+        spread(fill, 60, last)
+        return fill
+    # a shorter group: the same sequence, evenly over its gaps; a read sits between a copy's M0 write and its load
+    seq = []
+    for i, x in enumerate(rd):
+        seq += [split[i][0], x, split[i][1]] if i < copies else [x]
+    seq += [x for part in ops for x in part] + last
+    n = 8 * nb()
+    for i, x in enumerate(seq):
+        fill.setdefault(i * n // len(seq), []).append(x)
     return fill
 
 
@@ -562,7 +632,7 @@ def build_tile_sample():
     e("v_lshlrev_b32 %[sw32], 2, %[sw32]")
     e("v_lshlrev_b32 %[sw48], 2, %[sw48]")
     e("v_lshlrev_b32 %[sw16], 2, %[sw16]")
-    for tb in range(8):
+    for tb in range(nb()):
         reduce_column_sample(tb)
     done = label("done")
     e(f"s_branch {done}")
@@ -578,7 +648,7 @@ def build_tile():
     """The statement of the greedy kernel: the K-loop on accumulators it starts itself, then the reduction of the
     tile."""
     build_literal()
-    for tb in range(8):
+    for tb in range(nb()):
         reduce_column(tb)
 
 
@@ -609,31 +679,33 @@ def build():
     if LITERAL_ACC[0]:
         # the statement owns the accumulators: clear them while the first fragments are on their way (measured:
         # writing a tile's first products without an addend instead saves nothing)
-        for i in range(256):
+        for i in range(32 * nb()):
             e(f"v_accvgpr_write_b32 a{i}, 0")
     e("s_nop 7")
     top, steady, generic, out = label("top"), label("steady"), label("generic"), label("out")
     e(f"{top}:")
-    # Steady state (1 <= g and g + 2 < total): every copy and the sync happen, no branch inside the body, one taken
+    # Steady state (1 <= g and g + depth < total): every copy and the sync happen, no branch inside the body, one taken
     # branch per step (the back edge, issued right behind the last MFMA).
-    cond_g_ge1_and(2)
+    cond_g_ge1_and(depth())
     e(f"s_cbranch_scc0 {generic}")
     read_addr(1)
     e(f"{steady}:")
     leave = label("leave")
     e("s_waitcnt lgkmcnt(0)")
-    scheduled_group(0, steady_fill(0))                       # LM-head tile g+2 goes out
-    e("s_waitcnt vmcnt(8) lgkmcnt(0)")                       # all copies but the LM-head tile just issued; fragments
+    scheduled_group(0, steady_fill(0))                       # LM-head tile g + depth goes out
+    # all copies of step g + 1 have landed: younger are the LM-head tiles of steps g + 2 .. g + depth and the hidden
+    # tiles of steps g + 2 .. g + depth - 1; and this wave's fragments
+    e(f"s_waitcnt vmcnt({8 * (depth() - 1) + nb() * (depth() - 2)}) lgkmcnt(0)")
     e("s_barrier")
-    scheduled_group(1, steady_fill(1))                       # hidden tile g+2 goes out
+    scheduled_group(1, steady_fill(1))                       # hidden tile g + depth goes out
     e(f"s_cbranch_scc1 {steady}")
     e(f"{leave}:")
     e(f"s_cmp_lt_u32 {KT}, %[nk]")
     e(f"s_cbranch_scc0 {out}")
-    # First step and the last two: same schedule with every part guarded.
+    # First step and the last ones: same schedule with every part guarded.
     e(f"{generic}:")
     read_addr(1)
-    group(0, rd=reads(1), dma=[dma_w(i) for i in range(8)], cond=lambda: cond_g_ge1_and(2), after=advance_w, pos=COPY_POS)
+    group(0, rd=reads(1), dma=[dma_w(i) for i in range(8)], cond=lambda: cond_g_ge1_and(depth()), after=advance_w)
     nosync, stepend = label("nosync"), label("stepend")
     cond_plus(1)
     e(f"s_cbranch_scc0 {nosync}")
@@ -642,7 +714,7 @@ def build():
     e("s_barrier")
     rotate_read_slots()
     read_addr(0)
-    group(1, rd=reads(0), dma=[dma_h(i) for i in range(8)], cond=lambda: cond_plus(2), after=advance_h, pos=COPY_POS)
+    group(1, rd=reads(0), dma=[dma_h(i) for i in range(nb())], cond=lambda: cond_plus(depth()), after=advance_h)
     e(f"s_branch {stepend}")
     e(f"{nosync}:")
     group(1)
@@ -659,19 +731,20 @@ def build():
     e("s_mov_b32 %[hsrc_hi], s99")
 
 
-def write_statement(path, sample=False):
+def write_statement(f, blocks, sample):
+    SHAPE["nb"] = blocks
     lines.clear()
     uid[0] = 2000 if sample else 1000
     if sample:
         build_tile_sample()
         outs = []
-        for tb in range(8):
+        for tb in range(blocks):
             outs += [f'[m{tb}] "+v"(tile_m[{tb}])', f'[s{tb}] "+v"(tile_s[{tb}])', f'[i{tb}] "+v"(run_i[{tb}])',
                      f'[ym{tb}] "+v"(run_ym[{tb}])', f'[xa{tb}] "+v"(run_xa[{tb}])']
     else:
         build_tile()
         outs = []
-        for tb in range(8):
+        for tb in range(blocks):
             outs += [f'[m{tb}] "+v"(tile_m[{tb}])', f'[s{tb}] "+v"(tile_s[{tb}])', f'[i{tb}] "+v"(tile_i[{tb}])']
     for name in ("wsrc_lo", "wsrc_hi", "hsrc_lo", "hsrc_hi", "wrd", "hrd", "wdst", "hdst", "wk", "hk", "g"):
         outs.append(f'[{name}] "+s"(st_{name})')
@@ -684,37 +757,36 @@ def write_statement(path, sample=False):
         ins.append(f'[rdh{k}] "v"(rdh[{k}])')
     for i in range(8):
         ins.append(f'[woff{i}] "v"(woff[{i}])')
-    for i in range(8):
+    for i in range(blocks):
         ins.append(f'[hoff{i}] "v"(hoff[{i}])')
     for name in ("total", "nk", "wwrap", "hwrap"):
         ins.append(f'[{name}] "s"(st_{name})')
     clob = ['"s94"', '"s95"', '"s96"', '"s97"', '"s98"', '"s99"', '"vcc"', '"scc"', '"m0"', '"memory"']
     ins.append('[vb] "v"(vb)')
-    clob = [f'"a{i}"' for i in range(256)] + [f'"s{i}"' for i in range(88, 94)] + clob
+    clob = [f'"a{i}"' for i in range(32 * blocks)] + [f'"s{i}"' for i in range(88, 94)] + clob
     if sample:
-        ins += [f'[pos{tb}] "v"(pos[{tb}])' for tb in range(8)]
+        ins += [f'[pos{tb}] "v"(pos[{tb}])' for tb in range(blocks)]
         ins += ['[seed_lo] "s"(seed_lo)', '[seed_hi] "s"(seed_hi)']
         clob = [f'"s{i}"' for i in range(66, KEY1_BASE + 10)] + clob
         ins += ['[pm0] "s"(philox_m0)', '[pm1] "s"(philox_m1)', '[itl] "s"(inv_tau_log2e)', '[tau] "s"(tau_s)']
     clob = [f'"v{i}"' for i in range(FRAG_BASE, FRAG_BASE + 128)] + clob
-    with open(path, "w") as f:
-        f.write("// GENERATED by gen_w4_loop.py -- do not edit.  " +
-                ("One vocabulary tile of the sampling 4-wave kernel: K-loop and vocabulary reduction.\n" if sample else
-                 "One vocabulary tile of the greedy 4-wave kernel: K-loop and vocabulary reduction.\n"))
-        f.write("asm volatile(\n")
-        for ln in lines:
-            f.write(f'    "{ln}\\n"\n')
-        f.write("    : " + ",\n      ".join(outs) + "\n")
-        f.write("    : " + ",\n      ".join(ins) + "\n")
-        f.write("    : " + ", ".join(clob) + ");\n")
-    print(f"{path}: {len(lines)} asm lines, {len(outs) + len(ins)} operands")
+    f.write(f"if constexpr (NB == {blocks}) {{\nasm volatile(\n")
+    for ln in lines:
+        f.write(f'    "{ln}\\n"\n')
+    f.write("    : " + ",\n      ".join(outs) + "\n")
+    f.write("    : " + ",\n      ".join(ins) + "\n")
+    f.write("    : " + ", ".join(clob) + ");\n}\n")
 
 
 def main(folder):
-    write_statement(os.path.join(folder, "mosaic_w4_tile.inc"))
-    write_statement(os.path.join(folder, "mosaic_w4_tile_sample.inc"), sample=True)
+    for name, sample in (("mosaic_w4_tile.inc", False), ("mosaic_w4_tile_sample.inc", True)):
+        with open(os.path.join(folder, name), "w") as f:
+            f.write("// GENERATED by gen_w4_loop.py -- do not edit.  One vocabulary tile of the "
+                    f"{'sampling' if sample else 'greedy'} 4-wave kernel, K-loop and vocabulary reduction, per width.\n")
+            for blocks in range(1, 9):
+                write_statement(f, blocks, sample)
     lines.clear()
-    build()          # leave the bare K-loop listing (accumulators as operands) in `lines` for importers
+    build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers
 
 
 if __name__ == "__main__":

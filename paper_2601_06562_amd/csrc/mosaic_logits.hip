@@ -229,32 +229,29 @@ __global__ __launch_bounds__(256) void clear_round_counters_kernel(int32_t* sync
   if ((int)threadIdx.x < n) sync[threadIdx.x] = 0;
 }
 
-// For hidden tensors of 4 GiB or more: raises *flag when some group of 64 consecutive rows of the chunk's list (the
-// rows one wave of the 4-wave kernel copies, the last group padded with the last row as that kernel does) spans
-// rows whose byte offsets differ by 4 GiB or more.  One wave per group.
-__global__ __launch_bounds__(256) void span_check_kernel(const int32_t* idx, const int32_t* count, int32_t row0,
-                                                         int32_t chunk_rows, int32_t max_rows, int32_t T,
-                                                         int64_t ldh_bytes, int32_t* flag) {
-  int total = *count;
-  if (total > max_rows) total = max_rows;
-  int rows = total - row0;
-  if (rows > chunk_rows) rows = chunk_rows;
-  const int group = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6);
-  if (rows <= 0 || group * 64 >= rows) return;
-  int j = group * 64 + ((int)threadIdx.x & 63);
-  if (j > rows - 1) j = rows - 1;
-  int t = idx[row0 + j];
-  t = t < 0 ? 0 : (t > T - 1 ? T - 1 : t);
-  int lo = t, hi = t;
+// For hidden tensors of 4 GiB or more: raises *flag when some group of consecutive rows of the chunk's list that one
+// wave of the 4-wave kernel copies (8 times the width found; the last group padded with the last row as that kernel
+// does) spans rows whose byte offsets differ by 4 GiB or more.  One wave per group.
+__global__ __launch_bounds__(256) void span_check_kernel(const KernelParams p, int32_t* flag) {
+  const int rows = chunk_rows_found(p);
+  if (rows <= 0) return;
+  const int group_rows = 8 * launch_schedule(p, rows).width;
+  const int lane = (int)threadIdx.x & 63;
+  for (int group = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6); group * group_rows < rows; group += (int)gridDim.x * 4) {
+    int j = group * group_rows + (lane < group_rows ? lane : group_rows - 1);
+    if (j > rows - 1) j = rows - 1;
+    int t = p.idx[p.row0 + j];
+    t = t < 0 ? 0 : (t > p.T - 1 ? p.T - 1 : t);
+    int lo = t, hi = t;
 #pragma unroll
-  for (int x = 32; x >= 1; x >>= 1) {
-    const int a = __shfl_xor(lo, x, 64), b = __shfl_xor(hi, x, 64);
-    lo = a < lo ? a : lo;
-    hi = b > hi ? b : hi;
+    for (int x = 32; x >= 1; x >>= 1) {
+      const int a = __shfl_xor(lo, x, 64), b = __shfl_xor(hi, x, 64);
+      lo = a < lo ? a : lo;
+      hi = b > hi ? b : hi;
+    }
+    // the offset of a row from the group's lowest, plus the 16-byte chunk inside the row's K-tile, must fit 32 bits
+    if (lane == 0 && (uint64_t)(hi - lo) * (uint64_t)p.ldh_bytes >= ((uint64_t)1 << 32) - 256) atomicOr(flag, 1);
   }
-  // the offset of a row from the group's lowest, plus the 16-byte chunk inside the row's K-tile, must fit 32 bits
-  if (((int)threadIdx.x & 63) == 0 && (uint64_t)(hi - lo) * (uint64_t)ldh_bytes >= ((uint64_t)1 << 32) - 256)
-    atomicOr(flag, 1);
 }
 
 template <int N>
@@ -404,7 +401,7 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
   const Schedule sched = launch_schedule(p, rows);
-  const int n_tt = sched.row_tiles;
+  const int n_tt = (rows + kTileRows - 1) / kTileRows;   // its row tiles have the one width
 
   const int G = gridDim.x;
   const int pos = xcd_contiguous_position((int)blockIdx.x, G);
@@ -621,22 +618,30 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
   }
 }
 
-// ---- 4-wave fast path: one wave per SIMD, 128 (vocab) x 128 (token) per wave as 8 x 8 blocks of
+// ---- 4-wave fast path: one wave per SIMD, 128 (vocab) x 16*NB (token) per wave as 8 x NB blocks of
 // v_mfma_f32_16x16x32_bf16 (the more power-efficient bf16 shape on this part), accumulators in AGPRs.
 // A vocabulary tile is one hand-scheduled inline-asm statement (mosaic_w4_tile.inc greedy, mosaic_w4_tile_sample.inc
-// sampling; both generated): the K-loop, then the tile's reduction into the running per-column state.  In the K-loop
+// sampling; both generated): the K-loop, then the tile's reduction to a triple per column.  In the K-loop
 // every MFMA is followed by at most one LDS read or one direct-to-LDS copy, fragments are double-
-// buffered in fixed VGPRs, the LM-head ring runs two K-tiles ahead and the hidden ring one.
+// buffered in fixed VGPRs, the LM-head ring runs two K-tiles ahead and the hidden ring one (three and two at NB <= 2).
+// NB sets the width of the row tile, 32*NB tokens.  The widest, 256, has the fewest LDS and L2 bytes per product and is
+// the one for many rows; a list that does not fill its last row tile takes the width that pads it least
+// (mosaic_schedule.h): 280 rows as two tiles of 160 take 290 us, as two of 256 383 us; 32 rows
+// as one of 32 take 194 us (the LM head at 5.6 TB/s), as one of 256 252 us.
 // Preconditions (checked by the launcher): V % 256 == 0, 256*d*2 < 4 GiB; and, in a hidden tensor of 4 GiB or more,
-// no 64 consecutive rows of the list 4 GiB apart (checked on the device, see KernelParams::wide_flag).
-template <bool SAMPLE>
-__global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParams p) {
-  constexpr int NW = 3, NH = 2;
+// no wave's 8*NB consecutive rows of the list 4 GiB apart (checked on the device, see KernelParams::wide_flag).
+constexpr int kRowBytes = 128;                       // one K-tile of a row
+constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
+constexpr int kLdsBytes = 160 * 1024;
+template <bool SAMPLE, int NB>
+__device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, char* smem) {
+  constexpr int kDepth = NB <= 2 ? 3 : 2;            // K-tiles under way, as the generator's depth()
+  constexpr int NW = kDepth + 1, NH = kDepth;
+  constexpr int kHiddenSlot = 32 * NB * kRowBytes;
+  constexpr int kTokens = 32 * NB;
   constexpr int kTileK = 64;
-  constexpr int kRowBytes = 128;
-  constexpr int kOperandBytes = 256 * kRowBytes;        // 32 KiB
   constexpr int kSwzShift = 1;
-  __shared__ __attribute__((aligned(1024))) char smem[(NW + NH) * kOperandBytes];
+  static_assert(NW * kLmHeadSlot + NH * kHiddenSlot <= kLdsBytes, "rings");
   double* red_s = reinterpret_cast<double*>(smem);      // merge scratch aliases W slot 0 at unit end
   float* red_m = reinterpret_cast<float*>(red_s + 256);
   int* red_i = reinterpret_cast<int*>(red_m + 256);
@@ -648,25 +653,20 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   const int wt = wave >> 1;  // token half of the tile
   const int l16 = lane & 15, q = lane >> 4;   // MFMA 16x16x32: row/column lane%16, k group lane/16
 
-  if (p.wide_flag != nullptr && *p.wide_flag != p.wide_run_if) return;   // the other kernel of the two serves this list
-  const int rows = chunk_rows_found(p);
-  if (rows <= 0) return;
-  const Schedule sched = launch_schedule(p, rows);
   const int n_tt = sched.row_tiles;
 
   const int G = gridDim.x;
   const int pos = xcd_contiguous_position((int)blockIdx.x, G);
   const int S = sched.splits;
   const int n_units = n_tt * S;
-  const int A = p.panel < n_tt ? p.panel : n_tt;
+  const int A = NB == 8 ? (p.panel < n_tt ? p.panel : n_tt) : (int)panel_depth((uint32_t)n_tt, NB);
   const int full_panel_units = A * S;
   const int n_panels = (n_tt + A - 1) / A;
 
-  // Direct-to-LDS copy: instruction i (0..7) of this wave fills rows wave*64 + 8*i + lane/8; the swizzle
-  // of row drow + 8*i depends on i only through its parity.
-  const int drow = wave * 64 + (lane >> 3);
-  const uint32_t chunk_even = (uint32_t)(((lane & 7) ^ ((drow >> kSwzShift) & 7)) * 16);
-  const uint32_t chunk_odd = (uint32_t)(((lane & 7) ^ (((drow + 8) >> kSwzShift) & 7)) * 16);
+  // Direct-to-LDS copy: instruction i of this wave fills rows first + 8*i + lane/8 of the tile, first = 64*wave for
+  // the LM head (i = 0..7), 8*NB*wave for the hidden rows (i = 0..NB-1); 16-byte chunks are swizzled by row.
+  const int sub = lane >> 3;
+  auto chunk_of = [&](int row) { return (uint32_t)(((lane & 7) ^ ((row >> kSwzShift) & 7)) * 16); };
   const int nk = p.d / kTileK;
   const uint32_t w_row_bytes = (uint32_t)p.d * 2u;
 
@@ -676,10 +676,13 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   for (int ks = 0; ks < 2; ++ks) {
     const uint32_t o = (uint32_t)(l16 * kRowBytes + (((4 * ks + q) ^ ((l16 >> kSwzShift) & 7)) * 16));
     rdw[ks] = o + (uint32_t)(wv * 128 * kRowBytes);
-    rdh[ks] = o + (uint32_t)(NW * kOperandBytes + wt * 128 * kRowBytes);
+    rdh[ks] = o + (uint32_t)(NW * kLmHeadSlot + wt * (kTokens / 2) * kRowBytes);
   }
 #pragma unroll
-  for (int i = 0; i < 8; ++i) woff[i] = (uint32_t)(drow + 8 * i) * w_row_bytes + ((i & 1) ? chunk_odd : chunk_even);
+  for (int i = 0; i < 8; ++i) {
+    const int row = wave * 64 + 8 * i + sub;
+    woff[i] = (uint32_t)row * w_row_bytes + chunk_of(row);
+  }
 
   // sampling: the generator's key (the statement derives the round keys from it), its multipliers, 1/tau and tau
   const uint32_t seed_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)p.seed_lo);
@@ -690,7 +693,7 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   const uint32_t u_nk = (uint32_t)nk;
   const uint32_t u_wwrap = 256u * w_row_bytes - (uint32_t)(nk - 1) * 128u;
   const uint32_t u_hwrap = (uint32_t)(nk - 1) * 128u;
-  const uint32_t wave_dst = (uint32_t)wave * 64u * kRowBytes;
+  const uint32_t w_dst = (uint32_t)wave * 64u * kRowBytes, h_dst = (uint32_t)(wave * 8 * NB) * kRowBytes;
 
   for (int u = pos, round = 0; u < n_units; u += G, ++round) {
     if (round > 0) meet_before_round(p, round, n_units, G, tid);
@@ -706,14 +709,14 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
     const int total_steps = ntile * nk;
     const uint32_t u_total = (uint32_t)total_steps;
 
-    // Gather: 32-bit byte offsets of the 8 hidden rows this lane copies, from the lowest of the 64 rows this wave
+    // Gather: 32-bit byte offsets of the NB hidden rows this lane copies, from the lowest of the 8*NB rows this wave
     // copies (rows past the end of the chunk re-read the last valid row; their results are never stored).  The
     // offsets fit 32 bits when the hidden tensor is smaller than 4 GiB, and otherwise because this launch only
     // runs when no wave's rows lie that far apart (span_check_kernel).
-    int trow[8], tmin = INT_MAX;
+    int trow[NB], tmin = INT_MAX;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      int j = tt * kTileRows + drow + 8 * i;
+    for (int i = 0; i < NB; ++i) {
+      int j = tt * kTokens + wave * 8 * NB + 8 * i + sub;
       if (j > rows - 1) j = rows - 1;
       int t = p.idx[p.row0 + j];
       t = t < 0 ? 0 : (t > p.T - 1 ? p.T - 1 : t);   // a bad entry of a caller-built list reads a valid row
@@ -727,56 +730,58 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
     }
     tmin = __builtin_amdgcn_readfirstlane(tmin);
     const char* hidden_wave = p.hidden + (int64_t)tmin * p.ldh_bytes;
-    uint32_t hoff[8];
+    uint32_t hoff[NB];
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      hoff[i] = (uint32_t)(trow[i] - tmin) * (uint32_t)p.ldh_bytes + ((i & 1) ? chunk_odd : chunk_even);
+    for (int i = 0; i < NB; ++i)
+      hoff[i] = (uint32_t)(trow[i] - tmin) * (uint32_t)p.ldh_bytes + chunk_of(wave * 8 * NB + 8 * i + sub);
 
-    // Prologue copies, in this order: W0, H0, W1, W2, H1 (tile 0 is needed first, H1 at the first sync).
+    // Prologue copies: W0 and H0, which are needed first, then what else the rings hold.
     auto copy_w = [&](int gw) {
       const char* src = p.w + ((int64_t)(vt0 + gw / nk) * kTileVocab) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes;
-      char* dst = smem + (gw % NW) * kOperandBytes + wave_dst;
+      char* dst = smem + (gw % NW) * kLmHeadSlot + w_dst;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
     };
     auto copy_h = [&](int gh) {
       const char* src = hidden_wave + (gh % nk) * kRowBytes;
-      char* dst = smem + (NW + gh % NH) * kOperandBytes + wave_dst;
+      char* dst = smem + NW * kLmHeadSlot + (gh % NH) * kHiddenSlot + h_dst;
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < NB; ++i)
         __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + hoff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
     };
     wait_vm<0>();
     copy_w(0);
     copy_h(0);
-    int after0 = 0;
-    if (1 < total_steps) { copy_w(1); after0 += 1; }
-    if (2 < total_steps) { copy_w(2); after0 += 1; }
-    if (1 < total_steps) { copy_h(1); after0 += 1; }
-    if (after0 == 3) wait_vm<24>(); else if (after0 == 2) wait_vm<16>(); else if (after0 == 1) wait_vm<8>(); else wait_vm<0>();
+#pragma unroll
+    for (int g = 1; g < NW; ++g)
+      if (g < total_steps) copy_w(g);
+#pragma unroll
+    for (int g = 1; g < NH; ++g)
+      if (g < total_steps) copy_h(g);
+    if (total_steps >= NW && total_steps >= NH) wait_vm<8 * (NW - 1) + NB * (NH - 1)>(); else wait_vm<0>();
     __builtin_amdgcn_s_barrier();
 
-    // State of the asm loop: next tiles to copy are W(3) and H(2) (never issued if past the end).
-    const int gw = 3, gh = 2;
+    // State of the asm loop: next tiles to copy are W(NW) and H(NH) (never issued if past the end).
+    const int gw = NW, gh = NH;
     const uint64_t wsrc0 = (uint64_t)(p.w + ((int64_t)(vt0 + gw / nk) * kTileVocab) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes);
     const uint64_t hsrc0 = (uint64_t)(hidden_wave + (gh % nk) * kRowBytes);
     uint32_t st_wsrc_lo = (uint32_t)wsrc0, st_wsrc_hi = (uint32_t)(wsrc0 >> 32);
     uint32_t st_hsrc_lo = (uint32_t)hsrc0, st_hsrc_hi = (uint32_t)(hsrc0 >> 32);
     uint32_t st_wrd = 0, st_hrd = 0;
-    uint32_t st_wdst = (uint32_t)((gw % NW) * kOperandBytes) + wave_dst;
-    uint32_t st_hdst = (uint32_t)((gh % NH) * kOperandBytes) + wave_dst;
+    uint32_t st_wdst = (uint32_t)((gw % NW) * kLmHeadSlot) + w_dst;
+    uint32_t st_hdst = (uint32_t)((gh % NH) * kHiddenSlot) + h_dst;
     uint32_t st_wk = (uint32_t)(gw % nk), st_hk = (uint32_t)(gh % nk);
     uint32_t st_g = 0;
 
-    float run_m[8], run_ym[8], run_xa[8];
-    double run_s[8];
-    int run_i[8], pos[8];
+    float run_m[NB], run_ym[NB], run_xa[NB];
+    double run_s[NB];
+    int run_i[NB], pos[NB];
 #pragma unroll
-    for (int tb = 0; tb < 8; ++tb) {
+    for (int tb = 0; tb < NB; ++tb) {
       run_m[tb] = kNeg; run_s[tb] = 0.0; run_i[tb] = INT_MAX; run_ym[tb] = kNeg; run_xa[tb] = 0.f; pos[tb] = 0;
       if constexpr (SAMPLE) {   // the position whose row this lane's column tb holds
-        int j = tt * kTileRows + wt * 128 + tb * 16 + l16;
+        int j = tt * kTokens + wt * (kTokens / 2) + tb * 16 + l16;
         if (j > rows - 1) j = rows - 1;
         pos[tb] = p.noise_idx[p.row0 + j];
       }
@@ -801,10 +806,10 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
       const uint32_t st_hwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_hwrap);
         uint32_t addr_tmp0, addr_tmp1;
         const int vb = (vt0 + n) * kTileVocab + wv * 128 + 4 * q;   // vocabulary id of this lane's element 0
-        float tile_m[8], tile_s[8];   // this tile's own triples
-        int tile_i[8];
+        float tile_m[NB], tile_s[NB];   // this tile's own triples
+        int tile_i[NB];
 #pragma unroll
-        for (int tb = 0; tb < 8; ++tb) { tile_m[tb] = kNeg; tile_s[tb] = 0.f; tile_i[tb] = INT_MAX; }
+        for (int tb = 0; tb < NB; ++tb) { tile_m[tb] = kNeg; tile_s[tb] = 0.f; tile_i[tb] = INT_MAX; }
         if constexpr (SAMPLE) {
           // sampling: the same, with the Gumbel-max draw in the reduction (round keys by number too).  The drawn
           // candidate is carried from tile to tile: it bounds what can still win
@@ -817,7 +822,7 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
         }
         // the fold, ~25 instructions per column and tile of 64 K-tiles: 0.5% of the tile
 #pragma unroll
-        for (int tb = 0; tb < 8; ++tb) {
+        for (int tb = 0; tb < NB; ++tb) {
           if constexpr (!SAMPLE) run_i[tb] = tile_m[tb] > run_m[tb] ? tile_i[tb] : run_i[tb];   // ascending tiles
           merge_sum(run_m[tb], run_s[tb], tile_m[tb], tile_sum(tile_m[tb], tile_s[tb]));
         }
@@ -827,7 +832,7 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
     // Unit end: fold the four lanes that share a token (lane ^ 16, lane ^ 32), then the two waves that
     // share it (vocabulary halves) through LDS, and publish one partial triple per row.
 #pragma unroll
-    for (int tb = 0; tb < 8; ++tb) {
+    for (int tb = 0; tb < NB; ++tb) {
 #pragma unroll
       for (int x = 16; x <= 32; x <<= 1) {
         const float m2 = __shfl_xor(run_m[tb], x, 64);
@@ -844,8 +849,8 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
     __syncthreads();  // every wave is done with the ring (the merge scratch aliases it)
     if (wv == 1 && q == 0) {
 #pragma unroll
-      for (int tb = 0; tb < 8; ++tb) {
-        const int e = wt * 128 + tb * 16 + l16;
+      for (int tb = 0; tb < NB; ++tb) {
+        const int e = wt * (kTokens / 2) + tb * 16 + l16;
         red_m[e] = run_m[tb];
         red_s[e] = run_s[tb];
         red_i[e] = run_i[tb];
@@ -858,10 +863,10 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
     __syncthreads();
     if (wv == 0 && q == 0) {
 #pragma unroll
-      for (int tb = 0; tb < 8; ++tb) {
-        const int e = wt * 128 + tb * 16 + l16;
-        if (tt * kTileRows + e >= rows) continue;
-        const int64_t slot = (int64_t)sp * sched.stride + tt * kTileRows + e;
+      for (int tb = 0; tb < NB; ++tb) {
+        const int e = wt * (kTokens / 2) + tb * 16 + l16;
+        if (tt * kTokens + e >= rows) continue;
+        const int64_t slot = (int64_t)sp * sched.stride + tt * kTokens + e;
         if constexpr (SAMPLE) {
           merge_sum(run_m[tb], run_s[tb], red_m[e], red_s[e]);
           merge_pick(run_ym[tb], run_xa[tb], run_i[tb], red_ym[e], red_xa[e], red_i[e]);
@@ -875,6 +880,25 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
       }
     }
     __syncthreads();
+  }
+}
+
+template <bool SAMPLE>
+__global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParams p) {
+  __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
+  if (p.wide_flag != nullptr && *p.wide_flag != p.wide_run_if) return;   // the other kernel of the two serves this list
+  const int rows = chunk_rows_found(p);
+  if (rows <= 0) return;
+  const Schedule sched = launch_schedule(p, rows);
+  switch (sched.width) {
+    case 1: w4_units<SAMPLE, 1>(p, sched, rows, smem); break;
+    case 2: w4_units<SAMPLE, 2>(p, sched, rows, smem); break;
+    case 3: w4_units<SAMPLE, 3>(p, sched, rows, smem); break;
+    case 4: w4_units<SAMPLE, 4>(p, sched, rows, smem); break;
+    case 5: w4_units<SAMPLE, 5>(p, sched, rows, smem); break;
+    case 6: w4_units<SAMPLE, 6>(p, sched, rows, smem); break;
+    case 7: w4_units<SAMPLE, 7>(p, sched, rows, smem); break;
+    default: w4_units<SAMPLE, 8>(p, sched, rows, smem); break;
   }
 }
 
@@ -1009,6 +1033,8 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   int32_t* const flag = p.found_splits + 1;
   const int32_t vocab_tiles = (a.V + kTileVocab - 1) / kTileVocab;
   p.sched.vocab_tiles = (uint32_t)(paired ? vocab_tiles - 1 : vocab_tiles);
+  p.sched.k_tiles = (uint32_t)(a.d / MOSAIC_K_TILE);
+  p.sched.widths = fast || paired ? 0xff : 0x80;   // the general kernel has the one width
   p.sched.grid = (uint32_t)plan.grid;
   p.sched.extra = paired ? 1 : 0;
   p.sched.slots64 = (uint32_t)(slots / 64 < INT32_MAX ? slots / 64 : INT32_MAX);
@@ -1033,14 +1059,13 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
     p.bound_rows = tail.bound_rows = (int32_t)cap;
     p.bound = tail.bound = choose_schedule(p.sched, (int32_t)cap);
     const int64_t tiles = (cap + kTileRows - 1) / kTileRows;
-    const bool several_rounds = tiles * p.bound.splits > plan.grid || (paired && tiles > plan.grid);
+    const bool several_rounds = (int64_t)p.bound.row_tiles * p.bound.splits > plan.grid || (paired && tiles > plan.grid);
     if (several_rounds || wide)
       rc |= launch_kernel(clear_round_counters_kernel, dim3(1), dim3(256), stream, counters, kSyncSlots + 2);
     p.sync = several_rounds ? counters : nullptr;   // not cleared: nobody meets (fewer rows may still take two rounds)
     if (!several_rounds) tail.sync = nullptr;
     if (wide)
-      rc |= launch_kernel(span_check_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), stream, a.idx, a.count,
-                          (int32_t)row0, plan.rows_per_chunk, (int32_t)a.max_rows, (int32_t)a.T, p.ldh_bytes, flag);
+      rc |= launch_kernel(span_check_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), stream, p, flag);
     auto launch_general = [&](const KernelParams& kp, int64_t blocks) {
       return sample ? launch_kernel(masked_logits_kernel<3, 2, true>, dim3((unsigned)blocks), dim3(kThreads), stream, kp)
                     : launch_kernel(masked_logits_kernel<3, 2, false>, dim3((unsigned)blocks), dim3(kThreads), stream, kp);
@@ -1051,6 +1076,8 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
       if (wide) {   // the same work on the general kernel, for lists the span check flags
         KernelParams fallback = p;
         fallback.wide_run_if = 1;
+        fallback.sched.widths = 0x80;
+        fallback.bound = choose_schedule(fallback.sched, (int32_t)cap);
         rc |= launch_general(fallback, plan.grid);
       }
     } else {

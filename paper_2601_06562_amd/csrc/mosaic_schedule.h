@@ -16,6 +16,7 @@
 namespace mosaic {
 
 struct Schedule {
+  int32_t width;       // of a row tile, in units of 32 rows
   int32_t row_tiles;   // row tiles that hold rows
   int32_t splits;      // vocabulary ranges of every row tile
   int32_t stride;      // rows of one split in the partial arrays
@@ -23,6 +24,8 @@ struct Schedule {
 
 struct ScheduleInput {
   uint32_t vocab_tiles;   // tiles to divide (without the ragged last one where a second launch covers it)
+  uint32_t k_tiles;       // K-tiles of a vocabulary tile
+  uint32_t widths;        // bit w - 1: row tiles of 32*w rows are on offer
   uint32_t grid;          // workgroups of the launch
   uint32_t extra;         // partial slots per row beyond the splits (1 where a second launch adds its own)
   uint32_t slots64;       // rows x splits the partial arrays hold, in units of 64
@@ -33,16 +36,40 @@ __host__ __device__ inline uint32_t ceil_div(uint32_t a, uint32_t b) { return (a
 // Rows of one split in the partial arrays.
 __host__ __device__ inline int32_t partial_stride(int32_t rows) { return (rows + 63) & ~63; }
 
-// The candidate that uses `extra_rounds` rounds of the grid more than the fewest possible, as (cost, splits) packed
-// into one integer: the smaller one is the better one.  A round lasts as long as its longest unit, a unit costs half
-// a tile on top of its tiles (pipeline fill, merge); of the split counts that fit the same rounds the largest has the
-// shortest units, and of those with equally long units the smallest makes the fewest partial results.  At least four
-// splits where vocabulary and memory allow: the 32 workgroups that share an L2 then work on 8 row tiles x 4 splits
-// (256 row tiles in one split each: 62 ms; in four: 47 ms).
-constexpr int kScheduleRounds = 64;   // candidates looked at: the rounds' quantisation is below 2% beyond
-__host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, int32_t rows, uint32_t extra_rounds) {
+// Row tiles scheduled side by side: the workgroups behind one L2 share the LM-head tiles of that many, and the hidden
+// tiles of as many splits as are left of them.  Eight tiles of 256 rows (8 x 4 of the 32 workgroups), sixteen of the
+// narrow ones, whose traffic is nearly all LM head; evenly deep panels, since a lone row tile streams the whole LM head
+// once more (280 rows as 8 + 1 tiles of 32: 861 us, as 9: 595 us).
+__host__ __device__ inline uint32_t panel_depth(uint32_t row_tiles, uint32_t width) {
+  const uint32_t side = width <= 4 ? 16 : 8;
+  return ceil_div(row_tiles, ceil_div(row_tiles, side));
+}
+
+// What a unit's parts take, in units of 10 ns, fitted to measurements at widths 1..8 and 32..4096 rows of a 126464 x 4096
+// and a 32000 x 1024 LM head (most within 10%).  A K-tile: bound by the copies into LDS up to four token blocks a wave
+// (0.64 to 0.76 us), by the matrix cores beyond (1.26 us at eight); or by memory, which brings the 32 KiB of LM head
+// for all compute units at 5.6 TB/s in 1.48 us, shared by the panel's row tiles; the shorter of the two hides
+// but for a sixth.  The reduction of a tile: 0.56 us per token block.  A unit besides: pipeline fill and merge.
+__host__ __device__ inline uint32_t k_tile_time(uint32_t width, uint32_t share) {
+  const uint32_t compute = width <= 4 ? 60 + 4 * width : (36 + 27 * width) / 2, memory = 148 / share;
+  return compute > memory ? compute + memory / 6 : memory + compute / 6;
+}
+__host__ __device__ inline uint32_t reduction_time(uint32_t width) { return 56 * width; }
+__host__ __device__ inline uint32_t unit_time(uint32_t width) { return 600 + 150 * width; }
+
+// The candidate with row tiles of 32*width rows that uses `extra_rounds` rounds of the grid more than the fewest
+// possible, as (cost, width, splits) packed into one integer: the smaller one is the better one.  A round lasts as
+// long as its longest unit; of the split counts that fit the same rounds the largest has the shortest units, and of
+// those with equally long units the smallest makes the fewest partial results.  At least four splits where vocabulary
+// and memory allow: the 32 workgroups that share an L2 then work on 8 row tiles x 4 splits (256 row tiles in one
+// split each: 62 ms; in four: 47 ms).
+constexpr uint32_t kScheduleRounds = 32;       // candidates per width: the rounds' quantisation is below 3% beyond
+constexpr int32_t kNarrowRows = 1 << 20;       // beyond, the widest tile always pays (and 32 bits hold its units)
+__host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, int32_t rows, uint32_t width,
+                                                       uint32_t extra_rounds) {
+  if ((in.widths >> (width - 1) & 1) == 0 || (width < 8 && rows > kNarrowRows)) return ~(uint64_t)0;
   // 32-bit throughout (rows < 2^31, so at most 2^23 row tiles and 2^31 units): a wide division costs the device 10x
-  const uint32_t row_tiles = ceil_div((uint32_t)rows, MOSAIC_ROW_TILE);
+  const uint32_t row_tiles = ceil_div((uint32_t)rows, 32 * width);
   const uint32_t fit = in.slots64 / ((uint32_t)partial_stride(rows) >> 6);
   uint32_t most = in.vocab_tiles < MOSAIC_MAX_VOCAB_SPLITS ? in.vocab_tiles : MOSAIC_MAX_VOCAB_SPLITS;
   if (fit < most + in.extra) most = fit <= in.extra + 1 ? 1 : fit - in.extra;
@@ -54,35 +81,44 @@ __host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, 
   uint32_t splits = ceil_div(in.vocab_tiles, longest);
   if (splits < least) splits = least;
   const uint32_t rounds = ceil_div(row_tiles * splits, in.grid);
-  return (uint64_t)rounds * (2 * longest + 1) << 16 | splits;
+  const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(row_tiles, width)) + reduction_time(width);
+  const uint64_t cost = (uint64_t)rounds * (((uint64_t)longest * tile + unit_time(width)) >> 3);
+  return cost << 20 | (uint64_t)(8 - width) << 16 | splits;
 }
 
 __host__ __device__ inline Schedule schedule_of(int32_t rows, uint64_t best) {
-  return Schedule{(int32_t)ceil_div((uint32_t)rows, MOSAIC_ROW_TILE), (int32_t)(best & 0xffff), partial_stride(rows)};
+  const int32_t width = 8 - (int32_t)(best >> 16 & 15);
+  return Schedule{width, (int32_t)ceil_div((uint32_t)rows, 32 * (uint32_t)width), (int32_t)(best & 0xffff),
+                  partial_stride(rows)};
 }
 
 // On the host: for the bound the plan was made for, handed to the kernels so that they need not search when the
 // count turns out to be that bound.
 inline Schedule choose_schedule(const ScheduleInput& in, int32_t rows) {
   uint64_t best = ~(uint64_t)0;
-  for (int32_t r = 0; r < kScheduleRounds; ++r) {
-    const uint64_t c = schedule_candidate(in, rows, (uint32_t)r);
-    best = c < best ? c : best;
-  }
+  for (uint32_t w = 1; w <= 8; ++w)
+    for (uint32_t r = 0; r < kScheduleRounds; ++r) {
+      const uint64_t c = schedule_candidate(in, rows, w, r);
+      best = c < best ? c : best;
+    }
   return schedule_of(rows, best);
 }
 
-// On the device: one candidate per lane, the same result in every wave (~1 us).
+// On the device: eight lanes per width, the same result in every wave (~1 us).
 __device__ __forceinline__ Schedule choose_schedule_wave(const ScheduleInput& in, int32_t rows) {
-  uint64_t best = schedule_candidate(in, rows, threadIdx.x & 63);
+  const uint32_t lane = threadIdx.x & 63;
+  uint64_t best = ~(uint64_t)0;
+  for (uint32_t r = lane & 7; r < kScheduleRounds; r += 8) {
+    const uint64_t c = schedule_candidate(in, rows, 1 + (lane >> 3), r);
+    best = c < best ? c : best;
+  }
 #pragma unroll
   for (int x = 32; x >= 1; x >>= 1) {
     const uint64_t other = __shfl_xor((unsigned long long)best, x, 64);
     best = other < best ? other : best;
   }
-  Schedule s = schedule_of(rows, best);
-  s.splits = __builtin_amdgcn_readfirstlane(s.splits);
-  return s;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)best);   // width and splits sit there
+  return schedule_of(rows, lo);
 }
 
 }  // namespace mosaic

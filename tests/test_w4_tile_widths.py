@@ -1,0 +1,182 @@
+"""The generated statements of the narrower row tiles (32 to 224 tokens), on the CPU: the K-loop of each under the ring
+protocol of test_w4_loop_protocol.py (its interpreter, with this width's ring geometry), and the reduction of each,
+which has to be the widest tile's, column by column, on this width's accumulators."""
+import re
+from fractions import Fraction
+
+import pytest
+
+import test_w4_loop_protocol as protocol
+from test_w4_loop_protocol import H_BASE, MASK32, W_BASE
+
+spec = protocol.importlib.util.spec_from_file_location("gen_w4_loop", protocol.GEN)
+gen = protocol.importlib.util.module_from_spec(spec)
+spec.loader.exec_module(gen)
+
+
+def listing(nb, sample):
+    gen.SHAPE["nb"] = nb
+    gen.lines.clear()
+    gen.uid[0] = 0
+    gen.build_tile_sample() if sample else gen.build_tile()
+    out = [ln.strip() for ln in gen.lines]
+    gen.lines.clear()
+    cut = next(i for i, ln in enumerate(out) if ln.startswith(("v_accvgpr_read_b32", "s_mov_b32 s68, %[seed_lo]")))
+    return out[:cut], out[cut:]
+
+
+class Sim(protocol.Sim):
+    """The interpreter with this width's rings: its LM-head slots of 32 KiB, then its hidden slots of 4*nb KiB.
+    A width's 8*nb MFMAs per group count as the 64 of the widest tile."""
+
+    def __init__(self, lines, nb, nk, ntile):
+        super().__init__(lines, nk, ntile)
+        self.nb, self.nw, self.nh = nb, gen.depth() + 1, gen.depth()
+        assert (self.nw * 0x8000 + self.nh * nb * 0x1000) <= 160 * 1024
+        self.mfma_count = Fraction(0)
+
+    def slot_of(self, addr):
+        ring = self.nw * 0x8000
+        slot = addr // 0x8000 if addr < ring else self.nw + (addr - ring) // (self.nb * 0x1000)
+        assert slot < self.nw + self.nh
+        return slot
+
+    def offset_in(self, addr):
+        ring = self.nw * 0x8000
+        return addr % 0x8000 if addr < ring else (addr - ring) % (self.nb * 0x1000)
+
+    def copy(self, operand):
+        m0 = self.reg["m0"]
+        slot = self.slot_of(m0)
+        parts = self.copy_parts.get(slot, 0)
+        if operand == "W":
+            tile, rest = divmod((self.reg["s96"] | self.reg["s97"] << 32) - W_BASE, self.tile_stride)
+            ident = tile * self.nk + rest // 128
+            assert rest % 128 == 0 and rest // 128 < self.nk and ident < self.total and slot < self.nw
+            assert ident == self.next_w_copy and slot == ident % self.nw
+        else:
+            off = (self.reg["s98"] | self.reg["s99"] << 32) - H_BASE
+            ident = off // 128
+            assert off % 128 == 0 and 0 <= ident < self.nk and slot >= self.nw
+            assert ident == self.next_h_copy % self.nk and self.next_h_copy < self.total
+            assert slot - self.nw == self.next_h_copy % self.nh
+        assert slot not in self.reads_this_interval, f"copy into slot {slot} that a wave may still be reading"
+        if parts == 0:
+            assert slot not in self.unpublished
+            self.unpublished[slot] = ident
+            self.copies_this_interval.add(slot)
+        assert self.unpublished[slot] == ident and self.offset_in(m0) == 1024 * parts
+        self.vm_queue.append(slot)
+        self.copy_parts[slot] = (parts + 1) % (8 if operand == "W" else self.nb)
+        if self.copy_parts[slot] == 0:
+            if operand == "W":
+                self.next_w_copy += 1
+            else:
+                self.next_h_copy += 1
+
+    def ds_read(self, dst, addr_reg, offset):
+        base = self.reg[addr_reg]
+        slot = self.slot_of(base + offset)
+        operand = "W" if slot < self.nw else "H"
+        assert self.slot_of(base) == slot and (operand == "W") == (addr_reg == "%[vt0]")
+        first = int(re.fullmatch(r"v\[(\d+):\d+\]", dst).group(1))
+        n = (first - 112) // 4 % 16
+        assert n == offset // 2048 + (0 if operand == "W" else 8)
+        assert slot not in self.unpublished and slot in self.published and slot not in self.copies_this_interval
+        self.reads_this_interval.add(slot)
+        group = self.mfma_count // 64
+        assert self.frag_last_group.get(dst, -1) < group or self.mfma_count % 64 == 0
+        self.frag[dst] = (operand, self.published[slot], 1 if self.offset_in(base) % 128 == 64 else 0, False)
+
+    def mfma(self, a, b, dst=None, src_c=None):
+        super().mfma(a, b, dst, src_c)
+        self.mfma_count += Fraction(8, self.nb) - 1
+
+    def prologue(self):
+        NW, NH, wptr = self.nw, self.nh, lambda g: W_BASE + (g // self.nk) * self.tile_stride + (g % self.nk) * 128
+        self.published[0] = 0
+        self.published[self.nw] = 0
+        for g in range(1, min(NW, self.total)):              # as the kernel issues them
+            self.unpublished[g] = g
+            self.vm_queue += [g] * 8
+        for g in range(1, min(NH, self.total)):
+            self.unpublished[NW + g] = g % self.nk
+            self.vm_queue += [NW + g] * self.nb
+        self.next_w_copy, self.next_h_copy = NW, NH
+        w, h = wptr(NW), H_BASE + (NH % self.nk) * 128
+        self.reg.update({
+            "%[wsrc_lo]": w & MASK32, "%[wsrc_hi]": w >> 32, "%[hsrc_lo]": h & MASK32, "%[hsrc_hi]": h >> 32,
+            "%[wrd]": 0, "%[hrd]": 0, "%[wdst]": 0, "%[hdst]": 0, "%[wk]": NW % self.nk, "%[hk]": NH % self.nk,
+            "%[g]": 0, "%[total]": self.total, "%[nk]": self.nk,
+            "%[wwrap]": (self.tile_stride - (self.nk - 1) * 128) & MASK32, "%[hwrap]": (self.nk - 1) * 128,
+            "%[rdw0]": 0, "%[rdw1]": 64, "%[rdh0]": self.nw * 0x8000, "%[rdh1]": self.nw * 0x8000 + 64,
+        })
+
+
+@pytest.mark.parametrize("sample", [False, True])
+@pytest.mark.parametrize("nb", range(1, 9))
+def test_ring_protocol_of_every_width(nb, sample):
+    loop, _ = listing(nb, sample)
+    for nk, ntile in [(1, 1), (1, 5), (2, 3), (3, 1), (3, 4), (4, 2), (5, 31), (8, 2), (56, 2), (64, 1)]:
+        sim = Sim(loop, nb, nk, ntile)
+        sim.prologue()
+        for _ in range(ntile):
+            sim.run_statement()
+        total = nk * ntile
+        assert sim.mfma_count == 128 * total and sim.reg["%[g]"] == total
+        assert sim.started == set(range(32 * nb))
+        assert sim.next_w_copy == max(total, sim.nw) and sim.next_h_copy == max(total, sim.nh)
+        assert not sim.unpublished
+
+
+@pytest.mark.parametrize("nb", range(1, 8))
+def test_a_missing_wait_is_caught_at_every_width(nb):
+    loop, _ = listing(nb, False)
+    sim = Sim([ln for ln in loop if not ln.startswith("s_waitcnt vmcnt")], nb, 5, 3)
+    sim.prologue()
+    with pytest.raises(AssertionError):
+        for _ in range(3):
+            sim.run_statement()
+
+
+@pytest.mark.parametrize("nb", range(1, 9))
+def test_copies_keep_the_wait_state_behind_their_m0_write(nb):
+    """A direct-to-LDS load needs an instruction between the write of M0 and itself."""
+    for sample in (False, True):
+        loop, _ = listing(nb, sample)
+        for a, b in zip(loop, loop[1:]):
+            assert not (a.startswith("s_add_u32 m0") and b.startswith("global_load_lds"))
+
+
+@pytest.mark.parametrize("sample", [False, True])
+@pytest.mark.parametrize("nb", range(1, 8))
+def test_reduction_of_every_width_is_the_widest_tiles(nb, sample):
+    plain = lambda ln: re.sub(r"\bL([a-z]+)\d+_%=", r"L\1", ln)
+    _, wide = listing(8, sample)
+    _, red = listing(nb, sample)
+
+    def widen(m):                       # accumulator (bi*nb + tb)*4 + r of this width -> (bi*8 + tb)*4 + r
+        block, r = divmod(int(m.group(1)), 4)
+        return f", a{(block // nb * 8 + block % nb) * 4 + r}"
+    got = [plain(re.sub(r", a(\d+)$", widen, ln)) if ln.startswith("v_accvgpr_read") else plain(ln) for ln in red]
+    wide = [plain(ln) for ln in wide]
+
+    def columns(prog):                  # cut at the first accumulator read of each column; drop what follows the last
+        starts = [i for i, ln in enumerate(prog) if re.match(r"v_accvgpr_read_b32 v112,", ln)]
+        head = starts[0]
+        while sample and not prog[head].startswith("ds_bpermute_b32 v177"):
+            head -= 1
+        back = starts[0] - head
+        return prog[:head], [prog[a - back:b - back] for a, b in zip(starts, starts[1:])], prog[starts[-1] - back:]
+    (head, cols, last), (whead, wcols, _) = columns(got), columns(wide)
+    assert head == whead and cols == wcols[:nb - 1]
+    body = wcols[nb - 1]
+    assert last[:len(body)] == body
+    rest = last[len(body):]
+    if not sample:
+        assert rest == []
+    else:                               # the exact paths out of line: one block per quad, the widest tile's first ones
+        at = next(i for i, ln in enumerate(wide) if ln == "s_branch Ldone")
+        names = lambda ln: re.sub(r"L(slow|flush|back|queue|full)\b", r"L", ln)
+        assert rest[0] == "s_branch Ldone" and rest[-1] == "Ldone:"
+        assert [names(x) for x in rest[1:-1]] == [names(x) for x in wide[at + 1:at + len(rest) - 1]]
