@@ -30,7 +30,8 @@ NK128 = "s94"
 
 lines = []
 uid = [0]
-SHAPE = {"nb": 8}          # token blocks of 16 per wave
+SHAPE = {"nb": 8,          # token blocks of 16 per wave
+         "ragged": False}  # the statement also serves a vocabulary's ragged last tile
 
 
 def nb():
@@ -652,6 +653,27 @@ def build_tile():
         reduce_column(tb)
 
 
+def mask_counted():
+    """The last tile of a vocabulary that is no multiple of 256 lies over the vocabulary's last 256 ids; those below
+    %[first] belong to the tile before it and are taken out here: their logits become -2^100.  %[first] is 0 for every
+    other tile.  One compare per element serves all columns; a compare's result is read two wait states later."""
+    skip = label("whole")
+    e("s_cmp_eq_u32 %[first], 0")
+    e(f"s_cbranch_scc1 {skip}")
+    e(f"v_sub_u32 {ET}, %[first], %[vb]")             # elements with a code below it (signed) are taken out
+    e(f"v_mov_b32 {EY}, {hex(KNEG)}")
+    for el in range(32):
+        e(f"v_cmp_lt_i32 vcc, {16 * (el // 4) + el % 4}, {ET}")
+        for tb in range(nb()):
+            e(f"v_accvgpr_read_b32 {X[tb]}, {acc_reg(el // 4, tb, el % 4)}")
+        e("s_nop 1")
+        for tb in range(nb()):
+            e(f"v_cndmask_b32 {X[tb]}, {X[tb]}, {EY}, vcc")
+        for tb in range(nb()):
+            e(f"v_accvgpr_write_b32 {acc_reg(el // 4, tb, el % 4)}, {X[tb]}")
+    e(f"{skip}:")
+
+
 def build_literal():
     """The K-loop on fragments and accumulators named by number."""
     saved = ([row[:] for row in FA], [row[:] for row in FB])
@@ -663,6 +685,8 @@ def build_literal():
     LITERAL_ACC[0] = False
     for b in range(2):
         FA[b][:], FB[b][:] = saved[0][b], saved[1][b]
+    if SHAPE["ragged"]:
+        mask_counted()
 
 
 def build():
@@ -732,7 +756,7 @@ def build():
 
 
 def write_statement(f, blocks, sample):
-    SHAPE["nb"] = blocks
+    SHAPE.update(nb=blocks, ragged=True)
     lines.clear()
     uid[0] = 2000 if sample else 1000
     if sample:
@@ -762,7 +786,7 @@ def write_statement(f, blocks, sample):
     for name in ("total", "nk", "wwrap", "hwrap"):
         ins.append(f'[{name}] "s"(st_{name})')
     clob = ['"s94"', '"s95"', '"s96"', '"s97"', '"s98"', '"s99"', '"vcc"', '"scc"', '"m0"', '"memory"']
-    ins.append('[vb] "v"(vb)')
+    ins += ['[vb] "v"(vb)', '[first] "s"(st_first)']
     clob = [f'"a{i}"' for i in range(32 * blocks)] + [f'"s{i}"' for i in range(88, 94)] + clob
     if sample:
         ins += [f'[pos{tb}] "v"(pos[{tb}])' for tb in range(blocks)]
@@ -786,6 +810,7 @@ def main(folder):
             for blocks in range(1, 9):
                 write_statement(f, blocks, sample)
     lines.clear()
+    SHAPE["ragged"] = False
     build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers
 
 

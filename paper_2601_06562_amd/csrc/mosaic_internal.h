@@ -53,7 +53,7 @@ struct KernelChoice {
   bool wide;     // hidden tensor of 4 GiB or more: the 4-wave launch(es) run only where every 64 consecutive rows of
                  // the list lie less than 4 GiB apart (checked on the device); else the general kernel does the work
 };
-KernelChoice choose_kernel(int64_t T, int64_t ld_h, int32_t d, int32_t V, const mosaic_plan& plan);
+KernelChoice choose_kernel(int64_t T, int64_t ld_h, int32_t d, int32_t V, const mosaic_plan& plan, bool sample);
 // Name(s) of the kernel(s) launch_masked_logits picks for these sizes and this plan (static storage).
 const char* masked_logits_kernel_name(int64_t T, int64_t ld_h, int32_t d, int32_t V, const mosaic_plan& plan,
                                       bool sample);

@@ -628,7 +628,11 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 // the one for many rows; a list that does not fill its last row tile takes the width that pads it least
 // (mosaic_schedule.h): 280 rows as two tiles of 160 take 290 us, as two of 256 383 us; 32 rows
 // as one of 32 take 194 us (the LM head at 5.6 TB/s), as one of 256 252 us.
-// Preconditions (checked by the launcher): V % 256 == 0, 256*d*2 < 4 GiB; and, in a hidden tensor of 4 GiB or more,
+// A vocabulary that is no multiple of 256 ends in a tile over its last 256 ids, of which those that the tile before it
+// has counted are taken out before the reduction; the general kernel on that tile alone, as a second launch, cost
+// 100 to 130 us for four row tiles.
+// Preconditions (checked by the launcher): V % 256 == 0, or V >= 256, five K-tiles and, sampling, V % 4 == 0;
+// 256*d*2 < 4 GiB; and, in a hidden tensor of 4 GiB or more,
 // no wave's 8*NB consecutive rows of the list 4 GiB apart (checked on the device, see KernelParams::wide_flag).
 constexpr int kRowBytes = 128;                       // one K-tile of a row
 constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
@@ -691,7 +695,11 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const float tau_s = p.tau;
   const float inv_tau_log2e = SAMPLE ? kLog2e / p.tau : 0.f;
   const uint32_t u_nk = (uint32_t)nk;
+  // from a vocabulary tile's last K-tile to the next tile's first: 256 rows on, or, into the ragged last tile, V % 256
   const uint32_t u_wwrap = 256u * w_row_bytes - (uint32_t)(nk - 1) * 128u;
+  const int ragged_rows = p.V % kTileVocab, ragged_tile = ragged_rows != 0 ? p.V / kTileVocab : -1;
+  const uint32_t u_wwrap_ragged = (uint32_t)ragged_rows * w_row_bytes - (uint32_t)(nk - 1) * 128u;
+  auto first_id = [&](int vt) { return vt == ragged_tile ? p.V - kTileVocab : vt * kTileVocab; };
   const uint32_t u_hwrap = (uint32_t)(nk - 1) * 128u;
   const uint32_t w_dst = (uint32_t)wave * 64u * kRowBytes, h_dst = (uint32_t)(wave * 8 * NB) * kRowBytes;
 
@@ -737,7 +745,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
 
     // Prologue copies: W0 and H0, which are needed first, then what else the rings hold.
     auto copy_w = [&](int gw) {
-      const char* src = p.w + ((int64_t)(vt0 + gw / nk) * kTileVocab) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes;
+      const char* src = p.w + (int64_t)first_id(vt0 + gw / nk) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes;
       char* dst = smem + (gw % NW) * kLmHeadSlot + w_dst;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
@@ -764,7 +772,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
 
     // State of the asm loop: next tiles to copy are W(NW) and H(NH) (never issued if past the end).
     const int gw = NW, gh = NH;
-    const uint64_t wsrc0 = (uint64_t)(p.w + ((int64_t)(vt0 + gw / nk) * kTileVocab) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes);
+    const uint64_t wsrc0 = (uint64_t)(p.w + (int64_t)first_id(vt0 + gw / nk) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes);
     const uint64_t hsrc0 = (uint64_t)(hidden_wave + (gh % nk) * kRowBytes);
     uint32_t st_wsrc_lo = (uint32_t)wsrc0, st_wsrc_hi = (uint32_t)(wsrc0 >> 32);
     uint32_t st_hsrc_lo = (uint32_t)hsrc0, st_hsrc_hi = (uint32_t)(hsrc0 >> 32);
@@ -802,10 +810,12 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       {
       const uint32_t st_total = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_total);
       const uint32_t st_nk = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_nk);
-      const uint32_t st_wwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_wwrap);
+      const bool ragged_next = vt0 + n + 1 == ragged_tile, ragged = vt0 + n == ragged_tile;
+      const uint32_t st_wwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ragged_next ? u_wwrap_ragged : u_wwrap));
+      const uint32_t st_first = (uint32_t)__builtin_amdgcn_readfirstlane(ragged ? ragged_tile * kTileVocab : 0);
       const uint32_t st_hwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_hwrap);
         uint32_t addr_tmp0, addr_tmp1;
-        const int vb = (vt0 + n) * kTileVocab + wv * 128 + 4 * q;   // vocabulary id of this lane's element 0
+        const int vb = first_id(vt0 + n) + wv * 128 + 4 * q;   // vocabulary id of this lane's element 0
         float tile_m[NB], tile_s[NB];   // this tile's own triples
         int tile_i[NB];
 #pragma unroll
@@ -1027,7 +1037,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.wide_flag = nullptr;
   p.wide_run_if = 0;
 
-  const KernelChoice choice = choose_kernel(a.T, a.ld_h, a.d, a.V, plan);
+  const KernelChoice choice = choose_kernel(a.T, a.ld_h, a.d, a.V, plan, sample);
   const bool fast = choice.fast, paired = choice.paired, wide = choice.wide;
   p.found_splits = p.sync + kSyncSlots;
   int32_t* const flag = p.found_splits + 1;

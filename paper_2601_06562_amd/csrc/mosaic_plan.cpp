@@ -47,18 +47,23 @@ int32_t choose_vocab_splits(int64_t row_tiles, int64_t vocab_tiles, int32_t num_
   return best;
 }
 
-// Which kernel(s) serve a call.  The hand-scheduled 4-wave kernel needs whole vocabulary tiles and addresses the 64
-// rows a wave copies by 32-bit offsets from the lowest of them: always possible in a hidden tensor smaller than
-// 4 GiB, and in a larger one unless such a group of rows lies 4 GiB or more apart, which only the device can tell
-// (`wide`: both kernels are launched and a flag decides).  A vocabulary with a ragged last tile is covered by a pair
-// of launches: the 4-wave kernel on the whole tiles with S - 1 splits and the general 8-wave kernel on the last
-// tile as split S - 1.  Everything else (and plans that ask for it) goes to the general kernel alone.
-KernelChoice choose_kernel(int64_t T, int64_t ld_h, int32_t d, int32_t V, const mosaic_plan& plan) {
+// Which kernel(s) serve a call.  The hand-scheduled 4-wave kernel addresses the rows a wave copies by 32-bit offsets
+// from the lowest of them: always possible in a hidden tensor smaller than 4 GiB, and in a larger one unless such a
+// group of rows lies 4 GiB or more apart, which only the device can tell (`wide`: both kernels are launched and a flag
+// decides).  A ragged last vocabulary tile is the 4-wave kernel's own from kRaggedKTiles K-tiles on: its copies run up
+// to four K-tiles ahead and must not reach past the next tile while the step into a ragged one is another than into a
+// whole one.  That tile begins at id V - 256, and a sampling step draws its noise for four ids at a time from a multiple
+// of four on, so there V has to be one.  Otherwise the vocabulary is covered by a pair of launches: the 4-wave kernel on the whole tiles and the
+// general 8-wave kernel on the last tile as one more split.  Everything else (and plans that ask for it) goes to the
+// general kernel alone.
+constexpr int32_t kRaggedKTiles = 5;
+KernelChoice choose_kernel(int64_t T, int64_t ld_h, int32_t d, int32_t V, const mosaic_plan& plan, bool sample) {
   const int64_t vocab_tiles = ((int64_t)V + MOSAIC_VOCAB_TILE - 1) / MOSAIC_VOCAB_TILE;
   const bool fast_ok = (plan.flags & MOSAIC_PLAN_GENERAL_KERNEL) == 0 &&
                        (uint64_t)MOSAIC_VOCAB_TILE * (uint64_t)d * 2u < ((uint64_t)1 << 32);
   KernelChoice c;
-  c.fast = fast_ok && V % MOSAIC_VOCAB_TILE == 0;
+  c.fast = fast_ok && (V % MOSAIC_VOCAB_TILE == 0 || (V >= MOSAIC_VOCAB_TILE && d / MOSAIC_K_TILE >= kRaggedKTiles &&
+                                                              (!sample || V % 4 == 0)));
   c.paired = fast_ok && !c.fast && vocab_tiles >= 2 && plan.vocab_splits >= 2;
   c.wide = (c.fast || c.paired) && (uint64_t)T * (uint64_t)(ld_h * 2) >= ((uint64_t)1 << 32);
   return c;
@@ -66,7 +71,7 @@ KernelChoice choose_kernel(int64_t T, int64_t ld_h, int32_t d, int32_t V, const 
 
 const char* masked_logits_kernel_name(int64_t T, int64_t ld_h, int32_t d, int32_t V, const mosaic_plan& plan,
                                       bool sample) {
-  const KernelChoice c = choose_kernel(T, ld_h, d, V, plan);
+  const KernelChoice c = choose_kernel(T, ld_h, d, V, plan, sample);
   if (c.wide)
     return sample ? "masked_logits_kernel_w4<true>, or masked_logits_kernel<3,2,true> where 64 consecutive rows of "
                     "the list lie 4 GiB apart (decided on the device)"
@@ -96,8 +101,8 @@ extern "C" int mosaic_plan_workspace(int64_t T, int64_t max_rows, int32_t d, int
     const int64_t per = (rows + K - 1) / K;
     const int64_t C = (per + MOSAIC_ROW_TILE - 1) / MOSAIC_ROW_TILE * MOSAIC_ROW_TILE;
     const int64_t row_tiles = C / MOSAIC_ROW_TILE;
-    // A vocabulary with a ragged last tile is run as a pair of launches: the whole tiles in S - 1 splits chosen to
-    // fill the chip, the last tile as one more split.
+    // Room for a vocabulary with a ragged last tile to run as a pair of launches (choose_kernel): the whole tiles in
+    // S - 1 splits chosen to fill the chip, the last tile as one more split.
     const bool ragged = V % MOSAIC_VOCAB_TILE != 0 && vocab_tiles >= 2;
     int64_t S = ragged ? choose_vocab_splits(row_tiles, vocab_tiles - 1, num_cus) + 1
                        : choose_vocab_splits(row_tiles, vocab_tiles, num_cus);

@@ -29,8 +29,9 @@ class Sim(protocol.Sim):
     """The interpreter with this width's rings: its LM-head slots of 32 KiB, then its hidden slots of 4*nb KiB.
     A width's 8*nb MFMAs per group count as the 64 of the widest tile."""
 
-    def __init__(self, lines, nb, nk, ntile):
+    def __init__(self, lines, nb, nk, ntile, ragged_rows=0):
         super().__init__(lines, nk, ntile)
+        self.ragged_rows = ragged_rows           # rows from the last tile but one to the last one, 0: 256 as elsewhere
         self.nb, self.nw, self.nh = nb, gen.depth() + 1, gen.depth()
         assert (self.nw * 0x8000 + self.nh * nb * 0x1000) <= 160 * 1024
         self.mfma_count = Fraction(0)
@@ -50,10 +51,9 @@ class Sim(protocol.Sim):
         slot = self.slot_of(m0)
         parts = self.copy_parts.get(slot, 0)
         if operand == "W":
-            tile, rest = divmod((self.reg["s96"] | self.reg["s97"] << 32) - W_BASE, self.tile_stride)
-            ident = tile * self.nk + rest // 128
-            assert rest % 128 == 0 and rest // 128 < self.nk and ident < self.total and slot < self.nw
-            assert ident == self.next_w_copy and slot == ident % self.nw
+            ident = self.next_w_copy
+            assert (self.reg["s96"] | self.reg["s97"] << 32) == self.wptr(ident) and ident < self.total
+            assert slot == ident % self.nw
         else:
             off = (self.reg["s98"] | self.reg["s99"] << 32) - H_BASE
             ident = off // 128
@@ -92,8 +92,21 @@ class Sim(protocol.Sim):
         super().mfma(a, b, dst, src_c)
         self.mfma_count += Fraction(8, self.nb) - 1
 
+    def wptr(self, g):
+        tile = g // self.nk
+        rows = tile * 256
+        if self.ragged_rows and tile == self.ntile - 1 and tile > 0:
+            rows += self.ragged_rows - 256
+        return W_BASE + rows * (self.nk * 128) + (g % self.nk) * 128
+
+    def run_tiles(self):
+        for n in range(self.ntile):              # the kernel hands every statement its step into the next tile
+            rows = self.ragged_rows if self.ragged_rows and n + 2 == self.ntile else 256
+            self.reg["%[wwrap]"] = (rows * self.nk * 128 - (self.nk - 1) * 128) & MASK32
+            self.run_statement()
+
     def prologue(self):
-        NW, NH, wptr = self.nw, self.nh, lambda g: W_BASE + (g // self.nk) * self.tile_stride + (g % self.nk) * 128
+        NW, NH, wptr = self.nw, self.nh, self.wptr
         self.published[0] = 0
         self.published[self.nw] = 0
         for g in range(1, min(NW, self.total)):              # as the kernel issues them
@@ -108,7 +121,7 @@ class Sim(protocol.Sim):
             "%[wsrc_lo]": w & MASK32, "%[wsrc_hi]": w >> 32, "%[hsrc_lo]": h & MASK32, "%[hsrc_hi]": h >> 32,
             "%[wrd]": 0, "%[hrd]": 0, "%[wdst]": 0, "%[hdst]": 0, "%[wk]": NW % self.nk, "%[hk]": NH % self.nk,
             "%[g]": 0, "%[total]": self.total, "%[nk]": self.nk,
-            "%[wwrap]": (self.tile_stride - (self.nk - 1) * 128) & MASK32, "%[hwrap]": (self.nk - 1) * 128,
+            "%[hwrap]": (self.nk - 1) * 128,
             "%[rdw0]": 0, "%[rdw1]": 64, "%[rdh0]": self.nw * 0x8000, "%[rdh1]": self.nw * 0x8000 + 64,
         })
 
@@ -117,11 +130,11 @@ class Sim(protocol.Sim):
 @pytest.mark.parametrize("nb", range(1, 9))
 def test_ring_protocol_of_every_width(nb, sample):
     loop, _ = listing(nb, sample)
-    for nk, ntile in [(1, 1), (1, 5), (2, 3), (3, 1), (3, 4), (4, 2), (5, 31), (8, 2), (56, 2), (64, 1)]:
-        sim = Sim(loop, nb, nk, ntile)
+    for nk, ntile, ragged in [(1, 1, 0), (1, 5, 0), (2, 3, 0), (3, 1, 0), (3, 4, 0), (4, 2, 0), (5, 31, 0), (8, 2, 0),
+                              (56, 2, 0), (64, 1, 0), (5, 1, 7), (5, 2, 1), (5, 4, 255), (6, 3, 128), (9, 2, 77)]:
+        sim = Sim(loop, nb, nk, ntile, ragged)
         sim.prologue()
-        for _ in range(ntile):
-            sim.run_statement()
+        sim.run_tiles()
         total = nk * ntile
         assert sim.mfma_count == 128 * total and sim.reg["%[g]"] == total
         assert sim.started == set(range(32 * nb))
@@ -135,8 +148,7 @@ def test_a_missing_wait_is_caught_at_every_width(nb):
     sim = Sim([ln for ln in loop if not ln.startswith("s_waitcnt vmcnt")], nb, 5, 3)
     sim.prologue()
     with pytest.raises(AssertionError):
-        for _ in range(3):
-            sim.run_statement()
+        sim.run_tiles()
 
 
 @pytest.mark.parametrize("nb", range(1, 9))
