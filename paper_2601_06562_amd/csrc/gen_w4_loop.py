@@ -31,7 +31,8 @@ NK128 = "s94"
 lines = []
 uid = [0]
 SHAPE = {"nb": 8,          # token blocks of 16 per wave
-         "ragged": False}  # the statement also serves a vocabulary's ragged last tile
+         "ragged": False,  # the statement also serves a vocabulary's ragged last tile
+         "tight": False}   # sampling: a quad that passes the column's bound is held against its own (as built in)
 
 
 def nb():
@@ -412,6 +413,7 @@ slow_blocks = []
 # registers the statement fills itself from the seed: neither costs the register allocator anything.
 SAMPLE_TEMPS = {name: f"v{FRAG_BASE + 32 + k}" for k, name in enumerate(
     ("et", "emn", "enml", "ey", "yt", "xsel", "sels", "wlo", "wm", "v4b", "v4q", "a0", "sw16", "sw32", "sw48", "pw", "px", "pe", "cnt", "nq"))}
+SAMPLE_TEMPS.update(best="v180", wq="v181")
 KEY0_BASE, KEY1_BASE = 68, 78
 SAMPLE_TEMPS.update({f"k0_{r}": f"s{KEY0_BASE + r}" for r in range(10)})
 SAMPLE_TEMPS.update({f"k1_{r}": f"s{KEY1_BASE + r}" for r in range(10)})
@@ -464,8 +466,20 @@ def philox_quad(tb, bi, XS):
     passes = [f"v_cmp_ge_u32_e64 {M3}, {words[3]}, %[wlo]",
               f"v_cmp_ge_u32_e64 {M2}, {words[2]}, %[wlo]",
               f"v_cmp_ge_u32_e64 {M1}, {words[1]}, %[wlo]"]
-    blk = [f"{slow}:"] + passes + [
-           f"v_cmp_ge_u32 vcc, {words[0]}, %[wlo]",
+    if SHAPE["tight"]:
+        # The quad's own bound: its four logits against the best score known by now.  The column's bound, made of the
+        # lane's largest logit of 32 and the best score before the tile, passes nearly every quad of a unit's first
+        # tiles in some lane; this one leaves a few, and 11 instructions take the place of 35 to 200.
+        xs = [XS[x] for x in els]
+        own = [f"v_max3_f32 v174, {xs[0]}, {xs[1]}, {xs[2]}", f"v_max_f32 v174, v174, {xs[3]}"]
+        own += word_bound("v174", "%[best]", "v175", "%[wq]")
+        own += [f"v_cmp_ge_u32 vcc, %[wm], %[wq]", f"s_cbranch_vccz {back}"]
+        passes = [ln.replace("%[wlo]", "%[wq]") for ln in passes]
+    else:
+        own = []
+    low = "%[wq]" if SHAPE["tight"] else "%[wlo]"
+    blk = [f"{slow}:"] + own + passes + [
+           f"v_cmp_ge_u32 vcc, {words[0]}, {low}",
            f"v_addc_co_u32_e64 %[nq], {SINK}, 0, 0, {M3}",               # candidates of this quad, per lane
            f"v_addc_co_u32_e64 %[nq], {SINK}, 0, %[nq], {M2}",
            f"v_addc_co_u32_e64 %[nq], {SINK}, 0, %[nq], {M1}",
@@ -474,7 +488,7 @@ def philox_quad(tb, bi, XS):
            f"v_cmp_lt_u32 vcc, 1, %[cnt]",
            f"s_cbranch_vccnz {flush}",
            f"{queue}:",
-           f"v_cmp_ge_u32 vcc, {words[0]}, %[wlo]"]
+           f"v_cmp_ge_u32 vcc, {words[0]}, {low}"]
     for mk, r in ((M3, 3), (M2, 2), (M1, 1)):
         blk += [f"v_cndmask_b32_e64 %[pw], %[pw], {words[r]}, {mk}",
                 f"v_cndmask_b32_e64 %[px], %[px], {XS[els[r]]}, {mk}",
@@ -484,14 +498,45 @@ def philox_quad(tb, bi, XS):
             f"v_cndmask_b32_e64 %[pe], %[pe], {els[0]}, vcc",
             f"s_branch {back}",
             f"{flush}:"]
-    blk += score_candidate("%[pw]", "%[px]", "%[pe]") + empty_queue()
+    if SHAPE["tight"]:                     # nothing to score where no lane's queue held anything
+        nothing = label(f"nothing{tb}{bi}")
+        blk += ["v_cmp_ne_u32 vcc, %[cnt], %[nq]", f"s_cbranch_vccz {nothing}"]
+        blk += score_candidate("%[pw]", "%[px]", "%[pe]") + empty_queue() + share_best() + [f"{nothing}:"]
+    else:
+        blk += score_candidate("%[pw]", "%[px]", "%[pe]") + empty_queue()
     blk += [f"v_cmp_lt_u32 vcc, 1, %[nq]",
             f"s_cbranch_vccnz {full}"]
     blk += passes + ["v_mov_b32 %[cnt], %[nq]", f"s_branch {queue}", f"{full}:"]
     for r in range(3, -1, -1):
         blk += score_candidate(words[r], XS[els[r]], str(els[r]))
-    blk.append(f"s_branch {back}")
+    blk += (["v_mov_b32 %[cnt], 0"] + share_best() if SHAPE["tight"] else []) + [f"s_branch {back}"]
     slow_blocks.append(blk)
+
+
+def word_bound(x, best, tmp, out):
+    """the lowest word of a logit up to x that can still win against the score `best`: candidates have
+    (w >> 9) >= 2^23 - Z, Z = min(2^23, 1.01 * 2^23 * exp((x - best) / tau) + 2)"""
+    return [f"v_sub_f32 {tmp}, {x}, {best}",
+            f"v_mul_f32 {tmp}, %[itl], {tmp}",                           # log2(e) / tau
+            f"v_exp_f32 {tmp}, {tmp}",
+            "s_nop 0",
+            f"v_mul_f32 {tmp}, {hex(TWO23_101)}, {tmp}",
+            f"v_add_f32 {tmp}, 2.0, {tmp}",
+            f"v_min_f32 {tmp}, {hex(TWO23)}, {tmp}",
+            f"v_cvt_u32_f32 {out}, {tmp}",
+            f"v_sub_u32 {out}, {hex(0x800000)}, {out}",
+            f"v_lshlrev_b32 {out}, 9, {out}"]
+
+
+def share_best():
+    """the best score known of the token: what its four lanes have scored in this tile, and the best before it"""
+    return ["ds_bpermute_b32 v177, %[sw16], %[yt]",
+            "ds_bpermute_b32 v178, %[sw32], %[yt]",
+            "ds_bpermute_b32 v179, %[sw48], %[yt]",
+            "v_max_f32 %[best], %[best], %[yt]",
+            "s_waitcnt lgkmcnt(0)",
+            "v_max3_f32 %[best], %[best], v177, v178",
+            "v_max_f32 %[best], %[best], v179"]
 
 
 def empty_queue():
@@ -560,6 +605,8 @@ def reduce_column_sample(tb):
     e("s_waitcnt lgkmcnt(0)")
     e(f"v_max3_f32 v177, v177, v178, v179")
     e(f"v_max_f32 v177, v177, {YM}")
+    if SHAPE["tight"]:
+        e("v_mov_b32 %[best], v177")
     e(f"v_sub_f32 {EY}, {ET}, v177")
     e(f"v_mul_f32 {EY}, %[itl], {EY}")                               # log2(e) / tau
     e(f"v_exp_f32 {EY}, {EY}")
@@ -756,7 +803,7 @@ def build():
 
 
 def write_statement(f, blocks, sample):
-    SHAPE.update(nb=blocks, ragged=True)
+    SHAPE.update(nb=blocks, ragged=True, tight=True)
     lines.clear()
     uid[0] = 2000 if sample else 1000
     if sample:
@@ -810,7 +857,7 @@ def main(folder):
             for blocks in range(1, 9):
                 write_statement(f, blocks, sample)
     lines.clear()
-    SHAPE["ragged"] = False
+    SHAPE.update(ragged=False, tight=False)
     build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers
 
 

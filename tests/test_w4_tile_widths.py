@@ -1,9 +1,11 @@
 """The generated statements of the narrower row tiles (32 to 224 tokens), on the CPU: the K-loop of each under the ring
 protocol of test_w4_loop_protocol.py (its interpreter, with this width's ring geometry), and the reduction of each,
-which has to be the widest tile's, column by column, on this width's accumulators."""
+which has to be the widest tile's, column by column, on this width's accumulators.  The sampling reduction with a
+quad's own bound draws what it draws without, and leaves few quads to the exact path."""
 import re
 from fractions import Fraction
 
+import numpy as np
 import pytest
 
 import test_w4_loop_protocol as protocol
@@ -192,3 +194,35 @@ def test_reduction_of_every_width_is_the_widest_tiles(nb, sample):
         names = lambda ln: re.sub(r"L(slow|flush|back|queue|full)\b", r"L", ln)
         assert rest[0] == "s_branch Ldone" and rest[-1] == "Ldone:"
         assert [names(x) for x in rest[1:-1]] == [names(x) for x in wide[at + 1:at + len(rest) - 1]]
+
+
+@pytest.mark.parametrize("tau", [1.0, 0.3])
+def test_a_quads_own_bound_changes_no_draw(tau):
+    import test_w4_tile_reduce as reduce
+    reduce.TEMPS.update(gen.SAMPLE_TEMPS)
+    rng = np.random.default_rng(int(10 * tau))
+    n, seed = 64, 0x0F1E2D3C4B5A6978
+    lane = np.arange(n, dtype=np.uint32)
+    vb = np.full(n, 11 * 256, np.uint32) + 4 * (lane >> 4)
+    pos = [rng.integers(0, 4096, 16).astype(np.uint32)[lane % 16] for _ in range(8)]
+    i0 = (300000 + rng.permutation(8 * n).reshape(8, n)).astype(np.uint32)
+    xa0 = rng.standard_normal((8, n)).astype(np.float32)
+    plain = listing(8, True)[1]
+    gen.SHAPE["tight"] = True
+    tight = listing(8, True)[1]
+    gen.SHAPE["tight"] = False
+    for best in (-2.0 ** 100, 2 + 2 * tau, 3 + 5 * tau, 3 + 9 * tau):   # fresh columns, then ever later in a split
+        for planted in (False, True):
+            agpr = reduce.planted_tile(rng, n) if planted else rng.standard_normal((256, n)).astype(np.float32)
+            m0, s0 = reduce.running_state(rng, agpr, n)
+            ym0 = np.full((8, n), best, np.float32)
+            ym0[:, lane % 16 == 5] = -2.0 ** 100                        # one token is fresh in any case
+            out = {}
+            for key, red, exact in (("exact", plain, True), ("plain", plain, False), ("tight", tight, False)):
+                out[key] = reduce.sampling_wave(red, agpr, m0, s0, ym0, xa0, i0, pos, vb, seed, tau, force_exact=exact)
+            for tb in range(8):
+                assert reduce.token_level(out["tight"], tb) == reduce.token_level(out["exact"], tb), (best, planted, tb)
+                for name in ("m", "s"):
+                    assert np.array_equal(out["tight"].reg[f"%[{name}{tb}]"], out["exact"].reg[f"%[{name}{tb}]"])
+            assert out["tight"].flushes <= out["plain"].flushes and out["tight"].fulls <= out["plain"].fulls
+            print(tau, best, planted, *((k, o.issued, o.slow_taken, o.flushes, o.fulls) for k, o in out.items()))
