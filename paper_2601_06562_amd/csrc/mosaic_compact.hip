@@ -100,23 +100,40 @@ __global__ __launch_bounds__(1024) void compact_scan_kernel(int32_t* __restrict_
   if (tid == 1023) *out_count = part[1023];
 }
 
+// Writes the ascending positions of every block.  SUM: block_counts still holds the counts, and every block adds up
+// those before it by itself (the last one publishes the total); else they have been turned into offsets.
+template <bool SUM>
 __global__ __launch_bounds__(kCompactThreads) void compact_scatter_kernel(const uint8_t* __restrict__ mask, int64_t T,
-                                                                          const int32_t* __restrict__ block_offsets,
-                                                                          int32_t* __restrict__ out_idx) {
-  __shared__ int wave_totals[kCompactThreads / 64];
+                                                                          const int32_t* __restrict__ block_counts,
+                                                                          int32_t* __restrict__ out_idx,
+                                                                          int32_t* __restrict__ out_count) {
+  __shared__ int wave_totals[kCompactThreads / 64], before_totals[kCompactThreads / 64];
   const bool aligned16 = (reinterpret_cast<uintptr_t>(mask) & 15u) == 0;
   const int64_t base = (int64_t)blockIdx.x * kCompactBlockElems + (int64_t)threadIdx.x * kBytesPerThread;
   uint32_t bits = load_flags(mask, base, T, aligned16);
+  int offset;
+  if constexpr (SUM) {
+    int part = 0;
+    for (int i = (int)threadIdx.x; i < (int)blockIdx.x; i += kCompactThreads) part += block_counts[i];
+    (void)block_inclusive_scan(part, before_totals, &offset);
+  } else {
+    offset = block_counts[blockIdx.x];
+  }
   const int c = __popc(bits);
   int total;
   const int incl = block_inclusive_scan(c, wave_totals, &total);
-  int64_t out = (int64_t)block_offsets[blockIdx.x] + (incl - c);
+  int64_t out = (int64_t)offset + (incl - c);
   while (bits) {
     const int j = __ffs(bits) - 1;
     bits &= bits - 1;
     out_idx[out++] = (int32_t)(base + j);
   }
+  if (SUM && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *out_count = offset + total;
 }
+
+// Up to this many blocks (4 million positions) a block adds up the counts before it itself: at most four loads per
+// thread, where the scan of the counts costs a launch of its own (~5 us, of 15 for the three).
+constexpr int64_t kSumBlocks = 1024;
 
 // Everything in one block, for masks of up to kSingleMax positions: passes of 16384 positions, the running
 // offset carried from pass to pass.  One launch instead of three where launches are all the cost.
@@ -152,14 +169,14 @@ int launch_compact(const uint8_t* mask, int64_t T, int32_t* out_idx, int32_t* ou
     return launch_kernel(compact_single_kernel, dim3(1), dim3(kSingleThreads), stream, mask, T, out_idx, out_count);
   }
   const int64_t nb = compact_num_blocks(T);
-  int rc = 0;
-  if (nb > 0)
-    rc |= launch_kernel(compact_count_kernel, dim3((unsigned)nb), dim3(kCompactThreads), stream, mask, T, block_counts);
-  // nb == 0 still has to publish count = 0.
-  rc |= launch_kernel(compact_scan_kernel, dim3(1), dim3(1024), stream, block_counts, nb, out_count);
-  if (nb > 0)
-    rc |= launch_kernel(compact_scatter_kernel, dim3((unsigned)nb), dim3(kCompactThreads), stream, mask, T, block_counts,
-                        out_idx);
+  const dim3 grid((unsigned)nb), block(kCompactThreads);
+  int rc = launch_kernel(compact_count_kernel, grid, block, stream, mask, T, block_counts);
+  if (nb <= kSumBlocks) {
+    rc |= launch_kernel(compact_scatter_kernel<true>, grid, block, stream, mask, T, block_counts, out_idx, out_count);
+  } else {
+    rc |= launch_kernel(compact_scan_kernel, dim3(1), dim3(1024), stream, block_counts, nb, out_count);
+    rc |= launch_kernel(compact_scatter_kernel<false>, grid, block, stream, mask, T, block_counts, out_idx, out_count);
+  }
   return rc;
 }
 

@@ -201,6 +201,10 @@ __device__ __forceinline__ Schedule launch_schedule(const KernelParams& p, int r
   return sched;
 }
 
+__device__ __forceinline__ int choose_width(const KernelParams& p, int rows) {
+  return rows == p.bound_rows ? p.bound.width : choose_schedule_wave(p.sched, rows).width;
+}
+
 // Round alignment of the persistent grid.  A workgroup that takes more than one unit meets the others before each
 // further one: the workgroups behind one L2 share LM-head and hidden tiles only while they walk their units in
 // step, and once they have drifted apart (units end at slightly different times) every tile is fetched several
@@ -232,26 +236,43 @@ __global__ __launch_bounds__(256) void clear_round_counters_kernel(int32_t* sync
 // For hidden tensors of 4 GiB or more: raises *flag when some group of consecutive rows of the chunk's list that one
 // wave of the 4-wave kernel copies (8 times the width found; the last group padded with the last row as that kernel
 // does) spans rows whose byte offsets differ by 4 GiB or more.  One wave per group.
+__device__ __forceinline__ bool group_spans_4gib(const KernelParams& p, int rows, int group, int group_rows) {
+  const int lane = (int)threadIdx.x & 63;
+  int j = group * group_rows + (lane < group_rows ? lane : group_rows - 1);
+  if (j > rows - 1) j = rows - 1;
+  int t = p.idx[p.row0 + j];
+  t = t < 0 ? 0 : (t > p.T - 1 ? p.T - 1 : t);
+  int lo = t, hi = t;
+#pragma unroll
+  for (int x = 32; x >= 1; x >>= 1) {
+    const int a = __shfl_xor(lo, x, 64), b = __shfl_xor(hi, x, 64);
+    lo = a < lo ? a : lo;
+    hi = b > hi ? b : hi;
+  }
+  // the offset of a row from the group's lowest, plus the 16-byte chunk inside the row's K-tile, must fit 32 bits
+  return (uint64_t)(hi - lo) * (uint64_t)p.ldh_bytes >= ((uint64_t)1 << 32) - 256;
+}
 __global__ __launch_bounds__(256) void span_check_kernel(const KernelParams p, int32_t* flag) {
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
-  const int group_rows = 8 * launch_schedule(p, rows).width;
-  const int lane = (int)threadIdx.x & 63;
-  for (int group = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6); group * group_rows < rows; group += (int)gridDim.x * 4) {
-    int j = group * group_rows + (lane < group_rows ? lane : group_rows - 1);
-    if (j > rows - 1) j = rows - 1;
-    int t = p.idx[p.row0 + j];
-    t = t < 0 ? 0 : (t > p.T - 1 ? p.T - 1 : t);
-    int lo = t, hi = t;
-#pragma unroll
-    for (int x = 32; x >= 1; x >>= 1) {
-      const int a = __shfl_xor(lo, x, 64), b = __shfl_xor(hi, x, 64);
-      lo = a < lo ? a : lo;
-      hi = b > hi ? b : hi;
-    }
-    // the offset of a row from the group's lowest, plus the 16-byte chunk inside the row's K-tile, must fit 32 bits
-    if (lane == 0 && (uint64_t)(hi - lo) * (uint64_t)p.ldh_bytes >= ((uint64_t)1 << 32) - 256) atomicOr(flag, 1);
+  const int group_rows = 8 * choose_width(p, rows);
+  for (int group = (int)blockIdx.x * 4 + ((int)threadIdx.x >> 6); group * group_rows < rows; group += (int)gridDim.x * 4)
+    if (group_spans_4gib(p, rows, group, group_rows) && ((int)threadIdx.x & 63) == 0) atomicOr(flag, 1);
+}
+
+// Few rows: one block clears the round counters and checks the list, a launch (~5 us) less than the two kernels above.
+constexpr int64_t kOneBlockCheckRows = 4096;   // at most four groups a wave
+__global__ __launch_bounds__(1024) void clear_and_check_kernel(const KernelParams p, int32_t* counters, int n, int32_t* flag) {
+  if ((int)threadIdx.x < n) counters[threadIdx.x] = 0;
+  const int rows = chunk_rows_found(p);
+  bool far = false;
+  if (rows > 0) {
+    const int group_rows = 8 * choose_width(p, rows);
+    for (int group = (int)threadIdx.x >> 6; group * group_rows < rows; group += 16)
+      far |= group_spans_4gib(p, rows, group, group_rows);
   }
+  const int any = __syncthreads_or(far);
+  if (threadIdx.x == 0) *flag = any ? 1 : 0;
 }
 
 template <int N>
@@ -1070,12 +1091,16 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
     p.bound = tail.bound = choose_schedule(p.sched, (int32_t)cap);
     const int64_t tiles = (cap + kTileRows - 1) / kTileRows;
     const bool several_rounds = (int64_t)p.bound.row_tiles * p.bound.splits > plan.grid || (paired && tiles > plan.grid);
-    if (several_rounds || wide)
-      rc |= launch_kernel(clear_round_counters_kernel, dim3(1), dim3(256), stream, counters, kSyncSlots + 2);
-    p.sync = several_rounds ? counters : nullptr;   // not cleared: nobody meets (fewer rows may still take two rounds)
-    if (!several_rounds) tail.sync = nullptr;
-    if (wide)
-      rc |= launch_kernel(span_check_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), stream, p, flag);
+    if (!several_rounds) p.sync = tail.sync = nullptr;   // nobody meets (fewer rows may still take two rounds)
+    else p.sync = counters, tail.sync = counters + kSyncSlots / 2;
+    if (wide && cap <= kOneBlockCheckRows) {
+      rc |= launch_kernel(clear_and_check_kernel, dim3(1), dim3(1024), stream, p, counters, kSyncSlots + 1, flag);
+    } else {
+      if (several_rounds || wide)
+        rc |= launch_kernel(clear_round_counters_kernel, dim3(1), dim3(256), stream, counters, kSyncSlots + 2);
+      if (wide)
+        rc |= launch_kernel(span_check_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), stream, p, flag);
+    }
     auto launch_general = [&](const KernelParams& kp, int64_t blocks) {
       return sample ? launch_kernel(masked_logits_kernel<3, 2, true>, dim3((unsigned)blocks), dim3(kThreads), stream, kp)
                     : launch_kernel(masked_logits_kernel<3, 2, false>, dim3((unsigned)blocks), dim3(kThreads), stream, kp);

@@ -1,4 +1,4 @@
-"""Top-n unmasking at the sizes where its paths meet: sequences around the row count up to which rows are ranked
+"""Compaction and top-n unmasking at the sizes where their paths meet: sequences around the row count up to which rows are ranked
 directly, none, one and all rows taken, sequence lengths around the block's 1024 threads, many exact ties, a
 confidence of zero.  Bit-exact against the oracle."""
 import numpy as np
@@ -43,3 +43,24 @@ def test_sequences_around_the_path_boundaries(rows, levels):
         torch.cuda.synchronize()
         assert np.array_equal(d_mask.cpu().numpy(), want_mask), n_per_seq
         assert np.array_equal(d_tokens.cpu().numpy(), want_tokens), n_per_seq
+
+
+@pytest.mark.parametrize("T", [65536, 65537, 69632, 1024 * 4096, 1024 * 4096 + 1])
+def test_compaction_where_its_paths_meet(T):
+    """One block up to 65536 positions; then blocks that add up the counts before them themselves; from 1024 blocks of
+    4096 positions on, a scan of the counts."""
+    print(f"compaction edges T={T}", flush=True)
+    rng = np.random.default_rng(T)
+    for p in (0.0, 0.001, 0.6):
+        mask = (rng.random(T) < p).astype(np.uint8)
+        mask[[0, T - 1]] = 1 if p else 0
+        want = np.nonzero(mask)[0].astype(np.int32)
+        d_mask = torch.as_tensor(mask, device=DEV)
+        idx = torch.full((T,), -7, dtype=torch.int32, device=DEV)
+        count = torch.full((1,), -7, dtype=torch.int32, device=DEV)
+        scratch = torch.empty(binding.mosaic_compact_scratch_bytes(T), dtype=torch.uint8, device=DEV)
+        binding.mosaic_mask_compact(d_mask, idx, count, scratch)
+        torch.cuda.synchronize()
+        got = idx.cpu().numpy()
+        assert int(count.item()) == want.size
+        assert np.array_equal(got[:want.size], want) and np.all(got[want.size:] == -7)
