@@ -667,11 +667,13 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   constexpr int kTileK = 64;
   constexpr int kSwzShift = 1;
   static_assert(NW * kLmHeadSlot + NH * kHiddenSlot <= kLdsBytes, "rings");
-  double* red_s = reinterpret_cast<double*>(smem);      // merge scratch aliases W slot 0 at unit end
-  float* red_m = reinterpret_cast<float*>(red_s + 256);
-  int* red_i = reinterpret_cast<int*>(red_m + 256);
-  float* red_ym = reinterpret_cast<float*>(red_i + 256);   // sampling only
-  float* red_xa = red_ym + 256;
+  // merge scratch, over the rings at unit end: eight entries per token
+  double* red_s = reinterpret_cast<double*>(smem);
+  float* red_m = reinterpret_cast<float*>(red_s + 8 * kTokens);
+  int* red_i = reinterpret_cast<int*>(red_m + 8 * kTokens);
+  float* red_ym = reinterpret_cast<float*>(red_i + 8 * kTokens);   // sampling only
+  float* red_xa = red_ym + 8 * kTokens;
+  static_assert(8 * kTokens * 24 <= NW * kLmHeadSlot + NH * kHiddenSlot, "merge scratch");
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wv = wave & 1;   // vocabulary half of the tile
@@ -860,55 +862,43 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       }
     }
 
-    // Unit end: fold the four lanes that share a token (lane ^ 16, lane ^ 32), then the two waves that
-    // share it (vocabulary halves) through LDS, and publish one partial triple per row.
+    // Unit end: a token's state lies in eight lanes (four of a wave, times the two vocabulary halves).  All of them go to
+    // LDS, and one thread per token merges its eight in a loop: a tenth of the code of a tree of shuffles over NB
+    // columns, and it is code that runs once a unit, cold.
+    __syncthreads();  // every wave is done with the ring (the merge scratch aliases it)
 #pragma unroll
     for (int tb = 0; tb < NB; ++tb) {
-#pragma unroll
-      for (int x = 16; x <= 32; x <<= 1) {
-        const float m2 = __shfl_xor(run_m[tb], x, 64);
-        const double s2 = __shfl_xor(run_s[tb], x, 64);
-        const int i2 = __shfl_xor(run_i[tb], x, 64);
-        if constexpr (SAMPLE) {
-          merge_sum(run_m[tb], run_s[tb], m2, s2);
-          merge_pick(run_ym[tb], run_xa[tb], run_i[tb], __shfl_xor(run_ym[tb], x, 64), __shfl_xor(run_xa[tb], x, 64), i2);
-        } else {
-          merge_triple(run_m[tb], run_s[tb], run_i[tb], m2, s2, i2);
-        }
-      }
-    }
-    __syncthreads();  // every wave is done with the ring (the merge scratch aliases it)
-    if (wv == 1 && q == 0) {
-#pragma unroll
-      for (int tb = 0; tb < NB; ++tb) {
-        const int e = wt * (kTokens / 2) + tb * 16 + l16;
-        red_m[e] = run_m[tb];
-        red_s[e] = run_s[tb];
-        red_i[e] = run_i[tb];
-        if constexpr (SAMPLE) {
-          red_ym[e] = run_ym[tb];
-          red_xa[e] = run_xa[tb];
-        }
+      const int e = (wv * 4 + q) * kTokens + wt * (kTokens / 2) + tb * 16 + l16;
+      red_m[e] = run_m[tb];
+      red_s[e] = run_s[tb];
+      red_i[e] = run_i[tb];
+      if constexpr (SAMPLE) {
+        red_ym[e] = run_ym[tb];
+        red_xa[e] = run_xa[tb];
       }
     }
     __syncthreads();
-    if (wv == 0 && q == 0) {
-#pragma unroll
-      for (int tb = 0; tb < NB; ++tb) {
-        const int e = wt * (kTokens / 2) + tb * 16 + l16;
-        if (tt * kTokens + e >= rows) continue;
-        const int64_t slot = (int64_t)sp * sched.stride + tt * kTokens + e;
+    if (tid < kTokens && tt * kTokens + tid < rows) {
+      float m = red_m[tid], ym = kNeg, xa = 0.f;
+      double s = red_s[tid];
+      int i = red_i[tid];
+      if constexpr (SAMPLE) { ym = red_ym[tid]; xa = red_xa[tid]; }
+#pragma unroll 1
+      for (int e = tid + kTokens; e < 8 * kTokens; e += kTokens) {
         if constexpr (SAMPLE) {
-          merge_sum(run_m[tb], run_s[tb], red_m[e], red_s[e]);
-          merge_pick(run_ym[tb], run_xa[tb], run_i[tb], red_ym[e], red_xa[e], red_i[e]);
-          p.part_ym[slot] = run_ym[tb];
-          p.part_xa[slot] = run_xa[tb];
+          merge_sum(m, s, red_m[e], red_s[e]);
+          merge_pick(ym, xa, i, red_ym[e], red_xa[e], red_i[e]);
         } else {
-          merge_triple(run_m[tb], run_s[tb], run_i[tb], red_m[e], red_s[e], red_i[e]);
+          merge_triple(m, s, i, red_m[e], red_s[e], red_i[e]);
         }
-        p.part_m[slot] = run_m[tb];
-        p.part_si[slot] = pack_sum_id(run_s[tb], run_i[tb], p.id_bits);
       }
+      const int64_t slot = (int64_t)sp * sched.stride + tt * kTokens + tid;
+      if constexpr (SAMPLE) {
+        p.part_ym[slot] = ym;
+        p.part_xa[slot] = xa;
+      }
+      p.part_m[slot] = m;
+      p.part_si[slot] = pack_sum_id(s, i, p.id_bits);
     }
     __syncthreads();
   }
@@ -933,95 +923,72 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   }
 }
 
-// Merge the S partial results of every row and emit the outputs.  A block of 256 threads handles ROWS rows at a time
-// with G = 256 / ROWS thread groups: group g folds the splits g, g + G, g + 2G, ... (their loads issued together),
-// then the G group results are folded pairwise, group g with group g + stride for stride = G/2, G/4, ..., 1: a row's
-// chain of dependent steps is S / G + log2 G long instead of S.  Few splits: 16 rows x 16 groups; many splits (one row
-// tile spread over ~250 of them, where this kernel is a visible part of the step): 4 rows x 64 groups -- a
-// sequential merge took 114 us there, 16 groups with a sequential second level 16 us.
-struct CombineScratch {
-  double s[256];
-  float m[256], ym[256], xa[256];
-  int i[256];
-};
+// Merge the S partial results of every row and emit the outputs.  A wave handles ROWS rows with G = 64 / ROWS lanes
+// each, without a barrier: the largest logit of the row first, by a butterfly of shuffles, so that every sum is scaled
+// once and the sums meet in a second butterfly of plain additions.  Few splits: four rows a wave; many (one row tile
+// spread over ~250 of them, where this kernel is a visible part of the step): one.  Bound by latency: a launch, the
+// loads of count and splits, the partials, twelve shuffles.
+constexpr int kWideMergeSplits = 64;   // from this many splits on, a wave per row
 template <int ROWS>
-__device__ __forceinline__ void combine_rows(const KernelParams& p, int splits, int rows, CombineScratch& sh) {
-  constexpr int G = 256 / ROWS;
-  constexpr int kPerGroup = (MOSAIC_MAX_VOCAB_SPLITS + 1 + G - 1) / G;   // splits one group folds at most
+__device__ __forceinline__ void combine_rows(const KernelParams& p, int splits, int rows) {
+  constexpr int G = 64 / ROWS;
+  constexpr int kMost = ROWS == 1 ? MOSAIC_MAX_VOCAB_SPLITS + 1 : kWideMergeSplits - 1;
+  constexpr int kPerLane = (kMost + G - 1) / G;   // splits one lane loads at most
   const bool sample = p.tau > 0.f;   // sampling: the token is the arg-max of the perturbed scores
-  const int lr = threadIdx.x % ROWS, g = threadIdx.x / ROWS;
-  for (int r0 = (int)blockIdx.x * ROWS; r0 < rows; r0 += (int)gridDim.x * ROWS) {
-    const int r = r0 + lr;
-    const bool valid = r < rows;
-    float m = kNeg, ym = kNeg, xa = 0.f;
+  const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
+  const int lr = lane % ROWS, g = lane / ROWS;
+  for (int r0 = ((int)blockIdx.x * 4 + wave) * ROWS; r0 < rows; r0 += (int)gridDim.x * 4 * ROWS) {
+    const bool valid = r0 + lr < rows;
+    const int r = valid ? r0 + lr : rows - 1;
+    float lm[kPerLane], lym[kPerLane], lxa[kPerLane];
+    uint64_t lsi[kPerLane];
+#pragma unroll
+    for (int k = 0; k < kPerLane; ++k) {
+      const int sp = g + k * G;
+      const bool on = sp < splits;
+      const int64_t slot = (int64_t)(on ? sp : 0) * partial_stride(rows) + r;
+      lm[k] = on ? p.part_m[slot] : kNeg;        // beyond S: the neutral element
+      lsi[k] = on ? p.part_si[slot] : 0;
+      lym[k] = (on && sample) ? p.part_ym[slot] : kNeg;
+      lxa[k] = (on && sample) ? p.part_xa[slot] : 0.f;
+    }
+    float m = kNeg;
+#pragma unroll
+    for (int k = 0; k < kPerLane; ++k) m = fmaxf(m, lm[k]);
+#pragma unroll
+    for (int x = ROWS; x < 64; x <<= 1) m = fmaxf(m, __shfl_xor(m, x, 64));
+    const float e = ref_exponent(m);
     double s = 0.0;
+    float best = kNeg, xa = 0.f;     // what the token is the arg-max of; its plain logit
     int i = INT_MAX;
-    if (valid) {
-      float lm[kPerGroup], lym[kPerGroup], lxa[kPerGroup];
-      uint64_t lsi[kPerGroup];
 #pragma unroll
-      for (int k = 0; k < kPerGroup; ++k) {
-        const int sp = g + k * G;
-        const bool on = sp < splits;
-        const int64_t slot = (int64_t)(on ? sp : 0) * partial_stride(rows) + r;
-        lm[k] = on ? p.part_m[slot] : kNeg;        // beyond S: the neutral element
-        lsi[k] = on ? p.part_si[slot] : 0;
-        lym[k] = (on && sample) ? p.part_ym[slot] : kNeg;
-        lxa[k] = (on && sample) ? p.part_xa[slot] : 0.f;
-      }
-#pragma unroll
-      for (int k = 0; k < kPerGroup; ++k) {
-        if (g + k * G >= splits) break;
-        double s2;
-        int i2;
-        unpack_sum_id(lsi[k], p.id_bits, s2, i2);
-        if (sample) {
-          merge_sum(m, s, lm[k], s2);
-          merge_pick(ym, xa, i, lym[k], lxa[k], i2);
-        } else {
-          merge_triple(m, s, i, lm[k], s2, i2);
-        }
-      }
+    for (int k = 0; k < kPerLane; ++k) {
+      double s2;
+      int i2;
+      unpack_sum_id(lsi[k], p.id_bits, s2, i2);
+      s += __builtin_ldexp(s2, scale_steps(ref_exponent(lm[k]) - e));
+      if (g + k * G < splits) merge_pick(best, xa, i, sample ? lym[k] : lm[k], lxa[k], i2);
     }
 #pragma unroll
-    for (int stride = G / 2; stride >= 1; stride >>= 1) {
-      if (g >= stride && g < 2 * stride) {
-        const int e = (g - stride) * ROWS + lr;
-        sh.m[e] = m;
-        sh.s[e] = s;
-        sh.i[e] = i;
-        sh.ym[e] = ym;
-        sh.xa[e] = xa;
-      }
-      __syncthreads();
-      if (g < stride) {
-        const int e = g * ROWS + lr;
-        if (sample) {
-          merge_sum(m, s, sh.m[e], sh.s[e]);
-          merge_pick(ym, xa, i, sh.ym[e], sh.xa[e], sh.i[e]);
-        } else {
-          merge_triple(m, s, i, sh.m[e], sh.s[e], sh.i[e]);
-        }
-      }
-      __syncthreads();
+    for (int x = ROWS; x < 64; x <<= 1) {
+      s += __shfl_xor(s, x, 64);
+      merge_pick(best, xa, i, __shfl_xor(best, x, 64), __shfl_xor(xa, x, 64), __shfl_xor(i, x, 64));
     }
     if (g == 0 && valid) {
       // back from 2^E to exp(m)
-      const float rel = (float)(s / (double)__builtin_amdgcn_exp2f(__builtin_fmaf(m, kLog2e, -ref_exponent(m))));
+      const float rel = (float)(s / (double)__builtin_amdgcn_exp2f(__builtin_fmaf(m, kLog2e, -e)));
       p.out_token[p.row0 + r] = i;
       p.out_lse[p.row0 + r] = m + __builtin_amdgcn_logf(rel) * kLn2;
       p.out_conf[p.row0 + r] = sample ? __builtin_amdgcn_exp2f((xa - m) * kLog2e) / rel : 1.0f / rel;
     }
   }
 }
-constexpr int kWideMergeSplits = 64;   // from this many splits on, the 64-group merge
 __global__ __launch_bounds__(256) void combine_kernel(const KernelParams p) {
-  __shared__ CombineScratch sh;
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
   const int splits = *p.found_splits + (int)p.sched.extra;   // a pair's second launch adds one
-  if (splits >= kWideMergeSplits) combine_rows<4>(p, splits, rows, sh);
-  else combine_rows<16>(p, splits, rows, sh);
+  if (splits >= kWideMergeSplits) combine_rows<1>(p, splits, rows);
+  else combine_rows<4>(p, splits, rows);
 }
 
 int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream_t stream) {
