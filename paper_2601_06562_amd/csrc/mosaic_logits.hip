@@ -1033,6 +1033,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.sched.vocab_tiles = (uint32_t)(paired ? vocab_tiles - 1 : vocab_tiles);
   p.sched.k_tiles = (uint32_t)(a.d / MOSAIC_K_TILE);
   p.sched.widths = fast || paired ? 0xff : 0x80;   // the general kernel has the one width
+  p.sched.sampling = sample ? 1 : 0;
   p.sched.grid = (uint32_t)plan.grid;
   p.sched.extra = paired ? 1 : 0;
   p.sched.slots64 = (uint32_t)(slots / 64 < INT32_MAX ? slots / 64 : INT32_MAX);

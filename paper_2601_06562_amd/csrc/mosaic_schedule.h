@@ -26,6 +26,7 @@ struct ScheduleInput {
   uint32_t vocab_tiles;   // tiles to divide (without the ragged last one where a second launch covers it)
   uint32_t k_tiles;       // K-tiles of a vocabulary tile
   uint32_t widths;        // bit w - 1: row tiles of 32*w rows are on offer
+  uint32_t sampling;      // 1: the reduction draws, too
   uint32_t grid;          // workgroups of the launch
   uint32_t extra;         // partial slots per row beyond the splits (1 where a second launch adds its own)
   uint32_t slots64;       // rows x splits the partial arrays hold, in units of 64
@@ -49,13 +50,15 @@ __host__ __device__ inline uint32_t panel_depth(uint32_t row_tiles, uint32_t wid
 // and a 32000 x 1024 LM head (most within 10%).  A K-tile: bound by the copies into LDS up to four token blocks a wave
 // (0.64 to 0.76 us), by the matrix cores beyond (1.26 us at eight); or by memory, which brings the 32 KiB of LM head
 // for all compute units at 5.6 TB/s in 1.48 us, shared by the panel's row tiles; the shorter of the two hides
-// but for a sixth.  The reduction of a tile: 0.56 us per token block.  A unit besides: pipeline fill and merge.
+// but for a sixth.  The reduction of a tile: 0.56 us per token block, with a draw 1.66 us.  A further round of
+// units (pipeline fill, merge, a fresh start of the draw's bound): half a tile and 4 us.
 __host__ __device__ inline uint32_t k_tile_time(uint32_t width, uint32_t share) {
   const uint32_t compute = width <= 4 ? 60 + 4 * width : (36 + 27 * width) / 2, memory = 148 / share;
   return compute > memory ? compute + memory / 6 : memory + compute / 6;
 }
-__host__ __device__ inline uint32_t reduction_time(uint32_t width) { return 56 * width; }
-__host__ __device__ inline uint32_t unit_time(uint32_t width) { return 600 + 150 * width; }
+__host__ __device__ inline uint32_t reduction_time(uint32_t width, uint32_t sampling) {
+  return (sampling != 0 ? 166 : 56) * width;
+}
 
 // The candidate with row tiles of 32*width rows that uses `extra_rounds` rounds of the grid more than the fewest
 // possible, as (cost, width, splits) packed into one integer: the smaller one is the better one.  A round lasts as
@@ -81,8 +84,10 @@ __host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, 
   uint32_t splits = ceil_div(in.vocab_tiles, longest);
   if (splits < least) splits = least;
   const uint32_t rounds = ceil_div(row_tiles * splits, in.grid);
-  const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(row_tiles, width)) + reduction_time(width);
-  const uint64_t cost = (uint64_t)rounds * (((uint64_t)longest * tile + unit_time(width)) >> 3);
+  const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(row_tiles, width)) + reduction_time(width, in.sampling);
+  uint64_t cost = ((uint64_t)rounds * longest * tile + (uint64_t)(rounds - 1) * (tile / 2 + 400)) >> 3;
+  if (width < 8) cost += cost >> 6;   // a narrower tile has to win by more than the model is off (5748 rows of 32000 x
+                                      // 1024: 36 x 7 units of 160 rows 300 us, 23 x 11 of 256 rows 294 us)
   return cost << 20 | (uint64_t)(8 - width) << 16 | splits;
 }
 
