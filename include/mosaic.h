@@ -74,7 +74,8 @@ typedef struct {
 } mosaic_plan;
 
 /* plan.flags bit: use the general 8-wave kernel even where the hand-scheduled 4-wave kernel applies
- * (it applies to the whole tiles of the vocabulary; in a hidden tensor of 4 GiB or more it needs every 64
+ * (it applies to the whole tiles of the vocabulary, and to a ragged last tile where d >= 320 and, sampling,
+ * V % 4 == 0; in a hidden tensor of 4 GiB or more it needs every 64
  * consecutive rows of the gather list to lie less than 4 GiB apart, which a small kernel checks on the device
  * before the launch, handing lists with such a gap to the general kernel).  Both give the same results; the flag
  * exists for testing and tuning. */
