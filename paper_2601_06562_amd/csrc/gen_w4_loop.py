@@ -32,6 +32,7 @@ lines = []
 uid = [0]
 SHAPE = {"nb": 8,          # token blocks of 16 per wave
          "ragged": False,  # the statement also serves a vocabulary's ragged last tile
+         "fresh": False,   # the reduction yields the tile's own (max, sum-exp[, arg-max]), no running ones (as built in)
          "tight": False}   # sampling: a quad that passes the column's bound is held against its own (as built in)
 
 
@@ -342,6 +343,20 @@ ET, EMN, ENML, EY, ESEL = (f"v{FRAG_BASE + 32 + k}" for k in range(5))
 MASK = ["s[88:89]", "s[90:91]", "s[92:93]"]
 
 
+def tile_exponentials(XS, S):
+    """S = sum of 2^(x log2 e + ENML) over the column's 32 logits, in four chains"""
+    for el in range(32):
+        e(f"v_fmamk_f32 {XS[el]}, {XS[el]}, {hex(LOG2E)}, {ENML}")
+    for el in range(32):
+        e(f"v_exp_f32 {XS[el]}, {XS[el]}")
+    for step in range(1, 8):
+        for r in range(4):
+            e(f"v_add_f32 {XS[r]}, {XS[r]}, {XS[4 * step + r]}")
+    e(f"v_add_f32 {XS[0]}, {XS[0]}, {XS[1]}")
+    e(f"v_add_f32 {XS[2]}, {XS[2]}, {XS[3]}")
+    e(f"v_add_f32 {S}, {XS[0]}, {XS[2]}")
+
+
 def reduce_column(tb):
     """The vocabulary reduction of one token column of the finished tile (this lane: 8 blocks x 4 ids, element
     e = 4*bi + r is vocabulary id vb + 16*bi + r) into the running (max, sum-exp, arg-max) of the column:
@@ -367,6 +382,17 @@ def reduce_column(tb):
         if len(pending) == 3:
             mk, pe = pending.pop(0)
             e(f"v_cndmask_b32_e64 {ESEL}, {ESEL}, {pe}, {mk}")
+    if SHAPE["fresh"]:
+        e(f"v_mul_f32 {ENML}, {hex(NEG_LOG2E)}, {ET}")
+        e(f"v_mov_b32 {M}, {ET}")
+        for mk, pe in pending:
+            e(f"v_cndmask_b32_e64 {ESEL}, {ESEL}, {pe}, {mk}")
+        e(f"v_lshrrev_b32 {EY}, 2, {ESEL}")           # code = 16 * (sel / 4) + sel % 4
+        e(f"v_and_b32 {ESEL}, 3, {ESEL}")
+        e(f"v_lshl_add_u32 {ESEL}, {EY}, 4, {ESEL}")
+        e(f"v_add_u32 {I}, %[vb], {ESEL}")
+        tile_exponentials(X, S)
+        return
     # two selects are still pending; the new-maximum test and the running maximum fill the wait states
     e(f"v_cmp_gt_f32 vcc, {ET}, {M}")                 # strict: an equal maximum in a later tile has a higher id
     e(f"v_max_f32 {EMN}, {M}, {ET}")
@@ -641,6 +667,11 @@ def reduce_column_sample(tb):
     e(f"v_cndmask_b32 {I}, {I}, %[sels], vcc")
     e(f"v_cndmask_b32 {XA}, {XA}, %[xsel], vcc")
     e(f"v_cndmask_b32 {YM}, {YM}, %[yt], vcc")
+    if SHAPE["fresh"]:
+        e(f"v_mul_f32 {ENML}, {hex(NEG_LOG2E)}, {ET}")
+        e(f"v_mov_b32 {M}, {ET}")
+        tile_exponentials(XS, S)
+        return
     # running maximum and sum of exponentials of the unperturbed logits
     e(f"v_max_f32 {EMN}, {M}, {ET}")
     e(f"v_sub_f32 {EY}, {M}, {EMN}")
@@ -803,20 +834,20 @@ def build():
 
 
 def write_statement(f, blocks, sample):
-    SHAPE.update(nb=blocks, ragged=True, tight=True)
+    SHAPE.update(nb=blocks, ragged=True, fresh=True, tight=True)
     lines.clear()
     uid[0] = 2000 if sample else 1000
     if sample:
         build_tile_sample()
         outs = []
         for tb in range(blocks):
-            outs += [f'[m{tb}] "+v"(tile_m[{tb}])', f'[s{tb}] "+v"(tile_s[{tb}])', f'[i{tb}] "+v"(run_i[{tb}])',
+            outs += [f'[m{tb}] "=&v"(tile_m[{tb}])', f'[s{tb}] "=&v"(tile_s[{tb}])', f'[i{tb}] "+v"(run_i[{tb}])',
                      f'[ym{tb}] "+v"(run_ym[{tb}])', f'[xa{tb}] "+v"(run_xa[{tb}])']
     else:
         build_tile()
         outs = []
         for tb in range(blocks):
-            outs += [f'[m{tb}] "+v"(tile_m[{tb}])', f'[s{tb}] "+v"(tile_s[{tb}])', f'[i{tb}] "+v"(tile_i[{tb}])']
+            outs += [f'[m{tb}] "=&v"(tile_m[{tb}])', f'[s{tb}] "=&v"(tile_s[{tb}])', f'[i{tb}] "=&v"(tile_i[{tb}])']
     for name in ("wsrc_lo", "wsrc_hi", "hsrc_lo", "hsrc_hi", "wrd", "hrd", "wdst", "hdst", "wk", "hk", "g"):
         outs.append(f'[{name}] "+s"(st_{name})')
     outs.append('[vt0] "=&v"(addr_tmp0)')
@@ -857,7 +888,7 @@ def main(folder):
             for blocks in range(1, 9):
                 write_statement(f, blocks, sample)
     lines.clear()
-    SHAPE.update(ragged=False, tight=False)
+    SHAPE.update(ragged=False, fresh=False, tight=False)
     build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers
 
 

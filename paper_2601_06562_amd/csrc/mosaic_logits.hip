@@ -841,8 +841,6 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
         const int vb = first_id(vt0 + n) + wv * 128 + 4 * q;   // vocabulary id of this lane's element 0
         float tile_m[NB], tile_s[NB];   // this tile's own triples
         int tile_i[NB];
-#pragma unroll
-        for (int tb = 0; tb < NB; ++tb) { tile_m[tb] = kNeg; tile_s[tb] = 0.f; tile_i[tb] = INT_MAX; }
         if constexpr (SAMPLE) {
           // sampling: the same, with the Gumbel-max draw in the reduction (round keys by number too).  The drawn
           // candidate is carried from tile to tile: it bounds what can still win

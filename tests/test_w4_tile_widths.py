@@ -226,3 +226,38 @@ def test_a_quads_own_bound_changes_no_draw(tau):
                     assert np.array_equal(out["tight"].reg[f"%[{name}{tb}]"], out["exact"].reg[f"%[{name}{tb}]"])
             assert out["tight"].flushes <= out["plain"].flushes and out["tight"].fulls <= out["plain"].fulls
             print(tau, best, planted, *((k, o.issued, o.slow_taken, o.flushes, o.fulls) for k, o in out.items()))
+
+
+@pytest.mark.parametrize("sample", [False, True])
+def test_a_tiles_own_triple_is_the_running_update_of_an_empty_state(sample):
+    import test_w4_tile_reduce as reduce
+    reduce.TEMPS.update(gen.SAMPLE_TEMPS)
+    rng = np.random.default_rng(3)
+    n = 64
+    lane = np.arange(n, dtype=np.uint32)
+    vb = np.full(n, 11 * 256, np.uint32) + 4 * (lane >> 4)
+    pos = [rng.integers(0, 4096, 16).astype(np.uint32)[lane % 16] for _ in range(8)]
+    running = listing(8, sample)[1]
+    gen.SHAPE["fresh"] = True
+    own = listing(8, sample)[1]
+    gen.SHAPE["fresh"] = False
+    agpr = reduce.planted_tile(rng, n)
+    agpr[:, 7] = -2.0 ** 100                                  # a lane whose ids all lie outside the vocabulary
+    empty = np.full((8, n), -2.0 ** 100, np.float32)
+    i0 = np.full((8, n), 0x7FFFFFFF, np.uint32)
+    zero = np.zeros((8, n), np.float32)
+    if sample:
+        a, b = (reduce.sampling_wave(p, agpr, empty, zero, empty, zero, i0, pos, vb, 77, 0.8) for p in (running, own))
+    else:
+        a, b = reduce.Wave(n, agpr), reduce.Wave(n, agpr)
+        for w, prog in ((a, running), (b, own)):
+            for tb in range(8):
+                if w is a:                                     # the other one has to write what it leaves
+                    w.fset(f"%[m{tb}]", empty[tb]), w.fset(f"%[s{tb}]", zero[tb]), w.iset(f"%[i{tb}]", i0[tb])
+            w.iset("%[vb]", vb)
+            w.run(prog)
+    for tb in range(8):
+        for name in ("m", "s") + (("ym", "xa", "i") if sample else ("i",)):
+            x, y = a.reg[f"%[{name}{tb}]"], b.reg[f"%[{name}{tb}]"]
+            keep = np.arange(n) != 7 if name == "i" and not sample else slice(None)   # no maximum, so no id: unused
+            assert np.array_equal(x[keep], y[keep]), (name, tb)
