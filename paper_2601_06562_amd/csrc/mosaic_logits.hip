@@ -87,7 +87,7 @@ struct KernelParams {
   float* part_xa;   // the unperturbed logit at that arg-max
   int32_t* sync;    // round counters of the persistent grid (cleared before the launch), sync_slots of them
   int32_t sync_slots;
-  int32_t* found_splits;   // the splits of the division a launch found, for the merge kernel
+  int32_t* found_splits;   // the splits of the division a launch found, for a pair's second one and the merge kernel
   // Hidden tensors of 4 GiB or more.  The 4-wave kernel addresses a wave's 64 rows by 32-bit offsets from the lowest of
   // them, which works unless those rows lie 4 GiB or more apart; a small kernel looks for such a group in the list
   // and raises *wide_flag, and of the two launches that follow (4-wave kernel, general kernel) the one whose
@@ -199,6 +199,13 @@ __device__ __forceinline__ Schedule launch_schedule(const KernelParams& p, int r
   const Schedule sched = rows == p.bound_rows ? p.bound : choose_schedule_wave(p.sched, rows);
   if (blockIdx.x == 0 && threadIdx.x == 0) *p.found_splits = sched.splits;
   return sched;
+}
+
+// The second launch of a pair stores behind the splits of the launch that ran before it, whichever of two that was:
+// its division is that launch's word, not a choice of its own (the 4-wave kernel and the general kernel in its place
+// settle on different counts, 40 and 49 splits for 769 rows of 50257 ids).
+__device__ __forceinline__ Schedule division_found(const KernelParams& p, int rows) {
+  return Schedule{8, (rows + kTileRows - 1) / kTileRows, *p.found_splits, partial_stride(rows)};
 }
 
 __device__ __forceinline__ int choose_width(const KernelParams& p, int rows) {
@@ -421,12 +428,12 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
   if (p.wide_flag != nullptr && *p.wide_flag != p.wide_run_if) return;   // the other kernel of the two serves this list
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
-  const Schedule sched = launch_schedule(p, rows);
+  const bool ragged_only = p.ragged_tile >= 0;
+  const Schedule sched = ragged_only ? division_found(p, rows) : launch_schedule(p, rows);
   const int n_tt = (rows + kTileRows - 1) / kTileRows;   // its row tiles have the one width
 
   const int G = gridDim.x;
   const int pos = xcd_contiguous_position((int)blockIdx.x, G);
-  const bool ragged_only = p.ragged_tile >= 0;
   const int S = ragged_only ? 1 : sched.splits;
   const int n_units = n_tt * S;
   const int A = p.panel < n_tt ? p.panel : n_tt;

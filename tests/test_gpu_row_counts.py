@@ -1,11 +1,13 @@
 """The division of the work follows the rows found on the device, not the bound the plan was made for: counts around
 the row tiles of a loose plan, on both kernels, greedy and sampled.  The results are the same bits as under a tight
-plan (the fold makes them independent of the split), and right against a plain fp64 evaluation."""
+plan (the fold makes them independent of the split), and right against a plain fp64 evaluation.  Hidden tensors of
+4 GiB or more with a ragged vocabulary: up to three launches share one division there."""
 import numpy as np
 import pytest
 import torch
 
 from paper_2601_06562_amd import binding, workloads
+from test_gpu_full_size import span_flag
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -46,3 +48,51 @@ def test_results_are_the_same_bits_for_any_bound(d, V, flags):
         assert np.abs(outs[0][2] - lse).max() <= 2e-5
         picked = x.gather(1, torch.as_tensor(outs[0][0], device=DEV).long()[:, None])[:, 0]
         assert float((x.max(1).values - picked).max()) <= 1e-4
+
+
+def test_a_pair_of_launches_beyond_4_gib_shares_one_division():
+    """A ragged vocabulary served by a pair of launches (fewer than five K-tiles; under sampling also V % 4 != 0), in a
+    hidden tensor beyond 4 GiB: where the list has a 4 GiB gap inside the rows of one wave the general kernel takes the
+    4-wave kernel's place, in 49 vocabulary splits for these 769 rows instead of 40, and the launch for the ragged tile
+    has to store behind those.  Expected: the general kernel on the same rows gathered into a small tensor."""
+    T, d, V = (1 << 23) + 8192, 256, 50257
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(workloads.BASE_SEED + 79)
+    hidden = torch.empty((T, d), dtype=torch.bfloat16, device=DEV)
+    for r in range(0, T, 1 << 20):
+        hidden[r:r + (1 << 20)].normal_(generator=gen)
+    w = workloads._normal_bf16(V, d, d ** -0.5, gen, torch.device(DEV))
+    assert T * d * 2 > 1 << 32
+    for M, bound in ((769, 769), (513, 4096), (40, 40), (40, 5000)):
+        lists = {1: torch.cat([torch.arange(3, 20), torch.arange(T - (M - 17) * 3, T, 3)]),   # the gap in the first group
+                 0: torch.arange(T - M * 3, T, 3)}
+        for flag, pos in lists.items():
+            pos = pos.to(DEV)
+            mask = torch.zeros(T, dtype=torch.uint8, device=DEV)
+            mask[pos] = 1
+            rows = hidden[pos].contiguous()
+            small = torch.arange(M, dtype=torch.int32, device=DEV)
+            lse = torch.logsumexp(rows.double() @ w.double().t(), 1).cpu().numpy()
+            for tau in (0.0, 0.8):
+                print(f"pair beyond 4 GiB: M={M} bound={bound} flag={flag} tau={tau}", flush=True)
+                op = binding.MaskOnlyLogits(T, d, V, max_rows=bound, device=DEV, sampling=tau > 0)
+                assert "ragged last vocabulary tile" in binding.mosaic_masked_logits_kernel_name(
+                    1000, d, d, V, op.plan, tau > 0)
+                ref = binding.MaskOnlyLogits(M, d, V, device=DEV, sampling=tau > 0)
+                ref.plan.flags |= binding.PLAN_GENERAL_KERNEL
+                if tau > 0:
+                    op.sample_step(hidden, w, mask, tau, 99)
+                    binding.mosaic_masked_logits_sample(rows, w, small, op.count, M, tau, 99, ref.token, ref.conf,
+                                                        ref.lse, ref.plan, ref.workspace, noise_idx=op.idx)
+                else:
+                    op.step(hidden, w, mask)
+                    binding.mosaic_masked_logits_reduce(rows, w, small, op.count, M, ref.token, ref.conf, ref.lse,
+                                                        ref.plan, ref.workspace)
+                torch.cuda.synchronize()
+                assert int(op.count.item()) == M and span_flag(op) == flag
+                what = (M, bound, flag, tau)
+                assert torch.equal(op.token[:M], ref.token[:M]), what
+                assert torch.allclose(op.conf[:M], ref.conf[:M], rtol=1e-5, atol=0), what    # sums in another order
+                assert np.abs(op.lse[:M].cpu().numpy() - lse).max() <= 2e-5, what
+    del hidden
+    torch.cuda.empty_cache()
