@@ -99,6 +99,8 @@ class Wave:
             idx = int(a[1][1:])
             self.fset(a[0], self.agpr[idx])
             self.accvgpr_reads.append(idx)
+        elif op == "v_accvgpr_write_b32":
+            self.agpr[int(a[0][1:])] = self.fget(a[1])
         elif op == "v_max3_f32":
             self.fset(a[0], np.maximum(np.maximum(self.fget(a[1]), self.fget(a[2])), self.fget(a[3])))
         elif op == "v_max_f32":
@@ -115,6 +117,11 @@ class Wave:
             x, y = self.iget(a[1]), self.iget(a[2])
             self.mask[a[0]] = {"ge": x >= y, "lt": x < y, "gt": x > y, "ne": x != y}[op[6:8]]
             self.mask_written[a[0]] = now
+        elif op == "v_cmp_lt_i32":
+            self.mask[a[0]] = self.iget(a[1]).view(np.int32) < self.iget(a[2]).view(np.int32)
+            self.mask_written[a[0]] = now
+        elif op == "s_cmp_eq_u32":
+            self.scc = int(self.iget(a[0])[0] == self.iget(a[1])[0])
         elif op == "v_addc_co_u32_e64":                       # d = s0 + s1 + carry-in; the carry-out goes to a[1]
             total = self.iget(a[2]).astype(np.uint64) + self.iget(a[3]) + self.mask[a[4]]
             self.iset(a[0], total)
@@ -227,6 +234,10 @@ class Wave:
             if op == "s_branch":
                 pc = labels[rest.strip()]
                 self.issued += 1
+            elif op == "s_cbranch_scc1":
+                self.issued += 1
+                if self.scc:
+                    pc = labels[rest.strip()]
             elif op == "s_cbranch_vccz":                   # taken when no lane's compare held
                 self.issued += 1
                 if not self.mask["vcc"].any():

@@ -27,6 +27,18 @@ def listing(nb, sample):
     return out[:cut], out[cut:]
 
 
+def built(nb, sample):
+    """The reduction of the statement that the library is built with, the ragged tile's part in front."""
+    gen.SHAPE.update(nb=nb, ragged=True, fresh=True, tight=True)
+    gen.lines.clear()
+    gen.uid[0] = 0
+    gen.build_tile_sample() if sample else gen.build_tile()
+    out = [ln.strip() for ln in gen.lines]
+    gen.lines.clear()
+    gen.SHAPE.update(ragged=False, fresh=False, tight=False)
+    return out[out.index("s_cmp_eq_u32 %[first], 0"):]
+
+
 class Sim(protocol.Sim):
     """The interpreter with this width's rings: its LM-head slots of 32 KiB, then its hidden slots of 4*nb KiB.
     A width's 8*nb MFMAs per group count as the 64 of the widest tile."""
@@ -261,3 +273,60 @@ def test_a_tiles_own_triple_is_the_running_update_of_an_empty_state(sample):
             x, y = a.reg[f"%[{name}{tb}]"], b.reg[f"%[{name}{tb}]"]
             keep = np.arange(n) != 7 if name == "i" and not sample else slice(None)   # no maximum, so no id: unused
             assert np.array_equal(x[keep], y[keep]), (name, tb)
+
+
+def reduce_built(nb, sample, agpr, vb, first, tau=0.8):
+    """One wave of the built reduction on empty running states: (m, s, i) of every column, or (m, s, ym, xa, i)."""
+    import test_w4_tile_reduce as reduce
+    reduce.TEMPS.update(gen.SAMPLE_TEMPS)
+    n = agpr.shape[1]
+    w = reduce.Wave(n, agpr.copy())
+    for name, v in (("vb", vb), ("first", np.full(n, first)), ("seed_lo", np.full(n, 77)), ("seed_hi", np.full(n, 5)),
+                    ("pm0", np.full(n, 0xD2511F53)), ("pm1", np.full(n, 0xCD9E8D57))):
+        w.iset(f"%[{name}]", v)
+    w.fset("%[itl]", np.full(n, np.float32(1.4426950408889634) / np.float32(tau)))
+    w.fset("%[tau]", np.full(n, tau))
+    for tb in range(nb):
+        if sample:
+            w.fset(f"%[ym{tb}]", np.full(n, -2.0 ** 100)), w.fset(f"%[xa{tb}]", np.zeros(n))
+            w.iset(f"%[i{tb}]", np.full(n, 0x7FFFFFFF))
+            w.iset(f"%[pos{tb}]", 1000 * tb + np.arange(n) % 16)
+    w.run(built(nb, sample))
+    return [[w.reg[f"%[{name}{tb}]"].view(np.uint32 if name == "i" else np.float32)
+             for name in (("m", "s", "ym", "xa", "i") if sample else ("m", "s", "i"))] for tb in range(nb)]
+
+
+def check_triples(nb, sample, got, agpr, taken_out):
+    """Every column's triple against its definition in 64 bits; taken_out: bool[32, n], elements that do not count."""
+    for tb in range(nb):
+        x = np.stack([agpr[(el // 4 * nb + tb) * 4 + el % 4] for el in range(32)]).astype(np.float64)
+        x[taken_out] = -2.0 ** 100
+        t = np.maximum(x.max(axis=0), -2.0 ** 100)
+        with np.errstate(over="ignore"):
+            want = np.exp(x - t).sum(axis=0)
+        assert np.array_equal(got[tb][0], t.astype(np.float32)), tb
+        assert np.all(np.abs(got[tb][1] - want) <= 2e-6 * want), (tb, got[tb][1], want)
+        if not sample:
+            sel = (x == t).argmax(axis=0)
+            some = t > -2.0 ** 100                            # (else the kernel takes no id from it)
+            code = 16 * (sel // 4) + sel % 4
+            assert np.array_equal((got[tb][2] & 0xFF)[some], code[some]), tb
+
+
+@pytest.mark.parametrize("sample", [False, True])
+@pytest.mark.parametrize("nb", range(1, 9))
+def test_ids_at_minus_infinity_count_for_nothing(nb, sample):
+    """A lane whose ids are all at minus infinity (a vocabulary's unused rows, say) yields an empty triple: with its
+    own maximum taken from its exponents its sum is NaN."""
+    rng = np.random.default_rng(nb)
+    n = 64
+    agpr = rng.standard_normal((256, n)).astype(np.float32)
+    agpr[:, 7] = -np.inf
+    agpr[:17 * nb, 9] = -np.inf
+    agpr[5, 11] = -np.inf
+    got = reduce_built(nb, sample, agpr, np.zeros(n), 0)
+    check_triples(nb, sample, got, agpr, np.zeros((32, n), bool))
+    for tb in range(nb):
+        assert got[tb][1][7] == 0
+        if sample:
+            assert got[tb][4][7] == 0x7FFFFFFF and got[tb][2][7] == -2.0 ** 100
