@@ -74,7 +74,7 @@ struct KernelParams {
   Schedule bound;      // ... and the division for bound_rows rows
   int32_t bound_rows;
   int32_t ragged_tile; // second launch of a pair: it covers this vocabulary tile alone, behind the other splits; else -1
-  int32_t id_bits;     // bits of a vocabulary id in a packed partial
+  int32_t id_bits;     // bits of V, which a vocabulary id has in a packed partial
   float* part_m;       // largest logit per row and split
   uint64_t* part_si;   // the sum of exponentials and the id (pack_sum_id)
   int32_t* out_token;
@@ -125,21 +125,26 @@ __device__ __forceinline__ void merge_triple(float& m, double& s, int& i, float 
 
 // A partial result is 12 bytes: m, and one 64-bit word with the id in its low id_bits bits and above them s as a
 // floating-point number of 6 exponent bits (s lies between 1/2 and the number of ids) and the remaining
-// 58 - id_bits mantissa bits (41 for 126464 ids), rounded to nearest.  0 stands for an empty sum.
+// 58 - id_bits mantissa bits (41 for 126464 ids), rounded to nearest.  0 stands for an empty sum, the largest exponent
+// for one that is not a number (a NaN or an infinity among the logits); logits so large that the rounding of m log2 e
+// moves s out of those bounds (10^8 and more) have s clamped.  id_bits hold the number of ids, so that all ones are no
+// id: they stand for INT_MAX, the id of a state that no logit has entered.
 constexpr int kSumBias = 1019;   // exponent field of a double that is stored as 0
+constexpr int kNoSum = 63;       // stored exponent of a sum that is not a number
 __device__ __forceinline__ uint64_t pack_sum_id(double s, int i, int id_bits) {
   const int drop = id_bits > 6 ? id_bits - 6 : 0;       // mantissa bits of the double that do not fit
-  uint64_t b = (uint64_t)__double_as_longlong(s);
+  uint64_t b = (uint64_t)__double_as_longlong(__builtin_fmin(__builtin_fmax(s, 0x1p-3), 0x1p57));
   if (drop > 0) b += (uint64_t)1 << (drop - 1);
   b = (b >> drop) - ((uint64_t)kSumBias << (52 - drop));
-  if (s == 0.0) b = 0;
+  if (!(s > 0.0)) b = s == 0.0 ? 0 : ~(uint64_t)0;
   return b << id_bits | ((uint64_t)(uint32_t)i & (((uint64_t)1 << id_bits) - 1));
 }
 __device__ __forceinline__ void unpack_sum_id(uint64_t w, int id_bits, double& s, int& i) {
   const int drop = id_bits > 6 ? id_bits - 6 : 0;
-  i = (int)(w & (((uint64_t)1 << id_bits) - 1));
-  const uint64_t b = w >> id_bits;
+  const uint64_t no_id = ((uint64_t)1 << id_bits) - 1, b = w >> id_bits;
+  i = (w & no_id) == no_id ? INT_MAX : (int)(w & no_id);
   s = b == 0 ? 0.0 : __longlong_as_double((long long)((b + ((uint64_t)kSumBias << (52 - drop))) << drop));
+  if (b >> (52 - drop) >= kNoSum) s = __builtin_nan("");
 }
 
 // Sampled candidate: best perturbed score, the plain logit there, its id (lowest id on equal scores).
@@ -1013,7 +1018,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   const int64_t slots = (int64_t)plan.vocab_splits * plan.rows_per_chunk;   // a multiple of 256
   p.part_si = static_cast<uint64_t*>(a.workspace);
   p.part_m = reinterpret_cast<float*>(p.part_si + slots);
-  p.id_bits = a.V > 1 ? 32 - __builtin_clz((unsigned)(a.V - 1)) : 1;
+  p.id_bits = 32 - __builtin_clz((unsigned)a.V);
   p.out_token = a.out_token;
   p.out_conf = a.out_conf;
   p.out_lse = a.out_lse;
