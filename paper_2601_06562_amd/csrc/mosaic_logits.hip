@@ -1044,7 +1044,11 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.sched.k_tiles = (uint32_t)(a.d / MOSAIC_K_TILE);
   p.sched.widths = fast || paired ? 0xff : 0x80;   // the general kernel has the one width
   p.sched.sampling = sample ? 1 : 0;
-  p.sched.grid = (uint32_t)plan.grid;
+  // never more workgroups than the plan has units, whatever its field says; with that many the division's products stay
+  // below 2^32 (a larger one could only be refused by the launch)
+  const int64_t units = (int64_t)(plan.rows_per_chunk / kTileRows) * plan.vocab_splits;
+  const int32_t grid = plan.grid < units ? plan.grid : (int32_t)units;
+  p.sched.grid = (uint32_t)(grid < 1 << 24 ? grid : 1 << 24);
   p.sched.extra = paired ? 1 : 0;
   p.sched.slots64 = (uint32_t)(slots / 64 < INT32_MAX ? slots / 64 : INT32_MAX);
   p.ragged_tile = -1;
@@ -1068,7 +1072,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
     p.bound_rows = tail.bound_rows = (int32_t)cap;
     p.bound = tail.bound = choose_schedule(p.sched, (int32_t)cap);
     const int64_t tiles = (cap + kTileRows - 1) / kTileRows;
-    const bool several_rounds = (int64_t)p.bound.row_tiles * p.bound.splits > plan.grid || (paired && tiles > plan.grid);
+    const bool several_rounds = (int64_t)p.bound.row_tiles * p.bound.splits > grid || (paired && tiles > grid);
     if (!several_rounds) p.sync = tail.sync = nullptr;   // nobody meets (fewer rows may still take two rounds)
     else p.sync = counters, tail.sync = counters + kSyncSlots / 2;
     if (wide && cap <= kOneBlockCheckRows) {
@@ -1084,19 +1088,19 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
                     : launch_kernel(masked_logits_kernel<3, 2, false>, dim3((unsigned)blocks), dim3(kThreads), stream, kp);
     };
     if (fast || paired) {
-      rc |= sample ? launch_kernel(masked_logits_kernel_w4<true>, dim3((unsigned)plan.grid), dim3(256), stream, p)
-                   : launch_kernel(masked_logits_kernel_w4<false>, dim3((unsigned)plan.grid), dim3(256), stream, p);
+      rc |= sample ? launch_kernel(masked_logits_kernel_w4<true>, dim3((unsigned)grid), dim3(256), stream, p)
+                   : launch_kernel(masked_logits_kernel_w4<false>, dim3((unsigned)grid), dim3(256), stream, p);
       if (wide) {   // the same work on the general kernel, for lists the span check flags
         KernelParams fallback = p;
         fallback.wide_run_if = 1;
         fallback.sched.widths = 0x80;
         fallback.bound = choose_schedule(fallback.sched, (int32_t)cap);
-        rc |= launch_general(fallback, plan.grid);
+        rc |= launch_general(fallback, grid);
       }
     } else {
-      rc |= launch_general(p, plan.grid);
+      rc |= launch_general(p, grid);
     }
-    if (paired) rc |= launch_general(tail, tiles < plan.grid ? tiles : plan.grid);
+    if (paired) rc |= launch_general(tail, tiles < grid ? tiles : grid);
     rc |= launch_kernel(combine_kernel, dim3((unsigned)((cap + 3) / 4 < 4096 ? (cap + 3) / 4 : 4096)), dim3(256), stream, p);
     if (rc != 0) break;
   }

@@ -50,6 +50,21 @@ def test_results_are_the_same_bits_for_any_bound(d, V, flags):
         assert float((x.max(1).values - picked).max()) <= 1e-4
 
 
+@pytest.mark.parametrize("V", [2560, 2500])
+def test_a_plans_grid_may_exceed_its_units(V):
+    T, d = 700, 128
+    wl = workloads.small_random(T, d, V, p=0.7, seed=V, device=DEV)
+    outs = []
+    for grid in (0, 1 << 20, 1 << 30):
+        print(f"grid {grid} V={V}", flush=True)
+        op = binding.MaskOnlyLogits(T, d, V, device=DEV)
+        op.plan.grid = grid or op.plan.grid
+        op.step(wl.hidden, wl.w, wl.mask)
+        torch.cuda.synchronize()
+        outs.append([t[:int(op.count.item())].cpu().numpy() for t in (op.token, op.conf, op.lse)])
+    assert all(np.array_equal(a, b) for out in outs[1:] for a, b in zip(outs[0], out))
+
+
 def test_a_pair_of_launches_beyond_4_gib_shares_one_division():
     """A ragged vocabulary served by a pair of launches (fewer than five K-tiles; under sampling also V % 4 != 0), in a
     hidden tensor beyond 4 GiB: where the list has a 4 GiB gap inside the rows of one wave the general kernel takes the

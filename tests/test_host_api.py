@@ -4,6 +4,8 @@ raised before anything is enqueued, so null device pointers are never dereferenc
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -260,3 +262,23 @@ def test_selector_keeps_at_least_four_splits_for_cache_sharing():
     assert binding.mosaic_plan_workspace(65536, 65536, 4096, 512, 0).vocab_splits == 2        # only two tiles
     tight = binding.mosaic_plan_workspace(65536, 65536, 4096, 126464, 12 * 65536 + 1024)     # budget for one split
     assert tight.vocab_splits == 1 and tight.num_chunks == 1
+
+
+@pytest.mark.parametrize("grid", [1 << 20, 1 << 30, 2 ** 31 - 1])
+def test_a_grid_beyond_the_units_reaches_the_launch(grid):
+    """plan.grid is only bounded from below: any size has to get through the host's side of a call (in a process of its
+    own without a device, where the launch is what fails)."""
+    code = f"""
+import ctypes
+from paper_2601_06562_amd import binding
+binding.LIB_PATH = {binding.LIB_PATH!r}
+plan = binding.mosaic_plan_workspace(3000, 300, 512, 10240, 0)
+plan.grid = {grid}
+fake, null = ctypes.c_void_p(0x1000), ctypes.c_void_p(0)
+print(binding.lib().mosaic_masked_logits_reduce(fake, 3000, 512, 512, fake, 10240, fake, fake, 300, fake, fake, fake,
+                                                ctypes.byref(plan), fake, plan.workspace_bytes, null))
+"""
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, env=env, stdout=subprocess.PIPE, stderr=subprocess.PIPE,
+                         text=True)
+    assert res.returncode == 0 and int(res.stdout) == binding.MOSAIC_ERR_HIP, (res.returncode, res.stderr[-500:])
