@@ -343,16 +343,11 @@ ET, EMN, ENML, EY, ESEL = (f"v{FRAG_BASE + 32 + k}" for k in range(5))
 MASK = ["s[88:89]", "s[90:91]", "s[92:93]"]
 
 
-def column_maximum(XS, tb):
-    """ET = the column's largest logit, -2^100 at least: a lane whose 32 ids are all at minus infinity is then an empty
-    one (x - m never is inf - inf), as it is to the merges, and a NaN shows in the sum alone.  The floor is the third
-    operand of the last max and costs nothing; it sits in a scalar register that the K-loop is done with."""
-    if tb == 0:
-        e(f"s_mov_b32 {KT}, {hex(KNEG)}")
-    e(f"v_max3_f32 {ET}, {XS[0]}, {XS[1]}, {XS[2]}")
-    for j in range(14):
-        e(f"v_max3_f32 {ET}, {ET}, {XS[3 + 2 * j]}, {XS[4 + 2 * j]}")
-    e(f"v_max3_f32 {ET}, {ET}, {XS[31]}, {KT}")
+def own_maximum(M):
+    """M = ET, the column's largest logit, -2^100 at least, and ENML = -M log2 e: a lane whose 32 ids are all at minus
+    infinity is then an empty one (x - M never is inf - inf), as it is to the merges, and a NaN shows in the sum alone."""
+    e(f"v_max_f32 {M}, {hex(KNEG)}, {ET}")
+    e(f"v_mul_f32 {ENML}, {hex(NEG_LOG2E)}, {M}")
 
 
 def tile_exponentials(XS, S):
@@ -379,7 +374,10 @@ def reduce_column(tb):
     M, S, I = f"%[m{tb}]", f"%[s{tb}]", f"%[i{tb}]"
     for el in range(32):
         e(f"v_accvgpr_read_b32 {X[el]}, {acc_reg(el // 4, tb, el % 4)}")
-    column_maximum(X, tb)
+    e(f"v_max3_f32 {ET}, {X[0]}, {X[1]}, {X[2]}")
+    for j in range(14):
+        e(f"v_max3_f32 {ET}, {ET}, {X[3 + 2 * j]}, {X[4 + 2 * j]}")
+    e(f"v_max_f32 {ET}, {ET}, {X[31]}")
     # lowest element attaining the maximum: descending scan, a lower match overwrites a higher one
     e(f"v_mov_b32 {ESEL}, 0")
     order = list(range(31, -1, -1))
@@ -392,8 +390,7 @@ def reduce_column(tb):
             mk, pe = pending.pop(0)
             e(f"v_cndmask_b32_e64 {ESEL}, {ESEL}, {pe}, {mk}")
     if SHAPE["fresh"]:
-        e(f"v_mul_f32 {ENML}, {hex(NEG_LOG2E)}, {ET}")
-        e(f"v_mov_b32 {M}, {ET}")
+        own_maximum(M)
         for mk, pe in pending:
             e(f"v_cndmask_b32_e64 {ESEL}, {ESEL}, {pe}, {mk}")
         e(f"v_lshrrev_b32 {EY}, 2, {ESEL}")           # code = 16 * (sel / 4) + sel % 4
@@ -632,7 +629,10 @@ def reduce_column_sample(tb):
     e(f"ds_bpermute_b32 v179, %[sw48], {YM}")
     for el in range(32):
         e(f"v_accvgpr_read_b32 {XS[el]}, {acc_reg(el // 4, tb, el % 4)}")
-    column_maximum(XS, tb)
+    e(f"v_max3_f32 {ET}, {XS[0]}, {XS[1]}, {XS[2]}")
+    for j in range(14):
+        e(f"v_max3_f32 {ET}, {ET}, {XS[3 + 2 * j]}, {XS[4 + 2 * j]}")
+    e(f"v_max_f32 {ET}, {ET}, {XS[31]}")
     # the bound on the words: candidates have (w >> 9) >= 2^23 - Z, Z = min(2^23, 1.01 * 2^23 * exp((t - ym)/tau) + 2)
     e("s_waitcnt lgkmcnt(0)")
     e(f"v_max3_f32 v177, v177, v178, v179")
@@ -674,8 +674,7 @@ def reduce_column_sample(tb):
     e(f"v_cndmask_b32 {XA}, {XA}, %[xsel], vcc")
     e(f"v_cndmask_b32 {YM}, {YM}, %[yt], vcc")
     if SHAPE["fresh"]:
-        e(f"v_mul_f32 {ENML}, {hex(NEG_LOG2E)}, {ET}")
-        e(f"v_mov_b32 {M}, {ET}")
+        own_maximum(M)
         tile_exponentials(XS, S)
         return
     # running maximum and sum of exponentials of the unperturbed logits
