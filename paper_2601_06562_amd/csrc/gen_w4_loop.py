@@ -30,10 +30,8 @@ NK128 = "s94"
 
 lines = []
 uid = [0]
-SHAPE = {"nb": 8,          # token blocks of 16 per wave
-         "ragged": False,  # the statement also serves a vocabulary's ragged last tile
-         "fresh": False,   # the reduction yields the tile's own (max, sum-exp[, arg-max]), no running ones (as built in)
-         "tight": False}   # sampling: a quad that passes the column's bound is held against its own (as built in)
+SHAPE = {"nb": 8,         # token blocks of 16 per wave
+         "tight": True}   # sampling: a quad that passes the column's bound is held against its own (off: for comparison)
 
 
 def nb():
@@ -339,7 +337,7 @@ NEG_LOG2E = 0xBFB8AA3B
 # compiler keeps 128 registers for what lives across a tile (with both as operands it spills).
 FRAG_BASE = 112
 X = [f"v{FRAG_BASE + i}" for i in range(32)]
-ET, EMN, ENML, EY, ESEL = (f"v{FRAG_BASE + 32 + k}" for k in range(5))
+ET, _, ENML, EY, ESEL = (f"v{FRAG_BASE + 32 + k}" for k in range(5))
 MASK = ["s[88:89]", "s[90:91]", "s[92:93]"]
 
 
@@ -366,9 +364,10 @@ def tile_exponentials(XS, S):
 
 def reduce_column(tb):
     """The vocabulary reduction of one token column of the finished tile (this lane: 8 blocks x 4 ids, element
-    e = 4*bi + r is vocabulary id vb + 16*bi + r) into the running (max, sum-exp, arg-max) of the column:
-        t = max_e x[e];  sel = lowest e with x[e] == t;  if t > m: i = vb + code(sel)
-        mn = max(m, t);  s = s * 2^((m - mn) log2 e) + sum_e 2^(x[e] log2 e - mn log2 e);  m = mn
+    e = 4*bi + r is vocabulary id vb + 16*bi + r) to its own (max, sum-exp, arg-max), which the kernel folds into the
+    running ones:
+        t = max_e x[e];  sel = lowest e with x[e] == t;  i = vb + code(sel)
+        m = max(t, -2^100);  s = sum_e 2^(x[e] log2 e - m log2 e)
     Written so that no instruction needs a wait state: a comparison result is consumed three instructions later
     (three SGPR pairs in rotation), an exponential at the earliest two instructions later."""
     M, S, I = f"%[m{tb}]", f"%[s{tb}]", f"%[i{tb}]"
@@ -389,43 +388,14 @@ def reduce_column(tb):
         if len(pending) == 3:
             mk, pe = pending.pop(0)
             e(f"v_cndmask_b32_e64 {ESEL}, {ESEL}, {pe}, {mk}")
-    if SHAPE["fresh"]:
-        own_maximum(M)
-        for mk, pe in pending:
-            e(f"v_cndmask_b32_e64 {ESEL}, {ESEL}, {pe}, {mk}")
-        e(f"v_lshrrev_b32 {EY}, 2, {ESEL}")           # code = 16 * (sel / 4) + sel % 4
-        e(f"v_and_b32 {ESEL}, 3, {ESEL}")
-        e(f"v_lshl_add_u32 {ESEL}, {EY}, 4, {ESEL}")
-        e(f"v_add_u32 {I}, %[vb], {ESEL}")
-        tile_exponentials(X, S)
-        return
-    # two selects are still pending; the new-maximum test and the running maximum fill the wait states
-    e(f"v_cmp_gt_f32 vcc, {ET}, {M}")                 # strict: an equal maximum in a later tile has a higher id
-    e(f"v_max_f32 {EMN}, {M}, {ET}")
+    own_maximum(M)                                    # and two selects are still pending
     for mk, pe in pending:
         e(f"v_cndmask_b32_e64 {ESEL}, {ESEL}, {pe}, {mk}")
     e(f"v_lshrrev_b32 {EY}, 2, {ESEL}")               # code = 16 * (sel / 4) + sel % 4
     e(f"v_and_b32 {ESEL}, 3, {ESEL}")
     e(f"v_lshl_add_u32 {ESEL}, {EY}, 4, {ESEL}")
-    e(f"v_add_u32 {ESEL}, %[vb], {ESEL}")
-    e(f"v_cndmask_b32 {I}, {I}, {ESEL}, vcc")
-    # rescale of the running sum, the common exponent offset
-    e(f"v_sub_f32 {EY}, {M}, {EMN}")
-    e(f"v_mul_f32 {EY}, {hex(LOG2E)}, {EY}")
-    e(f"v_exp_f32 {EY}, {EY}")
-    e(f"v_mul_f32 {ENML}, {hex(NEG_LOG2E)}, {EMN}")
-    e(f"v_mov_b32 {M}, {EMN}")
-    for el in range(32):
-        e(f"v_fmamk_f32 {X[el]}, {X[el]}, {hex(LOG2E)}, {ENML}")
-    for el in range(32):
-        e(f"v_exp_f32 {X[el]}, {X[el]}")
-    for step in range(1, 8):                          # four running sums, elements r, r + 4, r + 8, ...
-        for r in range(4):
-            e(f"v_add_f32 {X[r]}, {X[r]}, {X[4 * step + r]}")
-    e(f"v_add_f32 {X[0]}, {X[0]}, {X[1]}")
-    e(f"v_add_f32 {X[2]}, {X[2]}, {X[3]}")
-    e(f"v_add_f32 {X[0]}, {X[0]}, {X[2]}")
-    e(f"v_fma_f32 {S}, {S}, {EY}, {X[0]}")
+    e(f"v_add_u32 {I}, %[vb], {ESEL}")
+    tile_exponentials(X, S)
 
 
 # ---- the sampling statement (Gumbel-max at temperature tau; noise from Philox4x32-10 keyed by seed, counter =
@@ -444,7 +414,7 @@ slow_blocks = []
 # The reduction's temporaries live in fragment registers that are dead by then, the generator's round keys in scalar
 # registers the statement fills itself from the seed: neither costs the register allocator anything.
 SAMPLE_TEMPS = {name: f"v{FRAG_BASE + 32 + k}" for k, name in enumerate(
-    ("et", "emn", "enml", "ey", "yt", "xsel", "sels", "wlo", "wm", "v4b", "v4q", "a0", "sw16", "sw32", "sw48", "pw", "px", "pe", "cnt", "nq"))}
+    ("et", "unused", "enml", "ey", "yt", "xsel", "sels", "wlo", "wm", "v4b", "v4q", "a0", "sw16", "sw32", "sw48", "pw", "px", "pe", "cnt", "nq"))}
 SAMPLE_TEMPS.update(best="v180", wq="v181")
 KEY0_BASE, KEY1_BASE = 68, 78
 SAMPLE_TEMPS.update({f"k0_{r}": f"s{KEY0_BASE + r}" for r in range(10)})
@@ -616,7 +586,7 @@ def score_candidate(word, x, el):
 
 
 def reduce_column_sample(tb):
-    """Column tb of the finished tile under sampling: running (max, sum-exp) as in the greedy reduction, and the
+    """Column tb of the finished tile under sampling: (max, sum-exp) as in the greedy reduction, and the running
     arg-max of x + tau*g with the plain logit there.  Exact: an id is skipped only when its uniform lies below what
     the best score seen so far minus the column's largest logit of this tile demands (1 - u < exp((t - ym) / tau),
     taken with a 1% margin), which no winner can."""
@@ -673,28 +643,8 @@ def reduce_column_sample(tb):
     e(f"v_cndmask_b32 {I}, {I}, %[sels], vcc")
     e(f"v_cndmask_b32 {XA}, {XA}, %[xsel], vcc")
     e(f"v_cndmask_b32 {YM}, {YM}, %[yt], vcc")
-    if SHAPE["fresh"]:
-        own_maximum(M)
-        tile_exponentials(XS, S)
-        return
-    # running maximum and sum of exponentials of the unperturbed logits
-    e(f"v_max_f32 {EMN}, {M}, {ET}")
-    e(f"v_sub_f32 {EY}, {M}, {EMN}")
-    e(f"v_mul_f32 {EY}, {hex(LOG2E)}, {EY}")
-    e(f"v_exp_f32 {EY}, {EY}")
-    e(f"v_mul_f32 {ENML}, {hex(NEG_LOG2E)}, {EMN}")
-    e(f"v_mov_b32 {M}, {EMN}")
-    for el in range(32):
-        e(f"v_fmamk_f32 {XS[el]}, {XS[el]}, {hex(LOG2E)}, {ENML}")
-    for el in range(32):
-        e(f"v_exp_f32 {XS[el]}, {XS[el]}")
-    for step in range(1, 8):
-        for r in range(4):
-            e(f"v_add_f32 {XS[r]}, {XS[r]}, {XS[4 * step + r]}")
-    e(f"v_add_f32 {XS[0]}, {XS[0]}, {XS[1]}")
-    e(f"v_add_f32 {XS[2]}, {XS[2]}, {XS[3]}")
-    e(f"v_add_f32 {XS[0]}, {XS[0]}, {XS[2]}")
-    e(f"v_fma_f32 {S}, {S}, {EY}, {XS[0]}")
+    own_maximum(M)
+    tile_exponentials(XS, S)
 
 
 def build_tile_sample():
@@ -768,8 +718,7 @@ def build_literal():
     LITERAL_ACC[0] = False
     for b in range(2):
         FA[b][:], FB[b][:] = saved[0][b], saved[1][b]
-    if SHAPE["ragged"]:
-        mask_counted()
+    mask_counted()
 
 
 def build():
@@ -839,7 +788,7 @@ def build():
 
 
 def write_statement(f, blocks, sample):
-    SHAPE.update(nb=blocks, ragged=True, fresh=True, tight=True)
+    SHAPE["nb"] = blocks
     lines.clear()
     uid[0] = 2000 if sample else 1000
     if sample:
@@ -893,7 +842,6 @@ def main(folder):
             for blocks in range(1, 9):
                 write_statement(f, blocks, sample)
     lines.clear()
-    SHAPE.update(ragged=False, fresh=False, tight=False)
     build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers
 
 

@@ -39,7 +39,7 @@ def generated_lines(fused=False, sample=False):
     if fused:
         mod.build_tile_sample() if sample else mod.build_tile()
         out = list(mod.lines)
-        out = out[:next(i for i, ln in enumerate(out) if ln.strip().startswith(("v_accvgpr_read_b32", "s_mov_b32 s68, %[seed_lo]")))]
+        out = out[:next(i for i, ln in enumerate(out) if ln.strip() == "s_cmp_eq_u32 %[first], 0")]
     else:
         mod.build()
         out = list(mod.lines)

@@ -1,6 +1,6 @@
 """The generated statements of the narrower row tiles (32 to 224 tokens), on the CPU: the K-loop of each under the ring
 protocol of test_w4_loop_protocol.py (its interpreter, with this width's ring geometry), and the reduction of each,
-which has to be the widest tile's, column by column, on this width's accumulators.  The sampling reduction with a
+which has to be the widest tile's, column by column, on this width's accumulators, and the triples' own definition.  The sampling reduction with a
 quad's own bound draws what it draws without, and leaves few quads to the exact path."""
 import re
 from fractions import Fraction
@@ -17,26 +17,16 @@ spec.loader.exec_module(gen)
 
 
 def listing(nb, sample):
+    """The K-loop, the ragged tile's part and the reduction of a width's statement."""
     gen.SHAPE["nb"] = nb
     gen.lines.clear()
     gen.uid[0] = 0
     gen.build_tile_sample() if sample else gen.build_tile()
     out = [ln.strip() for ln in gen.lines]
     gen.lines.clear()
-    cut = next(i for i, ln in enumerate(out) if ln.startswith(("v_accvgpr_read_b32", "s_mov_b32 s68, %[seed_lo]")))
-    return out[:cut], out[cut:]
-
-
-def built(nb, sample):
-    """The reduction of the statement that the library is built with, the ragged tile's part in front."""
-    gen.SHAPE.update(nb=nb, ragged=True, fresh=True, tight=True)
-    gen.lines.clear()
-    gen.uid[0] = 0
-    gen.build_tile_sample() if sample else gen.build_tile()
-    out = [ln.strip() for ln in gen.lines]
-    gen.lines.clear()
-    gen.SHAPE.update(ragged=False, fresh=False, tight=False)
-    return out[out.index("s_cmp_eq_u32 %[first], 0"):]
+    cut = out.index("s_cmp_eq_u32 %[first], 0")
+    end = next(i for i in range(cut, len(out)) if out[i].startswith("Lwhole")) + 1
+    return out[:cut], out[cut:end], out[end:]
 
 
 class Sim(protocol.Sim):
@@ -143,7 +133,7 @@ class Sim(protocol.Sim):
 @pytest.mark.parametrize("sample", [False, True])
 @pytest.mark.parametrize("nb", range(1, 9))
 def test_ring_protocol_of_every_width(nb, sample):
-    loop, _ = listing(nb, sample)
+    loop, _, _ = listing(nb, sample)
     for nk, ntile, ragged in [(1, 1, 0), (1, 5, 0), (2, 3, 0), (3, 1, 0), (3, 4, 0), (4, 2, 0), (5, 31, 0), (8, 2, 0),
                               (56, 2, 0), (64, 1, 0), (5, 1, 7), (5, 2, 1), (5, 4, 255), (6, 3, 128), (9, 2, 77)]:
         sim = Sim(loop, nb, nk, ntile, ragged)
@@ -158,7 +148,7 @@ def test_ring_protocol_of_every_width(nb, sample):
 
 @pytest.mark.parametrize("nb", range(1, 8))
 def test_a_missing_wait_is_caught_at_every_width(nb):
-    loop, _ = listing(nb, False)
+    loop, _, _ = listing(nb, False)
     sim = Sim([ln for ln in loop if not ln.startswith("s_waitcnt vmcnt")], nb, 5, 3)
     sim.prologue()
     with pytest.raises(AssertionError):
@@ -169,7 +159,7 @@ def test_a_missing_wait_is_caught_at_every_width(nb):
 def test_copies_keep_the_wait_state_behind_their_m0_write(nb):
     """A direct-to-LDS load needs an instruction between the write of M0 and itself."""
     for sample in (False, True):
-        loop, _ = listing(nb, sample)
+        loop, _, _ = listing(nb, sample)
         for a, b in zip(loop, loop[1:]):
             assert not (a.startswith("s_add_u32 m0") and b.startswith("global_load_lds"))
 
@@ -178,8 +168,8 @@ def test_copies_keep_the_wait_state_behind_their_m0_write(nb):
 @pytest.mark.parametrize("nb", range(1, 8))
 def test_reduction_of_every_width_is_the_widest_tiles(nb, sample):
     plain = lambda ln: re.sub(r"\bL([a-z]+)\d+_%=", r"L\1", ln)
-    _, wide = listing(8, sample)
-    _, red = listing(nb, sample)
+    _, _, wide = listing(8, sample)
+    _, _, red = listing(nb, sample)
 
     def widen(m):                       # accumulator (bi*nb + tb)*4 + r of this width -> (bi*8 + tb)*4 + r
         block, r = divmod(int(m.group(1)), 4)
@@ -203,7 +193,7 @@ def test_reduction_of_every_width_is_the_widest_tiles(nb, sample):
         assert rest == []
     else:                               # the exact paths out of line: one block per quad, the widest tile's first ones
         at = next(i for i, ln in enumerate(wide) if ln == "s_branch Ldone")
-        names = lambda ln: re.sub(r"L(slow|flush|back|queue|full)\b", r"L", ln)
+        names = lambda ln: re.sub(r"L(slow|flush|back|queue|full|nothing)\b", r"L", ln)
         assert rest[0] == "s_branch Ldone" and rest[-1] == "Ldone:"
         assert [names(x) for x in rest[1:-1]] == [names(x) for x in wide[at + 1:at + len(rest) - 1]]
 
@@ -219,19 +209,18 @@ def test_a_quads_own_bound_changes_no_draw(tau):
     pos = [rng.integers(0, 4096, 16).astype(np.uint32)[lane % 16] for _ in range(8)]
     i0 = (300000 + rng.permutation(8 * n).reshape(8, n)).astype(np.uint32)
     xa0 = rng.standard_normal((8, n)).astype(np.float32)
-    plain = listing(8, True)[1]
-    gen.SHAPE["tight"] = True
-    tight = listing(8, True)[1]
+    tight = [ln for part in listing(8, True)[1:] for ln in part]
     gen.SHAPE["tight"] = False
+    plain = [ln for part in listing(8, True)[1:] for ln in part]
+    gen.SHAPE["tight"] = True
     for best in (-2.0 ** 100, 2 + 2 * tau, 3 + 5 * tau, 3 + 9 * tau):   # fresh columns, then ever later in a split
         for planted in (False, True):
             agpr = reduce.planted_tile(rng, n) if planted else rng.standard_normal((256, n)).astype(np.float32)
-            m0, s0 = reduce.running_state(rng, agpr, n)
             ym0 = np.full((8, n), best, np.float32)
             ym0[:, lane % 16 == 5] = -2.0 ** 100                        # one token is fresh in any case
             out = {}
             for key, red, exact in (("exact", plain, True), ("plain", plain, False), ("tight", tight, False)):
-                out[key] = reduce.sampling_wave(red, agpr, m0, s0, ym0, xa0, i0, pos, vb, seed, tau, force_exact=exact)
+                out[key] = reduce.sampling_wave(red, agpr, ym0, xa0, i0, pos, vb, seed, tau, force_exact=exact)
             for tb in range(8):
                 assert reduce.token_level(out["tight"], tb) == reduce.token_level(out["exact"], tb), (best, planted, tb)
                 for name in ("m", "s"):
@@ -240,43 +229,8 @@ def test_a_quads_own_bound_changes_no_draw(tau):
             print(tau, best, planted, *((k, o.issued, o.slow_taken, o.flushes, o.fulls) for k, o in out.items()))
 
 
-@pytest.mark.parametrize("sample", [False, True])
-def test_a_tiles_own_triple_is_the_running_update_of_an_empty_state(sample):
-    import test_w4_tile_reduce as reduce
-    reduce.TEMPS.update(gen.SAMPLE_TEMPS)
-    rng = np.random.default_rng(3)
-    n = 64
-    lane = np.arange(n, dtype=np.uint32)
-    vb = np.full(n, 11 * 256, np.uint32) + 4 * (lane >> 4)
-    pos = [rng.integers(0, 4096, 16).astype(np.uint32)[lane % 16] for _ in range(8)]
-    running = listing(8, sample)[1]
-    gen.SHAPE["fresh"] = True
-    own = listing(8, sample)[1]
-    gen.SHAPE["fresh"] = False
-    agpr = reduce.planted_tile(rng, n)
-    agpr[:, 7] = -2.0 ** 100                                  # a lane whose ids all lie outside the vocabulary
-    empty = np.full((8, n), -2.0 ** 100, np.float32)
-    i0 = np.full((8, n), 0x7FFFFFFF, np.uint32)
-    zero = np.zeros((8, n), np.float32)
-    if sample:
-        a, b = (reduce.sampling_wave(p, agpr, empty, zero, empty, zero, i0, pos, vb, 77, 0.8) for p in (running, own))
-    else:
-        a, b = reduce.Wave(n, agpr), reduce.Wave(n, agpr)
-        for w, prog in ((a, running), (b, own)):
-            for tb in range(8):
-                if w is a:                                     # the other one has to write what it leaves
-                    w.fset(f"%[m{tb}]", empty[tb]), w.fset(f"%[s{tb}]", zero[tb]), w.iset(f"%[i{tb}]", i0[tb])
-            w.iset("%[vb]", vb)
-            w.run(prog)
-    for tb in range(8):
-        for name in ("m", "s") + (("ym", "xa", "i") if sample else ("i",)):
-            x, y = a.reg[f"%[{name}{tb}]"], b.reg[f"%[{name}{tb}]"]
-            keep = np.arange(n) != 7 if name == "i" and not sample else slice(None)   # no maximum, so no id: unused
-            assert np.array_equal(x[keep], y[keep]), (name, tb)
-
-
-def reduce_built(nb, sample, agpr, vb, first, tau=0.8):
-    """One wave of the built reduction on empty running states: (m, s, i) of every column, or (m, s, ym, xa, i)."""
+def reduce_wave(nb, sample, agpr, vb, first, tau=0.8):
+    """One wave's reduction, on nothing drawn before: (m, s, i) of every column, or (m, s, ym, xa, i)."""
     import test_w4_tile_reduce as reduce
     reduce.TEMPS.update(gen.SAMPLE_TEMPS)
     n = agpr.shape[1]
@@ -291,7 +245,8 @@ def reduce_built(nb, sample, agpr, vb, first, tau=0.8):
             w.fset(f"%[ym{tb}]", np.full(n, -2.0 ** 100)), w.fset(f"%[xa{tb}]", np.zeros(n))
             w.iset(f"%[i{tb}]", np.full(n, 0x7FFFFFFF))
             w.iset(f"%[pos{tb}]", 1000 * tb + np.arange(n) % 16)
-    w.run(built(nb, sample))
+    _, ragged, red = listing(nb, sample)
+    w.run(ragged + red)
     return [[w.reg[f"%[{name}{tb}]"].view(np.uint32 if name == "i" else np.float32)
              for name in (("m", "s", "ym", "xa", "i") if sample else ("m", "s", "i"))] for tb in range(nb)]
 
@@ -324,9 +279,38 @@ def test_ids_at_minus_infinity_count_for_nothing(nb, sample):
     agpr[:, 7] = -np.inf
     agpr[:17 * nb, 9] = -np.inf
     agpr[5, 11] = -np.inf
-    got = reduce_built(nb, sample, agpr, np.zeros(n), 0)
+    got = reduce_wave(nb, sample, agpr, np.zeros(n), 0)
     check_triples(nb, sample, got, agpr, np.zeros((32, n), bool))
     for tb in range(nb):
         assert got[tb][1][7] == 0
         if sample:
             assert got[tb][4][7] == 0x7FFFFFFF and got[tb][2][7] == -2.0 ** 100
+
+
+@pytest.mark.parametrize("sample", [False, True])
+@pytest.mark.parametrize("nb", range(1, 9))
+def test_a_tiles_triple_and_the_ids_counted_before(nb, sample):
+    """The reduction of every width against its definition: a whole tile, and the ragged last one, which lies over the
+    vocabulary's last 256 ids and of which `left` have not been counted (1: one; 256: a whole tile, %[first] is 0).  Ties
+    go to the lowest id.  The interpreter checks the distances between comparisons and their use on the way."""
+    rng = np.random.default_rng(17 * nb)
+    n = 64
+    lane = np.arange(n)
+    for left in (256, 255, 200, 128, 44, 4, 1):
+        for half in (0, 128):                                 # the two waves' ids
+            vb = 1000 * 256 + left - 256 + half + 4 * (lane >> 4)
+            first = 0 if left == 256 else 1000 * 256
+            agpr = rng.standard_normal((256, n)).astype(np.float32) * 3
+            for k in range(3):                                # exact ties
+                agpr[rng.integers(0, 32 * nb, n), lane] = 20
+            code = np.array([16 * (el // 4) + el % 4 for el in range(32)])[:, None]
+            taken_out = vb + code < first
+            got = reduce_wave(nb, sample, agpr, vb, first)
+            if not sample:
+                for col in got:
+                    col[2] -= vb.astype(np.uint32)
+            check_triples(nb, sample, got, agpr, taken_out)
+            for m, s, ym, xa, i in got if sample else ():
+                some = ~taken_out.all(axis=0)
+                assert np.all(i[some] != 0x7FFFFFFF) and np.all((i >= first)[some]) and np.all(i[~some] == 0x7FFFFFFF)
+                assert np.all(np.abs(xa[some]) < 100) and np.all(xa[some] <= m[some])
