@@ -65,12 +65,14 @@ def test_a_plans_grid_may_exceed_its_units(V):
     assert all(np.array_equal(a, b) for out in outs[1:] for a, b in zip(outs[0], out))
 
 
-def test_a_pair_of_launches_beyond_4_gib_shares_one_division():
+@pytest.mark.parametrize("V", [50257, 4096])
+def test_a_pair_of_launches_beyond_4_gib_shares_one_division(V):
     """A ragged vocabulary served by a pair of launches (fewer than five K-tiles; under sampling also V % 4 != 0), in a
     hidden tensor beyond 4 GiB: where the list has a 4 GiB gap inside the rows of one wave the general kernel takes the
     4-wave kernel's place, in 49 vocabulary splits for these 769 rows instead of 40, and the launch for the ragged tile
-    has to store behind those.  Expected: the general kernel on the same rows gathered into a small tensor."""
-    T, d, V = (1 << 23) + 8192, 256, 50257
+    has to store behind those.  And a vocabulary without one, whose width and division are searched for the rows found
+    all the same.  Expected: the general kernel on the same rows gathered into a small tensor."""
+    T, d = (1 << 23) + 8192, 256
     gen = torch.Generator(device=DEV)
     gen.manual_seed(workloads.BASE_SEED + 79)
     hidden = torch.empty((T, d), dtype=torch.bfloat16, device=DEV)
@@ -91,8 +93,8 @@ def test_a_pair_of_launches_beyond_4_gib_shares_one_division():
             for tau in (0.0, 0.8):
                 print(f"pair beyond 4 GiB: M={M} bound={bound} flag={flag} tau={tau}", flush=True)
                 op = binding.MaskOnlyLogits(T, d, V, max_rows=bound, device=DEV, sampling=tau > 0)
-                assert "ragged last vocabulary tile" in binding.mosaic_masked_logits_kernel_name(
-                    1000, d, d, V, op.plan, tau > 0)
+                name = binding.mosaic_masked_logits_kernel_name(1000, d, d, V, op.plan, tau > 0)
+                assert ("ragged last vocabulary tile" in name) == (V % 256 != 0)
                 ref = binding.MaskOnlyLogits(M, d, V, device=DEV, sampling=tau > 0)
                 ref.plan.flags |= binding.PLAN_GENERAL_KERNEL
                 if tau > 0:

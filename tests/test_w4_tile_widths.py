@@ -1,7 +1,8 @@
-"""The generated statements of the narrower row tiles (32 to 224 tokens), on the CPU: the K-loop of each under the ring
-protocol of test_w4_loop_protocol.py (its interpreter, with this width's ring geometry), and the reduction of each,
-which has to be the widest tile's, column by column, on this width's accumulators, and the triples' own definition.  The sampling reduction with a
-quad's own bound draws what it draws without, and leaves few quads to the exact path."""
+"""The generated statements of every width of the row tile (32 to 256 tokens), on the CPU: the K-loop of each under the
+ring protocol of test_w4_loop_protocol.py (its interpreter, with this width's ring geometry); the reduction of each
+against the definition of the triples it yields, the ragged last tile's included, and, instruction by instruction,
+against the widest tile's on this width's accumulators.  The sampling reduction with a quad's own bound draws what it
+draws without, and leaves few quads to the exact path."""
 import re
 from fractions import Fraction
 
