@@ -75,9 +75,9 @@ typedef struct {
 
 /* plan.flags bit: use the general 8-wave kernel even where the hand-scheduled 4-wave kernel applies
  * (it applies to the whole tiles of the vocabulary, and to a ragged last tile where d >= 320 and, sampling,
- * V % 4 == 0; in a hidden tensor of 4 GiB or more it needs every 64
- * consecutive rows of the gather list to lie less than 4 GiB apart, which a small kernel checks on the device
- * before the launch, handing lists with such a gap to the general kernel).  Both give the same results; the flag
+ * V % 4 == 0; in a hidden tensor of 4 GiB or more it needs the 8 to 64 consecutive rows of the gather list
+ * that one wave copies to lie less than 4 GiB apart, which a small kernel checks on the device before the
+ * launch, handing lists with such a gap to the general kernel).  Both give the same results; the flag
  * exists for testing and tuning. */
 #define MOSAIC_PLAN_GENERAL_KERNEL 1
 /* plan.flags bit, set by the selector: the plan was sized for a sampling step (20 bytes per row and
@@ -101,9 +101,11 @@ typedef struct {
  *   T          total positions, >= 0, < 2^31
  *   max_rows   host-side upper bound on M (the search in the paper is driven by the
  *              number of masks and the number of tokens; pass T if M is unknown), 0..T.  Results do
- *              not depend on it.  The device divides the work by the rows it finds, within the partial
- *              results this bound makes room for; a bound far above M costs little, a close one
- *              also saves that search (~1 us) and, for few rows, gives room for more splits
+ *              not depend on it (but for the last bit of a confidence or log-sum-exp, about once in a
+ *              million rows, as on all that moves the vocabulary splits).  The device divides the work
+ *              by the rows it finds, within the partial results this bound makes room for; a bound far
+ *              above M costs little, a close one also saves that search (~1 us) and, for few rows,
+ *              gives room for more splits
  *   d, V       hidden and vocabulary size; d must be a multiple of MOSAIC_K_TILE
  *   budget_bytes  <= 0 means unbounded
  *   num_cus    compute units to schedule for; <= 0 means 256 (one MI355X)

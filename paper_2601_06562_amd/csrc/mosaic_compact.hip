@@ -4,7 +4,8 @@
 // the paper leaves its production to the framework.  Here it is an explicit
 // exclusive prefix sum over (mask[t] != 0) followed by a scatter that never touches the host:
 // one single-block launch for up to 65536 positions (a denoising step of one long sequence),
-// otherwise three small launches (per-block counts, a scan of those counts, the scatter).
+// two small launches (per-block counts, the scatter, whose blocks add up the counts before them) for up
+// to 4 million, otherwise three (a scan of the counts in between).
 // Integer work only; the result is unique (stable order), so it is bit-exact by construction.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_scatter_kernel(const 
 constexpr int64_t kSumBlocks = 1024;
 
 // Everything in one block, for masks of up to kSingleMax positions: passes of 16384 positions, the running
-// offset carried from pass to pass.  One launch instead of three where launches are all the cost.
+// offset carried from pass to pass.  One launch instead of two where launches are all the cost.
 constexpr int kSingleThreads = 1024;
 constexpr int64_t kSingleMax = 65536;
 __global__ __launch_bounds__(kSingleThreads) void compact_single_kernel(const uint8_t* __restrict__ mask, int64_t T,

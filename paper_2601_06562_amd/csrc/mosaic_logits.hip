@@ -88,10 +88,10 @@ struct KernelParams {
   int32_t* sync;    // round counters of the persistent grid (cleared before the launch), sync_slots of them
   int32_t sync_slots;
   int32_t* found_splits;   // the splits of the division a launch found, for a pair's second one and the merge kernel
-  // Hidden tensors of 4 GiB or more.  The 4-wave kernel addresses a wave's 64 rows by 32-bit offsets from the lowest of
-  // them, which works unless those rows lie 4 GiB or more apart; a small kernel looks for such a group in the list
-  // and raises *wide_flag, and of the two launches that follow (4-wave kernel, general kernel) the one whose
-  // wide_run_if differs from the flag returns at once.  nullptr: no such check (the launch always runs).
+  // Hidden tensors of 4 GiB or more.  The 4-wave kernel addresses the rows a wave copies (8 times the width) by 32-bit
+  // offsets from the lowest of them, which works unless those rows lie 4 GiB or more apart; a small kernel looks for such
+  // a group in the list and raises *wide_flag, and of the two launches that follow (4-wave kernel, general kernel) the one
+  // whose wide_run_if differs from the flag returns at once.  nullptr: no such check (the launch always runs).
   const int32_t* wide_flag;
   int32_t wide_run_if;
 };
@@ -99,10 +99,12 @@ struct KernelParams {
 // Fold.  The running state of a row is (m, s, i): the largest logit, the sum of exponentials, and the lowest id that
 // attains m.  s is kept relative to 2^E, E = ceil(m log2 e), in double precision: a change of m only ever scales s by
 // an exact power of two, and what a tile adds depends on the tile alone.  Any order and any grouping of the tiles
-// then gives the same sum to ~2^-50, so the outputs, rounded to fp32, are those of one pass over the vocabulary
-// however it was split (only a sum within 2^-46 of a rounding boundary could tell), and the division of the work is
-// free to follow the number of rows.  A scale factor exp(m - m') rounded in fp32 at each step, as the state once had,
-// makes the last bits follow the split count.
+// then gives the same sum to ~2^-50 within a unit, and a unit's sum is rounded once more, to the 58 - id_bits mantissa
+// bits of its packed partial (2^-42 for 126464 ids).  So the outputs, rounded to fp32, are those of one pass over the
+// vocabulary however it was split, but for the last bit of a row whose sum lies that close to a rounding boundary (of
+// random rows 0.7 in a million at 126464 ids, 7 at 2^20), and the division of the work is free to follow the number of
+// rows.  A scale factor exp(m - m') rounded in fp32 at each step, as the state once had, makes the last bits follow the
+// split count everywhere.
 __device__ __forceinline__ float ref_exponent(float m) { return __builtin_ceilf(m * kLog2e); }
 __device__ __forceinline__ int scale_steps(float d) { return (int)fmaxf(d, -2000.f); }   // 2^-2000 is 0 either way
 

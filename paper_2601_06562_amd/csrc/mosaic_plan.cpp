@@ -53,9 +53,9 @@ int32_t choose_vocab_splits(int64_t row_tiles, int64_t vocab_tiles, int32_t num_
 // decides).  A ragged last vocabulary tile is the 4-wave kernel's own from kRaggedKTiles K-tiles on: its copies run up
 // to four K-tiles ahead and must not reach past the next tile while the step into a ragged one is another than into a
 // whole one.  That tile begins at id V - 256, and a sampling step draws its noise for four ids at a time from a multiple
-// of four on, so there V has to be one.  Otherwise the vocabulary is covered by a pair of launches: the 4-wave kernel on the whole tiles and the
-// general 8-wave kernel on the last tile as one more split.  Everything else (and plans that ask for it) goes to the
-// general kernel alone.
+// of four on, so there V has to be one.  Otherwise the vocabulary is covered by a pair of launches: the 4-wave kernel on
+// the whole tiles and the general 8-wave kernel on the last tile as one more split.  Everything else (and plans that ask
+// for it) goes to the general kernel alone.
 constexpr int32_t kRaggedKTiles = 5;
 KernelChoice choose_kernel(int64_t T, int64_t ld_h, int32_t d, int32_t V, const mosaic_plan& plan, bool sample) {
   const int64_t vocab_tiles = ((int64_t)V + MOSAIC_VOCAB_TILE - 1) / MOSAIC_VOCAB_TILE;
@@ -73,10 +73,10 @@ const char* masked_logits_kernel_name(int64_t T, int64_t ld_h, int32_t d, int32_
                                       bool sample) {
   const KernelChoice c = choose_kernel(T, ld_h, d, V, plan, sample);
   if (c.wide)
-    return sample ? "masked_logits_kernel_w4<true>, or masked_logits_kernel<3,2,true> where 64 consecutive rows of "
-                    "the list lie 4 GiB apart (decided on the device)"
-                  : "masked_logits_kernel_w4<false>, or masked_logits_kernel<3,2,false> where 64 consecutive rows of "
-                    "the list lie 4 GiB apart (decided on the device)";
+    return sample ? "masked_logits_kernel_w4<true>, or masked_logits_kernel<3,2,true> where the rows one wave copies lie "
+                    "4 GiB apart (decided on the device)"
+                  : "masked_logits_kernel_w4<false>, or masked_logits_kernel<3,2,false> where the rows one wave copies lie "
+                    "4 GiB apart (decided on the device)";
   if (c.fast) return sample ? "masked_logits_kernel_w4<true>" : "masked_logits_kernel_w4<false>";
   if (c.paired)
     return sample ? "masked_logits_kernel_w4<true> + masked_logits_kernel<3,2,true> (ragged last vocabulary tile)"

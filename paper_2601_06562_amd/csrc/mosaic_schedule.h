@@ -4,7 +4,7 @@
 // pass therefore works the division out itself, with the function below, from the same few numbers: a plan for 16
 // row tiles that finds 9 of them in use spreads those over all compute units instead of leaving 7/16 of its units
 // empty (4096 positions planned, 2077 masked: 2621 -> 1569 us).  What a pass computes does not depend on the
-// division (see Fold in mosaic_logits.hip), so neither do its results.
+// division but for a last bit here and there (see Fold in mosaic_logits.hip).
 #ifndef MOSAIC_SCHEDULE_H_
 #define MOSAIC_SCHEDULE_H_
 

@@ -72,15 +72,15 @@ def test_full_size_workload(name):
 
 
 def span_flag(op):
-    """The word the device-side span check leaves behind the round counters: 1 if some 64 consecutive rows of the
-    list lay 4 GiB or more apart (the general kernel then did the work), 0 if the 4-wave kernel did."""
+    """The word the device-side span check leaves behind the round counters: 1 if some rows that one wave
+    copies lay 4 GiB or more apart (the general kernel then did the work), 0 if the 4-wave kernel did."""
     return int(op.workspace[op.plan.workspace_bytes - 4:op.plan.workspace_bytes].view(torch.int32).item())
 
 
 def test_hidden_tensor_beyond_4_gib():
     """A hidden tensor larger than 4 GiB, where a 32-bit byte offset from the start of the tensor wraps.  The 4-wave
-    kernel addresses a wave's 64 rows from the lowest of them, so it serves such a tensor as long as no 64 consecutive
-    rows of the list lie 4 GiB apart (decided on the device); a list with such a gap goes to the general kernel,
+    kernel addresses the rows a wave copies from the lowest of them, so it serves such a tensor as long as none of those
+    lie 4 GiB apart (decided on the device); a list with such a gap goes to the general kernel,
     which addresses rows with 64-bit pointers.  Both lists here, greedy and sampled, against the oracle."""
     import oracle
     from paper_2601_06562_amd import binding

@@ -66,7 +66,7 @@ GUARD_SHAPES = [
     (1000, 128, 1280, 0.7, "4-wave kernel, several row tiles"),
     (700, 192, 777, 0.6, "general kernel, ragged vocabulary below one tile pair"),
     (900, 128, 1000, 0.9, "paired launch: 4-wave kernel + general kernel on the ragged last tile"),
-    (70000, 64, 512, 0.03, "three-launch compaction (T > 65536)"),
+    (70000, 64, 512, 0.03, "two-launch compaction (T > 65536)"),
     (513, 64, 512, 0.0, "empty mask"),
 ]
 
