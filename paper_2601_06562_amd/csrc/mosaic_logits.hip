@@ -212,7 +212,7 @@ __device__ __forceinline__ Schedule launch_schedule(const KernelParams& p, int r
 // its division is that launch's word, not a choice of its own (the 4-wave kernel and the general kernel in its place
 // settle on different counts, 40 and 49 splits for 769 rows of 50257 ids).
 __device__ __forceinline__ Schedule division_found(const KernelParams& p, int rows) {
-  return Schedule{8, (rows + kTileRows - 1) / kTileRows, *p.found_splits, partial_stride(rows)};
+  return Schedule{8, (rows + kTileRows - 1) / kTileRows, held_splits(p.sched, rows, *p.found_splits), partial_stride(rows)};
 }
 
 __device__ __forceinline__ int choose_width(const KernelParams& p, int rows) {
@@ -999,7 +999,7 @@ __device__ __forceinline__ void combine_rows(const KernelParams& p, int splits, 
 __global__ __launch_bounds__(256) void combine_kernel(const KernelParams p) {
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
-  const int splits = *p.found_splits + (int)p.sched.extra;   // a pair's second launch adds one
+  const int splits = held_splits(p.sched, rows, *p.found_splits) + (int)p.sched.extra;   // a pair's second launch adds one
   if (splits >= kWideMergeSplits) combine_rows<1>(p, splits, rows);
   else combine_rows<4>(p, splits, rows);
 }

@@ -100,6 +100,14 @@ __host__ __device__ inline Schedule schedule_of(int32_t rows, uint64_t best) {
                   partial_stride(rows)};
 }
 
+// The splits that a launch says it settled on, for the launches behind it.  The word lies in the caller's workspace (or in
+// the library's one array per GPU, which calls share): whatever another call leaves there, nobody is to be led beyond
+// the partial arrays by it.
+__host__ __device__ inline int32_t held_splits(const ScheduleInput& in, int32_t rows, int32_t found) {
+  const uint32_t column = (uint32_t)partial_stride(rows) >> 6;
+  return found >= 1 && ((uint64_t)(uint32_t)found + in.extra) * column <= in.slots64 ? found : 1;
+}
+
 // On the host: for the bound the plan was made for, handed to the kernels so that they need not search when the
 // count turns out to be that bound.
 inline Schedule choose_schedule(const ScheduleInput& in, int32_t rows) {

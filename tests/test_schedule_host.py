@@ -1,0 +1,74 @@
+"""The division of the work (csrc/mosaic_schedule.h), which host and device evaluate alike, on the CPU: every division has
+room in the partial arrays, for either of the two kernels that may do a launch's work, and the word through which a
+launch tells its division to the ones behind it leads nobody outside, whatever it holds."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2601_06562_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+PROGRAM = r"""
+#include <stdio.h>
+#include "mosaic_internal.h"
+#include "mosaic_schedule.h"
+using namespace mosaic;
+static long bad, divisions, differ;
+static void check(bool ok, const char* what, int64_t max_rows, int rows, int d, int V, long budget, int n) {
+  if (!ok && ++bad < 10) printf("%s: max_rows %ld rows %d d %d V %d budget %ld: %d\n", what, (long)max_rows, rows, d, V, budget, n);
+}
+int main() {
+  const int shapes[][2] = {{64, 300}, {256, 2500}, {256, 50257}, {4096, 50257}, {4096, 126464}, {3584, 151936}};
+  for (auto& shape : shapes) for (int64_t max_rows : {1, 40, 255, 769, 4096, 60000}) for (long budget : {0L, 20000L, 4L << 20})
+    for (int sample = 0; sample < 2; ++sample) {
+      const int d = shape[0], V = shape[1];
+      mosaic_plan plan;
+      if (mosaic_plan_workspace(131072, max_rows, d, V, budget, 256, sample, &plan) != MOSAIC_OK) { printf("no plan\n"); return 1; }
+      const KernelChoice choice = choose_kernel(131072, d, d, V, plan, sample != 0);
+      ScheduleInput in{};
+      in.vocab_tiles = (uint32_t)((V + 255) / 256 - (choice.paired ? 1 : 0));
+      in.k_tiles = (uint32_t)d / 64;
+      in.sampling = (uint32_t)sample;
+      in.grid = (uint32_t)plan.grid;
+      in.extra = choice.paired ? 1 : 0;
+      in.slots64 = (uint32_t)((int64_t)plan.vocab_splits * plan.rows_per_chunk / 64);
+      const int64_t slots = (int64_t)plan.vocab_splits * plan.rows_per_chunk;
+      const int most = (int)(max_rows < plan.rows_per_chunk ? max_rows : plan.rows_per_chunk);
+      for (int rows = 1; rows <= most; rows += 1 + rows / 7) {
+        int splits[2];
+        for (int general = 0; general < 2; ++general) {
+          in.widths = general ? 0x80 : 0xff;
+          const Schedule s = choose_schedule(in, rows);
+          ++divisions;
+          splits[general] = s.splits;
+          check(s.splits >= 1 && s.splits <= (int)in.vocab_tiles && s.stride == partial_stride(rows) &&
+                    (int64_t)s.row_tiles * 32 * s.width >= rows && (general == 0 || s.width == 8) &&
+                    ((int64_t)s.splits + in.extra) * s.stride <= slots, "division", max_rows, rows, d, V, budget, s.splits);
+          check(held_splits(in, rows, s.splits) == s.splits, "a division is not taken over", max_rows, rows, d, V, budget, s.splits);
+        }
+        differ += splits[0] != splits[1];
+        for (int found : {-2147483647 - 1, -7, 0, 1, 2, 3, 255, 256, 257, 4096, 1 << 20, 2147483647}) {
+          const int held = held_splits(in, rows, found);
+          check(held >= 1 && ((int64_t)held + in.extra) * partial_stride(rows) <= slots, "outside", max_rows, rows, d, V, budget, found);
+        }
+      }
+    }
+  printf("%ld divisions, %ld bad, %ld rows on which the two kernels' differ\n", divisions, bad, differ);
+  return bad != 0;
+}
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_divisions_have_room_and_a_foreign_word_leads_nowhere(tmp_path):
+    src = tmp_path / "schedule.hip"
+    src.write_text(PROGRAM)
+    exe = str(tmp_path / "schedule")
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-o",
+                    exe, str(src), os.path.join(CSRC, "mosaic_plan.cpp")], check=True, stderr=subprocess.DEVNULL)
+    res = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=120)
+    print(res.stdout)
+    assert res.returncode == 0, res.stdout
+    assert int(res.stdout.split(" bad, ")[1].split()[0]) > 0             # else the two kernels are not told apart here
