@@ -4,12 +4,13 @@ fused kernel as one inline-asm statement, the hand-scheduled K-loop followed by 
 each width of the row tile (32*NB tokens, NB = 1..8, chosen by `if constexpr`).
 
 The K-loop covers the nk K-tiles of the vocabulary tile.  Per K-tile (step g) a wave issues 16*nb
-v_mfma_f32_16x16x32_bf16 in two groups of 8*nb (k 0..31 and k 32..63 of the tile): its 128 vocabulary ids (8 blocks)
-against its half of the tokens (nb blocks).  Between the MFMAs of a group sit the ds_read_b128 that fetch the next
-group's fragments and the group's direct-to-LDS copies, so that nothing but MFMAs is ever waited on in steady state.
-The steady-state body (1 <= g, g + DEPTH < total) contains no branch at all -- a taken branch costs more than one
-16-cycle MFMA -- and all slot / pointer book-keeping is s_cselect arithmetic; the first step and the last DEPTH run a
-guarded copy of the same schedule.
+v_mfma_f32_16x16x32_bf16: its 128 vocabulary ids (8 blocks) against its half of the tokens (nb blocks), both K-halves of
+the tile.  Up to nb = 4 (build) one K-half after the other, in two groups of 8*nb; between the MFMAs of a group sit the
+ds_read_b128 that fetch the next group's fragments and the group's direct-to-LDS copies, so that nothing but MFMAs is
+ever waited on in steady state.  The steady-state body (1 <= g, g + DEPTH < total) contains no branch at all -- a taken
+branch costs more than one 16-cycle MFMA -- and all slot / pointer book-keeping is s_cselect arithmetic; the first step
+and the last DEPTH run a guarded copy of the same schedule.  From nb = PAIRS_FROM on (build_pairs) both halves of a block
+back to back; there every step is a steady one.
 
 A ring holds DEPTH + 1 LM-head slots of 32 KiB and DEPTH hidden slots of 4*nb KiB.  DEPTH is two from nb = 3 on (nb = 8
 fills the 160 KiB); one or two token blocks leave room for a third K-tile under way, which the copies need there,
@@ -24,6 +25,7 @@ import sys
 FA = [[f"%[fa{b}{i}]" for i in range(8)] for b in range(2)]
 FB = [[f"%[fb{b}{j}]" for j in range(8)] for b in range(2)]
 VT0, VT1 = "%[vt0]", "%[vt1]"
+VW, VH = ("%[vt0]", "%[vt2]"), ("%[vt1]", "%[vt3]")     # pair order: addresses of an LM-head and a hidden row, per K-half
 WSRC, HSRC = "s[96:97]", "s[98:99]"
 KT = "s95"
 NK128 = "s94"
@@ -31,6 +33,7 @@ NK128 = "s94"
 lines = []
 uid = [0]
 SHAPE = {"nb": 8,         # token blocks of 16 per wave
+         "pairs": False,  # the K-loop in pair order (write_statement: from PAIRS_FROM on)
          "tight": True}   # sampling: a quad that passes the column's bound is held against its own (off: for comparison)
 
 
@@ -714,7 +717,7 @@ def build_literal():
     for b in range(2):
         FA[b][:], FB[b][:] = fa[b], fb[b]
     LITERAL_ACC[0] = True
-    build()
+    build_pairs() if SHAPE["pairs"] else build()
     LITERAL_ACC[0] = False
     for b in range(2):
         FA[b][:], FB[b][:] = saved[0][b], saved[1][b]
@@ -787,8 +790,257 @@ def build():
     e("s_mov_b32 %[hsrc_hi], s99")
 
 
+# ---- The K-loop in pair order, for the widths whose time goes into the matrix cores.
+#
+# Under the power cap what a product costs is energy, and a product that accumulates where the one before it did costs
+# less: its addend need not come out of the register file.  Register-only loops over 64 accumulator blocks: 2.02 PFLOP/s
+# block after block with one K-half and then the other, 2.14 with the two halves of a block back to back (four or eight
+# products of a block in a row: 2.12 to 2.15).  So a step (K-tile) here takes block after block, both halves of each:
+# vocabulary block i = 0..7, under it the token blocks j = 0..nb-1, forward and backward in turn.  The sums run in the
+# order of the other loop, so the results are the same bits.
+#
+# Fragments, in 32 tuples as there: the token blocks, which every row of blocks uses, lie in X_PAIRS pairs (both halves)
+# and stay for a step, the vocabulary blocks pass through a ring of four pairs.  Up to six token blocks are double-
+# buffered; of seven and eight the last (2 nb - 12) are read into the registers of the blocks that the last row of
+# products, which runs backward, is done with.  The register numbers repeat every other step: two bodies.
+#
+# Rings, as deep as there: LM head three slots, hidden two.  The sync of a step (two rows in) publishes the next step's
+# hidden tile, its vocabulary blocks 0..3 and this step's blocks 4..7; it frees this step's hidden tile (read whole by
+# then), this step's blocks 0..3 and the last step's 4..7.  The waves that copy blocks 0..3 (the even ones) therefore run
+# three K-tiles ahead and the odd ones two.  The copies are spread over the whole time from one sync to the next, the
+# hidden tile's first, since only it has to land by the next sync.  Spread over two thirds of it 4096 rows took 0.4% more,
+# 2077 rows 0.7%, one row tile at the speed of memory 3 to 7%; over less still 3 to 8%.
+#
+# Every step of a unit copies, also the last ones, into slots that nobody reads any more: of the LM head the last K-tile
+# again, of the hidden rows what lies at the front of them.  A guarded form of the steps would be code that runs cold, a
+# few steps a unit (measured: 0.3% slower).
+#
+# 4096 x 126464 x 4096: 2641 -> 2535 us, 2077 rows (width 5) 1484 -> 1411, 58524 rows 39.7 -> 37.3 ms (one box each, in
+# turn with the other loop).
+PAIRS_FROM = 5
+X_PAIRS = 12
+Y_RING = 4
+
+
+def x_slot(par, j):
+    """where token block j of a step of this parity lies"""
+    if 2 * nb() <= X_PAIRS:
+        return par * nb() + j
+    early = X_PAIRS - nb()
+    if j < early:
+        return par * early + j
+    return 2 * early + (j - early if par == 0 else nb() - 1 - j)
+
+
+def x_frag(par, j, half):
+    base = FRAG_BASE + 8 * x_slot(par, j) + 4 * half
+    return f"v[{base}:{base + 3}]"
+
+
+def y_frag(i, half):
+    base = FRAG_BASE + 8 * X_PAIRS + 8 * (i % Y_RING) + 4 * half
+    return f"v[{base}:{base + 3}]"
+
+
+def read_y(i, half):
+    return f"ds_read_b128 {y_frag(i, half)}, {VW[half]}" + (f" offset:{2048 * i}" if i else "")
+
+
+def read_x(par, j, half):
+    return f"ds_read_b128 {x_frag(par, j, half)}, {VH[half]}" + (f" offset:{2048 * j}" if j else "")
+
+
+def addr_ops(v, slot, row):
+    return [f"v_add_u32 {v[0]}, %[{slot}], %[{row}]", f"v_xor_b32 {v[1]}, 64, {v[0]}"]
+
+
+def pair_blocks():
+    return [(i, j) for i in range(8) for j in (range(nb()) if i % 2 == 0 else range(nb() - 1, -1, -1))]
+
+
+class Gaps:
+    """What follows each MFMA of a step.  Two instructions fit behind an MFMA; `put` takes the first gap from `m` on that
+    has room for a chunk (instructions that nothing may come between: SCC and VCC are shared)."""
+
+    def __init__(self, n):
+        self.at = [[] for _ in range(n)]
+
+    def put(self, m, chunk, room=2):
+        chunk = [chunk] if isinstance(chunk, str) else list(chunk)
+        m = int(m)
+        while self.at[m] and len(self.at[m]) + len(chunk) > room:
+            m += 1
+        self.at[m] += chunk
+        return m
+
+    def chain(self, m, chunks):
+        for c in chunks:
+            m = self.put(m, c) + 1
+        return m
+
+
+def next_slot_chunks(dst, slot, ring):
+    ops = next_slot(dst, slot, ring)
+    return [ops] if len(ops) == 1 else [[ops[0]], ops[1:3], [ops[3]]]
+
+
+def copy_gaps(sync):
+    """gaps of a step's copies, hidden then LM head, spread over the time from one sync to the next (beyond the step's last
+    gap: in the next step)"""
+    n, m = nb(), 16 * nb()
+    first, h, end = sync + 2, m / 20, m + sync - 17
+    w0 = first + n * h + 1
+    at = [int(first + k * h) for k in range(n)] + [int(w0 + k * (end - w0) / 7) for k in range(8)]
+    # M0 is written a gap ahead, in the same step, and its write changes SCC: not behind the loop's last comparison
+    return [x if not m - 3 < x <= m else m - 3 if x < m - 1 else m + 1 for x in at]
+
+
+def late_pieces():
+    """of a step's eight LM-head copies, those that follow its sync (the others go ahead of the next one)"""
+    return sum(m < 16 * nb() for m in copy_gaps(4 * nb() + 1)[nb():])
+
+
+def pair_schedule(par):
+    """(gaps, gap behind which the sync stands) of a step: reads, copies, scalars"""
+    n, row, nxt = nb(), 2 * nb(), 1 - par
+    gaps = Gaps(8 * row)
+    sync = 2 * row + 1
+    # this step's vocabulary blocks 2 and 3 ahead of the sync, 4..7 and the next step's 0 and 1 behind it; each once the
+    # block four before it is done with
+    for i, at in ((2, .4), (3, .9)):
+        gaps.put(at * row, read_y(i, 0)), gaps.put(at * row + 2, read_y(i, 1))
+    for k, x in enumerate(addr_ops(VH, "hrd", "rdh0")):      # the next step's hidden slot
+        gaps.put(1.5 * row + 3 + k, x)
+    hrot = [[f"s_xor_b32 %[hrd], %[hrd], {hex(h_slot())}"]] if h_slot() & (h_slot() - 1) == 0 else \
+        [[f"s_add_u32 %[hrd], %[hrd], {hex(h_slot())}"], [f"s_cmp_ge_u32 %[hrd], {hex(h_ring())}", "s_cselect_b32 %[hrd], 0, %[hrd]"]]
+    end = gaps.chain(1.3 * row, hrot)
+    assert end <= 1.5 * row + 3
+    gaps.at[sync] = ["sync"]
+    # the hidden copies first, then the LM head's, the last of them ahead of the next sync
+    copies = copy_gaps(sync)
+    for k, m in enumerate(copies):
+        setup, load = dma_split(k if k < n else k - n, hidden=k < n)
+        m %= 8 * row
+        assert gaps.put(m - 1, setup) == m - 1
+        gaps.at[m].append(load)
+    for i, at in ((4, 2.3), (5, 3.1), (6, 4.0), (7, 4.8)):
+        gaps.put(at * row + 1, read_y(i, 0)), gaps.put(at * row + 3, read_y(i, 1))
+    early = min(n, X_PAIRS - n)
+    for k in range(2 * early):
+        gaps.put(2.4 * row + 2 + k * 4.4 * row / (2 * early), read_x(nxt, k // 2, k % 2))
+    wrot = [[f"s_add_u32 %[wrd], %[wrd], 0x8000"],
+            [f"s_cmp_ge_u32 %[wrd], {hex(w_ring())}", "s_cselect_b32 %[wrd], 0, %[wrd]"]]
+    end = gaps.chain(5.05 * row, wrot)
+    for x in addr_ops(VW, "wrd", "rdw0"):
+        end = gaps.put(end, x) + 1
+    for i, at in ((0, max(end, 5.6 * row)), (1, 6.4 * row)):
+        gaps.put(at, read_y(i, 0)), gaps.put(at + 2, read_y(i, 1))
+    for k, j in enumerate(range(early, n)):                   # into the registers of block n - 1 - k, done with by then
+        assert x_slot(nxt, j) == x_slot(par, n - 1 - k)
+        gaps.put(7 * row + 4 * k + 1, read_x(nxt, j, 0)), gaps.put(7 * row + 4 * k + 3, read_x(nxt, j, 1))
+    end = gaps.chain(copies[n - 1] + 1, [["s_add_u32 %[hk], %[hk], 1"], ["s_add_u32 s98, s98, 128", "s_addc_u32 s99, s99, 0"],
+                                     ["s_cmp_eq_u32 %[hk], %[nk]", f"s_cselect_b32 vcc_lo, {NK128}, 0",
+                                      "s_cselect_b32 %[hk], 0, %[hk]"],
+                                     ["s_sub_u32 s98, s98, vcc_lo", "s_subb_u32 s99, s99, 0"]]
+                     + next_slot_chunks("hdst", h_slot(), h_ring()))
+    # past the unit's last K-tile the pointer stays
+    wend = gaps.chain(copies[-1] % (8 * row) + 1,
+                      [["s_add_u32 %[wk], %[wk], 1"],
+                       ["s_cmp_eq_u32 %[wk], %[nk]", "s_cselect_b32 vcc_lo, %[wwrap], 128", "s_cselect_b32 %[wk], 0, %[wk]"],
+                       ["s_add_u32 vcc_hi, %[g], %[wnext]"],
+                       ["s_cmp_lt_u32 vcc_hi, %[total]", "s_cselect_b32 vcc_lo, vcc_lo, 0"],
+                       ["s_add_u32 s96, s96, vcc_lo", "s_addc_u32 s97, s97, 0"]] + next_slot_chunks("wdst", 0x8000, w_ring()))
+    # (the chains share VCC, and a pointer is on before its next copy)
+    assert copies[-1] >= 8 * row and wend <= sync and end <= copies[-1]
+    end = gaps.chain(max(end, 7 * row), [["s_add_u32 %[g], %[g], 1"], [f"s_add_u32 {KT}, {KT}, 1"]])
+    end = max(end, *(m + 1 for m in copies if m < 8 * row))      # (an M0 write changes SCC)
+    end = gaps.put(end, f"s_cmp_lt_u32 {KT}, %[nk]")
+    return gaps.at, sync
+
+
+def pair_waits():
+    """wait[parity][m] = n: ahead of MFMA m of a step of this parity, lgkmcnt(n) (fragment reads return in order)"""
+    wait = [{}, {}]
+    issued, done, last = 0, 0, {}
+    for par in range(2):
+        for j in range(nb()):
+            for h in range(2):
+                issued += 1
+                last[x_frag(0, j, h)] = issued
+    for step in range(6):
+        par = step % 2
+        at, sync = pair_schedule(par)
+        wait[par] = {}
+        for m, (i, j) in enumerate(b for b in pair_blocks() for _ in range(2)):
+            # for both halves of the block at once
+            need = max(last.get(f, 0) for h in range(2) for f in (y_frag(i, h), x_frag(par, j, h)))
+            if need > done:
+                n = min(15, issued - need)
+                wait[par][m] = n
+                done = issued - n
+            for x in at[m]:
+                if x == "sync":
+                    done = issued
+                elif x.startswith("ds_read"):
+                    issued += 1
+                    last[x.split()[1].rstrip(",")] = issued
+    return wait
+
+
+def pair_step(par, wait):
+    at, _ = pair_schedule(par)
+    for m, (i, j) in enumerate(b for b in pair_blocks() for _ in range(2)):
+        if m in wait[par]:
+            e(f"s_waitcnt lgkmcnt({wait[par][m]})")
+        e(f"v_mfma_f32_16x16x32_bf16 {acc_block(i, j)}, {y_frag(i, m % 2)}, {x_frag(par, j, m % 2)}, {acc_block(i, j)}")
+        for x in at[m]:
+            if x == "sync":
+                # landed: all but the LM-head copies of the last step, the eight youngest
+                e("s_waitcnt vmcnt(8) lgkmcnt(0)")
+                e("s_barrier")
+            else:
+                e(x)
+
+
+def build_pairs():
+    e("s_mov_b32 s96, %[wsrc_lo]")
+    e("s_mov_b32 s97, %[wsrc_hi]")
+    e("s_mov_b32 s98, %[hsrc_lo]")
+    e("s_mov_b32 s99, %[hsrc_hi]")
+    e(f"s_add_u32 {NK128}, %[hwrap], 128")
+    e(f"s_mov_b32 {KT}, 0")
+    for x in addr_ops(VW, "wrd", "rdw0") + addr_ops(VH, "hrd", "rdh0"):
+        e(x)
+    for h in range(2):
+        e(read_y(0, h))
+    for j in range(nb()):
+        for h in range(2):
+            e(read_x(0, j, h))
+    for h in range(2):
+        e(read_y(1, h))
+    for i in range(32 * nb()):
+        e(f"v_accvgpr_write_b32 a{i}, 0")
+    e("s_nop 7")
+    e("s_waitcnt lgkmcnt(0)")
+    wait = pair_waits()
+    top, out = label("steady"), label("out")
+    e(f"{top}:")
+    pair_step(0, wait)
+    e(f"s_cbranch_scc0 {out}")
+    pair_step(1, wait)
+    e(f"s_cbranch_scc1 {top}")
+    e(f"{out}:")
+    e("s_waitcnt lgkmcnt(0)")
+    e("s_nop 15")
+    e("s_nop 15")
+    e("s_mov_b32 %[wsrc_lo], s96")
+    e("s_mov_b32 %[wsrc_hi], s97")
+    e("s_mov_b32 %[hsrc_lo], s98")
+    e("s_mov_b32 %[hsrc_hi], s99")
+
+
 def write_statement(f, blocks, sample):
-    SHAPE["nb"] = blocks
+    SHAPE.update(nb=blocks, pairs=blocks >= PAIRS_FROM)
     lines.clear()
     uid[0] = 2000 if sample else 1000
     if sample:
@@ -807,9 +1059,11 @@ def write_statement(f, blocks, sample):
     outs.append('[vt0] "=&v"(addr_tmp0)')
     outs.append('[vt1] "=&v"(addr_tmp1)')
     ins = []
-    for k in range(2):
+    if SHAPE["pairs"]:
+        outs += ['[vt2] "=&v"(addr_tmp2)', '[vt3] "=&v"(addr_tmp3)']
+        ins.append('[wnext] "s"(st_wnext)')
+    for k in range(1 if SHAPE["pairs"] else 2):
         ins.append(f'[rdw{k}] "v"(rdw[{k}])')
-    for k in range(2):
         ins.append(f'[rdh{k}] "v"(rdh[{k}])')
     for i in range(8):
         ins.append(f'[woff{i}] "v"(woff[{i}])')
@@ -841,6 +1095,14 @@ def main(folder):
                     f"{'sampling' if sample else 'greedy'} 4-wave kernel, K-loop and vocabulary reduction, per width.\n")
             for blocks in range(1, 9):
                 write_statement(f, blocks, sample)
+    with open(os.path.join(folder, "mosaic_w4_pieces.inc"), "w") as f:
+        f.write("// GENERATED by gen_w4_loop.py -- do not edit.\n"
+                "constexpr int w4_late_pieces(int nb) {\n  constexpr int pieces[9] = {0, 0, 0, 0, 0")
+        for blocks in range(PAIRS_FROM, 9):
+            SHAPE["nb"] = blocks
+            f.write(f", {late_pieces()}")
+        f.write("};\n  return pieces[nb];\n}\n")
+    SHAPE["pairs"] = False
     lines.clear()
     build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers
 

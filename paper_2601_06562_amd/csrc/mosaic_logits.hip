@@ -660,6 +660,8 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 // sampling; both generated): the K-loop, then the tile's reduction to a triple per column.  In the K-loop
 // every MFMA is followed by at most one LDS read or one direct-to-LDS copy, fragments are double-
 // buffered in fixed VGPRs, the LM-head ring runs two K-tiles ahead and the hidden ring one (three and two at NB <= 2).
+// From NB = 5 on, where the matrix cores under the power cap are the bound, the two K-halves of a block's products go back
+// to back, which costs the least energy (the generator says how): 4096 rows 2641 -> 2535 us.
 // NB sets the width of the row tile, 32*NB tokens.  The widest, 256, has the fewest LDS and L2 bytes per product and is
 // the one for many rows; a list that does not fill its last row tile takes the width that pads it least
 // (mosaic_schedule.h): 280 rows as two tiles of 160 take 290 us, as two of 256 383 us; 32 rows
@@ -673,9 +675,12 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 constexpr int kRowBytes = 128;                       // one K-tile of a row
 constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
 constexpr int kLdsBytes = 160 * 1024;
+#include "mosaic_w4_pieces.inc"
 template <bool SAMPLE, int NB>
 __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, char* smem) {
   constexpr int kDepth = NB <= 2 ? 3 : 2;            // K-tiles under way, as the generator's depth()
+  constexpr bool kPairs = NB >= 5;                   // the K-loop in pair order, as the generator's PAIRS_FROM
+  constexpr int kLatePieces = w4_late_pieces(NB);    // of eight LM-head copies, those a step issues behind its sync
   constexpr int NW = kDepth + 1, NH = kDepth;
   constexpr int kHiddenSlot = 32 * NB * kRowBytes;
   constexpr int kTokens = 32 * NB;
@@ -693,6 +698,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wv = wave & 1;   // vocabulary half of the tile
   const int wt = wave >> 1;  // token half of the tile
+  const bool odd_wave = (__builtin_amdgcn_readfirstlane(wave) & 1) != 0;
   const int l16 = lane & 15, q = lane >> 4;   // MFMA 16x16x32: row/column lane%16, k group lane/16
 
   const int n_tt = sched.row_tiles;
@@ -782,12 +788,16 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       hoff[i] = (uint32_t)(trow[i] - tmin) * (uint32_t)p.ldh_bytes + chunk_of(wave * 8 * NB + 8 * i + sub);
 
     // Prologue copies: W0 and H0, which are needed first, then what else the rings hold.
-    auto copy_w = [&](int gw) {
-      const char* src = p.w + (int64_t)first_id(vt0 + gw / nk) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes;
+    auto w_source = [&](int gw) {   // past the end: the last one
+      const int g = gw < total_steps ? gw : total_steps - 1;
+      return p.w + (int64_t)first_id(vt0 + g / nk) * (int64_t)w_row_bytes + (g % nk) * kRowBytes;
+    };
+    auto copy_w = [&](int gw, int pieces = 8) {
+      const char* src = w_source(gw);
       char* dst = smem + (gw % NW) * kLmHeadSlot + w_dst;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
+        if (i < pieces) __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
     };
     auto copy_h = [&](int gh) {
       const char* src = hidden_wave + (gh % nk) * kRowBytes;
@@ -796,28 +806,41 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       for (int i = 0; i < NB; ++i)
         __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + hoff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
     };
+    // What the rings hold.  In pair order the waves that copy a half's vocabulary blocks 4..7 run a K-tile behind the
+    // others, and the copies that may be under way at the first sync, the eight youngest, are the LM head's.
+    const int lead = kPairs && odd_wave ? NW - 1 : NW;   // K-tiles of the LM head ahead of the step
     wait_vm<0>();
     copy_w(0);
     copy_h(0);
+    if constexpr (kPairs) {
+      if (!odd_wave && total_steps > 1) copy_w(1);
+      if (total_steps > 1) copy_h(1);
+      copy_w(lead - 1, kLatePieces);   // the first step copies the others
+      if (total_steps < NW) wait_vm<0>();
+      else if (odd_wave) wait_vm<kLatePieces + NB>();
+      else wait_vm<kLatePieces + 8 + NB>();
+    } else {
 #pragma unroll
-    for (int g = 1; g < NW; ++g)
-      if (g < total_steps) copy_w(g);
+      for (int g = 1; g < NW; ++g)
+        if (g < total_steps) copy_w(g);
 #pragma unroll
-    for (int g = 1; g < NH; ++g)
-      if (g < total_steps) copy_h(g);
-    if (total_steps >= NW && total_steps >= NH) wait_vm<8 * (NW - 1) + NB * (NH - 1)>(); else wait_vm<0>();
+      for (int g = 1; g < NH; ++g)
+        if (g < total_steps) copy_h(g);
+      if (total_steps >= NW && total_steps >= NH) wait_vm<8 * (NW - 1) + NB * (NH - 1)>(); else wait_vm<0>();
+    }
     __builtin_amdgcn_s_barrier();
 
-    // State of the asm loop: next tiles to copy are W(NW) and H(NH) (never issued if past the end).
-    const int gw = NW, gh = NH;
-    const uint64_t wsrc0 = (uint64_t)(p.w + (int64_t)first_id(vt0 + gw / nk) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes);
+    // State of the asm loop: next tiles to copy are W(gw) and H(NH).  Never issued if past the end, or, in pair order, into
+    // slots that nobody reads any more: the last LM-head tile again, and the front of the hidden rows.
+    const int gw = kPairs ? lead - 1 : NW, gh = NH;
+    const uint64_t wsrc0 = (uint64_t)(kPairs ? w_source(gw) : p.w + (int64_t)first_id(vt0 + gw / nk) * (int64_t)w_row_bytes + (gw % nk) * kRowBytes);
     const uint64_t hsrc0 = (uint64_t)(hidden_wave + (gh % nk) * kRowBytes);
     uint32_t st_wsrc_lo = (uint32_t)wsrc0, st_wsrc_hi = (uint32_t)(wsrc0 >> 32);
     uint32_t st_hsrc_lo = (uint32_t)hsrc0, st_hsrc_hi = (uint32_t)(hsrc0 >> 32);
     uint32_t st_wrd = 0, st_hrd = 0;
     uint32_t st_wdst = (uint32_t)((gw % NW) * kLmHeadSlot) + w_dst;
     uint32_t st_hdst = (uint32_t)((gh % NH) * kHiddenSlot) + h_dst;
-    uint32_t st_wk = (uint32_t)(gw % nk), st_hk = (uint32_t)(gh % nk);
+    uint32_t st_wk = (uint32_t)((kPairs && gw >= total_steps ? total_steps - 1 : gw) % nk), st_hk = (uint32_t)(gh % nk);
     uint32_t st_g = 0;
 
     float run_m[NB], run_ym[NB], run_xa[NB];
@@ -852,7 +875,9 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       const uint32_t st_wwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ragged_next ? u_wwrap_ragged : u_wwrap));
       const uint32_t st_first = (uint32_t)__builtin_amdgcn_readfirstlane(ragged ? ragged_tile * kTileVocab : 0);
       const uint32_t st_hwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_hwrap);
+        [[maybe_unused]] const uint32_t st_wnext = (uint32_t)__builtin_amdgcn_readfirstlane(lead);
         uint32_t addr_tmp0, addr_tmp1;
+        [[maybe_unused]] uint32_t addr_tmp2, addr_tmp3;
         const int vb = first_id(vt0 + n) + wv * 128 + 4 * q;   // vocabulary id of this lane's element 0
         float tile_m[NB], tile_s[NB];   // this tile's own triples
         int tile_i[NB];
@@ -878,6 +903,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     // Unit end: a token's state lies in eight lanes (four of a wave, times the two vocabulary halves).  All of them go to
     // LDS, and one thread per token merges its eight in a loop: a tenth of the code of a tree of shuffles over NB
     // columns, and it is code that runs once a unit, cold.
+    if constexpr (kPairs) wait_vm<0>();   // the copies that the last steps made for nobody
     __syncthreads();  // every wave is done with the ring (the merge scratch aliases it)
 #pragma unroll
     for (int tb = 0; tb < NB; ++tb) {
