@@ -1072,7 +1072,7 @@ def write_statement(f, blocks, sample):
     for name in ("total", "nk", "wwrap", "hwrap"):
         ins.append(f'[{name}] "s"(st_{name})')
     clob = ['"s94"', '"s95"', '"s96"', '"s97"', '"s98"', '"s99"', '"vcc"', '"scc"', '"m0"', '"memory"']
-    ins += ['[vb] "v"(vb)', '[first] "s"(st_first)']
+    ins += ['[vb] "v"(vb)', '[first] "s"(st_first)', '[nt] "n"(STREAM ? 1 : 0)']
     clob = [f'"a{i}"' for i in range(32 * blocks)] + [f'"s{i}"' for i in range(88, 94)] + clob
     if sample:
         ins += [f'[pos{tb}] "v"(pos[{tb}])' for tb in range(blocks)]
@@ -1082,7 +1082,10 @@ def write_statement(f, blocks, sample):
     clob = [f'"v{i}"' for i in range(FRAG_BASE, FRAG_BASE + 128)] + clob
     f.write(f"if constexpr (NB == {blocks}) {{\nasm volatile(\n")
     for ln in lines:
-        f.write(f'    "{ln}\\n"\n')
+        if ln.startswith("global_load_lds_dwordx4 %[woff"):     # the LM head, as the kernel's launch streams it or not
+            f.write(f'    ".if %[nt]\\n{ln} nt\\n.else\\n{ln}\\n.endif\\n"\n')
+        else:
+            f.write(f'    "{ln}\\n"\n')
     f.write("    : " + ",\n      ".join(outs) + "\n")
     f.write("    : " + ",\n      ".join(ins) + "\n")
     f.write("    : " + ", ".join(clob) + ");\n}\n")

@@ -70,6 +70,7 @@ struct KernelParams {
   int32_t chunk_rows;  // capacity of the chunk (C)
   int32_t max_rows;
   int32_t panel;       // row tiles scheduled side by side
+  int32_t stream_w;    // the LM head is larger than kStreamBytes
   ScheduleInput sched; // what the division of the work is made from (of a pair of launches: the first one's)
   Schedule bound;      // ... and the division for bound_rows rows
   int32_t bound_rows;
@@ -672,11 +673,17 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 // Preconditions (checked by the launcher): V % 256 == 0, or V >= 256, five K-tiles and, sampling, V % 4 == 0;
 // 256*d*2 < 4 GiB; and, in a hidden tensor of 4 GiB or more,
 // no wave's 8*NB consecutive rows of the list 4 GiB apart (checked on the device, see KernelParams::wide_flag).
+// Streaming.  A single row tile reads the LM head once, and one of more than the 256 MiB of the memory-side cache finds
+// nothing of it there from the step before: its copies then carry the nt bit, by which they pass that cache by (copies
+// alone: 6.6 instead of 5.9 TB/s).  126464 x 4096: 32 rows 204 -> 184 us a pass, 205 rows 223 -> 192, 256 rows 249 -> 237.
+// Not where it is smaller (64 rows of 65536 x 2048, 256 MiB: 55 -> 72 us; 81920 x 2048, 320 MiB: 82 -> 77), and not
+// where several row tiles share it behind an L2 (280 rows in two: 337 -> 349 us, 4096 rows 2551 -> 2592).
+constexpr int64_t kStreamBytes = (int64_t)288 << 20;
 constexpr int kRowBytes = 128;                       // one K-tile of a row
 constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
 constexpr int kLdsBytes = 160 * 1024;
 #include "mosaic_w4_pieces.inc"
-template <bool SAMPLE, int NB>
+template <bool SAMPLE, int NB, bool STREAM>
 __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, char* smem) {
   constexpr int kDepth = NB <= 2 ? 3 : 2;            // K-tiles under way, as the generator's depth()
   constexpr bool kPairs = NB >= 5;                   // the K-loop in pair order, as the generator's PAIRS_FROM
@@ -684,6 +691,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   constexpr int NW = kDepth + 1, NH = kDepth;
   constexpr int kHiddenSlot = 32 * NB * kRowBytes;
   constexpr int kTokens = 32 * NB;
+  constexpr int kAuxW = STREAM ? 2 : 0;              // the nt bit of the LM head's copies
   constexpr int kTileK = 64;
   constexpr int kSwzShift = 1;
   static_assert(NW * kLmHeadSlot + NH * kHiddenSlot <= kLdsBytes, "rings");
@@ -797,7 +805,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       char* dst = smem + (gw % NW) * kLmHeadSlot + w_dst;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (i < pieces) __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
+        if (i < pieces) __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, kAuxW);
     };
     auto copy_h = [&](int gh) {
       const char* src = hidden_wave + (gh % nk) * kRowBytes;
@@ -943,6 +951,20 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   }
 }
 
+template <bool SAMPLE, bool STREAM>
+__device__ __forceinline__ void w4_units_of(const KernelParams& p, const Schedule& sched, int rows, char* smem) {
+  switch (sched.width) {
+    case 1: w4_units<SAMPLE, 1, STREAM>(p, sched, rows, smem); break;
+    case 2: w4_units<SAMPLE, 2, STREAM>(p, sched, rows, smem); break;
+    case 3: w4_units<SAMPLE, 3, STREAM>(p, sched, rows, smem); break;
+    case 4: w4_units<SAMPLE, 4, STREAM>(p, sched, rows, smem); break;
+    case 5: w4_units<SAMPLE, 5, STREAM>(p, sched, rows, smem); break;
+    case 6: w4_units<SAMPLE, 6, STREAM>(p, sched, rows, smem); break;
+    case 7: w4_units<SAMPLE, 7, STREAM>(p, sched, rows, smem); break;
+    default: w4_units<SAMPLE, 8, STREAM>(p, sched, rows, smem); break;
+  }
+}
+
 template <bool SAMPLE>
 __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParams p) {
   __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
@@ -950,16 +972,8 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
   const Schedule sched = launch_schedule(p, rows);
-  switch (sched.width) {
-    case 1: w4_units<SAMPLE, 1>(p, sched, rows, smem); break;
-    case 2: w4_units<SAMPLE, 2>(p, sched, rows, smem); break;
-    case 3: w4_units<SAMPLE, 3>(p, sched, rows, smem); break;
-    case 4: w4_units<SAMPLE, 4>(p, sched, rows, smem); break;
-    case 5: w4_units<SAMPLE, 5>(p, sched, rows, smem); break;
-    case 6: w4_units<SAMPLE, 6>(p, sched, rows, smem); break;
-    case 7: w4_units<SAMPLE, 7>(p, sched, rows, smem); break;
-    default: w4_units<SAMPLE, 8>(p, sched, rows, smem); break;
-  }
+  if (p.stream_w != 0 && sched.row_tiles == 1) w4_units_of<SAMPLE, true>(p, sched, rows, smem);
+  else w4_units_of<SAMPLE, false>(p, sched, rows, smem);
 }
 
 // Merge the S partial results of every row and emit the outputs.  A wave handles ROWS rows with G = 64 / ROWS lanes
@@ -1044,6 +1058,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.chunk_rows = plan.rows_per_chunk;
   p.max_rows = (int32_t)a.max_rows;
   p.panel = plan.tile_panel;
+  p.stream_w = (int64_t)a.V * a.d * 2 > kStreamBytes ? 1 : 0;
   const int64_t slots = (int64_t)plan.vocab_splits * plan.rows_per_chunk;   // a multiple of 256
   p.part_si = static_cast<uint64_t*>(a.workspace);
   p.part_m = reinterpret_cast<float*>(p.part_si + slots);

@@ -186,7 +186,7 @@ class PairWave(protocol.Sim):
                 self.ds_read(args[0], m.group(1), int(m.group(2) or 0))
             elif op == "global_load_lds_dwordx4":
                 assert not self.prog[self.pc - 2].startswith("s_add_u32 m0")      # M0's wait state
-                self.copy("W" if args[1] == "s[96:97]" else "H")
+                self.copy("W" if args[1].split()[0] == "s[96:97]" else "H")
             elif op == "v_add_u32":
                 self.set(args[0], self.val(args[1]) + self.val(args[2]))
             elif op == "v_xor_b32":
