@@ -715,7 +715,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const int pos = xcd_contiguous_position((int)blockIdx.x, G);
   const int S = sched.splits;
   const int n_units = n_tt * S;
-  const int A = NB == 8 ? (p.panel < n_tt ? p.panel : n_tt) : (int)panel_depth((uint32_t)n_tt, NB);
+  const int A = (int)panel_depth((uint32_t)n_tt, NB, (uint32_t)p.panel);
   const int full_panel_units = A * S;
   const int n_panels = (n_tt + A - 1) / A;
 
@@ -1088,9 +1088,9 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.sched.k_tiles = (uint32_t)(a.d / MOSAIC_K_TILE);
   p.sched.widths = fast || paired ? 0xff : 0x80;   // the general kernel has the one width
   p.sched.sampling = sample ? 1 : 0;
-  // never more workgroups than the plan has units, whatever its field says; with that many the division's products stay
-  // below 2^32 (a larger one could only be refused by the launch)
-  const int64_t units = (int64_t)(plan.rows_per_chunk / kTileRows) * plan.vocab_splits;
+  // never more workgroups than the plan has units of the narrowest tiles, whatever its field says; with that many the
+  // division's products stay below 2^32 (a larger one could only be refused by the launch)
+  const int64_t units = (int64_t)(plan.rows_per_chunk / 32) * plan.vocab_splits;
   const int32_t grid = plan.grid < units ? plan.grid : (int32_t)units;
   p.sched.grid = (uint32_t)(grid < 1 << 24 ? grid : 1 << 24);
   p.sched.extra = paired ? 1 : 0;

@@ -38,14 +38,12 @@ __host__ __device__ inline uint32_t ceil_div(uint32_t a, uint32_t b) { return (a
 __host__ __device__ inline int32_t partial_stride(int32_t rows) { return (rows + 63) & ~63; }
 
 // Row tiles scheduled side by side: the workgroups behind one L2 share the LM-head tiles of that many, and the hidden
-// tiles of as many splits as are left of them.  Eight tiles of 256 rows (8 x 4 of the 32 workgroups), sixteen of the
-// narrow ones, whose traffic is nearly all LM head; evenly deep panels, since a lone row tile streams the whole LM head
-// once more (280 rows as 8 + 1 tiles of 32: 861 us, as 9: 595 us).  The kernels take it for tiles of up to 224 rows; the
-// tiles of 256 run in panels of the plan's tile_panel, up to 8 deep with a shallower last one, which the cost below
-// does not tell from even ones.  Even panels there: 4352 rows (17 tiles) 2906 -> 2877 us, 6672 rows 4760 -> 4668, but
-// 4096 rows of 32000 x 1024, whose panels are the same, 219.6 -> 221.2 for how the kernel then compiled: not kept.
-__host__ __device__ inline uint32_t panel_depth(uint32_t row_tiles, uint32_t width) {
-  const uint32_t side = width <= 4 ? 16 : 8;
+// tiles of as many splits as are left of them.  Eight tiles of 256 rows (8 x 4 of the 32 workgroups; the plan's tile_panel
+// if that is less), sixteen of the narrow ones, whose traffic is nearly all LM head; evenly deep panels, since a lone row
+// tile streams the whole LM head once more (280 rows as 8 + 1 tiles of 32: 861 us, as 9: 595 us; 6672 rows as 8 + 8 + 8 + 3
+// tiles of 256: 4545 us, as 7 + 7 + 7 + 6: 4519).
+__host__ __device__ inline uint32_t panel_depth(uint32_t row_tiles, uint32_t width, uint32_t widest = 8) {
+  const uint32_t side = width <= 4 ? 16 : width <= 7 || widest > 8 ? 8 : widest;
   return ceil_div(row_tiles, ceil_div(row_tiles, side));
 }
 
