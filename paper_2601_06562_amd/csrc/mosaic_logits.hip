@@ -1088,9 +1088,9 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.sched.k_tiles = (uint32_t)(a.d / MOSAIC_K_TILE);
   p.sched.widths = fast || paired ? 0xff : 0x80;   // the general kernel has the one width
   p.sched.sampling = sample ? 1 : 0;
-  // never more workgroups than the plan has units of the narrowest tiles, whatever its field says; with that many the
+  // never more workgroups than the plan has units of 64 rows, whatever its field says; with that many the
   // division's products stay below 2^32 (a larger one could only be refused by the launch)
-  const int64_t units = (int64_t)(plan.rows_per_chunk / 32) * plan.vocab_splits;
+  const int64_t units = (int64_t)(plan.rows_per_chunk / 64) * plan.vocab_splits;
   const int32_t grid = plan.grid < units ? plan.grid : (int32_t)units;
   p.sched.grid = (uint32_t)(grid < 1 << 24 ? grid : 1 << 24);
   p.sched.extra = paired ? 1 : 0;

@@ -1,4 +1,4 @@
-"""The selector's workgroups: as many as the narrowest row tiles (32 rows) of a chunk give units, the CUs at most."""
+"""The selector's workgroups: as many as row tiles of 64 rows of a chunk give units, the CUs at most."""
 import pytest
 
 from paper_2601_06562_amd import binding
@@ -10,5 +10,5 @@ from paper_2601_06562_amd import binding
 def test_workgroups_of_a_plan(rows, d, V, budget, cus):
     p = binding.mosaic_plan_workspace(4096, rows, d, V, budget, cus)
     K = next(k for k in range(1, rows + 1) if -(-(-(-rows // k)) // 256) * 256 == p.rows_per_chunk)
-    narrow = -(-(-(-rows // K)) // 32) * p.vocab_splits
-    assert p.grid == min(narrow, cus or 256)
+    units = -(-(-(-rows // K)) // 64) * p.vocab_splits
+    assert p.grid == min(units, cus or 256)
