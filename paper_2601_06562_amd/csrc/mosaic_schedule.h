@@ -69,23 +69,35 @@ __host__ __device__ inline uint32_t reduction_time(uint32_t width, uint32_t samp
 // split each: 62 ms; in four: 47 ms).
 constexpr uint32_t kScheduleRounds = 32;       // candidates per width: the rounds' quantisation is below 3% beyond
 constexpr int32_t kNarrowRows = 1 << 20;       // beyond, the widest tile always pays (and 32 bits hold its units)
-__host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, int32_t rows, uint32_t width,
-                                                       uint32_t extra_rounds) {
-  if ((in.widths >> (width - 1) & 1) == 0 || (width < 8 && rows > kNarrowRows)) return ~(uint64_t)0;
+struct SplitRange {
+  uint32_t row_tiles, least, most;   // splits on offer (most = 0: the width is not)
+  uint32_t first;                    // the fewest rounds
+};
+__host__ __device__ inline SplitRange split_range(const ScheduleInput& in, int32_t rows, uint32_t width) {
+  SplitRange range{0, 0, 0, 0};
+  if ((in.widths >> (width - 1) & 1) == 0 || (width < 8 && rows > kNarrowRows)) return range;
   // 32-bit throughout (rows < 2^31, so at most 2^23 row tiles and 2^31 units): a wide division costs the device 10x
-  const uint32_t row_tiles = ceil_div((uint32_t)rows, 32 * width);
+  range.row_tiles = ceil_div((uint32_t)rows, 32 * width);
   const uint32_t fit = in.slots64 / ((uint32_t)partial_stride(rows) >> 6);
-  uint32_t most = in.vocab_tiles < MOSAIC_MAX_VOCAB_SPLITS ? in.vocab_tiles : MOSAIC_MAX_VOCAB_SPLITS;
-  if (fit < most + in.extra) most = fit <= in.extra + 1 ? 1 : fit - in.extra;
-  const uint32_t least = most < 4 ? most : 4;
-  const uint32_t first = ceil_div(row_tiles * least, in.grid);
-  uint32_t s = (first + extra_rounds) * in.grid / row_tiles;
-  if (s > most) s = most;
+  range.most = in.vocab_tiles < MOSAIC_MAX_VOCAB_SPLITS ? in.vocab_tiles : MOSAIC_MAX_VOCAB_SPLITS;
+  if (fit < range.most + in.extra) range.most = fit <= in.extra + 1 ? 1 : fit - in.extra;
+  range.least = range.most < 4 ? range.most : 4;
+  range.first = ceil_div(range.row_tiles * range.least, in.grid);
+  return range;
+}
+__host__ __device__ inline uint32_t splits_in(const ScheduleInput& in, const SplitRange& range, uint32_t extra_rounds) {
+  return (range.first + extra_rounds) * in.grid / range.row_tiles;   // (may be more than `most`)
+}
+__host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, const SplitRange& range, uint32_t width,
+                                                       uint32_t extra_rounds) {
+  if (range.most == 0) return ~(uint64_t)0;
+  uint32_t s = splits_in(in, range, extra_rounds);
+  if (s > range.most) s = range.most;
   const uint32_t longest = ceil_div(in.vocab_tiles, s);
   uint32_t splits = ceil_div(in.vocab_tiles, longest);
-  if (splits < least) splits = least;
-  const uint32_t rounds = ceil_div(row_tiles * splits, in.grid);
-  const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(row_tiles, width)) + reduction_time(width, in.sampling);
+  if (splits < range.least) splits = range.least;
+  const uint32_t rounds = ceil_div(range.row_tiles * splits, in.grid);
+  const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(range.row_tiles, width)) + reduction_time(width, in.sampling);
   uint64_t cost = ((uint64_t)rounds * longest * tile + (uint64_t)(rounds - 1) * (tile / 2 + 400)) >> 3;
   if (width < 8) cost += cost >> 6;   // a narrower tile has to win by more than the model is off (5748 rows of 32000 x
                                       // 1024: 36 x 7 units of 160 rows 300 us, 23 x 11 of 256 rows 294 us)
@@ -107,23 +119,28 @@ __host__ __device__ inline int32_t held_splits(const ScheduleInput& in, int32_t 
 }
 
 // On the host: for the bound the plan was made for, handed to the kernels so that they need not search when the
-// count turns out to be that bound.
+// count turns out to be that bound.  A width whose most splits fit one round has one candidate (all of the smallest
+// steps, whose host side this is a part of: 256 candidates took 2.5 us).
 inline Schedule choose_schedule(const ScheduleInput& in, int32_t rows) {
   uint64_t best = ~(uint64_t)0;
-  for (uint32_t w = 1; w <= 8; ++w)
+  for (uint32_t w = 1; w <= 8; ++w) {
+    const SplitRange range = split_range(in, rows, w);
     for (uint32_t r = 0; r < kScheduleRounds; ++r) {
-      const uint64_t c = schedule_candidate(in, rows, w, r);
+      const uint64_t c = schedule_candidate(in, range, w, r);
       best = c < best ? c : best;
+      if (range.most == 0 || splits_in(in, range, r) >= range.most) break;   // further rounds change nothing
     }
+  }
   return schedule_of(rows, best);
 }
 
 // On the device: eight lanes per width, the same result in every wave (~1 us).
 __device__ __forceinline__ Schedule choose_schedule_wave(const ScheduleInput& in, int32_t rows) {
   const uint32_t lane = threadIdx.x & 63;
+  const SplitRange range = split_range(in, rows, 1 + (lane >> 3));
   uint64_t best = ~(uint64_t)0;
   for (uint32_t r = lane & 7; r < kScheduleRounds; r += 8) {
-    const uint64_t c = schedule_candidate(in, rows, 1 + (lane >> 3), r);
+    const uint64_t c = schedule_candidate(in, range, 1 + (lane >> 3), r);
     best = c < best ? c : best;
   }
 #pragma unroll
