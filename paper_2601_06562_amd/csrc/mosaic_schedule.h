@@ -50,11 +50,16 @@ __host__ __device__ inline uint32_t panel_depth(uint32_t row_tiles, uint32_t wid
 // What a unit's parts take, in units of 10 ns, fitted to measurements at widths 1..8 and 32..4096 rows of a 126464 x 4096
 // and a 32000 x 1024 LM head (most within 10%).  A K-tile: bound by the copies into LDS up to four token blocks a wave
 // (0.64 to 0.76 us), by the matrix cores beyond (1.26 us at eight); or by memory, which brings the 32 KiB of LM head
-// for all compute units at 5.6 TB/s in 1.48 us, shared by the panel's row tiles; the shorter of the two hides
-// but for a sixth.  The reduction of a tile: 0.56 us per token block, with a draw 1.66 us.  A further round of
-// units (pipeline fill, merge, a fresh start of the draw's bound): half a tile and 4 us.
-__host__ __device__ inline uint32_t k_tile_time(uint32_t width, uint32_t share) {
-  const uint32_t compute = width <= 4 ? 60 + 4 * width : (36 + 27 * width) / 2, memory = 148 / share;
+// for all compute units in 1.48 us, shared by the panel's row tiles; the shorter of the two hides but for a sixth.  A lone
+// row tile's workgroups all wait for bytes of their own: 1.26 us for 256 of them and less for fewer, down to what one can
+// have under way (594 vocabulary tiles, 100 rows: 198 workgroups on three tiles each 207 us, two row tiles in 119 splits
+// of five, which 1.48 us a K-tile for any number of workgroups preferred, 255; 240 rows 256 against 299).  The
+// reduction of a tile: 0.56 us per token block, with a draw 1.66 us.  A further round of units (pipeline fill, merge, a
+// fresh start of the draw's bound): half a tile and 4 us.  With the K-loop in pair order the wide tiles are 5% faster
+// throughout; at 21 row counts from 280 to 3500 of 126464 x 4096 no other width beats the one this picks by more than 1.4%.
+__host__ __device__ inline uint32_t k_tile_time(uint32_t width, uint32_t share, uint32_t workgroups) {
+  const uint32_t compute = width <= 4 ? 60 + 4 * width : (36 + 27 * width) / 2;
+  const uint32_t alone = workgroups < 128 ? 62 : workgroups * 126 / 256, memory = share == 1 ? alone : 148 / share;
   return compute > memory ? compute + memory / 6 : memory + compute / 6;
 }
 __host__ __device__ inline uint32_t reduction_time(uint32_t width, uint32_t sampling) {
@@ -97,7 +102,9 @@ __host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, 
   uint32_t splits = ceil_div(in.vocab_tiles, longest);
   if (splits < range.least) splits = range.least;
   const uint32_t rounds = ceil_div(range.row_tiles * splits, in.grid);
-  const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(range.row_tiles, width)) + reduction_time(width, in.sampling);
+  const uint32_t workgroups = range.row_tiles * splits < in.grid ? range.row_tiles * splits : in.grid;
+  const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(range.row_tiles, width), workgroups) +
+                        reduction_time(width, in.sampling);
   uint64_t cost = ((uint64_t)rounds * longest * tile + (uint64_t)(rounds - 1) * (tile / 2 + 400)) >> 3;
   if (width < 8) cost += cost >> 6;   // a narrower tile has to win by more than the model is off (5748 rows of 32000 x
                                       // 1024: 36 x 7 units of 160 rows 300 us, 23 x 11 of 256 rows 294 us)
