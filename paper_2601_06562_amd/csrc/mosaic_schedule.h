@@ -54,8 +54,11 @@ __host__ __device__ inline uint32_t panel_depth(uint32_t row_tiles, uint32_t wid
 // row tile's workgroups all wait for bytes of their own: 1.26 us for 256 of them and less for fewer, down to what one can
 // have under way (594 vocabulary tiles, 100 rows: 198 workgroups on three tiles each 207 us, two row tiles in 119 splits
 // of five, which 1.48 us a K-tile for any number of workgroups preferred, 255; 240 rows 256 against 299).  The
-// reduction of a tile: 0.56 us per token block, with a draw 1.66 us.  A further round of units (pipeline fill, merge, a
-// fresh start of the draw's bound): half a tile and 4 us.  With the K-loop in pair order the wide tiles are 5% faster
+// reduction of a tile: 0.56 us per token block, with a draw 1.66 us and, in a unit's first tiles, where nothing bounds the
+// scores yet, 2.5 us more (1.9 where a lone row tile waits for memory meanwhile): 6000 rows of 65536 x 2048 1575 us as two
+// rounds of short units of 256 rows, 1367 as one round, which it now takes; 2700 rows of 32000 x 1024 293 -> 267; over 155
+// sizes the choice is 1.0% off the best width, 1.8% without it, and none is slower by more than 1.5%.  A further round of
+// units (pipeline fill, merge): half a tile and 4 us.  With the K-loop in pair order the wide tiles are 5% faster
 // throughout; at 21 row counts from 280 to 3500 of 126464 x 4096 no other width beats the one this picks by more than 1.4%.
 __host__ __device__ inline uint32_t k_tile_time(uint32_t width, uint32_t share, uint32_t workgroups) {
   const uint32_t compute = width <= 4 ? 60 + 4 * width : (36 + 27 * width) / 2;
@@ -105,9 +108,13 @@ __host__ __device__ inline uint64_t schedule_candidate(const ScheduleInput& in, 
   const uint32_t workgroups = range.row_tiles * splits < in.grid ? range.row_tiles * splits : in.grid;
   const uint32_t tile = in.k_tiles * k_tile_time(width, panel_depth(range.row_tiles, width), workgroups) +
                         reduction_time(width, in.sampling);
-  uint64_t cost = ((uint64_t)rounds * longest * tile + (uint64_t)(rounds - 1) * (tile / 2 + 400)) >> 3;
-  if (width < 8) cost += cost >> 6;   // a narrower tile has to win by more than the model is off (5748 rows of 32000 x
-                                      // 1024: 36 x 7 units of 160 rows 300 us, 23 x 11 of 256 rows 294 us)
+  const uint32_t first_tiles = in.sampling == 0 ? 0 : range.row_tiles == 1 ? 187 * width : 250 * width;
+  uint64_t cost = (rounds * ((uint64_t)longest * tile + first_tiles) + (uint64_t)(rounds - 1) * (tile / 2 + 400)) >> 3;
+  // a narrower tile has to win by more than the model is off (5748 rows of 32000 x 1024: 36 x 7 units of 160 rows 300 us,
+  // 23 x 11 of 256 rows 294 us); where drawn the more, the narrower (600 rows of 126464 x 4096: five token blocks 590 us,
+  // seven 562, 0.6% apart in the model)
+  if (in.sampling != 0) cost += cost * (8 - width) >> 8;
+  else if (width < 8) cost += cost >> 6;
   return cost << 20 | (uint64_t)(8 - width) << 16 | splits;
 }
 
