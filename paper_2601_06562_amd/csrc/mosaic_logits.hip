@@ -185,17 +185,6 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
   }
 }
 
-// Workgroups are dealt to the 8 XCDs round-robin by id, and the workgroups of one XCD share an L2.  This maps
-// workgroup b of a grid of G to a position such that each XCD's workgroups hold one contiguous range of positions
-// (XCD x owns ceil((G - x) / 8) of them), so that consecutive work units -- which share LM-head and hidden tiles --
-// meet in one L2.  A bijection on [0, G) for any G.
-__device__ __forceinline__ int xcd_contiguous_position(int b, int G) {
-  const int x = b & 7;
-  int first = 0;
-  for (int y = 0; y < x; ++y) first += (G - y + 7) >> 3;
-  return first + (b >> 3);
-}
-
 // Rows of this launch's chunk, and the division of the work for them.
 __device__ __forceinline__ int chunk_rows_found(const KernelParams& p) {
   int total = *p.count;
@@ -441,9 +430,9 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
   const int n_tt = (rows + kTileRows - 1) / kTileRows;   // its row tiles have the one width
 
   const int G = gridDim.x;
-  const int pos = xcd_contiguous_position((int)blockIdx.x, G);
   const int S = ragged_only ? 1 : sched.splits;
   const int n_units = n_tt * S;
+  const int pos = first_unit((int)blockIdx.x, G, n_units);
   const int A = p.panel < n_tt ? p.panel : n_tt;
   const int full_panel_units = A * S;
   const int n_panels = (n_tt + A - 1) / A;
@@ -712,9 +701,9 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const int n_tt = sched.row_tiles;
 
   const int G = gridDim.x;
-  const int pos = xcd_contiguous_position((int)blockIdx.x, G);
   const int S = sched.splits;
   const int n_units = n_tt * S;
+  const int pos = first_unit((int)blockIdx.x, G, n_units);
   const int A = (int)panel_depth((uint32_t)n_tt, NB, (uint32_t)p.panel);
   const int full_panel_units = A * S;
   const int n_panels = (n_tt + A - 1) / A;

@@ -47,6 +47,24 @@ __host__ __device__ inline uint32_t panel_depth(uint32_t row_tiles, uint32_t wid
   return ceil_div(row_tiles, ceil_div(row_tiles, side));
 }
 
+// Workgroups are dealt to the 8 XCDs round-robin by id, and the workgroups of one XCD share an L2.  This maps
+// workgroup b of a grid of G to a position such that each XCD's workgroups hold one contiguous range of positions
+// (XCD x owns ceil((G - x) / 8) of them), so that consecutive work units -- which share LM-head and hidden tiles --
+// meet in one L2.  A bijection on [0, G) for any G.
+__host__ __device__ inline int xcd_contiguous_position(int b, int G) {
+  const int x = b & 7;
+  int first = 0;
+  for (int y = 0; y < x; ++y) first += (G - y + 7) >> 3;
+  return first + (b >> 3);
+}
+
+// The unit with which workgroup b of the grid begins (`units`: it has none).  A grid of more workgroups than units leaves
+// the last ones idle, a few on every XCD: the positions are those of the workgroups that work.
+__host__ __device__ inline int first_unit(int b, int grid, int units) {
+  const int working = grid < units ? grid : units;
+  return b < working ? xcd_contiguous_position(b, working) : units;
+}
+
 // What a unit's parts take, in units of 10 ns, fitted to measurements at widths 1..8 and 32..4096 rows of a 126464 x 4096
 // and a 32000 x 1024 LM head (most within 10%).  A K-tile: bound by the copies into LDS up to four token blocks a wave
 // (0.64 to 0.76 us), by the matrix cores beyond (1.26 us at eight); or by memory, which brings the 32 KiB of LM head

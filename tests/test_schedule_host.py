@@ -1,6 +1,8 @@
 """The division of the work (csrc/mosaic_schedule.h), which host and device evaluate alike, on the CPU: every division has
 room in the partial arrays, for either of the two kernels that may do a launch's work, and the word through which a
-launch tells its division to the ones behind it leads nobody outside, whatever it holds."""
+launch tells its division to the ones behind it leads nobody outside, whatever it holds.  Which unit a workgroup begins with:
+every unit has one workgroup, and the 8 XCDs, to which workgroups are dealt in turn, have equally many units (to one), also
+where the launch has more workgroups than the division has units."""
 import os
 import subprocess
 
@@ -61,14 +63,69 @@ int main() {
 """
 
 
-@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
-def test_divisions_have_room_and_a_foreign_word_leads_nowhere(tmp_path):
+PLACES = r"""
+#include <stdio.h>
+#include <vector>
+#include "mosaic_internal.h"
+#include "mosaic_schedule.h"
+using namespace mosaic;
+int main() {
+  long launches = 0, surplus = 0, bad = 0;
+  auto check = [&](int grid, int units, int V, int rows) {
+    std::vector<int> taken(units < grid ? units : grid), xcd(8);
+    bool ok = true;
+    for (int b = 0; b < grid; ++b) {
+      const int u = first_unit(b, grid, units);
+      if (u < units) ok = ok && u >= 0 && u < (int)taken.size() && ++taken[u] == 1, ++xcd[b % 8];
+    }
+    int least = grid, most = 0;
+    for (int n : xcd) least = n < least ? n : least, most = n > most ? n : most;
+    for (int n : taken) ok = ok && n == 1;
+    ++launches, surplus += grid > units;
+    if (!(ok && most - least <= 1) && ++bad < 10)
+      printf("V %d rows %d: %d units on %d workgroups, %d to %d an XCD\n", V, rows, units, grid, least, most);
+  };
+  for (int grid : {1, 7, 8, 9, 64, 100, 255, 256, 304}) for (int units = 1; units <= 320; ++units) check(grid, units, 0, 0);
+  const int shapes[][2] = {{512, 8192}, {1024, 32000}, {3584, 151936}, {3584, 152064}, {4096, 126464}};
+  for (auto& shape : shapes) for (int max_rows : {32, 100, 256, 700}) for (int sample = 0; sample < 2; ++sample) {
+    mosaic_plan plan;
+    if (mosaic_plan_workspace(4096, max_rows, shape[0], shape[1], 0, 256, sample, &plan) != MOSAIC_OK) return 1;
+    ScheduleInput in{};
+    in.vocab_tiles = (uint32_t)(shape[1] + 255) / 256;
+    in.k_tiles = (uint32_t)shape[0] / 64;
+    in.sampling = (uint32_t)sample;
+    in.grid = (uint32_t)plan.grid;
+    in.slots64 = (uint32_t)((int64_t)plan.vocab_splits * plan.rows_per_chunk / 64);
+    for (uint32_t widths : {0xffu, 0x80u}) for (int rows = 1; rows <= max_rows; ++rows) {
+      in.widths = widths;
+      const Schedule s = choose_schedule(in, rows);
+      check(plan.grid, s.row_tiles * s.splits, shape[1], rows);
+    }
+  }
+  printf("%ld launches, %ld with more workgroups than units, %ld bad\n", launches, surplus, bad);
+  return bad != 0 || surplus == 0;
+}
+"""
+
+
+def build_and_run(tmp_path, program):
     src = tmp_path / "schedule.hip"
-    src.write_text(PROGRAM)
+    src.write_text(program)
     exe = str(tmp_path / "schedule")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-o",
                     exe, str(src), os.path.join(CSRC, "mosaic_plan.cpp")], check=True, stderr=subprocess.DEVNULL)
     res = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=120)
     print(res.stdout)
     assert res.returncode == 0, res.stdout
-    assert int(res.stdout.split(" bad, ")[1].split()[0]) > 0             # else the two kernels are not told apart here
+    return res.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_units_are_spread_over_the_xcds(tmp_path):
+    build_and_run(tmp_path, PLACES)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_divisions_have_room_and_a_foreign_word_leads_nowhere(tmp_path):
+    out = build_and_run(tmp_path, PROGRAM)
+    assert int(out.split(" bad, ")[1].split()[0]) > 0             # else the two kernels are not told apart here
