@@ -8,6 +8,8 @@ import subprocess
 
 import pytest
 
+import test_gpu_streamed_head as streamed_head
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2601_06562_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -107,14 +109,39 @@ int main() {
 }
 """
 
+LONE = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "mosaic_internal.h"
+#include "mosaic_schedule.h"
+using namespace mosaic;
+int main(int argc, char** argv) {
+  for (int a = 1; a + 3 < argc; a += 4) {
+    const int d = atoi(argv[a]), V = atoi(argv[a + 1]), rows = atoi(argv[a + 2]), sample = atoi(argv[a + 3]);
+    mosaic_plan plan;
+    if (mosaic_plan_workspace(rows, rows, d, V, 0, 256, sample, &plan) != MOSAIC_OK) return 1;
+    if (!choose_kernel(rows, d, d, V, plan, sample != 0).fast) return 1;
+    ScheduleInput in{};
+    in.vocab_tiles = (uint32_t)(V + 255) / 256;
+    in.k_tiles = (uint32_t)d / 64;
+    in.widths = 0xff;
+    in.sampling = (uint32_t)sample;
+    in.grid = (uint32_t)plan.grid;
+    in.slots64 = (uint32_t)((int64_t)plan.vocab_splits * plan.rows_per_chunk / 64);
+    const Schedule s = choose_schedule(in, rows);
+    printf("%d %d\n", s.width, s.row_tiles);
+  }
+}
+"""
 
-def build_and_run(tmp_path, program):
+
+def build_and_run(tmp_path, program, *args):
     src = tmp_path / "schedule.hip"
     src.write_text(program)
     exe = str(tmp_path / "schedule")
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O1", "-std=c++17", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-o",
                     exe, str(src), os.path.join(CSRC, "mosaic_plan.cpp")], check=True, stderr=subprocess.DEVNULL)
-    res = subprocess.run([exe], stdout=subprocess.PIPE, text=True, timeout=120)
+    res = subprocess.run([exe, *map(str, args)], stdout=subprocess.PIPE, text=True, timeout=120)
     print(res.stdout)
     assert res.returncode == 0, res.stdout
     return res.stdout
@@ -129,3 +156,21 @@ def test_units_are_spread_over_the_xcds(tmp_path):
 def test_divisions_have_room_and_a_foreign_word_leads_nowhere(tmp_path):
     out = build_and_run(tmp_path, PROGRAM)
     assert int(out.split(" bad, ")[1].split()[0]) > 0             # else the two kernels are not told apart here
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_the_streamed_steps_are_lone_row_tiles_of_every_width(tmp_path):
+    """of tests/test_gpu_streamed_head.py: the nt copies are a lone row tile's, in code of its own per width and draw"""
+    steps = [(d, V, rows, drawn) for (d, V), counts in streamed_head.STEPS.items() for drawn in (0, 1) for rows in counts[drawn]]
+    out = build_and_run(tmp_path, LONE, *[x for step in steps for x in step]).split("\n")
+    found = [tuple(int(x) for x in line.split()) for line in out if line]
+    assert len(found) == len(steps)
+    shared = [s for s, f in zip(steps, found) if f[1] != 1]
+    assert all(d == 1024 and drawn and rows > 224 for d, _, rows, drawn in shared), shared
+    for ragged in (False, True):
+        for drawn in (0, 1):
+            widths = {f[0] for s, f in zip(steps, found) if f[1] == 1 and s[3] == drawn and (s[1] % 256 != 0) == ragged}
+            assert widths == set(range(1, 9)), (ragged, drawn, widths)
+    several = build_and_run(tmp_path, LONE, *[x for (d, V) in streamed_head.STEPS for drawn in (0, 1)
+                                              for x in (d, V, streamed_head.T, drawn)]).split("\n")
+    assert all(int(line.split()[1]) > 1 for line in several if line)     # what they are held against
