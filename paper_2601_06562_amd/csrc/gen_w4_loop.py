@@ -1091,6 +1091,18 @@ def write_statement(f, blocks, sample):
     f.write("    : " + ", ".join(clob) + ");\n}\n")
 
 
+def write_pieces(f):
+    """what the kernel's prologue has to know of the K-loop: the first width in pair order, and that loop's late_pieces"""
+    pieces = [0] * 9
+    for blocks in range(PAIRS_FROM, 9):
+        SHAPE["nb"] = blocks
+        pieces[blocks] = late_pieces()
+    f.write("// GENERATED by gen_w4_loop.py -- do not edit.\n"
+            f"constexpr int kW4PairsFrom = {PAIRS_FROM};\n"
+            f"constexpr int w4_late_pieces(int nb) {{\n  constexpr int pieces[9] = {{{', '.join(map(str, pieces))}}};\n"
+            "  return pieces[nb];\n}\n")
+
+
 def main(folder):
     for name, sample in (("mosaic_w4_tile.inc", False), ("mosaic_w4_tile_sample.inc", True)):
         with open(os.path.join(folder, name), "w") as f:
@@ -1099,12 +1111,7 @@ def main(folder):
             for blocks in range(1, 9):
                 write_statement(f, blocks, sample)
     with open(os.path.join(folder, "mosaic_w4_pieces.inc"), "w") as f:
-        f.write("// GENERATED by gen_w4_loop.py -- do not edit.\n"
-                "constexpr int w4_late_pieces(int nb) {\n  constexpr int pieces[9] = {0, 0, 0, 0, 0")
-        for blocks in range(PAIRS_FROM, 9):
-            SHAPE["nb"] = blocks
-            f.write(f", {late_pieces()}")
-        f.write("};\n  return pieces[nb];\n}\n")
+        write_pieces(f)
     SHAPE["pairs"] = False
     lines.clear()
     build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers

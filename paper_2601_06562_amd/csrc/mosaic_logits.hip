@@ -647,11 +647,14 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 // ---- 4-wave fast path: one wave per SIMD, 128 (vocab) x 16*NB (token) per wave as 8 x NB blocks of
 // v_mfma_f32_16x16x32_bf16 (the more power-efficient bf16 shape on this part), accumulators in AGPRs.
 // A vocabulary tile is one hand-scheduled inline-asm statement (mosaic_w4_tile.inc greedy, mosaic_w4_tile_sample.inc
-// sampling; both generated): the K-loop, then the tile's reduction to a triple per column.  In the K-loop
-// every MFMA is followed by at most one LDS read or one direct-to-LDS copy, fragments are double-
-// buffered in fixed VGPRs, the LM-head ring runs two K-tiles ahead and the hidden ring one (three and two at NB <= 2).
-// From NB = 5 on, where the matrix cores under the power cap are the bound, the two K-halves of a block's products go back
-// to back, which costs the least energy (the generator says how): 4096 rows 2641 -> 2535 us.
+// sampling; both generated): the K-loop, then the tile's reduction to a triple per column.  Up to NB = 4 the LDS reads,
+// direct-to-LDS copies and scalars are spread evenly behind the MFMAs (two instructions each at NB = 3 and 4, up to six at
+// NB = 1, which waits for memory), fragments are double-buffered in fixed VGPRs, the LM-head ring runs two K-tiles ahead
+// and the hidden ring one (three and two at NB <= 2).
+// From NB = 5 on (kW4PairsFrom), where the matrix cores under the power cap are the bound, the two K-halves of a block's
+// products go back to back, which costs the least energy (the generator says how; the waves that copy vocabulary blocks 0..3
+// of a half run three K-tiles ahead there, and at NB = 7 and 8 not all token fragments have two buffers): 4096 rows
+// 2641 -> 2535 us.
 // NB sets the width of the row tile, 32*NB tokens.  The widest, 256, has the fewest LDS and L2 bytes per product and is
 // the one for many rows; a list that does not fill its last row tile takes the width that pads it least
 // (mosaic_schedule.h): 280 rows as two tiles of 160 take 290 us, as two of 256 383 us; 32 rows
@@ -675,7 +678,7 @@ constexpr int kLdsBytes = 160 * 1024;
 template <bool SAMPLE, int NB, bool STREAM>
 __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, char* smem) {
   constexpr int kDepth = NB <= 2 ? 3 : 2;            // K-tiles under way, as the generator's depth()
-  constexpr bool kPairs = NB >= 5;                   // the K-loop in pair order, as the generator's PAIRS_FROM
+  constexpr bool kPairs = NB >= kW4PairsFrom;        // the K-loop in pair order
   constexpr int kLatePieces = w4_late_pieces(NB);    // of eight LM-head copies, those a step issues behind its sync
   constexpr int NW = kDepth + 1, NH = kDepth;
   constexpr int kHiddenSlot = 32 * NB * kRowBytes;

@@ -6,7 +6,9 @@ and a hidden slot, filled by all.  A copy may only go to a region that no wave h
 readable again once every wave that fills it has waited for its copies (vmcnt, in issue order) and met the others at a
 barrier.  A fragment is usable once an lgkmcnt wait covers its read (in issue order).  Every product must find the
 vocabulary block, token block, K-tile and K-half it stands for, first half then second half of a block."""
+import os
 import re
+import subprocess
 
 import pytest
 
@@ -293,3 +295,22 @@ def test_steady_steps_keep_every_gap_short(nb):
         else:
             gap += 1
     assert longest <= 4, longest
+
+
+def test_the_kernel_learns_the_first_width_in_pair_order(tmp_path, monkeypatch):
+    """The rings' prologue is the kernel's, the loop the generator's: from which width on, and how many of a step's copies
+    follow its sync, is written once and read from the generated header, whatever the first width is."""
+    for first in (gen.PAIRS_FROM, 6):
+        monkeypatch.setattr(gen, "PAIRS_FROM", first)
+        with open(tmp_path / "pieces.inc", "w") as f:
+            gen.write_pieces(f)
+        late = {}
+        for nb in range(first, 9):
+            gen.SHAPE["nb"] = nb
+            late[nb] = gen.late_pieces()
+        gen.SHAPE["nb"] = 8
+        checks = "".join(f"static_assert(w4_late_pieces({nb}) == {late.get(nb, 0)}, \"\");\n" for nb in range(1, 9))
+        (tmp_path / "check.cpp").write_text(f'#include "pieces.inc"\nstatic_assert(kW4PairsFrom == {first}, "");\n{checks}')
+        subprocess.run(["g++", "-std=c++17", "-fsyntax-only", str(tmp_path / "check.cpp")], check=True)
+    kernel = open(os.path.join(os.path.dirname(protocol.GEN), "mosaic_logits.hip")).read()
+    assert "kPairs = NB >= kW4PairsFrom;" in kernel
