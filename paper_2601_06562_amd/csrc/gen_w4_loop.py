@@ -20,10 +20,12 @@ import os
 import re
 import sys
 
-# fragment double buffer (2 x 16 tuples of 4 VGPRs) and two address temporaries.  Operand names here; the statements
-# that are built in name the fragments by number (frag_names_literal), so that the reduction can reuse them
-FA = [[f"%[fa{b}{i}]" for i in range(8)] for b in range(2)]
-FB = [[f"%[fb{b}{j}]" for j in range(8)] for b in range(2)]
+# Fragments by number: v[112:239].  The reduction's 32 logits and its temporaries alias the first of them, so that the
+# compiler keeps 128 registers for what lives across a tile (with both as operands it spills).
+FRAG_BASE = 112
+# Up to four token blocks: a double buffer of 16 tuples, the LM head's eight first
+FA = [[f"v[{FRAG_BASE + (b * 16 + i) * 4}:{FRAG_BASE + (b * 16 + i) * 4 + 3}]" for i in range(8)] for b in range(2)]
+FB = [[f"v[{FRAG_BASE + (b * 16 + 8 + j) * 4}:{FRAG_BASE + (b * 16 + 8 + j) * 4 + 3}]" for j in range(8)] for b in range(2)]
 VT0, VT1 = "%[vt0]", "%[vt1]"
 VW, VH = ("%[vt0]", "%[vt2]"), ("%[vt1]", "%[vt3]")     # pair order: addresses of an LM-head and a hidden row, per K-half
 WSRC, HSRC = "s[96:97]", "s[98:99]"
@@ -32,13 +34,17 @@ NK128 = "s94"
 
 lines = []
 uid = [0]
+PAIRS_FROM = 5            # token blocks from which on the K-loop is in pair order (build_pairs)
 SHAPE = {"nb": 8,         # token blocks of 16 per wave
-         "pairs": False,  # the K-loop in pair order (write_statement: from PAIRS_FROM on)
          "tight": True}   # sampling: a quad that passes the column's bound is held against its own (off: for comparison)
 
 
 def nb():
     return SHAPE["nb"]
+
+
+def pairs():
+    return nb() >= PAIRS_FROM
 
 
 def depth():
@@ -66,26 +72,18 @@ def label(name):
     return f"L{name}{uid[0]}_%="
 
 
-# Accumulators: operands of the statement ("+a", for the kernel whose epilogue is C++), or, when the statement
-# reduces the tile itself, the AGPR file by number: block (bi, bj) = a[(bi*8 + bj)*4 .. +3].
-LITERAL_ACC = [False]
-
-
+# Accumulators, the AGPR file by number: block (bi, bj) = a[(bi*nb + bj)*4 .. +3].
 def acc_block(bi, bj):
-    if LITERAL_ACC[0]:
-        base = (bi * nb() + bj) * 4
-        return f"a[{base}:{base + 3}]"
-    return f"%[a{bi}{bj}]"
+    base = (bi * nb() + bj) * 4
+    return f"a[{base}:{base + 3}]"
 
 
 def acc_reg(bi, bj, r):
     return f"a{(bi * nb() + bj) * 4 + r}"
 
 
-def mfma(bi, bj, buf, zero_c=False):
-    """acc += A * B, or acc = A * B (the first product of a tile: no clearing of the accumulator beforehand)"""
-    c = "0" if zero_c else acc_block(bi, bj)
-    e(f"v_mfma_f32_16x16x32_bf16 {acc_block(bi, bj)}, {FA[buf][bi]}, {FB[buf][bj]}, {c}")
+def mfma(bi, bj, buf):
+    e(f"v_mfma_f32_16x16x32_bf16 {acc_block(bi, bj)}, {FA[buf][bi]}, {FB[buf][bj]}, {acc_block(bi, bj)}")
 
 
 def read_addr(ks):
@@ -197,17 +195,8 @@ def cond_plus(plus):
     e("s_cmp_lt_u32 vcc_lo, %[total]")
 
 
-# The widest tile: copy i goes out after MFMA COPY_POS[i] of its group: early in the group, so a copy has the longest
-# possible time to land before the sync that publishes it, and four MFMAs apart, so the 16 KiB a workgroup
-# requests per position never queue up behind the texture addresser (denser or later placement measured slower).
-COPY_POS = [1, 5, 9, 13, 17, 21, 25, 29]
-
-
 def copy_pos(copies):
-    """positions of a group's copies: COPY_POS in the widest tile, else spread over the group's first half or, where
-    that is too short, over all of it"""
-    if nb() == 8:
-        return COPY_POS
+    """positions of a group's copies: spread over the group's first half or, where that is too short, over all of it"""
     n = 8 * nb()
     step = max(1, n // 2 // copies)
     return [min(1, n - copies) + i * step for i in range(copies)]
@@ -222,22 +211,13 @@ def read_pos(rd):
     return at
 
 
-def spread(fill, first, ops, per_gap=2):
-    """book-keeping instructions `ops`, `per_gap` at a time, into the gaps after MFMA first, first + 1, ..."""
-    k = first
-    for i in range(0, len(ops), per_gap):
-        fill.setdefault(k, []).extend(ops[i:i + per_gap])
-        k += 1
-    return k
-
-
-def scheduled_group(buf, fill, zero_c=False):
+def scheduled_group(buf, fill):
     """8*nb MFMAs on fragment buffer `buf`; fill[k] = the instructions that follow MFMA k.  A wave is alone on its
     SIMD and issues one instruction every few cycles, so whatever sits between two MFMAs beyond ~3 instructions
     delays the second one: the steady state keeps the gaps as short as the group's length allows."""
     order = [(bi, bj) for bi in range(8) for bj in range(nb())]
     for k in range(8 * nb()):
-        mfma(*order[k], buf, zero_c)
+        mfma(*order[k], buf)
         for x in fill.get(k, []):
             e(x)
 
@@ -303,20 +283,7 @@ def steady_fill(buf):
     last = ["s_add_u32 vcc_lo, %[g], " + str(depth()), "s_cmp_lt_u32 vcc_lo, %[total]",
             "s_cselect_b32 vcc_lo, %[nk], 0", f"s_cmp_lt_u32 {KT}, vcc_lo"] if buf == 1 else []
     fill = {}
-    if nb() == 8:
-        # the 16 reads after the even MFMAs of the first half, the copies after every fourth MFMA of that half, the
-        # book-keeping two instructions at a time over the second half
-        for k in range(0, 32, 2):
-            fill.setdefault(k, []).append(rd[k // 2])
-        for (setup, load), k in zip(split, COPY_POS):
-            fill.setdefault(k - 1, []).append(setup)
-            fill.setdefault(k, []).append(load)
-        k = spread(fill, 33, ops[0])
-        k = spread(fill, k + 1, ops[1])
-        spread(fill, k + 1, ops[2])
-        spread(fill, 60, last)
-        return fill
-    # a shorter group: the same sequence, evenly over its gaps; a read sits between a copy's M0 write and its load
+    # evenly over the gaps; a read sits between a copy's M0 write and its load
     seq = []
     for i, x in enumerate(rd):
         seq += [split[i][0], x, split[i][1]] if i < copies else [x]
@@ -336,9 +303,6 @@ def step_end(top):
 
 LOG2E = 0x3FB8AA3B        # fp32 1.4426950408889634
 NEG_LOG2E = 0xBFB8AA3B
-# Fragments by number: v[112:239].  The reduction's 32 logits and its temporaries alias the first of them, so that the
-# compiler keeps 128 registers for what lives across a tile (with both as operands it spills).
-FRAG_BASE = 112
 X = [f"v{FRAG_BASE + i}" for i in range(32)]
 ET, _, ENML, EY, ESEL = (f"v{FRAG_BASE + 32 + k}" for k in range(5))
 MASK = ["s[88:89]", "s[90:91]", "s[92:93]"]
@@ -422,13 +386,6 @@ SAMPLE_TEMPS.update(best="v180", wq="v181")
 KEY0_BASE, KEY1_BASE = 68, 78
 SAMPLE_TEMPS.update({f"k0_{r}": f"s{KEY0_BASE + r}" for r in range(10)})
 SAMPLE_TEMPS.update({f"k1_{r}": f"s{KEY1_BASE + r}" for r in range(10)})
-
-
-def frag_names_literal():
-    fa = [[f"v[{FRAG_BASE + (b * 16 + i) * 4}:{FRAG_BASE + (b * 16 + i) * 4 + 3}]" for i in range(8)] for b in range(2)]
-    fb = [[f"v[{FRAG_BASE + (b * 16 + 8 + j) * 4}:{FRAG_BASE + (b * 16 + 8 + j) * 4 + 3}]" for j in range(8)]
-          for b in range(2)]
-    return fa, fb
 
 
 def philox_quad(tb, bi, XS):
@@ -651,10 +608,10 @@ def reduce_column_sample(tb):
 
 
 def build_tile_sample():
-    """The statement of the sampling kernel: K-loop on fragments and accumulators named by number, then the
+    """The statement of the sampling kernel: the K-loop, then the
     reduction with the noise; the rare exact paths sit behind the end of the statement."""
     slow_blocks.clear()
-    build_literal()
+    build_loop()
     e(f"s_mov_b32 %[k0_0], %[seed_lo]")                              # key of round r = seed + r * (golden-ratio words)
     e(f"s_mov_b32 %[k1_0], %[seed_hi]")
     for r in range(1, 10):
@@ -684,7 +641,7 @@ def build_tile_sample():
 def build_tile():
     """The statement of the greedy kernel: the K-loop on accumulators it starts itself, then the reduction of the
     tile."""
-    build_literal()
+    build_loop()
     for tb in range(nb()):
         reduce_column(tb)
 
@@ -710,17 +667,9 @@ def mask_counted():
     e(f"{skip}:")
 
 
-def build_literal():
-    """The K-loop on fragments and accumulators named by number."""
-    saved = ([row[:] for row in FA], [row[:] for row in FB])
-    fa, fb = frag_names_literal()
-    for b in range(2):
-        FA[b][:], FB[b][:] = fa[b], fb[b]
-    LITERAL_ACC[0] = True
-    build_pairs() if SHAPE["pairs"] else build()
-    LITERAL_ACC[0] = False
-    for b in range(2):
-        FA[b][:], FB[b][:] = saved[0][b], saved[1][b]
+def build_loop():
+    """The width's K-loop, and what of its tile is not counted."""
+    build_pairs() if pairs() else build()
     mask_counted()
 
 
@@ -735,11 +684,10 @@ def build():
     read_addr(0)
     for r in reads(0):
         e(r)
-    if LITERAL_ACC[0]:
-        # the statement owns the accumulators: clear them while the first fragments are on their way (measured:
-        # writing a tile's first products without an addend instead saves nothing)
-        for i in range(32 * nb()):
-            e(f"v_accvgpr_write_b32 a{i}, 0")
+    # the statement owns the accumulators: clear them while the first fragments are on their way (measured: writing a
+    # tile's first products without an addend instead saves nothing)
+    for i in range(32 * nb()):
+        e(f"v_accvgpr_write_b32 a{i}, 0")
     e("s_nop 7")
     top, steady, generic, out = label("top"), label("steady"), label("generic"), label("out")
     e(f"{top}:")
@@ -815,9 +763,8 @@ def build():
 # again, of the hidden rows what lies at the front of them.  A guarded form of the steps would be code that runs cold, a
 # few steps a unit (measured: 0.3% slower).
 #
-# 4096 x 126464 x 4096: 2641 -> 2535 us, 2077 rows (width 5) 1484 -> 1411, 58524 rows 39.7 -> 37.3 ms (one box each, in
+# 4096 x 126464 x 4096: 2641 -> 2535 us, 2077 rows (width 6) 1484 -> 1411, 58524 rows 39.7 -> 37.3 ms (one box each, in
 # turn with the other loop).
-PAIRS_FROM = 5
 X_PAIRS = 12
 Y_RING = 4
 
@@ -1040,7 +987,7 @@ def build_pairs():
 
 
 def write_statement(f, blocks, sample):
-    SHAPE.update(nb=blocks, pairs=blocks >= PAIRS_FROM)
+    SHAPE["nb"] = blocks
     lines.clear()
     uid[0] = 2000 if sample else 1000
     if sample:
@@ -1059,10 +1006,10 @@ def write_statement(f, blocks, sample):
     outs.append('[vt0] "=&v"(addr_tmp0)')
     outs.append('[vt1] "=&v"(addr_tmp1)')
     ins = []
-    if SHAPE["pairs"]:
+    if pairs():
         outs += ['[vt2] "=&v"(addr_tmp2)', '[vt3] "=&v"(addr_tmp3)']
         ins.append('[wnext] "s"(st_wnext)')
-    for k in range(1 if SHAPE["pairs"] else 2):
+    for k in range(1 if pairs() else 2):
         ins.append(f'[rdw{k}] "v"(rdw[{k}])')
         ins.append(f'[rdh{k}] "v"(rdh[{k}])')
     for i in range(8):
@@ -1112,9 +1059,6 @@ def main(folder):
                 write_statement(f, blocks, sample)
     with open(os.path.join(folder, "mosaic_w4_pieces.inc"), "w") as f:
         write_pieces(f)
-    SHAPE["pairs"] = False
-    lines.clear()
-    build()          # leave the bare K-loop listing of the widest tile (accumulators as operands) for importers
 
 
 if __name__ == "__main__":

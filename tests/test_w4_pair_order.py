@@ -13,11 +13,8 @@ import subprocess
 import pytest
 
 import test_w4_loop_protocol as protocol
-from test_w4_loop_protocol import H_BASE, MASK32, W_BASE
+from test_w4_loop_protocol import H_BASE, MASK32, W_BASE, gen
 
-spec = protocol.importlib.util.spec_from_file_location("gen_w4_loop", protocol.GEN)
-gen = protocol.importlib.util.module_from_spec(spec)
-spec.loader.exec_module(gen)
 WIDTHS = range(gen.PAIRS_FROM, 9)
 LATE = {}
 for width in WIDTHS:
@@ -26,14 +23,7 @@ for width in WIDTHS:
 
 
 def listing(nb, sample=False):
-    gen.SHAPE.update(nb=nb, pairs=True)
-    gen.lines.clear()
-    gen.uid[0] = 0
-    gen.build_tile_sample() if sample else gen.build_tile()
-    out = [ln.strip() for ln in gen.lines]
-    gen.lines.clear()
-    gen.SHAPE.update(nb=8, pairs=False)
-    return out[:out.index("s_cmp_eq_u32 %[first], 0")]
+    return protocol.listing(nb, sample)[0]
 
 
 class Lds:
@@ -56,16 +46,10 @@ class PairWave(protocol.Sim):
     """One wave's stream up to its next barrier at a time (the base class's instruction set, its own events)."""
 
     def __init__(self, lines, nb, nk, ntile, ragged_rows, odd, lds):
-        super().__init__(lines, nk, ntile)
-        self.nb, self.odd, self.lds, self.ragged_rows = nb, odd, lds, ragged_rows
+        super().__init__(lines, nb, nk, ntile, ragged_rows)
+        self.odd, self.lds = odd, lds
         self.lgkm, self.frags, self.used, self.copied = [], {}, {}, {"W": 0, "H": 0}
         self.n, self.blocks = 0, set()
-
-    def wptr(self, g):
-        rows = g // self.nk * 256
-        if self.ragged_rows and g // self.nk == self.ntile - 1 > 0:
-            rows += self.ragged_rows - 256
-        return W_BASE + rows * self.nk * 128 + g % self.nk * 128
 
     def w_region(self, slot):
         return ("W", slot, "hi" if self.odd else "lo")

@@ -1,159 +1,13 @@
-"""The generated statements of every width of the row tile (32 to 256 tokens), on the CPU: the K-loop of each under the
-ring protocol of test_w4_loop_protocol.py (its interpreter, with this width's ring geometry); the reduction of each
+"""The generated statements of every width of the row tile (32 to 256 tokens), on the CPU: the reduction of each
 against the definition of the triples it yields, the ragged last tile's included, and, instruction by instruction,
 against the widest tile's on this width's accumulators.  The sampling reduction with a quad's own bound draws what it
-draws without, and leaves few quads to the exact path."""
+draws without, and leaves few quads to the exact path.  (The K-loops: test_w4_loop_protocol.py, test_w4_pair_order.py.)"""
 import re
-from fractions import Fraction
 
 import numpy as np
 import pytest
 
-import test_w4_loop_protocol as protocol
-from test_w4_loop_protocol import H_BASE, MASK32, W_BASE
-
-spec = protocol.importlib.util.spec_from_file_location("gen_w4_loop", protocol.GEN)
-gen = protocol.importlib.util.module_from_spec(spec)
-spec.loader.exec_module(gen)
-
-
-def listing(nb, sample):
-    """The K-loop, the ragged tile's part and the reduction of a width's statement."""
-    gen.SHAPE["nb"] = nb
-    gen.lines.clear()
-    gen.uid[0] = 0
-    gen.build_tile_sample() if sample else gen.build_tile()
-    out = [ln.strip() for ln in gen.lines]
-    gen.lines.clear()
-    cut = out.index("s_cmp_eq_u32 %[first], 0")
-    end = next(i for i in range(cut, len(out)) if out[i].startswith("Lwhole")) + 1
-    return out[:cut], out[cut:end], out[end:]
-
-
-class Sim(protocol.Sim):
-    """The interpreter with this width's rings: its LM-head slots of 32 KiB, then its hidden slots of 4*nb KiB.
-    A width's 8*nb MFMAs per group count as the 64 of the widest tile."""
-
-    def __init__(self, lines, nb, nk, ntile, ragged_rows=0):
-        super().__init__(lines, nk, ntile)
-        self.ragged_rows = ragged_rows           # rows from the last tile but one to the last one, 0: 256 as elsewhere
-        self.nb, self.nw, self.nh = nb, gen.depth() + 1, gen.depth()
-        assert (self.nw * 0x8000 + self.nh * nb * 0x1000) <= 160 * 1024
-        self.mfma_count = Fraction(0)
-
-    def slot_of(self, addr):
-        ring = self.nw * 0x8000
-        slot = addr // 0x8000 if addr < ring else self.nw + (addr - ring) // (self.nb * 0x1000)
-        assert slot < self.nw + self.nh
-        return slot
-
-    def offset_in(self, addr):
-        ring = self.nw * 0x8000
-        return addr % 0x8000 if addr < ring else (addr - ring) % (self.nb * 0x1000)
-
-    def copy(self, operand):
-        m0 = self.reg["m0"]
-        slot = self.slot_of(m0)
-        parts = self.copy_parts.get(slot, 0)
-        if operand == "W":
-            ident = self.next_w_copy
-            assert (self.reg["s96"] | self.reg["s97"] << 32) == self.wptr(ident) and ident < self.total
-            assert slot == ident % self.nw
-        else:
-            off = (self.reg["s98"] | self.reg["s99"] << 32) - H_BASE
-            ident = off // 128
-            assert off % 128 == 0 and 0 <= ident < self.nk and slot >= self.nw
-            assert ident == self.next_h_copy % self.nk and self.next_h_copy < self.total
-            assert slot - self.nw == self.next_h_copy % self.nh
-        assert slot not in self.reads_this_interval, f"copy into slot {slot} that a wave may still be reading"
-        if parts == 0:
-            assert slot not in self.unpublished
-            self.unpublished[slot] = ident
-            self.copies_this_interval.add(slot)
-        assert self.unpublished[slot] == ident and self.offset_in(m0) == 1024 * parts
-        self.vm_queue.append(slot)
-        self.copy_parts[slot] = (parts + 1) % (8 if operand == "W" else self.nb)
-        if self.copy_parts[slot] == 0:
-            if operand == "W":
-                self.next_w_copy += 1
-            else:
-                self.next_h_copy += 1
-
-    def ds_read(self, dst, addr_reg, offset):
-        base = self.reg[addr_reg]
-        slot = self.slot_of(base + offset)
-        operand = "W" if slot < self.nw else "H"
-        assert self.slot_of(base) == slot and (operand == "W") == (addr_reg == "%[vt0]")
-        first = int(re.fullmatch(r"v\[(\d+):\d+\]", dst).group(1))
-        n = (first - 112) // 4 % 16
-        assert n == offset // 2048 + (0 if operand == "W" else 8)
-        assert slot not in self.unpublished and slot in self.published and slot not in self.copies_this_interval
-        self.reads_this_interval.add(slot)
-        group = self.mfma_count // 64
-        assert self.frag_last_group.get(dst, -1) < group or self.mfma_count % 64 == 0
-        self.frag[dst] = (operand, self.published[slot], 1 if self.offset_in(base) % 128 == 64 else 0, False)
-
-    def mfma(self, a, b, dst=None, src_c=None):
-        super().mfma(a, b, dst, src_c)
-        self.mfma_count += Fraction(8, self.nb) - 1
-
-    def wptr(self, g):
-        tile = g // self.nk
-        rows = tile * 256
-        if self.ragged_rows and tile == self.ntile - 1 and tile > 0:
-            rows += self.ragged_rows - 256
-        return W_BASE + rows * (self.nk * 128) + (g % self.nk) * 128
-
-    def run_tiles(self):
-        for n in range(self.ntile):              # the kernel hands every statement its step into the next tile
-            rows = self.ragged_rows if self.ragged_rows and n + 2 == self.ntile else 256
-            self.reg["%[wwrap]"] = (rows * self.nk * 128 - (self.nk - 1) * 128) & MASK32
-            self.run_statement()
-
-    def prologue(self):
-        NW, NH, wptr = self.nw, self.nh, self.wptr
-        self.published[0] = 0
-        self.published[self.nw] = 0
-        for g in range(1, min(NW, self.total)):              # as the kernel issues them
-            self.unpublished[g] = g
-            self.vm_queue += [g] * 8
-        for g in range(1, min(NH, self.total)):
-            self.unpublished[NW + g] = g % self.nk
-            self.vm_queue += [NW + g] * self.nb
-        self.next_w_copy, self.next_h_copy = NW, NH
-        w, h = wptr(NW), H_BASE + (NH % self.nk) * 128
-        self.reg.update({
-            "%[wsrc_lo]": w & MASK32, "%[wsrc_hi]": w >> 32, "%[hsrc_lo]": h & MASK32, "%[hsrc_hi]": h >> 32,
-            "%[wrd]": 0, "%[hrd]": 0, "%[wdst]": 0, "%[hdst]": 0, "%[wk]": NW % self.nk, "%[hk]": NH % self.nk,
-            "%[g]": 0, "%[total]": self.total, "%[nk]": self.nk,
-            "%[hwrap]": (self.nk - 1) * 128,
-            "%[rdw0]": 0, "%[rdw1]": 64, "%[rdh0]": self.nw * 0x8000, "%[rdh1]": self.nw * 0x8000 + 64,
-        })
-
-
-@pytest.mark.parametrize("sample", [False, True])
-@pytest.mark.parametrize("nb", range(1, 9))
-def test_ring_protocol_of_every_width(nb, sample):
-    loop, _, _ = listing(nb, sample)
-    for nk, ntile, ragged in [(1, 1, 0), (1, 5, 0), (2, 3, 0), (3, 1, 0), (3, 4, 0), (4, 2, 0), (5, 31, 0), (8, 2, 0),
-                              (56, 2, 0), (64, 1, 0), (5, 1, 7), (5, 2, 1), (5, 4, 255), (6, 3, 128), (9, 2, 77)]:
-        sim = Sim(loop, nb, nk, ntile, ragged)
-        sim.prologue()
-        sim.run_tiles()
-        total = nk * ntile
-        assert sim.mfma_count == 128 * total and sim.reg["%[g]"] == total
-        assert sim.started == set(range(32 * nb))
-        assert sim.next_w_copy == max(total, sim.nw) and sim.next_h_copy == max(total, sim.nh)
-        assert not sim.unpublished
-
-
-@pytest.mark.parametrize("nb", range(1, 8))
-def test_a_missing_wait_is_caught_at_every_width(nb):
-    loop, _, _ = listing(nb, False)
-    sim = Sim([ln for ln in loop if not ln.startswith("s_waitcnt vmcnt")], nb, 5, 3)
-    sim.prologue()
-    with pytest.raises(AssertionError):
-        sim.run_tiles()
+from test_w4_loop_protocol import gen, listing
 
 
 @pytest.mark.parametrize("nb", range(1, 9))
