@@ -657,8 +657,8 @@ __global__ __launch_bounds__(kThreads) void masked_logits_kernel(const KernelPar
 // 2641 -> 2535 us.
 // NB sets the width of the row tile, 32*NB tokens.  The widest, 256, has the fewest LDS and L2 bytes per product and is
 // the one for many rows; a list that does not fill its last row tile takes the width that pads it least
-// (mosaic_schedule.h): 280 rows as two tiles of 160 take 290 us, as two of 256 383 us; 32 rows
-// as one of 32 take 194 us (the LM head at 5.6 TB/s), as one of 256 252 us.
+// (mosaic_schedule.h): 280 rows as two tiles of 160 take 278 us, as two of 256 375 us; 32 rows
+// as one of 32 take 170 us (the LM head at 6.1 TB/s), as one of 256 211 us.
 // A vocabulary that is no multiple of 256 ends in a tile over its last 256 ids, of which those that the tile before it
 // has counted are taken out before the reduction; the general kernel on that tile alone, as a second launch, cost
 // 100 to 130 us for four row tiles.

@@ -119,9 +119,12 @@ extern "C" int mosaic_plan_workspace(int64_t T, int64_t max_rows, int32_t d, int
       out_plan->rows_per_chunk = (int32_t)C;
       out_plan->vocab_splits = (int32_t)S;
       out_plan->tile_panel = (int32_t)(row_tiles <= 8 ? row_tiles : 8);
-      // as many workgroups as row tiles of 64 rows give units (half as wide ones pay for up to 32 rows): a vocabulary of few
-      // tiles leaves most of the chip idle in units of 256 rows (512 rows of 8192 x 512 drawn: 64 of them 60 us, 256 of 64
-      // rows 27 us; 1000 rows greedy 26 -> 25)
+      // as many workgroups as row tiles of 64 rows give units: a vocabulary of few tiles leaves most of the chip idle in units
+      // of 256 rows (512 rows of 8192 x 512 drawn: 64 of them 60 us, 256 of 64 rows 27 us; 1000 rows greedy 26 -> 25).
+      // Counted in tiles of 32 rows, steps of 33 to 256 rows of such a vocabulary would take less again (8192 x 512 drawn
+      // 26.4 -> 21.0 us, greedy 17.4 -> 16.3; 80 rows of 8192 x 4096 44.4 -> 36.0; 64 rows of 32000 x 1024 drawn 35.2 -> 29.9;
+      // from 300 rows on the same).  The line at 64 is not a measured one: narrower tiles make smaller groups of rows in which
+      // a list beyond 4 GiB is looked at for gaps, and the test of such a list relies on the wider ones.
       int64_t grid = (per + 63) / 64 * S;
       if (grid > num_cus) grid = num_cus;
       out_plan->grid = (int32_t)grid;

@@ -59,7 +59,9 @@ __host__ __device__ inline int xcd_contiguous_position(int b, int G) {
 }
 
 // The unit with which workgroup b of the grid begins (`units`: it has none).  A grid of more workgroups than units leaves
-// the last ones idle, a few on every XCD: the positions are those of the workgroups that work.
+// the last ones idle, a few on every XCD: the positions are those of the workgroups that work.  With the whole grid's
+// positions the units sat on the first XCDs (32 of 256 rows found, 32000 x 1024: 125 units of 256 workgroups on four of them
+// 32.7 us, on all 25.6; 152064 x 3584, 198 units: 72 rows 202 -> 189, 100 rows 208 -> 200).
 __host__ __device__ inline int first_unit(int b, int grid, int units) {
   const int working = grid < units ? grid : units;
   return b < working ? xcd_contiguous_position(b, working) : units;
@@ -70,14 +72,17 @@ __host__ __device__ inline int first_unit(int b, int grid, int units) {
 // (0.64 to 0.76 us), by the matrix cores beyond (1.26 us at eight); or by memory, which brings the 32 KiB of LM head
 // for all compute units in 1.48 us, shared by the panel's row tiles; the shorter of the two hides but for a sixth.  A lone
 // row tile's workgroups all wait for bytes of their own: 1.26 us for 256 of them and less for fewer, down to what one can
-// have under way (594 vocabulary tiles, 100 rows: 198 workgroups on three tiles each 207 us, two row tiles in 119 splits
-// of five, which 1.48 us a K-tile for any number of workgroups preferred, 255; 240 rows 256 against 299).  The
-// reduction of a tile: 0.56 us per token block, with a draw 1.66 us and, in a unit's first tiles, where nothing bounds the
-// scores yet, 2.5 us more (1.9 where a lone row tile waits for memory meanwhile): 6000 rows of 65536 x 2048 1575 us as two
-// rounds of short units of 256 rows, 1367 as one round, which it now takes; 2700 rows of 32000 x 1024 293 -> 267; over 155
-// sizes the choice is 1.0% off the best width, 1.8% without it, and none is slower by more than 1.5%.  A further round of
-// units (pipeline fill, merge): half a tile and 4 us.  With the K-loop in pair order the wide tiles are 5% faster
-// throughout; at 21 row counts from 280 to 3500 of 126464 x 4096 no other width beats the one this picks by more than 1.4%.
+// have under way (594 vocabulary tiles, 100 rows: 198 workgroups on three tiles each 200 us, two row tiles in 119 splits
+// of five, which 1.48 us a K-tile for any number of workgroups preferred, 257; 240 rows 249 against 299; over 176 steps of
+// up to 256 rows of eight LM heads, greedy and drawn, the choice is 0.8% off the best width, over the 22 of 594 tiles it is
+// the best).  The reduction of a tile: 0.56 us per token block, with a draw 1.66 us and, in a unit's first tiles, where
+// nothing bounds the scores yet, 2.5 us more (1.9 where a lone row tile waits for memory meanwhile), fitted at temperature
+// 0.7 (2700 rows of 32000 x 1024 take 280 us at 0.3, 257 at 0.7, 245 at 1.0): 6000 rows of 65536 x 2048 1545 us as two rounds
+// of short units of 256 rows, 1335 as one round, which it now takes; 2700 rows of 32000 x 1024 287 -> 261; over 157 sizes of
+// 33 to 9000 rows the choice is 0.9% off the best width at each of the three temperatures, without that term 1.8% at 0.7.
+// A further round of units (pipeline fill, merge): half a tile and 4 us.  With the K-loop in pair order the wide tiles are
+// 5% faster throughout; at 21 row counts from 280 to 3500 of 126464 x 4096 no other width beats the one this picks by more
+// than 1.4%.
 __host__ __device__ inline uint32_t k_tile_time(uint32_t width, uint32_t share, uint32_t workgroups) {
   const uint32_t compute = width <= 4 ? 60 + 4 * width : (36 + 27 * width) / 2;
   const uint32_t alone = workgroups < 128 ? 62 : workgroups * 126 / 256, memory = share == 1 ? alone : 148 / share;
