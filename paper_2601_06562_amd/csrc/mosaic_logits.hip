@@ -676,7 +676,7 @@ constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
 constexpr int kLdsBytes = 160 * 1024;
 #include "mosaic_w4_pieces.inc"
 template <bool SAMPLE, int NB, bool STREAM>
-__device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, char* smem) {
+__device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, int first, char* smem) {
   constexpr int kDepth = NB <= 2 ? 3 : 2;            // K-tiles under way, as the generator's depth()
   constexpr bool kPairs = NB >= kW4PairsFrom;        // the K-loop in pair order
   constexpr int kLatePieces = w4_late_pieces(NB);    // of eight LM-head copies, those a step issues behind its sync
@@ -706,7 +706,6 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const int G = gridDim.x;
   const int S = sched.splits;
   const int n_units = n_tt * S;
-  const int pos = first_unit((int)blockIdx.x, G, n_units);
   const int A = (int)panel_depth((uint32_t)n_tt, NB, (uint32_t)p.panel);
   const int full_panel_units = A * S;
   const int n_panels = (n_tt + A - 1) / A;
@@ -747,7 +746,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const uint32_t u_hwrap = (uint32_t)(nk - 1) * 128u;
   const uint32_t w_dst = (uint32_t)wave * 64u * kRowBytes, h_dst = (uint32_t)(wave * 8 * NB) * kRowBytes;
 
-  for (int u = pos, round = 0; u < n_units; u += G, ++round) {
+  for (int u = first, round = 0; u < n_units; u += G, ++round) {
     if (round > 0) meet_before_round(p, round, n_units, G, tid);
     int pnl = u / full_panel_units;
     if (pnl >= n_panels) pnl = n_panels - 1;
@@ -944,16 +943,16 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
 }
 
 template <bool SAMPLE, bool STREAM>
-__device__ __forceinline__ void w4_units_of(const KernelParams& p, const Schedule& sched, int rows, char* smem) {
+__device__ __forceinline__ void w4_units_of(const KernelParams& p, const Schedule& sched, int rows, int first, char* smem) {
   switch (sched.width) {
-    case 1: w4_units<SAMPLE, 1, STREAM>(p, sched, rows, smem); break;
-    case 2: w4_units<SAMPLE, 2, STREAM>(p, sched, rows, smem); break;
-    case 3: w4_units<SAMPLE, 3, STREAM>(p, sched, rows, smem); break;
-    case 4: w4_units<SAMPLE, 4, STREAM>(p, sched, rows, smem); break;
-    case 5: w4_units<SAMPLE, 5, STREAM>(p, sched, rows, smem); break;
-    case 6: w4_units<SAMPLE, 6, STREAM>(p, sched, rows, smem); break;
-    case 7: w4_units<SAMPLE, 7, STREAM>(p, sched, rows, smem); break;
-    default: w4_units<SAMPLE, 8, STREAM>(p, sched, rows, smem); break;
+    case 1: w4_units<SAMPLE, 1, STREAM>(p, sched, rows, first, smem); break;
+    case 2: w4_units<SAMPLE, 2, STREAM>(p, sched, rows, first, smem); break;
+    case 3: w4_units<SAMPLE, 3, STREAM>(p, sched, rows, first, smem); break;
+    case 4: w4_units<SAMPLE, 4, STREAM>(p, sched, rows, first, smem); break;
+    case 5: w4_units<SAMPLE, 5, STREAM>(p, sched, rows, first, smem); break;
+    case 6: w4_units<SAMPLE, 6, STREAM>(p, sched, rows, first, smem); break;
+    case 7: w4_units<SAMPLE, 7, STREAM>(p, sched, rows, first, smem); break;
+    default: w4_units<SAMPLE, 8, STREAM>(p, sched, rows, first, smem); break;
   }
 }
 
@@ -964,8 +963,10 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
   const Schedule sched = launch_schedule(p, rows);
-  if (p.stream_w != 0 && sched.row_tiles == 1) w4_units_of<SAMPLE, true>(p, sched, rows, smem);
-  else w4_units_of<SAMPLE, false>(p, sched, rows, smem);
+  const int units = sched.row_tiles * sched.splits, first = first_unit((int)blockIdx.x, (int)gridDim.x, units);
+  if (first >= units) return;
+  if (p.stream_w != 0 && sched.row_tiles == 1) w4_units_of<SAMPLE, true>(p, sched, rows, first, smem);
+  else w4_units_of<SAMPLE, false>(p, sched, rows, first, smem);
 }
 
 // Merge the S partial results of every row and emit the outputs.  A wave handles ROWS rows with G = 64 / ROWS lanes
