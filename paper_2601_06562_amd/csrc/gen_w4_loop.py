@@ -368,7 +368,7 @@ def reduce_column(tb):
 # ---- the sampling statement (Gumbel-max at temperature tau; noise from Philox4x32-10 keyed by seed, counter =
 # (vocabulary id / 4, position, 0, 0), word id % 4).  Its registers beyond the
 # greedy reduction's are fragment registers that are dead by then: v[164:171] two generations of the generator's two
-# 64-bit products, v[172:173] the per-column product, v[174:179] temporaries of the rare exact path.
+# 64-bit products, v[172:173] the per-column product, v[174:179] temporaries of the rare exact path, v[184:215] the ids' part.
 PHILOX_M0, PHILOX_M1 = "%[pm0]", "%[pm1]"
 KNEG = 0xF1800000          # -2^100
 TWO23_101 = 0x4B0147AE     # 2^23 * 1.01
@@ -388,22 +388,49 @@ SAMPLE_TEMPS.update({f"k0_{r}": f"s{KEY0_BASE + r}" for r in range(10)})
 SAMPLE_TEMPS.update({f"k1_{r}": f"s{KEY1_BASE + r}" for r in range(10)})
 
 
+# What of the first rounds depends on the ids alone is the same for every column of the tile, four registers per quad: the
+# counter is (v4, position, 0, 0), so round 0 multiplies v4 alone (the second product is zero), of round 1's products one has
+# the position alone and one v4 alone, and of round 2's the first v4 alone.  Kept: round 0's low half; round 1's low half xored
+# with round 2's key; round 2's high half xored with its key, and its low half.
+ID_BASE = 184
+
+
+def id_reg(bi, k):
+    return f"v{ID_BASE + 4 * bi + k}"
+
+
+def philox_ids():
+    """The ids' part of the generator, once a tile: three of a quad's eighteen products and four of its other instructions.
+    A wave is alone on its SIMD and issues an instruction every 4.6 cycles, the 64-bit product like any other, so what
+    counts is how many there are: 42 a quad with this in every column, 36 without."""
+    for bi in range(8):
+        low, b1, hi2, lo2 = (id_reg(bi, k) for k in range(4))
+        e(f"v_add_u32 %[v4q], {4 * bi}, %[v4b]")
+        e(f"v_mad_u64_u32 v[164:165], vcc, {PHILOX_M0}, %[v4q], 0")      # round 0: lo -> a3, hi
+        e(f"v_xor_b32 v165, %[k1_0], v165")                              # a2 = hi ^ k1
+        e(f"v_mov_b32 {low}, v164")
+        e(f"v_mad_u64_u32 v[166:167], vcc, {PHILOX_M1}, v165, 0")        # round 1, second product: lo -> b1, hi
+        e(f"v_xor_b32 v167, %[k0_1], v167")                              # b0 = hi ^ k0   (a1 = 0)
+        e(f"v_xor_b32 {b1}, %[k0_2], v166")
+        e(f"v_mad_u64_u32 v[168:169], vcc, {PHILOX_M0}, v167, 0")        # round 2, first product
+        e(f"v_xor_b32 {hi2}, %[k1_2], v169")
+        e(f"v_mov_b32 {lo2}, v168")
+
+
 def philox_quad(tb, bi, XS):
     """Words of the four ids vb + 16*bi .. +3 of column tb's position, and the jump to the exact path when one of
-    them could still win.  Rounds 0 and 1 use what is known of the counter: (v4, position, 0, 0) makes the second
-    product of round 0 vanish, and the first product of round 1 depends on the position alone (per column, in
-    v[172:173], its high half already xored with the round key)."""
+    them could still win.  Begins in round 1, with the ids' part (philox_ids) and the product of the position alone (per
+    column, in v[172:173], its high half already xored with the round key)."""
     A, B, C, D = ("v164", "v165"), ("v166", "v167"), ("v168", "v169"), ("v170", "v171")
     pair = lambda r: f"v[{r[0][1:]}:{r[1][1:]}]"
-    e(f"v_add_u32 %[v4q], {4 * bi}, %[v4b]")
-    e(f"v_mad_u64_u32 {pair(A)}, vcc, {PHILOX_M0}, %[v4q], 0")       # round 0: lo -> a3, hi
-    e(f"v_xor_b32 {A[1]}, %[k1_0], {A[1]}")                          # a2 = hi ^ k1
-    e(f"v_mad_u64_u32 {pair(B)}, vcc, {PHILOX_M1}, {A[1]}, 0")       # round 1, second product: lo -> b1, hi
-    e(f"v_xor_b32 {B[1]}, %[k0_1], {B[1]}")                          # b0 = hi ^ k0   (a1 = 0)
-    e(f"v_xor_b32 {A[1]}, v173, {A[0]}")                             # b2 = (hi(M0 a0) ^ k1) ^ a3
-    c0, c1, c2, c3 = B[1], B[0], A[1], "v172"                        # b3 = lo(M0 a0)
+    low, b1, hi2, lo2 = (id_reg(bi, k) for k in range(4))
+    e(f"v_xor_b32 {A[1]}, v173, {low}")                              # b2 = (hi(M0 a0) ^ k1) ^ a3
+    e(f"v_mad_u64_u32 {pair(B)}, vcc, {PHILOX_M1}, {A[1]}, 0")       # round 2, second product
+    e(f"v_xor_b32 {B[1]}, {b1}, {B[1]}")                             # hi ^ b1 ^ k0
+    e(f"v_xor_b32 {A[1]}, v172, {hi2}")                              # hi(M0 b0) ^ b3 ^ k1, b3 = lo(M0 a0)
+    c0, c1, c2, c3 = B[1], B[0], A[1], lo2
     cur, nxt = (A, B), (C, D)
-    for r in range(2, 10):
+    for r in range(3, 10):
         PA, PB = nxt
         e(f"v_mad_u64_u32 {pair(PA)}, vcc, {PHILOX_M0}, {c0}, 0")
         e(f"v_mad_u64_u32 {pair(PB)}, vcc, {PHILOX_M1}, {c2}, 0")
@@ -626,6 +653,7 @@ def build_tile_sample():
     e("v_lshlrev_b32 %[sw32], 2, %[sw32]")
     e("v_lshlrev_b32 %[sw48], 2, %[sw48]")
     e("v_lshlrev_b32 %[sw16], 2, %[sw16]")
+    philox_ids()
     for tb in range(nb()):
         reduce_column_sample(tb)
     done = label("done")
