@@ -151,6 +151,7 @@ int mosaic_mask_compact(const uint8_t *mask, int64_t T, int32_t *out_idx, int32_
  *              max_rows only the first max_rows rows are produced.
  *   max_rows   the bound the plan was made for
  *   out_*      dev, max_rows entries each; entries >= *count are left untouched
+ *              (a sampling call keeps intermediate values in out_conf[0 .. *count) while it runs)
  *   plan       host pointer, from mosaic_plan_workspace with the same T, max_rows, d, V
  *   workspace  dev, >= plan->workspace_bytes, 16-byte aligned; contents are scratch.  Calls that may run
  *              concurrently (different streams) need workspaces of their own

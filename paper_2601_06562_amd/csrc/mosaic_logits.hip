@@ -84,6 +84,7 @@ struct KernelParams {
   // sampling with temperature (tau > 0): two more partial planes and the generator key
   float tau;
   uint32_t seed_lo, seed_hi;
+  int32_t share;    // out_conf holds, per row, the best score that any unit has published so far
   float* part_ym;   // best perturbed score x + tau*g (the id in part_si is then this score's)
   float* part_xa;   // the unperturbed logit at that arg-max
   int32_t* sync;    // round counters of the persistent grid (cleared before the launch), sync_slots of them
@@ -185,6 +186,32 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
   }
 }
 
+// Shared bounds of a draw.  A score that any unit has reached for a row bounds what can still win it, and the units of a
+// row (its vocabulary splits, and the two halves of a tile) run side by side, so they publish their rows' best scores and
+// take the others' into their own running best.  The exact path, which ids that the bound lets pass go through, was more
+// than half of what the draw costs (a timing variant that never takes it: 4096 rows of 126464 x 4096 2786 -> 2644 us, 280
+// rows 347 -> 307).  With the bounds of all units 2831 -> 2763 and 343 -> 327 us, 6554 rows of 152064 x 3584 5206 -> 4934,
+// 2700 rows of 65536 x 2048 735 -> 666, 16000 rows of 32000 x 1024 1157 -> 1014; what is left is mostly the units' first
+// tiles.  Only where the longest unit has three tiles or more: the first finds nothing published, and what it publishes
+// reaches the second too late.
+//
+// The bounds lie in out_conf, which holds nothing else until the merge writes it; a small launch ahead clears them.
+// What is taken over is the next float below: an id of another unit with the very same score still counts, and the merge
+// then finds the lowest of them as it does without.  The lane's id and logit stay those of its own best, which no
+// longer matters: the unit that published the score holds it, or a better one, in its partial result.
+// Scores are compared as signed integers, which orders them from 0 on up; anything below stays at kNeg, that is unshared.
+__device__ __forceinline__ float just_below(float x) {
+  const int b = __float_as_int(x);
+  return b > 0 ? __int_as_float(b - 1) : kNeg;
+}
+// Largest of a token's four lanes (l, l ^ 16, l ^ 32, l ^ 48).
+__device__ __forceinline__ float token_max(float x) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
 // Rows of this launch's chunk, and the division of the work for them.
 __device__ __forceinline__ int chunk_rows_found(const KernelParams& p) {
   int total = *p.count;
@@ -233,8 +260,14 @@ __device__ __forceinline__ void meet_before_round(const KernelParams& p, int rou
   }
 }
 
-__global__ __launch_bounds__(256) void clear_round_counters_kernel(int32_t* sync, int n) {
-  if ((int)threadIdx.x < n) sync[threadIdx.x] = 0;
+// Clears what a launch counts or shares: n counters, and the best score of every row of the chunk.
+__device__ __forceinline__ void clear_row_best(const KernelParams& p, int rows, int thread, int threads) {
+  if (p.share != 0)
+    for (int r = thread; r < rows; r += threads) p.out_conf[p.row0 + r] = kNeg;
+}
+__global__ __launch_bounds__(256) void clear_before_kernel(const KernelParams p, int32_t* counters, int n) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < n) counters[threadIdx.x] = 0;
+  clear_row_best(p, chunk_rows_found(p), (int)(blockIdx.x * 256 + threadIdx.x), (int)gridDim.x * 256);
 }
 
 // For hidden tensors of 4 GiB or more: raises *flag when some group of consecutive rows of the chunk's list that one
@@ -269,6 +302,7 @@ constexpr int64_t kOneBlockCheckRows = 4096;   // at most four groups a wave
 __global__ __launch_bounds__(1024) void clear_and_check_kernel(const KernelParams p, int32_t* counters, int n, int32_t* flag) {
   if ((int)threadIdx.x < n) counters[threadIdx.x] = 0;
   const int rows = chunk_rows_found(p);
+  clear_row_best(p, rows, (int)threadIdx.x, 1024);
   bool far = false;
   if (rows > 0) {
     const int group_rows = 8 * choose_width(p, rows);
@@ -675,6 +709,49 @@ constexpr int kRowBytes = 128;                       // one K-tile of a row
 constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
 constexpr int kLdsBytes = 160 * 1024;
 #include "mosaic_w4_pieces.inc"
+// Exchanges come after 1, 2, 4, 8, ... tiles, since a bound from n tiles lets pass half of what one from n / 2 does
+// (after every tile: 4096 rows 2821 -> 2876 us).  Of a row's splits at most kPublishers publish: they all do so at once, and
+// atomics on one word take turns (280 rows in 124 splits, all of them publishing 357 us, 16 341, 8 332, 4 329; 1004 rows in
+// 62 splits, 16 792, 8 794, 4 805).  The read may be served by any cache: an old bound is a bound.
+constexpr int kPublishers = 8;
+// The lane, anew: what these few lines derive from it is not to be kept in registers from one tile to the next.
+__device__ __forceinline__ int fresh_lane() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+  return lane;
+}
+// Lane group q publishes and reads columns q and q + 4 of a wave.
+__device__ __forceinline__ int32_t* row_best_at(const KernelParams& p, int first_row, int column, int rows, int lane) {
+  int j = first_row + column * 16 + (lane & 15);
+  if (j > rows - 1) j = rows - 1;
+  return reinterpret_cast<int32_t*>(p.out_conf + p.row0) + (uint32_t)j;
+}
+template <int NB>
+__device__ __forceinline__ void publish_best(const KernelParams& p, const float (&ym)[NB], int first_row, int rows) {
+  const int lane = fresh_lane(), q = lane >> 4;
+#pragma unroll
+  for (int k = 0; k < (NB + 3) / 4; ++k) {
+    float own = kNeg;
+#pragma unroll
+    for (int tb = 4 * k; tb < NB && tb < 4 * k + 4; ++tb) {
+      const float t = token_max(ym[tb]);
+      own = q == (tb & 3) ? t : own;
+    }
+    if (4 * k + q < NB)
+      __hip_atomic_fetch_max(row_best_at(p, first_row, 4 * k + q, rows, lane), __float_as_int(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+template <int NB>
+__device__ __forceinline__ void take_best(const KernelParams& p, float (&ym)[NB], int first_row, int rows) {
+  const int lane = fresh_lane(), q = lane >> 4, l16 = lane & 15;
+  int32_t best[(NB + 3) / 4];
+#pragma unroll
+  for (int k = 0; k < (NB + 3) / 4; ++k)
+    best[k] = 4 * k + q < NB ? __hip_atomic_load(row_best_at(p, first_row, 4 * k + q, rows, lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
+#pragma unroll
+  for (int tb = 0; tb < NB; ++tb) ym[tb] = fmaxf(ym[tb], __shfl(just_below(__int_as_float(best[tb / 4])), (tb & 3) * 16 + l16, 64));
+}
+
 template <bool SAMPLE, int NB, bool STREAM>
 __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, int first, char* smem) {
   constexpr int kDepth = NB <= 2 ? 3 : 2;            // K-tiles under way, as the generator's depth()
@@ -709,6 +786,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const int A = (int)panel_depth((uint32_t)n_tt, NB, (uint32_t)p.panel);
   const int full_panel_units = A * S;
   const int n_panels = (n_tt + A - 1) / A;
+  [[maybe_unused]] const int publish_every = (S + kPublishers - 1) / kPublishers;
 
   // Direct-to-LDS copy: instruction i of this wave fills rows first + 8*i + lane/8 of the tile, first = 64*wave for
   // the LM head (i = 0..7), 8*NB*wave for the hidden rows (i = 0..NB-1); 16-byte chunks are swizzled by row.
@@ -856,6 +934,9 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     }
 
     for (int n = 0; n < ntile; ++n) {
+      if constexpr (SAMPLE)
+        if (p.share != 0 && (n & (n - 1)) == 0 && (n > 0 || round > 0))
+          take_best<NB>(p, run_ym, tt * kTokens + wt * (kTokens / 2), rows);
       st_wsrc_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_wsrc_lo);
       st_wsrc_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_wsrc_hi);
       st_hsrc_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_hsrc_lo);
@@ -890,6 +971,9 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
           // compiler's scheduling
 #include "mosaic_w4_tile.inc"
         }
+        if constexpr (SAMPLE)
+          if (p.share != 0 && (n & (n + 1)) == 0 && sp % publish_every == 0)
+            publish_best<NB>(p, run_ym, tt * kTokens + wt * (kTokens / 2), rows);
         // the fold, ~25 instructions per column and tile of 64 K-tiles: 0.5% of the tile
 #pragma unroll
         for (int tb = 0; tb < NB; ++tb) {
@@ -1065,6 +1149,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.seed_hi = (uint32_t)(a.seed >> 32);
   p.part_ym = p.part_m + slots;
   p.part_xa = p.part_ym + slots;
+  p.share = 0;
   // the round counters sit behind the partial planes (three for a greedy pass, five for a sampling one)
   constexpr int kSyncSlots = MOSAIC_SYNC_BYTES / 4 - 2;   // then the division found, and the flag of the span check
   p.sync = reinterpret_cast<int32_t*>(sample ? p.part_xa + slots : p.part_ym);
@@ -1112,11 +1197,13 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
     const bool several_rounds = (int64_t)p.bound.row_tiles * p.bound.splits > grid || (paired && tiles > grid);
     if (!several_rounds) p.sync = tail.sync = nullptr;   // nobody meets (fewer rows may still take two rounds)
     else p.sync = counters, tail.sync = counters + kSyncSlots / 2;
+    const bool share = sample && (fast || paired) && p.sched.vocab_tiles > 2 * (uint32_t)p.bound.splits;
+    p.share = share ? 1 : 0;
     if (wide && cap <= kOneBlockCheckRows) {
       rc |= launch_kernel(clear_and_check_kernel, dim3(1), dim3(1024), stream, p, counters, kSyncSlots + 1, flag);
     } else {
-      if (several_rounds || wide)
-        rc |= launch_kernel(clear_round_counters_kernel, dim3(1), dim3(256), stream, counters, kSyncSlots + 2);
+      if (several_rounds || wide || share)
+        rc |= launch_kernel(clear_before_kernel, dim3(share ? (unsigned)((cap + 1023) / 1024) : 1u), dim3(256), stream, p, counters, kSyncSlots + 2);
       if (wide)
         rc |= launch_kernel(span_check_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), stream, p, flag);
     }
