@@ -780,7 +780,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
 
   const int n_tt = sched.row_tiles;
 
-  const int G = gridDim.x;
+  const int G = (int)p.sched.grid;   // (gridDim would make the launch carry 256 bytes more of arguments)
   const int S = sched.splits;
   const int n_units = n_tt * S;
   const int A = (int)panel_depth((uint32_t)n_tt, NB, (uint32_t)p.panel);
@@ -838,16 +838,37 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     const int total_steps = ntile * nk;
     const uint32_t u_total = (uint32_t)total_steps;
 
-    // Gather: 32-bit byte offsets of the NB hidden rows this lane copies, from the lowest of the 8*NB rows this wave
-    // copies (rows past the end of the chunk re-read the last valid row; their results are never stored).  The
-    // offsets fit 32 bits when the hidden tensor is smaller than 4 GiB, and otherwise because this launch only
-    // runs when no wave's rows lie that far apart (span_check_kernel).
-    int trow[NB], tmin = INT_MAX;
+    auto w_source = [&](int gw) {   // past the end: the last one
+      const int g = gw < total_steps ? gw : total_steps - 1;
+      return p.w + (int64_t)first_id(vt0 + g / nk) * (int64_t)w_row_bytes + (g % nk) * kRowBytes;
+    };
+    auto copy_w = [&](int gw, int pieces = 8) {
+      const char* src = w_source(gw);
+      char* dst = smem + (gw % NW) * kLmHeadSlot + w_dst;
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (i < pieces) __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, kAuxW);
+    };
+    // The list's entries are asked for first, then the first LM-head tile, which does not depend on them (the two latencies
+    // one after the other: 1.0 us of a unit's start).
+    wait_vm<0>();
+    int trow[NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
       int j = tt * kTokens + wave * 8 * NB + 8 * i + sub;
       if (j > rows - 1) j = rows - 1;
-      int t = p.idx[p.row0 + j];
+      trow[i] = p.idx[p.row0 + j];
+    }
+    copy_w(0);
+
+    // Gather: 32-bit byte offsets of the NB hidden rows this lane copies, from the lowest of the 8*NB rows this wave
+    // copies (rows past the end of the chunk re-read the last valid row; their results are never stored).  The
+    // offsets fit 32 bits when the hidden tensor is smaller than 4 GiB, and otherwise because this launch only
+    // runs when no wave's rows lie that far apart (span_check_kernel).
+    int tmin = INT_MAX;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+      int t = trow[i];
       t = t < 0 ? 0 : (t > p.T - 1 ? p.T - 1 : t);   // a bad entry of a caller-built list reads a valid row
       trow[i] = t;
       tmin = t < tmin ? t : tmin;
@@ -865,17 +886,6 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       hoff[i] = (uint32_t)(trow[i] - tmin) * (uint32_t)p.ldh_bytes + chunk_of(wave * 8 * NB + 8 * i + sub);
 
     // Prologue copies: W0 and H0, which are needed first, then what else the rings hold.
-    auto w_source = [&](int gw) {   // past the end: the last one
-      const int g = gw < total_steps ? gw : total_steps - 1;
-      return p.w + (int64_t)first_id(vt0 + g / nk) * (int64_t)w_row_bytes + (g % nk) * kRowBytes;
-    };
-    auto copy_w = [&](int gw, int pieces = 8) {
-      const char* src = w_source(gw);
-      char* dst = smem + (gw % NW) * kLmHeadSlot + w_dst;
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if (i < pieces) __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, kAuxW);
-    };
     auto copy_h = [&](int gh) {
       const char* src = hidden_wave + (gh % nk) * kRowBytes;
       char* dst = smem + NW * kLmHeadSlot + (gh % NH) * kHiddenSlot + h_dst;
@@ -886,8 +896,6 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     // What the rings hold.  In pair order the waves that copy a half's vocabulary blocks 4..7 run a K-tile behind the
     // others, and the copies that may be under way at the first sync, the eight youngest, are the LM head's.
     const int lead = kPairs && odd_wave ? NW - 1 : NW;   // K-tiles of the LM head ahead of the step
-    wait_vm<0>();
-    copy_w(0);
     copy_h(0);
     if constexpr (kPairs) {
       if (!odd_wave && total_steps > 1) copy_w(1);
@@ -1040,14 +1048,25 @@ __device__ __forceinline__ void w4_units_of(const KernelParams& p, const Schedul
   }
 }
 
+// Asks for all lines of a launch's arguments at once: read where they are used, one line waits for the other (268 rows of
+// 8192 x 512, a step of three launches: 19.3 -> 19.0 us).
+__device__ __forceinline__ void fetch_arguments() {
+  static_assert(sizeof(KernelParams) > 192 && sizeof(KernelParams) <= 256, "four lines");
+  uint32_t a, b, c, d;
+  asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\ts_load_dword %3, %4, 0xc0\n\t"
+               "s_waitcnt lgkmcnt(0)"
+               : "=&s"(a), "=&s"(b), "=&s"(c), "=&s"(d) : "s"(__builtin_amdgcn_kernarg_segment_ptr()));
+}
+
 template <bool SAMPLE>
 __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParams p) {
   __shared__ __attribute__((aligned(1024))) char smem[kLdsBytes];
+  fetch_arguments();
   if (p.wide_flag != nullptr && *p.wide_flag != p.wide_run_if) return;   // the other kernel of the two serves this list
   const int rows = chunk_rows_found(p);
   if (rows <= 0) return;
   const Schedule sched = launch_schedule(p, rows);
-  const int units = sched.row_tiles * sched.splits, first = first_unit((int)blockIdx.x, (int)gridDim.x, units);
+  const int units = sched.row_tiles * sched.splits, first = first_unit((int)blockIdx.x, (int)p.sched.grid, units);
   if (first >= units) return;
   if (p.stream_w != 0 && sched.row_tiles == 1) w4_units_of<SAMPLE, true>(p, sched, rows, first, smem);
   else w4_units_of<SAMPLE, false>(p, sched, rows, first, smem);
@@ -1059,6 +1078,7 @@ __global__ __launch_bounds__(256) void masked_logits_kernel_w4(const KernelParam
 // spread over ~250 of them, where this kernel is a visible part of the step): one.  Bound by latency: a launch, the
 // loads of count and splits, the partials, twelve shuffles.
 constexpr int kWideMergeSplits = 64;   // from this many splits on, a wave per row
+__host__ __device__ inline int combine_blocks(int rows) { return rows < 4 * 4096 ? (rows + 3) / 4 : 4096; }
 template <int ROWS>
 __device__ __forceinline__ void combine_rows(const KernelParams& p, int splits, int rows) {
   constexpr int G = 64 / ROWS;
@@ -1067,7 +1087,7 @@ __device__ __forceinline__ void combine_rows(const KernelParams& p, int splits, 
   const bool sample = p.tau > 0.f;   // sampling: the token is the arg-max of the perturbed scores
   const int lane = (int)threadIdx.x & 63, wave = (int)threadIdx.x >> 6;
   const int lr = lane % ROWS, g = lane / ROWS;
-  for (int r0 = ((int)blockIdx.x * 4 + wave) * ROWS; r0 < rows; r0 += (int)gridDim.x * 4 * ROWS) {
+  for (int r0 = ((int)blockIdx.x * 4 + wave) * ROWS; r0 < rows; r0 += combine_blocks(p.bound_rows) * 4 * ROWS) {
     const bool valid = r0 + lr < rows;
     const int r = valid ? r0 + lr : rows - 1;
     float lm[kPerLane], lym[kPerLane], lxa[kPerLane];
@@ -1225,7 +1245,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
       rc |= launch_general(p, grid);
     }
     if (paired) rc |= launch_general(tail, tiles < grid ? tiles : grid);
-    rc |= launch_kernel(combine_kernel, dim3((unsigned)((cap + 3) / 4 < 4096 ? (cap + 3) / 4 : 4096)), dim3(256), stream, p);
+    rc |= launch_kernel(combine_kernel, dim3((unsigned)combine_blocks((int)cap)), dim3(256), stream, p);
     if (rc != 0) break;
   }
   return rc;
