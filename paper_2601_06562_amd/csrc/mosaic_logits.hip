@@ -191,7 +191,7 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
 // take the others' into their own running best.  The exact path, which ids that the bound lets pass go through, was more
 // than half of what the draw costs (a timing variant that never takes it: 4096 rows of 126464 x 4096 2786 -> 2644 us, 280
 // rows 347 -> 307).  With the bounds of all units 2831 -> 2763 and 343 -> 327 us, 6554 rows of 152064 x 3584 5206 -> 4934,
-// 2700 rows of 65536 x 2048 735 -> 666, 16000 rows of 32000 x 1024 1157 -> 1014; what is left is mostly the units' first
+// 2700 rows of 65536 x 2048 735 -> 666, 16000 rows of 32000 x 1024 1157 -> 1014 (the padding columns still published then); what is left is mostly the units' first
 // tiles.  Only where the longest unit has three tiles or more: the first finds nothing published, and what it publishes
 // reaches the second too late.
 //
@@ -713,6 +713,9 @@ constexpr int kLdsBytes = 160 * 1024;
 // (after every tile: 4096 rows 2821 -> 2876 us).  Of a row's splits at most kPublishers publish: they all do so at once, and
 // atomics on one word take turns (280 rows in 124 splits, all of them publishing 357 us, 16 341, 8 332, 4 329; 1004 rows in
 // 62 splits, 16 792, 8 794, 4 805).  The read may be served by any cache: an old bound is a bound.
+// The columns that pad a row tile hold the last row once more and publish nothing: their atomics all went to that one row's
+// word, up to 256 a publisher, and the next copies wait behind them (4105 rows 3114 -> 3006 us, 2700 rows of 65536 x 2048
+// 659 -> 619, 16000 rows of 32000 x 1024 1037 -> 971).
 constexpr int kPublishers = 8;
 // The lane, anew: what these few lines derive from it is not to be kept in registers from one tile to the next.
 __device__ __forceinline__ int fresh_lane() {
@@ -737,8 +740,9 @@ __device__ __forceinline__ void publish_best(const KernelParams& p, const float 
       const float t = token_max(ym[tb]);
       own = q == (tb & 3) ? t : own;
     }
-    if (4 * k + q < NB)
-      __hip_atomic_fetch_max(row_best_at(p, first_row, 4 * k + q, rows, lane), __float_as_int(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int column = 4 * k + q;
+    if (column < NB && first_row + column * 16 + (lane & 15) < rows)   // a padding column holds the last row
+      __hip_atomic_fetch_max(row_best_at(p, first_row, column, rows, lane), __float_as_int(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 template <int NB>
