@@ -716,7 +716,7 @@ constexpr int kLdsBytes = 160 * 1024;
 // The columns that pad a row tile hold the last row once more and publish nothing: their atomics all went to that one row's
 // word, up to 256 a publisher, and the next copies wait behind them (4105 rows 3114 -> 3006 us, 2700 rows of 65536 x 2048
 // 659 -> 619, 16000 rows of 32000 x 1024 1037 -> 971).
-constexpr int kPublishers = 8;
+constexpr int kPublishers = 32;
 // The lane, anew: what these few lines derive from it is not to be kept in registers from one tile to the next.
 __device__ __forceinline__ int fresh_lane() {
   int lane;
