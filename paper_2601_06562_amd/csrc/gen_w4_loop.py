@@ -103,7 +103,8 @@ def reads(buf):
 
 
 def dma_w(i):
-    return [f"s_add_u32 m0, %[wdst], {1024 * i}", "s_nop 0", f"global_load_lds_dwordx4 %[woff{i}], {WSRC}"]
+    # the place of piece i within the wave's 8 KiB, exclusive-or the order of this unit's copies, which %[wdst] brings along
+    return [f"s_xor_b32 m0, %[wdst], {1024 * i}", "s_nop 0", f"global_load_lds_dwordx4 %[woff{i}], {WSRC}"]
 
 
 def dma_h(i):
