@@ -756,6 +756,20 @@ __device__ __forceinline__ void take_best(const KernelParams& p, float (&ym)[NB]
   for (int tb = 0; tb < NB; ++tb) ym[tb] = fmaxf(ym[tb], __shfl(just_below(__int_as_float(best[tb / 4])), (tb & 3) * 16 + l16, 64));
 }
 
+// A prologue copy's address as a scalar base and a 32-bit offset a lane, which the copy's instruction takes as they are.  Left
+// alone the compiler widens the offsets ahead of the units and spills the 64-bit addresses: a unit's start then waited for a
+// reload, and the copies ahead of it, up to eight times (16000 rows of 32000 x 1024 drawn 1037 -> 1002 us, 9000 rows of
+// 8192 x 512 drawn 165 -> 161, greedy 88.1 -> 87.0; vector registers spilled 57 -> 13 sampling, 10 -> 3 greedy).
+__device__ __forceinline__ const char* scalar_pointer(const char* x) {
+  const uint64_t a = (uint64_t)x;
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+  return (const char*)((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ uint32_t local_offset(uint32_t x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 template <bool SAMPLE, int NB, bool STREAM>
 __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& sched, int rows, int first, char* smem) {
   constexpr int kDepth = NB <= 2 ? 3 : 2;            // K-tiles under way, as the generator's depth()
@@ -851,11 +865,11 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       return p.w + (int64_t)first_id(vt0 + g / nk) * (int64_t)w_row_bytes + (g % nk) * kRowBytes;
     };
     auto copy_w = [&](int gw, int pieces = 8) {
-      const char* src = w_source(gw);
+      const char* src = scalar_pointer(w_source(gw));
       char* dst = smem + (gw % NW) * kLmHeadSlot + w_dst;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (i < pieces) __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + woff[i]), (lds_ptr_t)(dst + (i ^ turn) * 1024), 16, 0, kAuxW);
+        if (i < pieces) __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + local_offset(woff[i])), (lds_ptr_t)(dst + (i ^ turn) * 1024), 16, 0, kAuxW);
     };
     // The list's entries are asked for first, then the first LM-head tile, which does not depend on them (the two latencies
     // one after the other: 1.0 us of a unit's start).
@@ -897,11 +911,11 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
 
     // Prologue copies: W0 and H0, which are needed first, then what else the rings hold.
     auto copy_h = [&](int gh) {
-      const char* src = hidden_wave + (gh % nk) * kRowBytes;
+      const char* src = scalar_pointer(hidden_wave + (gh % nk) * kRowBytes);
       char* dst = smem + NW * kLmHeadSlot + (gh % NH) * kHiddenSlot + h_dst;
 #pragma unroll
       for (int i = 0; i < NB; ++i)
-        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + hoff[i]), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gbl_ptr_t)(src + local_offset(hoff[i])), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
     };
     // What the rings hold.  In pair order the waves that copy a half's vocabulary blocks 4..7 run a K-tile behind the
     // others, and the copies that may be under way at the first sync, the eight youngest, are the LM head's.
