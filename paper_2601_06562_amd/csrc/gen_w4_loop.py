@@ -635,11 +635,45 @@ def reduce_column_sample(tb):
     tile_exponentials(XS, S)
 
 
+# %[first] = TAKE asks for it.
+TAKE = 0x80000000
+
+
+def take_published():
+    """The best scores that other units have published for this wave's rows (the kernel says how, at its shared bounds) into
+    the columns' running best, as the next float below.  Here, between the tile's products and its draw, a unit's second tile
+    finds what the first ones of all units have reached; ahead of the products, where it stood, they were still at it.
+    %[rb]: the first of the rows' words, %[rl]: the last row that is there."""
+    T = [f"v{FRAG_BASE + i}" for i in range(nb())]
+    best = ["v180", "v181"][:(nb() + 3) // 4]
+    e("v_mbcnt_lo_u32_b32 v176, -1, 0")
+    e("v_mbcnt_hi_u32_b32 v176, -1, v176")
+    for k, b in enumerate(best):                                     # lane group q: columns q and q + 4
+        e(f"v_add_u32 {b}, {64 * k}, v176")
+        e(f"v_min_i32 {b}, %[rl], {b}")
+        e(f"v_lshlrev_b32 {b}, 2, {b}")
+        e(f"global_load_dword {b}, {b}, %[rb] sc0")
+    e("v_and_b32 v176, 15, v176")
+    e("v_lshlrev_b32 v176, 2, v176")
+    e(f"v_mov_b32 v177, {hex(KNEG)}")
+    e("s_waitcnt vmcnt(0)")
+    for b in best:
+        e(f"v_cmp_lt_i32 vcc, 0, {b}")
+        e(f"v_add_u32 {b}, -1, {b}")
+        e("s_nop 1")
+        e(f"v_cndmask_b32 {b}, v177, {b}, vcc")
+    for tb in range(nb()):
+        e(f"ds_bpermute_b32 {T[tb]}, v176, {best[tb // 4]} offset:{64 * (tb % 4)}")
+    e("s_waitcnt lgkmcnt(0)")
+    for tb in range(nb()):
+        e(f"v_max_f32 %[ym{tb}], %[ym{tb}], {T[tb]}")
+
+
 def build_tile_sample():
     """The statement of the sampling kernel: the K-loop, then the
     reduction with the noise; the rare exact paths sit behind the end of the statement."""
     slow_blocks.clear()
-    build_loop()
+    build_loop(take_published)
     e(f"s_mov_b32 %[k0_0], %[seed_lo]")                              # key of round r = seed + r * (golden-ratio words)
     e(f"s_mov_b32 %[k1_0], %[seed_hi]")
     for r in range(1, 10):
@@ -675,13 +709,17 @@ def build_tile():
         reduce_column(tb)
 
 
-def mask_counted():
+def mask_counted(between=None):
     """The last tile of a vocabulary that is no multiple of 256 lies over the vocabulary's last 256 ids; those below
     %[first] belong to the tile before it and are taken out here: their logits become -2^100.  %[first] is 0 for every
     other tile.  One compare per element serves all columns; a compare's result is read two wait states later."""
     skip = label("whole")
     e("s_cmp_eq_u32 %[first], 0")
     e(f"s_cbranch_scc1 {skip}")
+    if between:
+        take = label("take")
+        e(f"s_cmp_eq_u32 %[first], {hex(TAKE)}")
+        e(f"s_cbranch_scc1 {take}")
     e(f"v_sub_u32 {ET}, %[first], %[vb]")             # elements with a code below it (signed) are taken out
     e(f"v_mov_b32 {EY}, {hex(KNEG)}")
     for el in range(32):
@@ -693,13 +731,17 @@ def mask_counted():
             e(f"v_cndmask_b32 {X[tb]}, {X[tb]}, {EY}, vcc")
         for tb in range(nb()):
             e(f"v_accvgpr_write_b32 {acc_reg(el // 4, tb, el % 4)}, {X[tb]}")
+    if between:                                       # a whole tile too
+        e(f"s_branch {skip}")
+        e(f"{take}:")
+        between()
     e(f"{skip}:")
 
 
-def build_loop():
+def build_loop(between=None):
     """The width's K-loop, and what of its tile is not counted."""
     build_pairs() if pairs() else build()
-    mask_counted()
+    mask_counted(between)
 
 
 def build():
@@ -1052,6 +1094,7 @@ def write_statement(f, blocks, sample):
     clob = [f'"a{i}"' for i in range(32 * blocks)] + [f'"s{i}"' for i in range(88, 94)] + clob
     if sample:
         ins += [f'[pos{tb}] "v"(pos[{tb}])' for tb in range(blocks)]
+        ins += ['[rb] "s"(row_best)', '[rl] "s"(last_row)']
         ins += ['[seed_lo] "s"(seed_lo)', '[seed_hi] "s"(seed_hi)']
         clob = [f'"s{i}"' for i in range(66, KEY1_BASE + 10)] + clob
         ins += ['[pm0] "s"(philox_m0)', '[pm1] "s"(philox_m1)', '[itl] "s"(inv_tau_log2e)', '[tau] "s"(tau_s)']
@@ -1075,6 +1118,7 @@ def write_pieces(f):
         pieces[blocks] = late_pieces()
     f.write("// GENERATED by gen_w4_loop.py -- do not edit.\n"
             f"constexpr int kW4PairsFrom = {PAIRS_FROM};\n"
+            f"constexpr int kW4Take = (int){hex(TAKE)}u;\n"
             f"constexpr int w4_late_pieces(int nb) {{\n  constexpr int pieces[9] = {{{', '.join(map(str, pieces))}}};\n"
             "  return pieces[nb];\n}\n")
 

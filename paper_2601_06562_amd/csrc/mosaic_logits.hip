@@ -191,19 +191,21 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
 // take the others' into their own running best.  The exact path, which ids that the bound lets pass go through, was more
 // than half of what the draw costs (a timing variant that never takes it: 4096 rows of 126464 x 4096 2786 -> 2644 us, 280
 // rows 347 -> 307).  With the bounds of all units 2831 -> 2763 and 343 -> 327 us, 6554 rows of 152064 x 3584 5206 -> 4934,
-// 2700 rows of 65536 x 2048 735 -> 666, 16000 rows of 32000 x 1024 1157 -> 1014 (the padding columns still published then); what is left is mostly the units' first
-// tiles.  Only where the longest unit has three tiles or more: the first finds nothing published, and what it publishes
-// reaches the second too late.
+// 2700 rows of 65536 x 2048 735 -> 666, 16000 rows of 32000 x 1024 1157 -> 1014 (padding columns still published then);
+// what is left is mostly the units' first tiles.  The scores are taken over between a tile's products and its draw, so that
+// a unit's second tile finds what the first ones of all units reached; taken ahead of the products, where all were still at
+// it, they helped from the third tile on: 205 rows, units of two tiles, 246 -> 236 us, 500 rows of 65536 x 2048 160 -> 148,
+// 900 rows of 32000 x 1024 105 -> 95, 2700 rows of 65536 x 2048 602 -> 592.  A unit of one tile has nothing to take, and
+// one of two gains less than the launch that clears the bounds where its tiles are narrower than 96 rows (kShareAtTwo:
+// 20 rows 173.9 -> 175.7 us, 64 rows 183.4 -> 184.9; 96 rows 193.4 -> 191.3, 180 rows 243.7 -> 233.3).
 //
 // The bounds lie in out_conf, which holds nothing else until the merge writes it; a small launch ahead clears them.
 // What is taken over is the next float below: an id of another unit with the very same score still counts, and the merge
 // then finds the lowest of them as it does without.  The lane's id and logit stay those of its own best, which no
 // longer matters: the unit that published the score holds it, or a better one, in its partial result.
 // Scores are compared as signed integers, which orders them from 0 on up; anything below stays at kNeg, that is unshared.
-__device__ __forceinline__ float just_below(float x) {
-  const int b = __float_as_int(x);
-  return b > 0 ? __int_as_float(b - 1) : kNeg;
-}
+// (Taking over is the sampling statements' own: take_published in gen_w4_loop.py.)
+
 // Largest of a token's four lanes (l, l ^ 16, l ^ 32, l ^ 48).
 __device__ __forceinline__ float token_max(float x) {
   const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -710,13 +712,14 @@ constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
 constexpr int kLdsBytes = 160 * 1024;
 #include "mosaic_w4_pieces.inc"
 // Exchanges come after 1, 2, 4, 8, ... tiles, since a bound from n tiles lets pass half of what one from n / 2 does
-// (after every tile: 4096 rows 2821 -> 2876 us).  Of a row's splits at most kPublishers publish: they all do so at once, and
-// atomics on one word take turns (280 rows in 124 splits, all of them publishing 357 us, 16 341, 8 332, 4 329; 1004 rows in
-// 62 splits, 16 792, 8 794, 4 805).  The read may be served by any cache: an old bound is a bound.
+// (after every tile: 4096 rows 2821 -> 2876 us).  Of a row's splits at most about kPublishers publish, since atomics on one
+// word take turns and a few are nearly as good a bound as all (1004 rows 785 us with 8, 775 with 32, 779 with 64; 280 rows 326,
+// 324, 333).  The read may be served by any cache: an old bound is a bound.
 // The columns that pad a row tile hold the last row once more and publish nothing: their atomics all went to that one row's
 // word, up to 256 a publisher, and the next copies wait behind them (4105 rows 3114 -> 3006 us, 2700 rows of 65536 x 2048
 // 659 -> 619, 16000 rows of 32000 x 1024 1037 -> 971).
 constexpr int kPublishers = 32;
+constexpr int kShareAtTwo = 3;   // widths from which on units of two tiles share, too
 // The lane, anew: what these few lines derive from it is not to be kept in registers from one tile to the next.
 __device__ __forceinline__ int fresh_lane() {
   int lane;
@@ -745,17 +748,6 @@ __device__ __forceinline__ void publish_best(const KernelParams& p, const float 
       __hip_atomic_fetch_max(row_best_at(p, first_row, column, rows, lane), __float_as_int(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
-template <int NB>
-__device__ __forceinline__ void take_best(const KernelParams& p, float (&ym)[NB], int first_row, int rows) {
-  const int lane = fresh_lane(), q = lane >> 4, l16 = lane & 15;
-  int32_t best[(NB + 3) / 4];
-#pragma unroll
-  for (int k = 0; k < (NB + 3) / 4; ++k)
-    best[k] = 4 * k + q < NB ? __hip_atomic_load(row_best_at(p, first_row, 4 * k + q, rows, lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) : 0;
-#pragma unroll
-  for (int tb = 0; tb < NB; ++tb) ym[tb] = fmaxf(ym[tb], __shfl(just_below(__int_as_float(best[tb / 4])), (tb & 3) * 16 + l16, 64));
-}
-
 // A prologue copy's address as a scalar base and a 32-bit offset a lane, which the copy's instruction takes as they are.  Left
 // alone the compiler widens the offsets ahead of the units and spills the 64-bit addresses: a unit's start then waited for a
 // reload, and the copies ahead of it, up to eight times (16000 rows of 32000 x 1024 drawn 1037 -> 1002 us, 9000 rows of
@@ -952,6 +944,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     uint32_t st_wk = (uint32_t)((kPairs && gw >= total_steps ? total_steps - 1 : gw) % nk), st_hk = (uint32_t)(gh % nk);
     uint32_t st_g = 0;
 
+    [[maybe_unused]] const int first_row = tt * kTokens + wt * (kTokens / 2);   // this wave's columns
     float run_m[NB], run_ym[NB], run_xa[NB];
     double run_s[NB];
     int run_i[NB], pos[NB];
@@ -966,9 +959,6 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     }
 
     for (int n = 0; n < ntile; ++n) {
-      if constexpr (SAMPLE)
-        if (p.share != 0 && (n & (n - 1)) == 0 && (n > 0 || round > 0))
-          take_best<NB>(p, run_ym, tt * kTokens + wt * (kTokens / 2), rows);
       st_wsrc_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_wsrc_lo);
       st_wsrc_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_wsrc_hi);
       st_hsrc_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_hsrc_lo);
@@ -985,7 +975,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       const uint32_t st_nk = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_nk);
       const bool ragged_next = vt0 + n + 1 == ragged_tile, ragged = vt0 + n == ragged_tile;
       const uint32_t st_wwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ragged_next ? u_wwrap_ragged : u_wwrap));
-      const uint32_t st_first = (uint32_t)__builtin_amdgcn_readfirstlane(ragged ? ragged_tile * kTileVocab : 0);
+      const uint32_t st_first = (uint32_t)__builtin_amdgcn_readfirstlane(ragged ? ragged_tile * kTileVocab : SAMPLE && p.share != 0 && (n & (n - 1)) == 0 && (n > 0 || round > 0) ? kW4Take : 0);
       const uint32_t st_hwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_hwrap);
         [[maybe_unused]] const uint32_t st_wnext = (uint32_t)__builtin_amdgcn_readfirstlane(lead);
         uint32_t addr_tmp0, addr_tmp1;
@@ -994,6 +984,11 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
         float tile_m[NB], tile_s[NB];   // this tile's own triples
         int tile_i[NB];
         if constexpr (SAMPLE) {
+          // the shared bounds of the wave's rows, and how many follow the first (a padding column takes the last one's; a wave
+          // of nothing else begins there)
+          const int from = first_row < rows ? first_row : rows - 1;
+          const uint64_t row_best = (uint64_t)scalar_pointer((const char*)(p.out_conf + p.row0 + (int64_t)from));
+          const int last_row = __builtin_amdgcn_readfirstlane(rows - 1 - from);
           // sampling: the same, with the Gumbel-max draw in the reduction (round keys by number too).  The drawn
           // candidate is carried from tile to tile: it bounds what can still win
 #include "mosaic_w4_tile_sample.inc"
@@ -1005,7 +1000,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
         }
         if constexpr (SAMPLE)
           if (p.share != 0 && (n & (n + 1)) == 0 && sp % publish_every == 0)
-            publish_best<NB>(p, run_ym, tt * kTokens + wt * (kTokens / 2), rows);
+            publish_best<NB>(p, run_ym, first_row, rows);
         // the fold, ~25 instructions per column and tile of 64 K-tiles: 0.5% of the tile
 #pragma unroll
         for (int tb = 0; tb < NB; ++tb) {
@@ -1241,7 +1236,7 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
     const bool several_rounds = (int64_t)p.bound.row_tiles * p.bound.splits > grid || (paired && tiles > grid);
     if (!several_rounds) p.sync = tail.sync = nullptr;   // nobody meets (fewer rows may still take two rounds)
     else p.sync = counters, tail.sync = counters + kSyncSlots / 2;
-    const bool share = sample && (fast || paired) && p.sched.vocab_tiles > 2 * (uint32_t)p.bound.splits;
+    const bool share = sample && (fast || paired) && p.sched.vocab_tiles > (p.bound.width < kShareAtTwo ? 2u : 1u) * (uint32_t)p.bound.splits;
     p.share = share ? 1 : 0;
     if (wide && cap <= kOneBlockCheckRows) {
       rc |= launch_kernel(clear_and_check_kernel, dim3(1), dim3(1024), stream, p, counters, kSyncSlots + 1, flag);

@@ -47,3 +47,8 @@ def test_shared_bounds_change_no_draw(rows, V, tau, offset):
         assert torch.equal(got[0], want[0])
         assert (got[2] != want[2]).sum() <= 1 and torch.allclose(got[2], want[2], rtol=2e-7, atol=0)   # a last bit, once in a million
         assert torch.allclose(got[1], want[1], rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("rows", [97, 180, 256])
+def test_units_of_two_tiles_share_too(rows):
+    test_shared_bounds_change_no_draw(rows, 130816, 0.7, 0.0)      # 511 vocabulary tiles, one row tile
