@@ -84,7 +84,6 @@ struct KernelParams {
   // sampling with temperature (tau > 0): two more partial planes and the generator key
   float tau;
   uint32_t seed_lo, seed_hi;
-  int32_t share;    // out_conf holds, per row, the best score that any unit has published so far
   float* part_ym;   // best perturbed score x + tau*g (the id in part_si is then this score's)
   float* part_xa;   // the unperturbed logit at that arg-max
   int32_t* sync;    // round counters of the persistent grid (cleared before the launch), sync_slots of them
@@ -190,16 +189,22 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
 // row (its vocabulary splits, and the two halves of a tile) run side by side, so they publish their rows' best scores and
 // take the others' into their own running best.  The exact path, which ids that the bound lets pass go through, was more
 // than half of what the draw costs (a timing variant that never takes it: 4096 rows of 126464 x 4096 2786 -> 2644 us, 280
-// rows 347 -> 307).  With the bounds of all units 2831 -> 2763 and 343 -> 327 us, 6554 rows of 152064 x 3584 5206 -> 4934,
-// 2700 rows of 65536 x 2048 735 -> 666, 16000 rows of 32000 x 1024 1157 -> 1014 (padding columns still published then);
-// what is left is mostly the units' first tiles.  The scores are taken over between a tile's products and its draw, so that
-// a unit's second tile finds what the first ones of all units reached; taken ahead of the products, where all were still at
-// it, they helped from the third tile on: 205 rows, units of two tiles, 246 -> 236 us, 500 rows of 65536 x 2048 160 -> 148,
-// 900 rows of 32000 x 1024 105 -> 95, 2700 rows of 65536 x 2048 602 -> 592.  A unit of one tile has nothing to take, and
-// one of two gains less than the launch that clears the bounds where its tiles are narrower than 96 rows (kShareAtTwo:
-// 20 rows 173.9 -> 175.7 us, 64 rows 183.4 -> 184.9; 96 rows 193.4 -> 191.3, 180 rows 243.7 -> 233.3).
+// rows 347 -> 307).  Without sharing and with it, temperature 0.7: 280 rows 331 -> 309 us, 205 rows 253 -> 241, 1004 rows
+// 835 -> 777, 4096 rows at temperature 1 2938 -> 2836; 6554 rows of 152064 x 3584 5298 -> 5039; 500 and 2700 rows of 65536 x
+// 2048 162 -> 144 and 701 -> 601; 900 and 16000 rows of 32000 x 1024 106 -> 88 and 1139 -> 997; 1000 and 9000 rows of 8192 x
+// 512 33.9 -> 31.5 and 174 -> 143.  What is left is mostly the units' first tiles.  The scores are taken over between a
+// tile's products and its draw, so that a unit's second tile finds what the first ones of all units reached; ahead of the
+// products all are still at it (units of two tiles: 205 rows 246 -> 236 us by the later point, 500 rows of 65536 x 2048 160 -> 148).
+// Which units share follows from the division found (units_share, mosaic_schedule.h).
 //
-// The bounds lie in out_conf, which holds nothing else until the merge writes it; a small launch ahead clears them.
+// The bounds lie in out_conf, which holds nothing else until the merge writes it.  Every unit clears the words of its rows
+// itself, at its start, and each lane reads only words that it has stored to: what it finds there was written by this
+// launch.  So the store need be seen by no other (at the scope of the workgroup it stays behind the XCD's own L2; through to
+// memory, where all units of a row queue for the same lines, 500 rows of 65536 x 2048 take 146 us instead of 141, 8 rows of
+// 152064 x 3584, 198 units on one line, 185 instead of 175), and a unit that starts late and wipes what others have published
+// costs them a bound and no result.  A launch ahead of the pass that cleared the rows cost every draw whose bound has
+// units that share 2 us, also where the units found do not: 16 rows of 32000 x 1024 under a bound of 512 27.0 -> 29.0 us, of
+// 8192 x 512 under 4096 19.1 -> 21.0 (without it 26.4 and 18.5).
 // What is taken over is the next float below: an id of another unit with the very same score still counts, and the merge
 // then finds the lowest of them as it does without.  The lane's id and logit stay those of its own best, which no
 // longer matters: the unit that published the score holds it, or a better one, in its partial result.
@@ -262,14 +267,8 @@ __device__ __forceinline__ void meet_before_round(const KernelParams& p, int rou
   }
 }
 
-// Clears what a launch counts or shares: n counters, and the best score of every row of the chunk.
-__device__ __forceinline__ void clear_row_best(const KernelParams& p, int rows, int thread, int threads) {
-  if (p.share != 0)
-    for (int r = thread; r < rows; r += threads) p.out_conf[p.row0 + r] = kNeg;
-}
-__global__ __launch_bounds__(256) void clear_before_kernel(const KernelParams p, int32_t* counters, int n) {
-  if (blockIdx.x == 0 && (int)threadIdx.x < n) counters[threadIdx.x] = 0;
-  clear_row_best(p, chunk_rows_found(p), (int)(blockIdx.x * 256 + threadIdx.x), (int)gridDim.x * 256);
+__global__ __launch_bounds__(256) void clear_round_counters_kernel(int32_t* sync, int n) {
+  if ((int)threadIdx.x < n) sync[threadIdx.x] = 0;
 }
 
 // For hidden tensors of 4 GiB or more: raises *flag when some group of consecutive rows of the chunk's list that one
@@ -304,7 +303,6 @@ constexpr int64_t kOneBlockCheckRows = 4096;   // at most four groups a wave
 __global__ __launch_bounds__(1024) void clear_and_check_kernel(const KernelParams p, int32_t* counters, int n, int32_t* flag) {
   if ((int)threadIdx.x < n) counters[threadIdx.x] = 0;
   const int rows = chunk_rows_found(p);
-  clear_row_best(p, rows, (int)threadIdx.x, 1024);
   bool far = false;
   if (rows > 0) {
     const int group_rows = 8 * choose_width(p, rows);
@@ -719,18 +717,25 @@ constexpr int kLdsBytes = 160 * 1024;
 // word, up to 256 a publisher, and the next copies wait behind them (4105 rows 3114 -> 3006 us, 2700 rows of 65536 x 2048
 // 659 -> 619, 16000 rows of 32000 x 1024 1037 -> 971).
 constexpr int kPublishers = 32;
-constexpr int kShareAtTwo = 3;   // widths from which on units of two tiles share, too
 // The lane, anew: what these few lines derive from it is not to be kept in registers from one tile to the next.
 __device__ __forceinline__ int fresh_lane() {
   int lane;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
   return lane;
 }
-// Lane group q publishes and reads columns q and q + 4 of a wave.
-__device__ __forceinline__ int32_t* row_best_at(const KernelParams& p, int first_row, int column, int rows, int lane) {
-  int j = first_row + column * 16 + (lane & 15);
-  if (j > rows - 1) j = rows - 1;
-  return reinterpret_cast<int32_t*>(p.out_conf + p.row0) + (uint32_t)j;
+// Lane group q clears, publishes and reads columns q and q + 4 of a wave.
+__device__ __forceinline__ int32_t* row_best_at(const KernelParams& p, int row) {
+  return reinterpret_cast<int32_t*>(p.out_conf + p.row0) + (uint32_t)row;
+}
+template <int NB>
+__device__ __forceinline__ void clear_best(const KernelParams& p, int first_row, int rows) {
+  const int lane = fresh_lane(), q = lane >> 4;
+#pragma unroll
+  for (int k = 0; k < (NB + 3) / 4; ++k) {
+    const int column = 4 * k + q, row = first_row + column * 16 + (lane & 15);
+    if (column < NB && row < rows)   // a padding column's draw is of no account, whatever it finds
+      __hip_atomic_store(row_best_at(p, row), __float_as_int(kNeg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  }
 }
 template <int NB>
 __device__ __forceinline__ void publish_best(const KernelParams& p, const float (&ym)[NB], int first_row, int rows) {
@@ -743,9 +748,9 @@ __device__ __forceinline__ void publish_best(const KernelParams& p, const float 
       const float t = token_max(ym[tb]);
       own = q == (tb & 3) ? t : own;
     }
-    const int column = 4 * k + q;
-    if (column < NB && first_row + column * 16 + (lane & 15) < rows)   // a padding column holds the last row
-      __hip_atomic_fetch_max(row_best_at(p, first_row, column, rows, lane), __float_as_int(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int column = 4 * k + q, row = first_row + column * 16 + (lane & 15);
+    if (column < NB && row < rows)   // a padding column holds the last row
+      __hip_atomic_fetch_max(row_best_at(p, row), __float_as_int(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 // A prologue copy's address as a scalar base and a 32-bit offset a lane, which the copy's instruction takes as they are.  Left
@@ -796,7 +801,6 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
   const int A = (int)panel_depth((uint32_t)n_tt, NB, (uint32_t)p.panel);
   const int full_panel_units = A * S;
   const int n_panels = (n_tt + A - 1) / A;
-  [[maybe_unused]] const int publish_every = (S + kPublishers - 1) / kPublishers;
 
   // Direct-to-LDS copy: instruction i of this wave fills rows first + 8*i + lane/8 of the tile, first = 64*wave for
   // the LM head (i = 0..7), 8*NB*wave for the hidden rows (i = 0..NB-1); 16-byte chunks are swizzled by row.  (wlane: a
@@ -877,6 +881,16 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     for (int i = 0; i < 8; ++i) woff[i] = wlane[i & 1] + (uint32_t)(8 * (i ^ turn)) * w_row_bytes;
     copy_w(0);
 
+    [[maybe_unused]] const int first_row = tt * kTokens + wt * (kTokens / 2);   // this wave's columns
+    [[maybe_unused]] int exchange = 0;   // 1: the unit takes shared bounds over; 2: it publishes, too
+    if constexpr (SAMPLE) {
+      if (units_share(p.sched.vocab_tiles, NB, S)) {
+        exchange = sp % ((S + kPublishers - 1) / kPublishers) == 0 ? 2 : 1;
+        clear_best<NB>(p, first_row, rows);
+      }
+      exchange = __builtin_amdgcn_readfirstlane(exchange);
+    }
+
     // Gather: 32-bit byte offsets of the NB hidden rows this lane copies, from the lowest of the 8*NB rows this wave
     // copies (rows past the end of the chunk re-read the last valid row; their results are never stored).  The
     // offsets fit 32 bits when the hidden tensor is smaller than 4 GiB, and otherwise because this launch only
@@ -944,7 +958,6 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
     uint32_t st_wk = (uint32_t)((kPairs && gw >= total_steps ? total_steps - 1 : gw) % nk), st_hk = (uint32_t)(gh % nk);
     uint32_t st_g = 0;
 
-    [[maybe_unused]] const int first_row = tt * kTokens + wt * (kTokens / 2);   // this wave's columns
     float run_m[NB], run_ym[NB], run_xa[NB];
     double run_s[NB];
     int run_i[NB], pos[NB];
@@ -958,7 +971,9 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       }
     }
 
+#pragma unroll 1
     for (int n = 0; n < ntile; ++n) {
+      if constexpr (SAMPLE) asm volatile("" : "+s"(exchange));   // one loop, not one for each of its values
       st_wsrc_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_wsrc_lo);
       st_wsrc_hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_wsrc_hi);
       st_hsrc_lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)st_hsrc_lo);
@@ -975,7 +990,10 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
       const uint32_t st_nk = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_nk);
       const bool ragged_next = vt0 + n + 1 == ragged_tile, ragged = vt0 + n == ragged_tile;
       const uint32_t st_wwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)(ragged_next ? u_wwrap_ragged : u_wwrap));
-      const uint32_t st_first = (uint32_t)__builtin_amdgcn_readfirstlane(ragged ? ragged_tile * kTileVocab : SAMPLE && p.share != 0 && (n & (n - 1)) == 0 && (n > 0 || round > 0) ? kW4Take : 0);
+      int tile_first = 0;   // what the statement does ahead of the reduction: nothing, the ids counted before, or
+      if (ragged) tile_first = ragged_tile * kTileVocab;
+      else if (SAMPLE && exchange > 0 && n > 0 && (n & (n - 1)) == 0) tile_first = kW4Take;   // the shared bounds, behind 1, 2, 4, ... tiles
+      const uint32_t st_first = (uint32_t)__builtin_amdgcn_readfirstlane(tile_first);
       const uint32_t st_hwrap = (uint32_t)__builtin_amdgcn_readfirstlane((int)u_hwrap);
         [[maybe_unused]] const uint32_t st_wnext = (uint32_t)__builtin_amdgcn_readfirstlane(lead);
         uint32_t addr_tmp0, addr_tmp1;
@@ -999,7 +1017,7 @@ __device__ __forceinline__ void w4_units(const KernelParams& p, const Schedule& 
 #include "mosaic_w4_tile.inc"
         }
         if constexpr (SAMPLE)
-          if (p.share != 0 && (n & (n + 1)) == 0 && sp % publish_every == 0)
+          if (exchange > 1 && (n & (n + 1)) == 0)
             publish_best<NB>(p, run_ym, first_row, rows);
         // the fold, ~25 instructions per column and tile of 64 K-tiles: 0.5% of the tile
 #pragma unroll
@@ -1188,7 +1206,6 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
   p.seed_hi = (uint32_t)(a.seed >> 32);
   p.part_ym = p.part_m + slots;
   p.part_xa = p.part_ym + slots;
-  p.share = 0;
   // the round counters sit behind the partial planes (three for a greedy pass, five for a sampling one)
   constexpr int kSyncSlots = MOSAIC_SYNC_BYTES / 4 - 2;   // then the division found, and the flag of the span check
   p.sync = reinterpret_cast<int32_t*>(sample ? p.part_xa + slots : p.part_ym);
@@ -1236,13 +1253,11 @@ int launch_masked_logits(const LogitsArgs& a, const mosaic_plan& plan, hipStream
     const bool several_rounds = (int64_t)p.bound.row_tiles * p.bound.splits > grid || (paired && tiles > grid);
     if (!several_rounds) p.sync = tail.sync = nullptr;   // nobody meets (fewer rows may still take two rounds)
     else p.sync = counters, tail.sync = counters + kSyncSlots / 2;
-    const bool share = sample && (fast || paired) && p.sched.vocab_tiles > (p.bound.width < kShareAtTwo ? 2u : 1u) * (uint32_t)p.bound.splits;
-    p.share = share ? 1 : 0;
     if (wide && cap <= kOneBlockCheckRows) {
       rc |= launch_kernel(clear_and_check_kernel, dim3(1), dim3(1024), stream, p, counters, kSyncSlots + 1, flag);
     } else {
-      if (several_rounds || wide || share)
-        rc |= launch_kernel(clear_before_kernel, dim3(share ? (unsigned)((cap + 1023) / 1024) : 1u), dim3(256), stream, p, counters, kSyncSlots + 2);
+      if (several_rounds || wide)
+        rc |= launch_kernel(clear_round_counters_kernel, dim3(1), dim3(256), stream, counters, kSyncSlots + 2);
       if (wide)
         rc |= launch_kernel(span_check_kernel, dim3((unsigned)((cap + 255) / 256)), dim3(256), stream, p, flag);
     }

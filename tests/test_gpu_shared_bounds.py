@@ -1,5 +1,6 @@
-"""A draw in which the units of a row share the best scores they have reached (a step whose units have three vocabulary tiles
-or more) against the same rows drawn a few at a time, in units of one or two tiles, which share nothing: the same bits."""
+"""A draw in which the units of a row share the best scores they have reached, against the same rows drawn a few at a time, in
+units of 32 rows and one or two vocabulary tiles, which share nothing: the same bits.  The array that the scores are shared in,
+the confidences', holds large values ahead of every draw: taken for scores they would leave nothing to be drawn."""
 import pytest
 import torch
 
@@ -12,6 +13,7 @@ DEV = "cuda:0"
 def drawn(op, hidden, w, gather, pos, tau, seed):
     n = gather.numel()
     op.count.fill_(n)
+    op.conf.fill_(1e30)
     binding.mosaic_masked_logits_sample(hidden, w, gather, op.count, op.max_rows, tau, seed, op.token, op.conf, op.lse,
                                         op.plan, op.workspace, noise_idx=pos)
     return [x[:n].clone() for x in (op.token, op.conf, op.lse)]

@@ -134,6 +134,34 @@ int main(int argc, char** argv) {
 }
 """
 
+SHARES = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "mosaic_internal.h"
+#include "mosaic_schedule.h"
+using namespace mosaic;
+int main(int argc, char** argv) {
+  for (int a = 1; a + 3 < argc; a += 4) {
+    const int d = atoi(argv[a]), V = atoi(argv[a + 1]), bound = atoi(argv[a + 2]), rows = atoi(argv[a + 3]);
+    mosaic_plan plan;
+    if (mosaic_plan_workspace(131072, bound, d, V, 0, 256, 1, &plan) != MOSAIC_OK) return 1;
+    const KernelChoice choice = choose_kernel(131072, d, d, V, plan, true);
+    if (!choice.fast && !choice.paired) return 1;
+    ScheduleInput in{};
+    in.vocab_tiles = (uint32_t)((V + 255) / 256 - (choice.paired ? 1 : 0));
+    in.k_tiles = (uint32_t)d / 64;
+    in.widths = 0xff;
+    in.sampling = 1;
+    in.grid = (uint32_t)plan.grid;
+    in.extra = choice.paired ? 1 : 0;
+    in.slots64 = (uint32_t)((int64_t)plan.vocab_splits * plan.rows_per_chunk / 64);
+    const Schedule s = choose_schedule(in, rows);
+    printf("%d %d %d %d\n", s.width, (int)ceil_div(in.vocab_tiles, (uint32_t)s.splits),
+           (int)ceil_div((uint32_t)(s.row_tiles * s.splits), in.grid), (int)units_share(in.vocab_tiles, s.width, s.splits));
+  }
+}
+"""
+
 
 def build_and_run(tmp_path, program, *args):
     src = tmp_path / "schedule.hip"
@@ -145,6 +173,31 @@ def build_and_run(tmp_path, program, *args):
     print(res.stdout)
     assert res.returncode == 0, res.stdout
     return res.stdout
+
+
+def divisions_found(tmp_path, draws):
+    """(width, tiles of the longest unit, rounds, whether units share) of draws given as (d, V, bound, rows found)"""
+    out = build_and_run(tmp_path, SHARES, *[x for draw in draws for x in draw])
+    found = [tuple(int(x) for x in line.split()) for line in out.split("\n") if line]
+    assert len(found) == len(draws)
+    return found
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_sharing_follows_the_rows_found(tmp_path):
+    """whatever the bound: a draw shares where its units, as found, have a second tile (a third where they are narrow)"""
+    heads = [(512, 8192), (1024, 32000), (2048, 65536), (3584, 152064), (3584, 151936), (4096, 126464), (512, 8130)]
+    draws = [(d, V, bound, rows) for d, V in heads for bound in (512, 4096, 16384)
+             for rows in (1, 16, 20, 64, 65, 200, 300, 512, 1000, 4096, 9000) if rows <= bound]
+    found = divisions_found(tmp_path, draws)
+    for draw, (width, tiles, _, shares) in zip(draws, found):
+        assert shares == (tiles > (1 if width >= 2 else 2)), draw
+    at = dict(zip(draws, found))
+    for bound in (512, 4096, 16384):
+        for rows in (16, 20, 64, 200):
+            assert not at[512, 8192, bound, rows][3] and not at[1024, 32000, bound, rows][3] and not at[2048, 65536, bound, rows][3]
+        assert not at[4096, 126464, bound, 20][3] and at[4096, 126464, bound, 200][3] and at[4096, 126464, bound, 300][3]
+    assert all(at[d, V, 16384, 9000][3] for d, V in heads)
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
