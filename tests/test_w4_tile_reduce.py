@@ -228,7 +228,7 @@ class Wave:
             pc += 1
             steps += 1
             assert steps < 500000, "the listing does not terminate"
-            if ins.endswith(":"):
+            if ins.endswith(":") or ins.startswith(".p2align"):
                 continue
             op, _, rest = ins.partition(" ")
             if op == "s_branch":
