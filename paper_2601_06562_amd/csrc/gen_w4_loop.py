@@ -645,7 +645,7 @@ TAKE = 0x80000000
 
 def take_published():
     """The best scores that other units have published for this wave's rows (the kernel says how, at its shared bounds) into
-    the columns' running best, as the next float below.  Here, between the tile's products and its draw, a unit's second tile
+    the columns' running best, as a float just below.  Here, between the tile's products and its draw, a unit's second tile
     finds what the first ones of all units have reached; ahead of the products, where it stood, they were still at it.
     %[rb]: the first of the rows' words, %[rl]: the last row that is there."""
     T = [f"v{FRAG_BASE + i}" for i in range(nb())]
@@ -659,13 +659,12 @@ def take_published():
         e(f"global_load_dword {b}, {b}, %[rb] sc0")
     e("v_and_b32 v176, 15, v176")
     e("v_lshlrev_b32 v176, 2, v176")
-    e(f"v_mov_b32 v177, {hex(KNEG)}")
     e("s_waitcnt vmcnt(0)")
-    for b in best:
-        e(f"v_cmp_lt_i32 vcc, 0, {b}")
-        e(f"v_add_u32 {b}, -1, {b}")
-        e("s_nop 1")
-        e(f"v_cndmask_b32 {b}, v177, {b}, vcc")
+    for b in best:                                                   # below, and back from the words' order (its own inverse)
+        e(f"v_add_u32 {b}, -2, {b}")
+        e(f"v_ashrrev_i32 v177, 31, {b}")
+        e("v_lshrrev_b32 v177, 1, v177")
+        e(f"v_xor_b32 {b}, v177, {b}")
     for tb in range(nb()):
         e(f"ds_bpermute_b32 {T[tb]}, v176, {best[tb // 4]} offset:{64 * (tb % 4)}")
     e("s_waitcnt lgkmcnt(0)")

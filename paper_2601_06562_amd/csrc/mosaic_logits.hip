@@ -205,10 +205,12 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
 // costs them a bound and no result.  A launch ahead of the pass that cleared the rows cost every draw whose bound has
 // units that share 2 us, also where the units found do not: 16 rows of 32000 x 1024 under a bound of 512 27.0 -> 29.0 us, of
 // 8192 x 512 under 4096 19.1 -> 21.0 (without it 26.4 and 18.5).
-// What is taken over is the next float below: an id of another unit with the very same score still counts, and the merge
-// then finds the lowest of them as it does without.  The lane's id and logit stay those of its own best, which no
-// longer matters: the unit that published the score holds it, or a better one, in its partial result.
-// Scores are compared as signed integers, which orders them from 0 on up; anything below stays at kNeg, that is unshared.
+// What is taken over is a float below (two steps: one below +0 is -0, its equal): an id of another unit with the very same
+// score still counts, and the merge then finds the lowest of them as it does without.  The lane's id and logit stay those of
+// its own best, which no longer matters: the unit that published the score holds it, or a better one, in its partial result.
+// The words are integers in the scores' order (score_order).  As the scores' own bits, which are in order from 0 on up only,
+// they left rows whose best score is below zero unshared, at the cost of the exchange: with all logits 300 lower 32 rows of
+// 152064 x 3584 take 183.3 us so, 182.0 without any sharing, 180.1 in this order; 280 rows 319 -> 299; 900 rows of 32000 x 1024 103 -> 84.
 // (Taking over is the sampling statements' own: take_published in gen_w4_loop.py.)
 
 // Largest of a token's four lanes (l, l ^ 16, l ^ 32, l ^ 48).
@@ -723,6 +725,10 @@ __device__ __forceinline__ int fresh_lane() {
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
   return lane;
 }
+__device__ __forceinline__ int score_order(float x) {
+  const int b = __float_as_int(x);
+  return b ^ (int)((uint32_t)(b >> 31) >> 1);
+}
 // Lane group q clears, publishes and reads columns q and q + 4 of a wave.
 __device__ __forceinline__ int32_t* row_best_at(const KernelParams& p, int row) {
   return reinterpret_cast<int32_t*>(p.out_conf + p.row0) + (uint32_t)row;
@@ -734,7 +740,7 @@ __device__ __forceinline__ void clear_best(const KernelParams& p, int first_row,
   for (int k = 0; k < (NB + 3) / 4; ++k) {
     const int column = 4 * k + q, row = first_row + column * 16 + (lane & 15);
     if (column < NB && row < rows)   // a padding column's draw is of no account, whatever it finds
-      __hip_atomic_store(row_best_at(p, row), __float_as_int(kNeg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      __hip_atomic_store(row_best_at(p, row), score_order(kNeg), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 }
 template <int NB>
@@ -750,7 +756,7 @@ __device__ __forceinline__ void publish_best(const KernelParams& p, const float 
     }
     const int column = 4 * k + q, row = first_row + column * 16 + (lane & 15);
     if (column < NB && row < rows)   // a padding column holds the last row
-      __hip_atomic_fetch_max(row_best_at(p, row), __float_as_int(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_fetch_max(row_best_at(p, row), score_order(own), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 // A prologue copy's address as a scalar base and a 32-bit offset a lane, which the copy's instruction takes as they are.  Left

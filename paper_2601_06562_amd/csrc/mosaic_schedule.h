@@ -149,8 +149,8 @@ __host__ __device__ inline Schedule schedule_of(int32_t rows, uint64_t best) {
 
 // Whether the units of a draw share the best scores of their rows (shared bounds, mosaic_logits.hip).  A unit of one tile has
 // nothing to take over.  One of two does at row tiles of 64 rows and more (40 rows of 126464 x 4096 177.1 -> 174.1 us, 1000
-// rows of 8192 x 512 33.9 -> 31.5), at 32 rows it gains less than the runs differ (20 rows of 126464 x 4096 169.7 -> 168.6, and
-// with all logits below zero, which share nothing, 169.6 -> 170.2); three tiles of 32 rows gain (32 rows of 152064 x 3584 181.8 -> 180.5).
+// rows of 8192 x 512 33.9 -> 31.5), at 32 rows it gains less than the runs differ (20 rows of 126464 x 4096 169.7 -> 168.6);
+// three tiles of 32 rows gain (32 rows of 152064 x 3584 181.8 -> 180.5).
 constexpr int32_t kShareAtTwo = 2;   // widths from which on units of two tiles share, too
 __host__ __device__ inline bool units_share(uint32_t vocab_tiles, int32_t width, int32_t splits) {
   return vocab_tiles > (width < kShareAtTwo ? 2u : 1u) * (uint32_t)splits;
