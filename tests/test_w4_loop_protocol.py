@@ -47,6 +47,18 @@ def listing(nb, sample=False):
     return out[:cut], out[cut:end], out[end:]
 
 
+def writes_m0(ins):
+    """A direct-to-LDS load needs an instruction between the write of M0, by whatever operation, and itself."""
+    return re.match(r"s_\w+ m0,", ins) is not None
+
+
+def without_wait_state(lines, base):
+    """A planted mistake: the first write of M0 from `base` right ahead of its load."""
+    at = next(i for i, ln in enumerate(lines) if writes_m0(ln) and base in ln)
+    load = next(i for i in range(at, len(lines)) if lines[i].startswith("global_load_lds"))
+    return lines[:at] + lines[at + 1:load] + [lines[at]] + lines[load:]
+
+
 class Sim:
     def __init__(self, lines, nb, nk, ntile, ragged_rows=0):
         self.nb, self.nk, self.ntile, self.total = nb, nk, ntile, nk * ntile
@@ -237,6 +249,7 @@ class Sim:
                 m = re.fullmatch(r"(\S+)(?: offset:(\d+))?", args[1])
                 self.ds_read(args[0], m.group(1), int(m.group(2) or 0))
             elif op == "global_load_lds_dwordx4":
+                assert not writes_m0(self.prog[pc - 2]), "no instruction between the write of M0 and the load that reads it"
                 self.copy("W" if args[1] == "s[96:97]" else "H")
             elif op == "v_add_u32":
                 self.set(args[0], self.val(args[1]) + self.val(args[2]))
@@ -326,6 +339,14 @@ def test_the_checker_catches_a_copy_into_a_slot_in_use(loop):
     broken = [ln.replace("s_add_u32 %[wdst], %[wdst], 0x8000", "s_add_u32 %[wdst], %[wdst], 0x10000") for ln in lines]
     with pytest.raises(AssertionError, match="may still be reading"):
         run(broken, nb, 4, 3)
+
+
+def test_the_checker_catches_a_load_right_behind_its_m0_write(loop):
+    """What lies between the two moved ahead of both, LM-head and hidden copies alike."""
+    nb, lines = loop
+    for base in ("%[wdst]", "%[hdst]"):
+        with pytest.raises(AssertionError, match="M0"):
+            run(without_wait_state(lines, base), nb, 5, 3)
 
 
 def test_steady_state_spreads_what_lies_between_the_mfmas_evenly(loop):

@@ -171,7 +171,7 @@ class PairWave(protocol.Sim):
                 m = re.fullmatch(r"(\S+)(?: offset:(\d+))?", args[1])
                 self.ds_read(args[0], m.group(1), int(m.group(2) or 0))
             elif op == "global_load_lds_dwordx4":
-                assert not self.prog[self.pc - 2].startswith("s_add_u32 m0")      # M0's wait state
+                assert not protocol.writes_m0(self.prog[self.pc - 2]), "no instruction between the write of M0 and the load"
                 self.copy("W" if args[1].split()[0] == "s[96:97]" else "H")
             elif op == "v_add_u32":
                 self.set(args[0], self.val(args[1]) + self.val(args[2]))
@@ -246,7 +246,8 @@ def test_pair_order_protocol(nb, sample):
 
 
 @pytest.mark.parametrize("nb", WIDTHS)
-@pytest.mark.parametrize("mistake", ["no vmcnt", "no lgkmcnt", "late vmcnt", "barrier early", "one lead for all"])
+@pytest.mark.parametrize("mistake", ["no vmcnt", "no lgkmcnt", "late vmcnt", "barrier early", "one lead for all", "W load behind M0",
+                                     "H load behind M0"])
 def test_planted_mistakes_are_caught(nb, mistake, monkeypatch):
     """Planted in a copy of the listing, or in the checker's glue."""
     loop = listing(nb)
@@ -256,6 +257,8 @@ def test_planted_mistakes_are_caught(nb, mistake, monkeypatch):
         loop = [ln for ln in loop if not re.fullmatch(r"s_waitcnt lgkmcnt\(([1-9]|1\d)\)", ln)]
     elif mistake == "late vmcnt":
         loop = [re.sub(r"vmcnt\(8\)", f"vmcnt({8 + nb})", ln) for ln in loop]
+    elif mistake.endswith("M0"):
+        loop = protocol.without_wait_state(loop, "%[wdst]" if mistake[0] == "W" else "%[hdst]")
     elif mistake == "barrier early":
         at = next(i for i, ln in enumerate(loop) if ln == "s_barrier")
         first = next(i for i, ln in enumerate(loop) if ln.startswith("v_mfma"))
@@ -263,7 +266,7 @@ def test_planted_mistakes_are_caught(nb, mistake, monkeypatch):
         loop = loop[:first + 1] + [wait, "s_barrier"] + loop[first + 1:at - 1] + loop[at + 1:]
     else:
         monkeypatch.setattr(PairWave, "w_region", lambda self, slot: ("W", slot, "hi"))
-    with pytest.raises(AssertionError):
+    with pytest.raises(AssertionError, match="M0" if mistake.endswith("M0") else None):
         run(loop, nb, 6, 3)
 
 

@@ -7,7 +7,7 @@ import re
 import numpy as np
 import pytest
 
-from test_w4_loop_protocol import gen, listing
+from test_w4_loop_protocol import gen, listing, writes_m0
 
 
 @pytest.mark.parametrize("nb", range(1, 9))
@@ -15,8 +15,11 @@ def test_copies_keep_the_wait_state_behind_their_m0_write(nb):
     """A direct-to-LDS load needs an instruction between the write of M0 and itself."""
     for sample in (False, True):
         loop, _, _ = listing(nb, sample)
+        writes = [ln for ln in loop if writes_m0(ln)]
+        loads = sum(ln.startswith("global_load_lds") for ln in loop)
+        assert len(writes) == loads and len({ln.split()[0] for ln in writes}) == 2   # LM-head and hidden copies: none is overlooked
         for a, b in zip(loop, loop[1:]):
-            assert not (a.startswith("s_add_u32 m0") and b.startswith("global_load_lds"))
+            assert not (writes_m0(a) and b.startswith("global_load_lds"))
 
 
 @pytest.mark.parametrize("sample", [False, True])
