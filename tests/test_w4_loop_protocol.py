@@ -60,6 +60,8 @@ def without_wait_state(lines, base):
 
 
 class Sim:
+    turn = 0                                     # of this unit's LM-head copies: copy i brings piece i ^ turn to its place
+
     def __init__(self, lines, nb, nk, ntile, ragged_rows=0):
         self.nb, self.nk, self.ntile, self.total = nb, nk, ntile, nk * ntile
         self.ragged_rows = ragged_rows           # rows from the last tile but one to the last one, 0: 256 as elsewhere
@@ -120,7 +122,12 @@ class Sim:
             rows += self.ragged_rows - 256
         return W_BASE + rows * (self.nk * 128) + (g % self.nk) * 128
 
-    def copy(self, operand):
+    def source_piece(self, operand, offset):
+        """The piece of a tile that a copy's offsets stand for, which the kernel makes: %[woff i] is piece i ^ turn."""
+        i = int(re.fullmatch(r"%\[[wh]off(\d)\]", offset).group(1))
+        return i ^ self.turn if operand == "W" else i
+
+    def copy(self, operand, offset):
         m0 = self.reg["m0"]
         slot = self.slot_of(m0)
         assert slot not in self.reads_this_interval, f"copy into slot {slot} that a wave may still be reading"
@@ -141,7 +148,9 @@ class Sim:
             self.unpublished[slot] = ident
             self.copies_this_interval.add(slot)
         assert self.unpublished[slot] == ident
-        assert self.offset_in(m0) == 1024 * parts, "the pieces of a tile go to consecutive KiB of the slot"
+        place, piece = self.offset_in(m0), self.source_piece(operand, offset)
+        assert place == 1024 * piece, f"piece {piece} of a tile goes to byte {place} of the slot, not to its own KiB"
+        assert piece == (parts ^ self.turn if operand == "W" else parts), "every piece once, in the unit's order"
         self.copy_parts[slot] = (parts + 1) % pieces
         self.vm_queue.append(slot)
         if self.copy_parts[slot] == 0:
@@ -216,7 +225,7 @@ class Sim:
         w, h = self.wptr(NW), H_BASE + (NH % self.nk) * 128
         self.reg.update({
             "%[wsrc_lo]": w & MASK32, "%[wsrc_hi]": w >> 32, "%[hsrc_lo]": h & MASK32, "%[hsrc_hi]": h >> 32,
-            "%[wrd]": 0, "%[hrd]": 0, "%[wdst]": 0, "%[hdst]": 0, "%[wk]": NW % self.nk, "%[hk]": NH % self.nk,
+            "%[wrd]": 0, "%[hrd]": 0, "%[wdst]": 1024 * self.turn, "%[hdst]": 0, "%[wk]": NW % self.nk, "%[hk]": NH % self.nk,
             "%[g]": 0, "%[total]": self.total, "%[nk]": self.nk,
             "%[hwrap]": (self.nk - 1) * 128,
             "%[rdw0]": 0, "%[rdw1]": 64, "%[rdh0]": NW * SLOT, "%[rdh1]": NW * SLOT + 64,
@@ -250,7 +259,7 @@ class Sim:
                 self.ds_read(args[0], m.group(1), int(m.group(2) or 0))
             elif op == "global_load_lds_dwordx4":
                 assert not writes_m0(self.prog[pc - 2]), "no instruction between the write of M0 and the load that reads it"
-                self.copy("W" if args[1] == "s[96:97]" else "H")
+                self.copy("W" if args[1] == "s[96:97]" else "H", args[0])
             elif op == "v_add_u32":
                 self.set(args[0], self.val(args[1]) + self.val(args[2]))
             elif op == "s_waitcnt":
@@ -298,8 +307,9 @@ class Sim:
                 raise AssertionError(f"instruction the checker does not know: {ins}")
 
 
-def run(lines, nb, nk, ntile, ragged=0):
+def run(lines, nb, nk, ntile, ragged=0, turn=0):
     sim = Sim(lines, nb, nk, ntile, ragged)
+    sim.turn = turn
     sim.prologue()
     sim.run_tiles()
     return sim

@@ -71,7 +71,7 @@ class PairWave(protocol.Sim):
         w, h = self.wptr(min(lead - 1, self.total - 1)), H_BASE + 2 % self.nk * 128
         self.reg.update({
             "%[wsrc_lo]": w & MASK32, "%[wsrc_hi]": w >> 32, "%[hsrc_lo]": h & MASK32, "%[hsrc_hi]": h >> 32,
-            "%[wrd]": 0, "%[hrd]": 0, "%[wdst]": (lead - 1) % 3 * 0x8000, "%[hdst]": 0, "%[wk]": min(lead - 1, self.total - 1) % self.nk,
+            "%[wrd]": 0, "%[hrd]": 0, "%[wdst]": (lead - 1) % 3 * 0x8000 + 1024 * self.turn, "%[hdst]": 0, "%[wk]": min(lead - 1, self.total - 1) % self.nk,
             "%[hk]": 2 % self.nk, "%[g]": 0, "%[total]": self.total, "%[nk]": self.nk, "%[hwrap]": (self.nk - 1) * 128,
             "%[wnext]": lead, "%[rdw0]": 0, "%[rdh0]": 0x18000})
 
@@ -83,7 +83,7 @@ class PairWave(protocol.Sim):
         self.used.clear()
         self.started.clear()
 
-    def copy(self, op):
+    def copy(self, op, offset):
         m0, off = self.reg["m0"], None
         if op == "W":
             ident, region, slot = self.copied["W"], self.w_region(self.copied["W"] % 3), m0 // 0x8000
@@ -99,7 +99,9 @@ class PairWave(protocol.Sim):
         assert region not in self.lds.reads, f"copy into {region}, which a wave may still be reading"
         parts = self.lds.pending.setdefault(region, {})
         done = parts[int(self.odd)][2] if int(self.odd) in parts else 0
-        assert done < pieces and off == 1024 * done
+        piece = self.source_piece(op, offset)
+        assert off == 1024 * piece, f"piece {piece} of a tile goes to byte {off} of the slot, not to its own KiB"
+        assert done < pieces and piece == (done ^ self.turn if op == "W" else done), "every piece once, in the unit's order"
         parts[int(self.odd)] = (ident, False, done + 1)
         self.lds.holds.pop(region, None)
         self.vm_queue.append(region)
@@ -172,7 +174,7 @@ class PairWave(protocol.Sim):
                 self.ds_read(args[0], m.group(1), int(m.group(2) or 0))
             elif op == "global_load_lds_dwordx4":
                 assert not protocol.writes_m0(self.prog[self.pc - 2]), "no instruction between the write of M0 and the load"
-                self.copy("W" if args[1].split()[0] == "s[96:97]" else "H")
+                self.copy("W" if args[1].split()[0] == "s[96:97]" else "H", args[0])
             elif op == "v_add_u32":
                 self.set(args[0], self.val(args[1]) + self.val(args[2]))
             elif op == "v_xor_b32":
@@ -212,10 +214,11 @@ class PairWave(protocol.Sim):
         return False
 
 
-def run(lines, nb, nk, ntile, ragged=0):
+def run(lines, nb, nk, ntile, ragged=0, turn=0):
     lds = Lds()
     waves = [PairWave(lines, nb, nk, ntile, ragged, odd, lds) for odd in (False, True)]
     for w in waves:
+        w.turn = turn
         w.prologue()
     for n in range(ntile):
         for w in waves:
