@@ -12,6 +12,8 @@ DEV = "cuda:0"
 INF = float("inf")
 # rows, d, V, flags: the 4-wave kernel in several widths, with a ragged last tile, the general kernel, a pair of launches
 SHAPES = [(20, 320, 1024, 0), (300, 320, 1111, 0), (150, 320, 1024, binding.PLAN_GENERAL_KERNEL), (40, 128, 1000, 0)]
+# ... and draws whose units share their scores (tests/test_schedule_host.py holds that they do)
+SHAPES += [(1100, 320, 8192, 0), (1100, 320, 8132, 0)]
 
 
 def inputs(T, d, V):

@@ -8,6 +8,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_shared_bounds as shared_bounds
 import test_gpu_streamed_head as streamed_head
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -141,10 +142,11 @@ SHARES = r"""
 #include "mosaic_schedule.h"
 using namespace mosaic;
 int main(int argc, char** argv) {
-  for (int a = 1; a + 3 < argc; a += 4) {
-    const int d = atoi(argv[a]), V = atoi(argv[a + 1]), bound = atoi(argv[a + 2]), rows = atoi(argv[a + 3]);
+  for (int a = 1; a + 4 < argc; a += 5) {
+    const int d = atoi(argv[a]), V = atoi(argv[a + 1]), bound = atoi(argv[a + 2]), found = atoi(argv[a + 3]);
     mosaic_plan plan;
-    if (mosaic_plan_workspace(131072, bound, d, V, 0, 256, 1, &plan) != MOSAIC_OK) return 1;
+    if (mosaic_plan_workspace(131072, bound, d, V, atol(argv[a + 4]), 256, 1, &plan) != MOSAIC_OK) return 1;
+    const int rows = found < plan.rows_per_chunk ? found : plan.rows_per_chunk;
     const KernelChoice choice = choose_kernel(131072, d, d, V, plan, true);
     if (!choice.fast && !choice.paired) return 1;
     ScheduleInput in{};
@@ -156,8 +158,9 @@ int main(int argc, char** argv) {
     in.extra = choice.paired ? 1 : 0;
     in.slots64 = (uint32_t)((int64_t)plan.vocab_splits * plan.rows_per_chunk / 64);
     const Schedule s = choose_schedule(in, rows);
-    printf("%d %d %d %d\n", s.width, (int)ceil_div(in.vocab_tiles, (uint32_t)s.splits),
-           (int)ceil_div((uint32_t)(s.row_tiles * s.splits), in.grid), (int)units_share(in.vocab_tiles, s.width, s.splits));
+    printf("%d %d %d %d %d\n", s.width, (int)ceil_div(in.vocab_tiles, (uint32_t)s.splits),
+           (int)ceil_div((uint32_t)(s.row_tiles * s.splits), in.grid), (int)units_share(in.vocab_tiles, s.width, s.splits),
+           plan.num_chunks);
   }
 }
 """
@@ -176,7 +179,8 @@ def build_and_run(tmp_path, program, *args):
 
 
 def divisions_found(tmp_path, draws):
-    """(width, tiles of the longest unit, rounds, whether units share) of draws given as (d, V, bound, rows found)"""
+    """(width, tiles of the longest unit, rounds, whether units share, chunks), of the first chunk, of draws given as (d, V,
+    bound, rows found, budget)"""
     out = build_and_run(tmp_path, SHARES, *[x for draw in draws for x in draw])
     found = [tuple(int(x) for x in line.split()) for line in out.split("\n") if line]
     assert len(found) == len(draws)
@@ -187,17 +191,28 @@ def divisions_found(tmp_path, draws):
 def test_sharing_follows_the_rows_found(tmp_path):
     """whatever the bound: a draw shares where its units, as found, have a second tile (a third where they are narrow)"""
     heads = [(512, 8192), (1024, 32000), (2048, 65536), (3584, 152064), (3584, 151936), (4096, 126464), (512, 8130)]
-    draws = [(d, V, bound, rows) for d, V in heads for bound in (512, 4096, 16384)
+    draws = [(d, V, bound, rows, 0) for d, V in heads for bound in (512, 4096, 16384)
              for rows in (1, 16, 20, 64, 65, 200, 300, 512, 1000, 4096, 9000) if rows <= bound]
     found = divisions_found(tmp_path, draws)
-    for draw, (width, tiles, _, shares) in zip(draws, found):
+    for draw, (width, tiles, _, shares, _) in zip(draws, found):
         assert shares == (tiles > (1 if width >= 2 else 2)), draw
-    at = dict(zip(draws, found))
+    at = {draw[:4]: f for draw, f in zip(draws, found)}
     for bound in (512, 4096, 16384):
         for rows in (16, 20, 64, 200):
             assert not at[512, 8192, bound, rows][3] and not at[1024, 32000, bound, rows][3] and not at[2048, 65536, bound, rows][3]
         assert not at[4096, 126464, bound, 20][3] and at[4096, 126464, bound, 200][3] and at[4096, 126464, bound, 300][3]
     assert all(at[d, V, 16384, 9000][3] for d, V in heads)
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
+def test_the_draws_that_hold_shared_bounds_do_share(tmp_path):
+    """of tests/test_gpu_shared_bounds.py and test_gpu_non_finite.py, and what those are held against does not; one round and
+    several; in chunks"""
+    for draw, (_, _, rounds, share, chunks) in zip(shared_bounds.SHARING, divisions_found(tmp_path, shared_bounds.SHARING)):
+        assert share == 1, draw
+        assert (rounds > 1) == (draw[3] > 16384) and (chunks > 1) == (draw[4] > 0), (draw, rounds, chunks)
+    for draw, (_, _, _, share, _) in zip(shared_bounds.ALONE, divisions_found(tmp_path, shared_bounds.ALONE)):
+        assert share == 0, draw
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
