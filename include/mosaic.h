@@ -151,7 +151,6 @@ int mosaic_mask_compact(const uint8_t *mask, int64_t T, int32_t *out_idx, int32_
  *              max_rows only the first max_rows rows are produced.
  *   max_rows   the bound the plan was made for
  *   out_*      dev, max_rows entries each; entries >= *count are left untouched
- *              (a sampling call keeps intermediate values in out_conf[0 .. *count) while it runs)
  *   plan       host pointer, from mosaic_plan_workspace with the same T, max_rows, d, V
  *   workspace  dev, >= plan->workspace_bytes, 16-byte aligned; contents are scratch.  Calls that may run
  *              concurrently (different streams) need workspaces of their own
@@ -215,6 +214,9 @@ int mosaic_masked_logits_reduce_static(const void *hidden, int64_t T, int32_t d,
  *              idx[j] when the gather list is shifted (mosaic_shift_indices: position p reads hidden row
  *              p - 1, and a sequence start s and s + 1 both read row s); passing the unshifted positions
  *              here keeps the draws of different positions independent.  Any int32 value is valid
+ *   out_conf   dev, in memory on which the device's 32-bit atomics work (hipMalloc's; not mapped host memory): with
+ *              temperature > 0 the call's workgroups exchange intermediate values in out_conf[0 .. *count), so
+ *              until it has ended these entries hold neither what was there before nor confidences
  *   workspace  dev, >= mosaic_sample_workspace_bytes(plan) when temperature > 0 (20 bytes per row of a
  *              chunk and vocabulary split instead of 12, plus MOSAIC_SYNC_BYTES; plan->workspace_bytes
  *              already says so when the plan was made with sampling = 1), 16-byte aligned

@@ -274,7 +274,8 @@ def mosaic_sample_workspace_bytes(plan) -> int:
 def mosaic_masked_logits_sample(hidden, w, idx, count, max_rows, temperature, seed, out_token, out_conf, out_lse, plan,
                                 workspace, stream=None, noise_idx=None):
     """As mosaic_masked_logits_reduce, with Gumbel-max sampling at `temperature` from the 64-bit `seed`;
-    noise_idx (int32 device tensor or None) names the position each row predicts when idx is a shifted list."""
+    noise_idx (int32 device tensor or None) names the position each row predicts when idx is a shifted list.  While a
+    call with temperature > 0 runs, out_conf holds intermediate values that its workgroups exchange by atomics."""
     T, d = hidden.shape
     V, d2 = w.shape
     if d != d2:
