@@ -712,9 +712,9 @@ constexpr int kLmHeadSlot = 256 * kRowBytes;         // 32 KiB
 constexpr int kLdsBytes = 160 * 1024;
 #include "mosaic_w4_pieces.inc"
 // Exchanges come after 1, 2, 4, 8, ... tiles, since a bound from n tiles lets pass half of what one from n / 2 does
-// (after every tile: 4096 rows 2821 -> 2876 us).  Of a row's splits at most about kPublishers publish, since atomics on one
-// word take turns and a few are nearly as good a bound as all (1004 rows 785 us with 8, 775 with 32, 779 with 64; 280 rows 326,
-// 324, 333).  The read may be served by any cache: an old bound is a bound.
+// (after every tile: 4096 rows 2779 -> 2787 us, of 11 sizes none faster than its runs differ).  Of a row's splits at most about
+// kPublishers publish, since atomics on one word take turns and a few are nearly as good a bound as all (205 rows 252.9 us with
+// 8, 250.5 with 32, 250.6 with 64, 253.8 with all 247; 900 rows of 32000 x 1024, 125 splits, 88.6, 85.7, 85.0, 84.7).  The read may be served by any cache: an old bound is a bound.
 // The columns that pad a row tile hold the last row once more and publish nothing: their atomics all went to that one row's
 // word, up to 256 a publisher, and the next copies wait behind them (4105 rows 3114 -> 3006 us, 2700 rows of 65536 x 2048
 // 659 -> 619, 16000 rows of 32000 x 1024 1037 -> 971).
@@ -762,7 +762,7 @@ __device__ __forceinline__ void publish_best(const KernelParams& p, const float 
 // A prologue copy's address as a scalar base and a 32-bit offset a lane, which the copy's instruction takes as they are.  Left
 // alone the compiler widens the offsets ahead of the units and spills the 64-bit addresses: a unit's start then waited for a
 // reload, and the copies ahead of it, up to eight times (16000 rows of 32000 x 1024 drawn 1037 -> 1002 us, 9000 rows of
-// 8192 x 512 drawn 165 -> 161, greedy 88.1 -> 87.0; vector registers spilled 57 -> 13 sampling, 10 -> 3 greedy).
+// 8192 x 512 drawn 165 -> 161, greedy 88.1 -> 87.0; vector registers spilled 69 -> 19 sampling, 10 -> 3 greedy).
 __device__ __forceinline__ const char* scalar_pointer(const char* x) {
   const uint64_t a = (uint64_t)x;
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
