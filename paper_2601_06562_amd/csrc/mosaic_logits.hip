@@ -198,8 +198,8 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
 // Which units share follows from the division found (units_share, mosaic_schedule.h).
 //
 // The bounds lie in out_conf, which holds nothing else until the merge writes it.  Every unit clears the words of its rows
-// itself, at its start, and each lane reads only words that it has stored to: what it finds there was written by this
-// launch.  So the store need be seen by no other (at the scope of the workgroup it stays behind the XCD's own L2; through to
+// itself, at its start, and each lane reads only words that it has stored to (but for lanes that pad a row tile, whose draw
+// nobody sees): what it finds there was written by this launch.  So the store need be seen by no other (at the scope of the workgroup it stays behind the XCD's own L2; through to
 // memory, where all units of a row queue for the same lines, 500 rows of 65536 x 2048 take 146 us instead of 141, 8 rows of
 // 152064 x 3584, 198 units on one line, 185 instead of 175), and a unit that starts late and wipes what others have published
 // costs them a bound and no result.  A launch ahead of the pass that cleared the rows cost every draw whose bound has
