@@ -199,12 +199,12 @@ __device__ __forceinline__ void gumbel4(uint32_t k0, uint32_t k1, uint32_t pos, 
 //
 // The bounds lie in out_conf, which holds nothing else until the merge writes it.  Every unit clears the words of its rows
 // itself, at its start, and each lane reads only words that it has stored to (but for lanes that pad a row tile, whose draw
-// nobody sees): what it finds there was written by this launch.  So the store need be seen by no other (at the scope of the workgroup it stays behind the XCD's own L2; through to
-// memory, where all units of a row queue for the same lines, 500 rows of 65536 x 2048 take 146 us instead of 141, 8 rows of
-// 152064 x 3584, 198 units on one line, 185 instead of 175), and a unit that starts late and wipes what others have published
-// costs them a bound and no result.  A launch ahead of the pass that cleared the rows cost every draw whose bound has
-// units that share 2 us, also where the units found do not: 16 rows of 32000 x 1024 under a bound of 512 27.0 -> 29.0 us, of
-// 8192 x 512 under 4096 19.1 -> 21.0 (without it 26.4 and 18.5).
+// nobody sees): what it finds there was written by this launch.  So the store need be seen by no other (at the scope of the
+// workgroup it stays behind the XCD's own L2; through to memory, where all units of a row queue for the same lines, 500 rows
+// of 65536 x 2048 take 146 us instead of 141, 8 rows of 152064 x 3584, 198 units on one line, 185 instead of 175), and a unit
+// that starts late and wipes what others have published costs them a bound and no result.  A launch ahead of the pass that
+// cleared the rows cost every draw whose bound has units that share 2 us, also where the units found do not: 16 rows of
+// 32000 x 1024 under a bound of 512 27.0 -> 29.0 us, of 8192 x 512 under 4096 19.1 -> 21.0 (without it 26.4 and 18.5).
 // What is taken over is a float below (two steps: one below +0 is -0, its equal): an id of another unit with the very same
 // score still counts, and the merge then finds the lowest of them as it does without.  The lane's id and logit stay those of
 // its own best, which no longer matters: the unit that published the score holds it, or a better one, in its partial result.
